@@ -105,10 +105,11 @@ const char* dkv_status_string(int status);
 size_t dkv_workspace_bytes(const dkv_desc* desc);
 
 /*
- * Which kernels a scoring call (Eq. 1-2) with this descriptor and key token stride (elements) runs on: 1 = the bf16
- * matrix-core kernels (bf16, head_dim 128, and a token stride short enough for their 32-bit row offsets: at most
- * about 485 000 elements), 0 = the vector-ALU kernels (everything else the library accepts), negative = a status.
- * Host only, launches nothing.
+ * Which kernels a scoring call (Eq. 1-2) with this descriptor and key token stride (elements) runs on: 1 = the
+ * kernels that stream bf16 keys of head_dim 128 through LDS (a token stride short enough for their 32-bit row offsets:
+ * at most about 485 000 elements), 0 = others (bf16 at head_dim 64 and fp32: matrix-core kernels that keep their keys
+ * in registers; longer strides, and fp32 at head_dim 128 with more than 128 score rows: the vector ALU), negative = a
+ * status. Host only, launches nothing.
  */
 int dkv_score_path(const dkv_desc* desc, int64_t k_stride_token);
 

@@ -206,6 +206,10 @@ static int score_window_phases(int phases, const dkv_desc* desc, int n_layers, c
     e = launch_score_mfma(p, phases, n_layers, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens, scores_out,
                           scores_stride_head, scores_stride_layer, static_cast<char*>(workspace), wl, lse_in, lse_layers,
                           lse_out, hs);
+  } else if (score_tiles_supported(p, desc->dtype, k_stride_token)) {
+    e = launch_score_tiles(p, phases, desc->dtype, n_layers, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens,
+                           scores_out, scores_stride_head, scores_stride_layer, static_cast<char*>(workspace), wl, lse_in,
+                           lse_layers, lse_out, hs);
   } else {
     // the vector-ALU kernels take one layer at a time (both sweeps of a layer before the next layer's)
     for (int i = 0; i < (sweeps ? n_layers : 1) && e == hipSuccess; ++i)

@@ -1,6 +1,6 @@
 // Observation-window scoring, generic VALU path (Eq. 1-2; Algorithm 1: softmax(Q_win K^T).mean(-2).pooling(-1)).
-// Handles every element type / head size the library accepts; used for fp32 inputs and for shapes the MFMA
-// path is not built for. One thread owns one key: its row lives in registers, the query rows are staged
+// Handles every element type / head size the library accepts; used for what the matrix-core kernels do not take: key
+// token strides past 32-bit row offsets, and fp32 at head size 128 with more than 128 score rows. One thread owns one key: its row lives in registers, the query rows are staged
 // through LDS 32 at a time.
 //
 // Two kernels, because a column of softmax(QK^T) summed over the rows needs every row's normaliser first:

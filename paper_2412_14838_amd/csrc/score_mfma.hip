@@ -26,21 +26,14 @@
 // workspace, and one small kernel for all layers (score_fix_borders) completes the outputs there. Identical keys
 // give bit-identical sums whichever workgroup or lane computes them (fixed summation order per column), and a
 // layer gets the same bits whether it is scored alone or as part of a multi-layer call.
-#include "dkv_internal.h"
+#include "score_common.h"
 
 #include <type_traits>
 
 namespace dkv {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 constexpr int kLdsRow = 272;          // bytes per staged key row: 256 data + 16 pad (conflict-free 16-byte reads)
 constexpr int kLdsBudget = 152 * 1024; // dynamic LDS a workgroup may ask for (160 KB per compute unit, less the static part)
-constexpr int kMaxHalo = 64;          // >= 2 * half
-constexpr float kLog2e = 1.4426950408889634f;
-
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <int RS, int KS>
 struct Tile {
@@ -307,15 +300,6 @@ __device__ inline bool find_chunk2(const int32_t* __restrict__ cu, int n_seqs, i
   return false;
 }
 
-// Workgroup barrier that orders LDS traffic only. __syncthreads() also waits for every global load the wavefront
-// has in flight (its release fence covers global memory), which would cut the prefetch of the key tiles down to
-// what fits between two barriers; the wavefronts of a score kernel talk to each other through LDS alone.
-__device__ inline void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Q and K of the layers one launch covers (kernel argument, indexed by the layer's place in the launch).
 struct ScoreLayers {
   const uint16_t* q[DKV_MAX_SELECT_LAYERS];
@@ -548,13 +532,6 @@ __device__ inline int emit_tile(int n_iter, int it) { return it < n_iter ? n_ite
 // mgrp + KS, ... online in chunk order into `mstage`; after a barrier thread `row` combines the KS groups.
 // Written once and used both inside the emit kernel (single-layer launches) and by the merge kernel below, so
 // that both give the same bits.
-__device__ inline void merge_pair(float& M, float& Lsum, const float2 v) {
-  const float Mn = fmaxf(M, v.x);
-  const float Mu = Mn == -INFINITY ? 0.0f : Mn;
-  Lsum = fmaf(Lsum, fast_exp2(M - Mu), v.y * fast_exp2(v.x - Mu));   // spelled out: every call site rounds alike
-  M = Mn;
-}
-
 // psrc: partials of chunk 0 of this (layer, sequence, head), float2 [chunk][Hkv][rows_pad]
 template <int RS, int KS>
 __device__ inline void merge_chunks(const float2* __restrict__ psrc, int n_full, uint32_t chunk_step, float2* __restrict__ mstage) {
@@ -940,15 +917,10 @@ static int pick_chunk(const Params& p, int cus) {
   return best;
 }
 
-static int device_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-      cus = 256;
-  }
-  return cus;
+void launch_import_lse(const Params& p, int n_layers, const float* const* lse_layers, float* lse_rows, hipStream_t st) {
+  LseLayers in{};
+  for (int i = 0; i < n_layers; ++i) in.lse[i] = lse_layers[i];
+  launch(DKV_KERNEL_SCORE_MERGE, score_import_lse, dim3(p.n_seqs, p.Hkv, n_layers), dim3(256), 0, st, p, in, lse_rows);
 }
 
 template <int RS, int KS>
@@ -1000,9 +972,7 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     if (n_layers > 1) {
       lse_rows = reinterpret_cast<float*>(ws + wl.lse_rows);
       if (lse_layers != nullptr) {       // single sweep: the caller's normalisers, no statistics
-        LseLayers in{};
-        for (int i = 0; i < n_layers; ++i) in.lse[i] = lse_layers[i];
-        launch(DKV_KERNEL_SCORE_MERGE, score_import_lse, dim3(p.n_seqs, p.Hkv, n_layers), dim3(256), 0, st, p, in, lse_rows);
+        launch_import_lse(p, n_layers, lse_layers, lse_rows, st);
       } else {
         launch(DKV_KERNEL_SCORE_MERGE, (score_merge_mfma<RS, KS>), dim3(p.n_seqs, p.Hkv, n_layers), dim3(TL::kThreads), 0, st,
                p, chunk, grid_x, cu, static_cast<const float*>(partials), partials_stride_layer, lse_rows);
