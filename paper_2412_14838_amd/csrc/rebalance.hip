@@ -13,8 +13,9 @@
 //   scan1   histograms the middle digit of the elements that share digit 0 and counts, per layer, the elements
 //           whose digit 0 is larger (they are above T).
 //   pick1   digit 1 of T from that histogram.
-//   scan2   the same one digit down: histograms the last digit (per layer and in total), counts per layer the
-//           elements that share digit 0 and have a larger middle digit.
+//   scan2   the same one digit down, over the few elements that reach the upper digits of the thresholds: histograms the
+//           last digit (per layer and in total), counts per layer the elements that share digit 0 and have a larger
+//           middle digit.
 //   final   one workgroup per sequence: digit 2, then cnt_i = #{> T in layer i} + the share of the elements
 //           equal to T that the tie rule (lower layer first) gives to layer i, then Z, Z' and counts.
 // The scans read the scores as 16-byte vectors, all loads of a workgroup's chunk in flight together.
@@ -32,8 +33,17 @@ namespace dkv {
 
 constexpr int kFinalThreads = 1024;
 constexpr int kHist0Copies = 4;      // interleaved LDS copies of the top-digit histogram (every element lands there)
-constexpr int kHist0Chunk = 8192;    // prefix positions per workgroup, top-digit histogram
-constexpr int kScanChunk = 8192;     // prefix positions per workgroup, scans 1 and 2
+// Workgroups of the three passes over the scores: four heads of one chunk of prefix positions in one layer, 256 threads to
+// a head. Heads of a layer share every histogram, and a workgroup's fixed work - its histogram cleared, read back and added
+// to the global one, where all workgroups of a sequence meet in the same 2048 words - is paid once for all four. Registers
+// are kept below 64, so that two workgroups fit a compute unit. Measured, us per call, one head to a workgroup / four: scans
+// 1 and 2 of a single update over up to 32 layers of 8 x 32736 positions 35 / 18.5 (average), of eight updates in one call
+// 43 / 24, of eight updates over 2048 ragged rows 93 / 54; top digit 12.8 / 11.3 and 24.6 / 20 for the last two.
+constexpr int kHeadsPerGroup = 4;
+constexpr int kHeadThreads = 256;
+constexpr int kPassThreads = kHeadsPerGroup * kHeadThreads;
+constexpr int kPassChunk = 8192;     // prefix positions of a head per workgroup
+constexpr int kListCap = 4096;       // elements scan 2 collects (its threshold is reached by 1 to 3 % of a workgroup's 32768)
 constexpr int kLowBins = 1024;       // the last digit has 10 bits
 constexpr uint32_t kHeaderMagic = 0x646b7631u;
 
@@ -77,13 +87,13 @@ __global__ __launch_bounds__(256) void rebalance_clear_kernel(uint32_t* __restri
 }
 
 // A workgroup's chunk of one (layer, head, sequence) score row as 16-byte vectors: element e of the score tensor
-// is covered by vector e / 4, thread t takes vectors t, t + 256, ... counted from the first one that touches the
-// chunk. ok[j] has bit q set when lane q of vector j lies inside the chunk [e_lo, e_hi): 0xf for all but the
-// vectors on the chunk's two edges, which the consumers treat element by element.
+// is covered by vector e / 4, thread t of the head's 256 takes vectors t, t + 256, ... counted from the first one that
+// touches the chunk [e_lo, e_hi). Lanes outside the chunk are zeros, `outside` of them in this thread: whoever counts
+// zeros takes these off again (a mask per vector would cost a register each, and with it half the occupancy).
 template <int NV>
 struct ChunkVectors {
   uint4 v[NV];
-  uint32_t ok[NV];
+  int outside;
 };
 
 // n_elems: elements of the whole score tensor; its last, partial vector (if any) is read element by element.
@@ -98,29 +108,33 @@ __device__ inline void load_chunk(const float* __restrict__ scores_all, int64_t 
   const int whole_rel = whole > (int64_t)0x7fffffff ? 0x7fffffff : (int)whole;
 #pragma unroll
   for (int j = 0; j < NV; ++j) cv.v[j] = make_uint4(0, 0, 0, 0);
+  cv.outside = 4 * NV;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
-    const int rel = 4 * (threadIdx.x + 256 * j);
+    const int rel = 4 * ((threadIdx.x & (kHeadThreads - 1)) + kHeadThreads * j);
     int first = lo_rel - rel, last = hi_rel - rel;                         // valid lanes [first, last) of 0..4
     first = first < 0 ? 0 : (first > 4 ? 4 : first);
     last = last < 0 ? 0 : (last > 4 ? 4 : last);
-    const uint32_t ok = last > first ? ((1u << last) - 1u) & ~((1u << first) - 1u) : 0u;
-    cv.ok[j] = ok;
-    if (ok) {
+    if (last > first) {
+      cv.outside -= last - first;
       if (rel + 4 <= whole_rel) {
         cv.v[j] = *reinterpret_cast<const uint4*>(row + rel);
       } else {                                                             // the tensor's last, partial vector
         uint32_t e[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (ok >> q & 1) e[q] = row[rel + q];
+          if (q >= first && q < last) e[q] = row[rel + q];
         cv.v[j] = make_uint4(e[0], e[1], e[2], e[3]);
+      }
+      if (last - first < 4) {                                              // an edge of the chunk
+        if (first > 0) cv.v[j].x = 0u;
+        if (first > 1 || last < 2) cv.v[j].y = 0u;
+        if (first > 2 || last < 3) cv.v[j].z = 0u;
+        if (last < 4) cv.v[j].w = 0u;
       }
     }
   }
 }
-
-__device__ inline uint32_t lane_of(const uint4& v, int q) { return q == 0 ? v.x : (q == 1 ? v.y : (q == 2 ? v.z : v.w)); }
 
 // A thread's share of a histogram of NB bins for a workgroup of NT threads: thread t owns the NB / NT bins just
 // below those of thread t - 1 (thread 0 the top ones).
@@ -187,28 +201,28 @@ __device__ inline int global_k(const int32_t* __restrict__ cu, int seq, int w, i
   return (int)(want < have ? want : have);                  // kg of Eq. 4, clamped to the population
 }
 
-// Top-digit histogram of the layers not yet counted. grid = (chunk upper bound, Hkv, layers_done), 256 threads.
+// Top-digit histogram of the layers not yet counted. grid = (chunk upper bound, groups of heads, layers_done).
 // layers_done: of the call's first update; layers at or past it belong to the later updates' slots.
-__global__ __launch_bounds__(256) void rebalance_hist0_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
+__global__ __launch_bounds__(kPassThreads, 8) void rebalance_hist0_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
                                                               int layers_done, int interval,
                                                               const float* __restrict__ scores_all,
                                                               const int32_t* __restrict__ cu,
                                                               const int32_t* __restrict__ header, uint32_t epoch,
                                                               int32_t* __restrict__ tot0, int64_t tot0_words) {
   __shared__ int h[kRadixBins * kHist0Copies];
-  const int head = blockIdx.y, layer = blockIdx.z;
+  const int head = blockIdx.y * kHeadsPerGroup + threadIdx.x / kHeadThreads, layer = blockIdx.z;
   if (layer < layers_already_counted(header, scores_all, layers_done, interval, n_seqs, total_tokens, epoch)) return;
   const int slot = layer < layers_done ? 0 : 1 + (layer - layers_done) / interval;
   int seq, c, begin, len;
-  if (!find_chunk(cu, n_seqs, kHist0Chunk, w, blockIdx.x, seq, c, begin, len)) return;
+  if (!find_chunk(cu, n_seqs, kPassChunk, w, blockIdx.x, seq, c, begin, len)) return;
   const int n = len - w;
-  const int i0 = c * kHist0Chunk;
-  const int i1 = i0 + kHist0Chunk < n ? i0 + kHist0Chunk : n;
-  constexpr int NV = kHist0Chunk / 4 / 256 + 1;
+  const int i0 = c * kPassChunk;
+  const int i1 = head >= Hkv ? i0 : (i0 + kPassChunk < n ? i0 + kPassChunk : n);
+  constexpr int NV = kPassChunk / 4 / kHeadThreads + 1;
   ChunkVectors<NV> cv;
   const int64_t e_lo = ((int64_t)layer * Hkv + head) * total_tokens + begin + i0;
   load_chunk<NV>(scores_all, (int64_t)L * Hkv * total_tokens, e_lo, e_lo + (i1 - i0), cv);
-  for (int b = threadIdx.x; b < kRadixBins * kHist0Copies; b += 256) h[b] = 0;
+  for (int b = threadIdx.x; b < kRadixBins * kHist0Copies; b += kPassThreads) h[b] = 0;
   __syncthreads();
   int* __restrict__ hc = h + (threadIdx.x & (kHist0Copies - 1));
   // Scores crowd into a few top digits (a quarter of an octave each) and pooling repeats values along a row, so a
@@ -227,21 +241,16 @@ __global__ __launch_bounds__(256) void rebalance_hist0_kernel(int n_seqs, int Hk
   };
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
-    if (cv.ok[j] == 0xf) {
-      count(cv.v[j].x);
-      count(cv.v[j].y);
-      count(cv.v[j].z);
-      count(cv.v[j].w);
-    } else if (cv.ok[j]) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (cv.ok[j] >> q & 1) count(lane_of(cv.v[j], q));
-    }
+    count(cv.v[j].x);
+    count(cv.v[j].y);
+    count(cv.v[j].z);
+    count(cv.v[j].w);
   }
+  if (cv.outside) atomicAdd(&hc[0], -cv.outside);
   if (run) atomicAdd(&hc[run_digit * kHist0Copies], run);
   __syncthreads();
   int32_t* __restrict__ g = tot0 + slot * tot0_words + (int64_t)seq * kRadixBins;
-  for (int b = threadIdx.x; b < kRadixBins; b += 256) {
+  for (int b = threadIdx.x; b < kRadixBins; b += kPassThreads) {
     int v = 0;
 #pragma unroll
     for (int c2 = 0; c2 < kHist0Copies; ++c2) v += h[b * kHist0Copies + c2];
@@ -310,7 +319,7 @@ __global__ __launch_bounds__(kFinalThreads) void rebalance_pick_kernel(int n_seq
   if (threadIdx.x == 0) { mine[2 * LEVEL] = digit; mine[2 * LEVEL + 1] = left; }
 }
 
-// Scans 1 and 2. grid = (chunk upper bound, Hkv, layers of the call's last update), 256 threads. A workgroup reads
+// Scans 1 and 2. grid = (chunk upper bound, groups of heads, layers of the call's last update). A workgroup reads
 // its chunk of one layer's scores once and takes it through the classes of the updates that cover the layer
 // (usually one: T moves little from one update to the next):
 //   PASS 1: histogram of the middle digit over elements with digit 0 == d0 -> tot1 (slot of the layer);
@@ -323,7 +332,7 @@ __global__ __launch_bounds__(kFinalThreads) void rebalance_pick_kernel(int n_seq
 // the L2, while its scores are on their way), and the sequence's first workgroup records it in `picks` for the
 // kernels behind.
 template <int PASS, bool PICKS_HERE>
-__global__ __launch_bounds__(256) void rebalance_scan_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
+__global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
                                                              int layers_done, int interval, int n_updates,
                                                              int mean_budget, const int32_t* __restrict__ tot0,
                                                              const float* __restrict__ scores_all,
@@ -341,30 +350,32 @@ __global__ __launch_bounds__(256) void rebalance_scan_kernel(int n_seqs, int Hkv
   __shared__ int cls_update[DKV_MAX_UPDATES];         // the classes of the updates that cover this layer (first members)
   __shared__ int n_cls;
   __shared__ int n_above[ROUND];
+  __shared__ uint32_t list[PASS == 2 ? kListCap : 1];
+  __shared__ int list_size;
   int seq, c, begin, len;
-  if (!find_chunk(cu, n_seqs, kScanChunk, w, blockIdx.x, seq, c, begin, len)) return;
-  const int head = blockIdx.y, layer = blockIdx.z;
+  if (!find_chunk(cu, n_seqs, kPassChunk, w, blockIdx.x, seq, c, begin, len)) return;
+  const int head = blockIdx.y * kHeadsPerGroup + threadIdx.x / kHeadThreads, layer = blockIdx.z;
   const int first_update = first_update_of(layer, layers_done, interval);   // < n_updates by the grid
   const int n = len - w;
-  const int i0 = c * kScanChunk;
-  const int i1 = i0 + kScanChunk < n ? i0 + kScanChunk : n;
-  constexpr int NV = kScanChunk / 4 / 256 + 1;
+  const int i0 = c * kPassChunk;
+  const int i1 = head >= Hkv ? i0 : (i0 + kPassChunk < n ? i0 + kPassChunk : n);
+  constexpr int NV = kPassChunk / 4 / kHeadThreads + 1;
   ChunkVectors<NV> cv;
   const int64_t e_lo = ((int64_t)layer * Hkv + head) * total_tokens + begin + i0;
   load_chunk<NV>(scores_all, (int64_t)L * Hkv * total_tokens, e_lo, e_lo + (i1 - i0), cv);
   if (PICKS_HERE) {                                      // n_updates == 1: update 0, class 0, slot 0
-    __shared__ int pick_scratch[256 / 64];
+    __shared__ int pick_scratch[kPassThreads / 64];
     __shared__ int pick_sh[2];
     int32_t* __restrict__ pk = picks + (int64_t)seq * 4;
-    const Bins<256, kRadixBins> bins = load_bins<256, kRadixBins>(
+    const Bins<kPassThreads, kRadixBins> bins = load_bins<kPassThreads, kRadixBins>(
         PASS == 1 ? tot0 + (int64_t)seq * kRadixBins : tot1 + (int64_t)seq * DKV_MAX_UPDATES * kRadixBins);
     const int rem = PASS == 1 ? global_k(cu, seq, w, Hkv, mean_budget, layers_done) : pk[1];
     const int d_top = PASS == 1 ? 0 : pk[0];
     int digit, left;
-    pick_digit<256, kRadixBins>(bins, rem, pick_scratch, pick_sh, digit, left);
+    pick_digit<kPassThreads, kRadixBins>(bins, rem, pick_scratch, pick_sh, digit, left);
     if (threadIdx.x == 0) {
       key_of[0] = PASS == 1 ? (uint32_t)digit : (((uint32_t)d_top << 11) | (uint32_t)digit);
-      if (c == 0 && head == 0 && layer == 0) { pk[2 * (PASS - 1)] = digit; pk[2 * (PASS - 1) + 1] = left; }
+      if (c == 0 && blockIdx.y == 0 && layer == 0) { pk[2 * (PASS - 1)] = digit; pk[2 * (PASS - 1) + 1] = left; }
     }
   } else if (threadIdx.x < n_updates) {
     const int32_t* __restrict__ pk = picks + ((int64_t)threadIdx.x * n_seqs + seq) * 4;
@@ -372,6 +383,7 @@ __global__ __launch_bounds__(256) void rebalance_scan_kernel(int n_seqs, int Hkv
   }
   __syncthreads();
   if (threadIdx.x == 0) {
+    list_size = 0;
     int k = 0;
     for (int update = first_update; update < n_updates; ++update)
       if (class_of(key_of, first_update, update) == update) cls_update[k++] = update;
@@ -383,49 +395,63 @@ __global__ __launch_bounds__(256) void rebalance_scan_kernel(int n_seqs, int Hkv
   // p lies in (key, end): PASS 1 any larger top digit, PASS 2 a larger middle digit under the same top digit.
   constexpr int SH = PASS == 1 ? 21 : 10;
   auto bin_of = [](uint32_t u) { return PASS == 1 ? ((u >> 10) & (uint32_t)(kRadixBins - 1)) : (u & (uint32_t)(kLowBins - 1)); };
-  for (int c0 = 0; c0 < classes; c0 += ROUND) {
-    const int in_round = classes - c0 < ROUND ? classes - c0 : ROUND;
-    for (int b = threadIdx.x; b < in_round * BINS; b += 256) h[b] = 0;
-    if (threadIdx.x < ROUND) n_above[threadIdx.x] = 0;
-    __syncthreads();
-    int mine[ROUND];
+  // Scan 2 looks at the elements that reach the lowest of the thresholds' prefixes: one or two in a hundred. They are
+  // collected first (list, any order), and the classes are taken through the list instead of through every element. With
+  // too many of them (long plateaus of equal scores at the threshold) the classes go through all elements, read again.
+  int n_listed = 0;
+  if constexpr (PASS == 2) {
+    uint32_t lowest = key_of[cls_update[0]];
+    for (int r = 1; r < classes; ++r) lowest = key_of[cls_update[r]] < lowest ? key_of[cls_update[r]] : lowest;
+    const uint32_t bound = lowest << 10;
+    if (lowest != 0u) {                                       // else everything reaches it, the zeros outside the chunk too
+      int mine = 0;
 #pragma unroll
-    for (int r = 0; r < ROUND; ++r) mine[r] = 0;
+      for (int j = 0; j < NV; ++j)
+        mine += (cv.v[j].x >= bound) + (cv.v[j].y >= bound) + (cv.v[j].z >= bound) + (cv.v[j].w >= bound);
+      const int incl = wave_prefix_sum(mine);
+      int base = 0;
+      if ((threadIdx.x & 63) == 63 && incl) base = atomicAdd(&list_size, incl);
+      int slot = __builtin_amdgcn_readlane(base, 63) + incl - mine;
+      __syncthreads();
+      n_listed = list_size;
+      if (n_listed <= kListCap) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      if (cv.ok[j] == 0xf) {
-        const uint32_t p0 = cv.v[j].x >> SH, p1 = cv.v[j].y >> SH, p2 = cv.v[j].z >> SH, p3 = cv.v[j].w >> SH;
-#pragma unroll
-        for (int r = 0; r < ROUND; ++r) {
-          if (r >= in_round) break;
-          const uint32_t key = key_of[cls_update[c0 + r]];
-          const uint32_t end = PASS == 1 ? (uint32_t)kRadixBins : (((key >> 11) + 1u) << 11);
-          const uint32_t span = end - key - 1u;   // p in (key, end)  <=>  p - key - 1 < span (unsigned)
-          mine[r] += (p0 - key - 1u < span) + (p1 - key - 1u < span) + (p2 - key - 1u < span) + (p3 - key - 1u < span);
-          if (p0 == key || p1 == key || p2 == key || p3 == key) {       // one branch per vector and class
-            int* __restrict__ hr = h + r * BINS;
-            if (p0 == key) atomicAdd(&hr[bin_of(cv.v[j].x)], 1);
-            if (p1 == key) atomicAdd(&hr[bin_of(cv.v[j].y)], 1);
-            if (p2 == key) atomicAdd(&hr[bin_of(cv.v[j].z)], 1);
-            if (p3 == key) atomicAdd(&hr[bin_of(cv.v[j].w)], 1);
-          }
-        }
-      } else if (cv.ok[j]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!(cv.ok[j] >> q & 1)) continue;
-          const uint32_t u = lane_of(cv.v[j], q), pq = u >> SH;
-#pragma unroll
-          for (int r = 0; r < ROUND; ++r) {
-            if (r >= in_round) break;
-            const uint32_t key = key_of[cls_update[c0 + r]];
-            const uint32_t end = PASS == 1 ? (uint32_t)kRadixBins : (((key >> 11) + 1u) << 11);
-            mine[r] += pq - key - 1u < end - key - 1u;
-            if (pq == key) atomicAdd(&h[r * BINS + bin_of(u)], 1);
-          }
+        for (int j = 0; j < NV; ++j) {
+          if (cv.v[j].x >= bound) list[slot++] = cv.v[j].x;
+          if (cv.v[j].y >= bound) list[slot++] = cv.v[j].y;
+          if (cv.v[j].z >= bound) list[slot++] = cv.v[j].z;
+          if (cv.v[j].w >= bound) list[slot++] = cv.v[j].w;
+          __builtin_amdgcn_sched_barrier(0);                  // vector by vector: side by side they take registers that cost occupancy
         }
       }
+    } else {
+      n_listed = kListCap + 1;
     }
+  }
+  int mine[ROUND];
+  auto start = [&](int in_round) {
+    for (int b = threadIdx.x; b < in_round * BINS; b += kPassThreads) h[b] = 0;
+    if (threadIdx.x < ROUND) n_above[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUND; ++r) mine[r] = 0;
+  };
+  // element by element, for the in_round classes from c0 on
+  auto take = [&](uint32_t u, int c0, int in_round) {
+    const uint32_t pq = u >> SH;
+#pragma unroll
+    for (int r = 0; r < ROUND; ++r) {
+      if (r >= in_round) break;
+      const uint32_t key = key_of[cls_update[c0 + r]];
+      mine[r] += pq > key && (PASS == 1 || pq >> 11 == key >> 11);
+      if (pq == key) atomicAdd(&h[r * BINS + bin_of(u)], 1);
+    }
+  };
+  auto take_all = [&](int c0, int in_round) {
+    const uint32_t* __restrict__ row = reinterpret_cast<const uint32_t*>(scores_all) + e_lo;
+    for (int i = threadIdx.x & (kHeadThreads - 1); i < i1 - i0; i += kHeadThreads) take(row[i], c0, in_round);
+  };
+  auto finish = [&](int c0, int in_round) {
 #pragma unroll
     for (int r = 0; r < ROUND; ++r) {
       if (r >= in_round) break;
@@ -438,7 +464,7 @@ __global__ __launch_bounds__(256) void rebalance_scan_kernel(int n_seqs, int Hkv
       const int64_t cls = (int64_t)cls_update[c0 + r] * always_words;   // the class's block
       if (threadIdx.x == 0 && n_above[r])
         atomicAdd(&above[cls + ((int64_t)(PASS - 1) * n_seqs + seq) * L + layer], n_above[r]);
-      for (int b = threadIdx.x; b < BINS; b += 256) {
+      for (int b = threadIdx.x; b < BINS; b += kPassThreads) {
         const int v = h[r * BINS + b];
         if (!v) continue;
         if (PASS == 1) {
@@ -449,7 +475,39 @@ __global__ __launch_bounds__(256) void rebalance_scan_kernel(int n_seqs, int Hkv
         }
       }
     }
-    __syncthreads();                                                    // h and n_above are reused by the next round
+  };
+  if constexpr (PASS == 2) {
+    static_assert(ROUND >= DKV_MAX_UPDATES, "all classes in one round");
+    start(classes);
+    if (n_listed <= kListCap) {
+      for (int i = threadIdx.x; i < n_listed; i += kPassThreads) take(list[i], 0, classes);
+    } else {
+      take_all(0, classes);
+    }
+    finish(0, classes);
+  } else {
+    start(1);
+    const uint32_t key = key_of[cls_update[0]];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const uint32_t p0 = cv.v[j].x >> SH, p1 = cv.v[j].y >> SH, p2 = cv.v[j].z >> SH, p3 = cv.v[j].w >> SH;
+      mine[0] += (p0 > key) + (p1 > key) + (p2 > key) + (p3 > key);
+      if (p0 == key || p1 == key || p2 == key || p3 == key) {           // one branch per vector
+        if (p0 == key) atomicAdd(&h[bin_of(cv.v[j].x)], 1);
+        if (p1 == key) atomicAdd(&h[bin_of(cv.v[j].y)], 1);
+        if (p2 == key) atomicAdd(&h[bin_of(cv.v[j].z)], 1);
+        if (p3 == key) atomicAdd(&h[bin_of(cv.v[j].w)], 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);                      // as above
+    }
+    if (cv.outside && key == 0u) atomicAdd(&h[0], -cv.outside);         // the zeros outside the chunk
+    finish(0, 1);
+    for (int c0 = 1; c0 < classes; ++c0) {                    // updates whose thresholds lie in other top digits: rare
+      __syncthreads();                                        // h and n_above are reused
+      start(1);
+      take_all(c0, 1);
+      finish(c0, 1);
+    }
   }
 }
 
@@ -596,27 +654,27 @@ hipError_t launch_rebalance(const Params& p, int layers_done, int n_updates, uin
          reinterpret_cast<uint32_t*>(tot1), clear_words, reinterpret_cast<uint32_t*>(tot0), (size_t)tot0_words, header,
          scores_all, layers_done, p.interval, p.n_seqs, p.total_tokens, epoch, picks, n_updates * p.n_seqs * 4);
   const int last_done = layers_done + (n_updates - 1) * p.interval;
-  const dim3 grid0(p.total_tokens / kHist0Chunk + p.n_seqs, p.Hkv, last_done);
-  launch(DKV_KERNEL_REBALANCE_HIST, rebalance_hist0_kernel, grid0, dim3(256), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+  const int head_groups = (p.Hkv + kHeadsPerGroup - 1) / kHeadsPerGroup;
+  const dim3 grid(p.total_tokens / kPassChunk + p.n_seqs, head_groups, last_done);
+  launch(DKV_KERNEL_REBALANCE_HIST, rebalance_hist0_kernel, grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
          p.total_tokens, layers_done, p.interval, scores_all, cu, header, epoch, tot0, tot0_words);
   const dim3 grid_pick(p.n_seqs, n_updates);
-  const dim3 grid(p.total_tokens / kScanChunk + p.n_seqs, p.Hkv, last_done);
   if (n_updates == 1) {     // the scans pick their digits themselves: two launches less
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<1, true>), grid, dim3(256), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<1, true>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<2, true>), grid, dim3(256), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<2, true>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
   } else {
     launch(DKV_KERNEL_REBALANCE_PICK, rebalance_pick_kernel<0>, grid_pick, dim3(kFinalThreads), 0, st, p.n_seqs, p.w, p.Hkv,
            p.mean_budget, layers_done, p.interval, cu, tot0, tot0_words, tot1, always_words, picks);
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<1, false>), grid, dim3(256), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<1, false>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
     launch(DKV_KERNEL_REBALANCE_PICK, rebalance_pick_kernel<1>, grid_pick, dim3(kFinalThreads), 0, st, p.n_seqs, p.w, p.Hkv,
            p.mean_budget, layers_done, p.interval, cu, tot0, tot0_words, tot1, always_words, picks);
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<2, false>), grid, dim3(256), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<2, false>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
   }

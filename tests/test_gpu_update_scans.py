@@ -1,0 +1,54 @@
+"""GPU parity of the update's passes over the scores where their workgroups' shares end or overflow: one to nine heads
+(four share a workgroup), rows of one position, of a chunk of 8192 and one more or less, rows that start off a 16-byte
+boundary, more equal scores at the threshold than a workgroup of the last scan collects, zero scores at the threshold,
+updates whose thresholds lie in different top digits. Hit counts and budgets bit-exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dkv_oracle as O
+from paper_2412_14838_amd import workloads as W
+from paper_2412_14838_amd.pipeline import Compressor
+
+pytestmark = pytest.mark.gpu
+
+
+def _scores(kind, cfg, rng):
+    shape = (cfg.L, cfg.Hkv, cfg.total_tokens)
+    A = np.abs(rng.standard_normal(shape)).astype(np.float32) + np.float32(1e-3)
+    if kind == "plateau":
+        A[rng.random(shape) < 0.4] = 8.0
+    elif kind == "zeros":
+        A[rng.random(shape) < 0.995] = 0.0
+    elif kind == "scaled":                                    # every layer an eighth of the one before: the thresholds fall
+        A *= np.float32(0.125) ** np.arange(cfg.L, dtype=np.float32)[::-1, None, None]
+    return A
+
+
+@pytest.mark.parametrize("kind", ["smooth", "plateau", "zeros", "scaled"])
+@pytest.mark.parametrize("Hkv,seqlens", [(1, (8192 + 8, 9)), (3, (8191 + 8, 8193 + 8, 41)), (4, (1201,)), (5, (16384 + 9, 77)),
+                                         (9, (333, 8, 2050))])
+def test_update_scans_match_the_oracle(Hkv, seqlens, kind):
+    cfg = W.Workload("scans", L=6, Hq=Hkv, Hkv=Hkv, d=64, seqlens=seqlens, dtype="bf16", w=8, P=7, mean_budget=40, layer_max=160,
+                     interval=2, seed=1)
+    A = _scores(kind, cfg, np.random.default_rng(7 * Hkv + len(kind)))
+    cu = cfg.cu_seqlens
+    for batch in (False, True):
+        comp = Compressor(cfg, keep_cache=False)
+        comp.scores.copy_(torch.from_numpy(A))
+        comp.select_layers(0, cfg.L)
+        if batch:
+            comp.rebalance_batch(2, 3)
+        else:
+            for l in (2, 4, 6):
+                comp.rebalance(l)
+        torch.cuda.synchronize()
+        hits, budgets = comp.hits_all.cpu().numpy(), comp.budgets_all.cpu().numpy()
+        for slot, l in enumerate((2, 4, 6)):
+            for s in range(cfg.n_seqs):
+                pre = seqlens[s] - cfg.w
+                if pre <= 0:
+                    continue
+                cnt, _, Zp = O.update_buffer_length([A[i][:, cu[s]:cu[s] + pre] for i in range(l)], cfg.layer_max, cfg.mean_budget, cfg.L)
+                assert np.array_equal(hits[slot, s, :l], cnt), (batch, l, s)
+                assert np.array_equal(budgets[slot, s, :l], np.minimum(Zp, 2**31 - 1)), (batch, l, s)
