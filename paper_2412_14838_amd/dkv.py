@@ -124,16 +124,36 @@ def desc_from_workload(cfg, **override) -> dkv_desc:
 
 
 def _ptr(t) -> Optional[int]:
-    return None if t is None else t.data_ptr()
+    """Device address of a tensor; None and addresses (ints) pass through."""
+    return t if t is None or t.__class__ is int else t.data_ptr()
+
+
+def layer_ptr(t, layer: int) -> int:
+    """Address of t[layer], without the tensor (a view costs more than the rest of a call's marshalling)."""
+    n = t.shape[0]
+    if not -n <= layer < n:
+        raise IndexError("layer %d of a tensor of %d layers" % (layer, n))
+    return t.data_ptr() + int(layer if layer >= 0 else layer + n) * t.stride(0) * t.element_size()
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        # the address of torch.cuda.current_stream(), without the Stream object
+        return _torch()._C._cuda_getCurrentRawStream(_torch().cuda.current_device()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
+
+
+_torch_module = None
+
+
+def _torch():
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _check(status: int, where: str) -> None:
@@ -176,7 +196,7 @@ def dkv_score_window(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, 
                      workspace, stream=None) -> None:
     _check(load().dkv_score_window(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head, _ptr(cu_seqlens),
                                    _ptr(scores_out), scores_stride_head, _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream(stream)), "dkv_score_window")
+                                   workspace.nbytes, _stream(stream)), "dkv_score_window")
 
 
 def dkv_score_window_static(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
@@ -215,7 +235,7 @@ def dkv_score_window_layers(desc, layer_begin, q_layers, k_layers, k_stride_toke
     ks = (C.c_void_p * n)(*[t.data_ptr() for t in k_layers])
     _check(load().dkv_score_window_layers(C.byref(desc), layer_begin, n, qs, ks, k_stride_token, k_stride_head,
                                           _ptr(cu_seqlens), _ptr(scores_all), _ptr(workspace),
-                                          workspace.numel() * workspace.element_size(), _stream(stream)),
+                                          workspace.nbytes, _stream(stream)),
            "dkv_score_window_layers")
 
 
@@ -228,7 +248,7 @@ def dkv_score_window_lse_layers(desc, layer_begin, q_layers, k_layers, k_stride_
     ls = (C.c_void_p * n)(*[t.data_ptr() for t in lse_layers])
     _check(load().dkv_score_window_lse_layers(C.byref(desc), layer_begin, n, qs, ks, k_stride_token, k_stride_head,
                                               _ptr(cu_seqlens), ls, _ptr(scores_all), _ptr(workspace),
-                                              workspace.numel() * workspace.element_size(), _stream(stream)),
+                                              workspace.nbytes, _stream(stream)),
            "dkv_score_window_lse_layers")
 
 
@@ -236,7 +256,7 @@ def dkv_score_window_stats(desc, q_win, k, k_stride_token, k_stride_head, cu_seq
                            workspace, stream=None) -> None:
     _check(load().dkv_score_window_stats(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head,
                                          _ptr(cu_seqlens), _ptr(scores_out), scores_stride_head, _ptr(workspace),
-                                         workspace.numel() * workspace.element_size(), _stream(stream)),
+                                         workspace.nbytes, _stream(stream)),
            "dkv_score_window_stats")
 
 
@@ -244,7 +264,7 @@ def dkv_score_window_emit(desc, q_win, k, k_stride_token, k_stride_head, cu_seql
                           workspace, stream=None) -> None:
     _check(load().dkv_score_window_emit(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head,
                                         _ptr(cu_seqlens), _ptr(scores_out), scores_stride_head, _ptr(workspace),
-                                        workspace.numel() * workspace.element_size(), _stream(stream)),
+                                        workspace.nbytes, _stream(stream)),
            "dkv_score_window_emit")
 
 
@@ -257,21 +277,21 @@ def dkv_score_window_lse(desc, q_win, k, k_stride_token, k_stride_head, cu_seqle
 
 def dkv_row_lse(desc, k_stride_token, cu_seqlens, lse_out, workspace, stream=None) -> None:
     _check(load().dkv_row_lse(C.byref(desc), k_stride_token, _ptr(cu_seqlens), _ptr(lse_out), _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _stream(stream)), "dkv_row_lse")
+                              workspace.nbytes, _stream(stream)), "dkv_row_lse")
 
 
 def dkv_select_topk(desc, layer, scores, scores_stride_head, cu_seqlens, idx_out, counts, workspace,
                     stream=None) -> None:
     _check(load().dkv_select_topk(C.byref(desc), layer, _ptr(scores), scores_stride_head, _ptr(cu_seqlens),
                                   _ptr(idx_out), _ptr(counts), _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), _stream(stream)), "dkv_select_topk")
+                                  workspace.nbytes, _stream(stream)), "dkv_select_topk")
 
 
 def dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, idx_all, counts, workspace,
                            stream=None) -> None:
     _check(load().dkv_select_topk_layers(C.byref(desc), layer_begin, n_layers, _ptr(scores_all), _ptr(cu_seqlens),
                                          _ptr(idx_all), _ptr(counts), _ptr(workspace),
-                                         workspace.numel() * workspace.element_size(), _stream(stream)),
+                                         workspace.nbytes, _stream(stream)),
            "dkv_select_topk_layers")
 
 
@@ -291,14 +311,14 @@ def dkv_rebalance(desc, layers_done, epoch, scores_all, cu_seqlens, counts, budg
                   stream=None) -> None:
     _check(load().dkv_rebalance(C.byref(desc), layers_done, epoch, _ptr(scores_all), _ptr(cu_seqlens), _ptr(counts),
                                 _ptr(budgets_out), _ptr(hits_out), _ptr(workspace),
-                                workspace.numel() * workspace.element_size(), _stream(stream)), "dkv_rebalance")
+                                workspace.nbytes, _stream(stream)), "dkv_rebalance")
 
 
 def dkv_rebalance_batch(desc, layers_done, n_updates, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out,
                         out_stride_update, workspace, stream=None) -> None:
     _check(load().dkv_rebalance_batch(C.byref(desc), layers_done, n_updates, epoch, _ptr(scores_all), _ptr(cu_seqlens),
                                       _ptr(counts), _ptr(budgets_out), _ptr(hits_out), out_stride_update,
-                                      _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                      _ptr(workspace), workspace.nbytes,
                                       _stream(stream)), "dkv_rebalance_batch")
 
 
@@ -320,7 +340,7 @@ def dkv_decode_attention(desc, layer, q_new, kb, vb, stride_seq, stride_head, cu
                          stream=None) -> None:
     _check(load().dkv_decode_attention(C.byref(desc), layer, _ptr(q_new), _ptr(kb), _ptr(vb), stride_seq, stride_head,
                                        _ptr(cu_seqlens), _ptr(counts), _ptr(out), _ptr(lse_out), _ptr(workspace),
-                                       workspace.numel() * workspace.element_size(), _stream(stream)),
+                                       workspace.nbytes, _stream(stream)),
            "dkv_decode_attention")
 
 
@@ -329,7 +349,7 @@ def dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, 
     _check(load().dkv_decode_attention_layers(C.byref(desc), layer_begin, n_layers, _ptr(q_new_all), _ptr(kb_all),
                                               _ptr(vb_all), stride_layer, stride_seq, stride_head, _ptr(cu_seqlens),
                                               _ptr(counts), _ptr(out_all), _ptr(lse_all), _ptr(workspace),
-                                              workspace.numel() * workspace.element_size(), _stream(stream)),
+                                              workspace.nbytes, _stream(stream)),
            "dkv_decode_attention_layers")
 
 

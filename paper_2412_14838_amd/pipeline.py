@@ -85,16 +85,16 @@ class Compressor:
         d = self.cfg.d
         st = d if stride_token is None else stride_token
         sh = self.cfg.total_tokens * d if stride_head is None else stride_head
-        dkv.dkv_score_window(self.desc, q_win, k, st, sh, self.cu, self.scores[layer], self.cfg.total_tokens, self.ws,
-                             stream)
+        dkv.dkv_score_window(self.desc, q_win, k, st, sh, self.cu, dkv.layer_ptr(self.scores, layer),
+                             self.cfg.total_tokens, self.ws, stream)
 
     def score_from_lse(self, layer, q_win, k, lse, stride_token=None, stride_head=None, stream=None):
         """One sweep over K with the caller's row normalisers lse [n_seqs][Hq][w] (natural log, fp32)."""
         d = self.cfg.d
         st = d if stride_token is None else stride_token
         sh = self.cfg.total_tokens * d if stride_head is None else stride_head
-        dkv.dkv_score_window_lse(self.desc, q_win, k, st, sh, self.cu, lse, self.scores[layer], self.cfg.total_tokens,
-                                 stream)
+        dkv.dkv_score_window_lse(self.desc, q_win, k, st, sh, self.cu, lse, dkv.layer_ptr(self.scores, layer),
+                                 self.cfg.total_tokens, stream)
 
     def row_lse(self, lse_out, stride_token=None, stream=None):
         """The normalisers of the layer scored last: lse_out [n_seqs][Hq][w] fp32."""
@@ -102,15 +102,16 @@ class Compressor:
         dkv.dkv_row_lse(self.desc, st, self.cu, lse_out, self.ws, stream)
 
     def select(self, layer, stream=None):
-        dkv.dkv_select_topk(self.desc, layer, self.scores[layer], self.cfg.total_tokens, self.cu, self.idx[layer],
-                            self.counts, self.ws, stream)
+        dkv.dkv_select_topk(self.desc, layer, dkv.layer_ptr(self.scores, layer), self.cfg.total_tokens, self.cu,
+                            dkv.layer_ptr(self.idx, layer), self.counts, self.ws, stream)
 
     def gather(self, layer, k, v, stride_token=None, stride_head=None, stream=None):
         d = self.cfg.d
         st = d if stride_token is None else stride_token
         sh = self.cfg.total_tokens * d if stride_head is None else stride_head
-        dkv.dkv_gather_kv(self.desc, layer, k, v, st, sh, self.cu, self.idx[layer], self.counts, self.kb[layer],
-                          self.vb[layer], self.cfg.Hkv * self.slots * d, self.slots * d, stream)
+        dkv.dkv_gather_kv(self.desc, layer, k, v, st, sh, self.cu, dkv.layer_ptr(self.idx, layer), self.counts,
+                          dkv.layer_ptr(self.kb, layer), dkv.layer_ptr(self.vb, layer), self.cfg.Hkv * self.slots * d,
+                          self.slots * d, stream)
 
     def select_layers(self, layer_begin, n_layers, stream=None):
         dkv.dkv_select_topk_layers(self.desc, layer_begin, n_layers, self.scores, self.cu, self.idx, self.counts,
@@ -139,8 +140,8 @@ class Compressor:
     def decode_attention(self, layer, q_new, out, lse_out=None, stream=None):
         """Attention of one new token per sequence (q_new [n_seqs][Hq][d]) over layer `layer` of the compressed cache."""
         d = self.cfg.d
-        dkv.dkv_decode_attention(self.desc, layer, q_new, self.kb[layer], self.vb[layer], self.cfg.Hkv * self.slots * d,
-                                 self.slots * d, self.cu, self.counts, out, lse_out, self.ws, stream)
+        dkv.dkv_decode_attention(self.desc, layer, q_new, dkv.layer_ptr(self.kb, layer), dkv.layer_ptr(self.vb, layer),
+                                 self.cfg.Hkv * self.slots * d, self.slots * d, self.cu, self.counts, out, lse_out, self.ws, stream)
 
     def decode_attention_layers(self, layer_begin, n_layers, q_new_all, out_all, lse_all=None, stream=None):
         """The same for n_layers consecutive layers in one call: q_new_all, out_all [n_layers][n_seqs][Hq][d]."""
@@ -182,7 +183,7 @@ class Compressor:
         dkv.dkv_apply_budgets(self.desc, n_layers, self.preset, self.counts, stream)
 
     def select_recent(self, layer, stream=None):
-        dkv.dkv_select_recent(self.desc, layer, self.n_sink, self.cu, self.idx[layer], self.counts, stream)
+        dkv.dkv_select_recent(self.desc, layer, self.n_sink, self.cu, dkv.layer_ptr(self.idx, layer), self.counts, stream)
 
     def _step_preset(self, layer, q_win, k, v, **strides):
         # the comparison patterns: the layer's candidates, cut to the preset budget, then the compaction of what is left
