@@ -356,6 +356,13 @@ int dkv_pack_cache(const dkv_desc* desc, const int32_t* cu_seqlens, const int32_
                    void* v_packed, int64_t capacity_rows, int64_t* row_offsets, void* stream);
 
 /*
+ * Zeros in the rows of k_packed and v_packed that dkv_pack_cache with the same capacity_rows and the row_offsets it wrote
+ * left alone: for a caller that takes uninitialised tensors and wants no garbage behind the last row. One kernel.
+ */
+int dkv_pack_zero_tail(const dkv_desc* desc, const int64_t* row_offsets, void* k_packed, void* v_packed,
+                       int64_t capacity_rows, void* stream);
+
+/*
  * Decode-phase attention of one new token per sequence over the compressed cache of layer `layer` (Section 4.3:
  * the decoding phase is unchanged, i.e. ordinary softmax attention over the keys and values the prefill
  * retained). For sequence q and query head g (KV head h = g / G):

@@ -439,6 +439,17 @@ int dkv_pack_cache(const dkv_desc* desc, const int32_t* cu_seqlens, const int32_
   return e == hipSuccess ? DKV_OK : DKV_ERR_LAUNCH;
 }
 
+int dkv_pack_zero_tail(const dkv_desc* desc, const int64_t* row_offsets, void* k_packed, void* v_packed, int64_t capacity_rows,
+                       void* stream) {
+  const int st = validate_desc(desc);
+  if (st != DKV_OK) return st;
+  if (!row_offsets || !k_packed || !v_packed || !aligned16(k_packed) || !aligned16(v_packed)) return DKV_ERR_INVALID_ARG;
+  if (reinterpret_cast<uintptr_t>(row_offsets) % 8 != 0 || capacity_rows < 0) return DKV_ERR_INVALID_ARG;
+  const hipError_t e = launch_pack_zero_tail(make_params(*desc), desc->dtype == DKV_BF16 ? 2 : 4, row_offsets, k_packed, v_packed,
+                                             capacity_rows, static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? DKV_OK : DKV_ERR_LAUNCH;
+}
+
 int dkv_decode_attention(const dkv_desc* desc, int32_t layer, const void* q_new, const void* kb, const void* vb,
                          int64_t stride_seq, int64_t stride_head, const int32_t* cu_seqlens, const int32_t* counts,
                          float* out, float* lse_out, void* workspace, size_t workspace_bytes, void* stream) {

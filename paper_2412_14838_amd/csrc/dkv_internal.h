@@ -171,6 +171,8 @@ hipError_t launch_pack_cache(const Params& p, int elt_bytes, const int32_t* cu, 
                              const void* vb, int64_t stride_layer, int64_t stride_seq, int64_t stride_head,
                              void* k_packed, void* v_packed, int64_t capacity_rows, int64_t* row_offsets,
                              hipStream_t st);
+hipError_t launch_pack_zero_tail(const Params& p, int elt_bytes, const int64_t* row_offsets, void* k_packed, void* v_packed,
+                                 int64_t capacity_rows, hipStream_t st);
 hipError_t launch_decode(const Params& p, int dtype, int layer, int n_layers, const void* q_new, const void* kb,
                          const void* vb, int64_t stride_layer, int64_t stride_seq, int64_t stride_head, const int32_t* cu,
                          const int32_t* counts, float* out, float* lse_out, char* ws, const WorkspaceLayout& wl,

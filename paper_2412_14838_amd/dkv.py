@@ -22,7 +22,7 @@ EXPORTS = ("dkv_version", "dkv_status_string", "dkv_workspace_bytes", "dkv_profi
            "dkv_score_window_layers", "dkv_score_window_stats", "dkv_score_window_emit", "dkv_score_window_lse", "dkv_score_window_lse_layers", "dkv_row_lse", "dkv_select_topk", "dkv_select_topk_layers", "dkv_rebalance", "dkv_rebalance_batch",
            "dkv_gather_kv", "dkv_gather_kv_layers", "dkv_pack_cache", "dkv_decode_attention", "dkv_layer_budgets",
            "dkv_apply_budgets", "dkv_select_recent", "dkv_score_window_static", "dkv_static_scratch_limit", "dkv_score_path",
-           "dkv_decode_attention_layers")
+           "dkv_decode_attention_layers", "dkv_pack_zero_tail")
 DKV_SCHEDULE_FIXED, DKV_SCHEDULE_PYRAMID = 0, 1
 
 
@@ -82,6 +82,8 @@ def load() -> C.CDLL:
     lib.dkv_gather_kv_layers.argtypes = [D, I32, I32, P, P, I64, I64, P, P, P, P, P, I64, I64, I64, P]
     lib.dkv_pack_cache.restype = C.c_int
     lib.dkv_pack_cache.argtypes = [D, P, P, P, P, I64, I64, I64, P, P, I64, P, P]
+    lib.dkv_pack_zero_tail.restype = C.c_int
+    lib.dkv_pack_zero_tail.argtypes = [D, P, P, P, I64, P]
     lib.dkv_decode_attention.restype = C.c_int
     lib.dkv_decode_attention.argtypes = [D, I32, P, P, P, I64, I64, P, P, P, P, P, SZ, P]
     lib.dkv_decode_attention_layers.restype = C.c_int
@@ -336,6 +338,11 @@ def dkv_pack_cache(desc, cu_seqlens, counts, kb_all, vb_all, stride_layer, strid
                                  _ptr(row_offsets), _stream(stream)), "dkv_pack_cache")
 
 
+def dkv_pack_zero_tail(desc, row_offsets, k_packed, v_packed, capacity_rows, stream=None) -> None:
+    _check(load().dkv_pack_zero_tail(C.byref(desc), _ptr(row_offsets), _ptr(k_packed), _ptr(v_packed), capacity_rows,
+                                     _stream(stream)), "dkv_pack_zero_tail")
+
+
 def dkv_decode_attention(desc, layer, q_new, kb, vb, stride_seq, stride_head, cu_seqlens, counts, out, lse_out, workspace,
                          stream=None) -> None:
     _check(load().dkv_decode_attention(C.byref(desc), layer, _ptr(q_new), _ptr(kb), _ptr(vb), stride_seq, stride_head,
@@ -350,7 +357,7 @@ def dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, 
                                               _ptr(vb_all), stride_layer, stride_seq, stride_head, _ptr(cu_seqlens),
                                               _ptr(counts), _ptr(out_all), _ptr(lse_all), _ptr(workspace),
                                               workspace.nbytes, _stream(stream)),
-           "dkv_decode_attention_layers")
+           "dkv_decode_attention_layers", "dkv_pack_zero_tail")
 
 
 def alloc_workspace(desc, device="cuda"):

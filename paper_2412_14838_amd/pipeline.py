@@ -126,15 +126,17 @@ class Compressor:
                                  self.cfg.Hkv * self.slots * d, self.slots * d, stream)
 
     def pack(self, capacity_rows=None, stream=None):
-        """Tight copy of the final cache: returns (k_packed [rows][d], v_packed, row_offsets int64 [n_seqs*L + 1])."""
+        """Tight copy of the final cache: returns (k_packed [rows][d], v_packed, row_offsets int64 [n_seqs*L + 1]); rows
+        past the last block that fits are zeros."""
         cfg, d = self.cfg, self.cfg.d
         if capacity_rows is None:
             capacity_rows = cfg.n_seqs * cfg.L * cfg.Hkv * self.slots
-        kp = torch.zeros((capacity_rows, d), dtype=self.tdtype, device=self.device)
-        vp = torch.zeros_like(kp)
-        off = torch.zeros(cfg.n_seqs * cfg.L + 1, dtype=torch.int64, device=self.device)
+        kp = torch.empty((capacity_rows, d), dtype=self.tdtype, device=self.device)
+        vp = torch.empty_like(kp)
+        off = torch.empty(cfg.n_seqs * cfg.L + 1, dtype=torch.int64, device=self.device)
         dkv.dkv_pack_cache(self.desc, self.cu, self.counts, self.kb, self.vb, cfg.n_seqs * cfg.Hkv * self.slots * d,
                            cfg.Hkv * self.slots * d, self.slots * d, kp, vp, capacity_rows, off, stream)
+        dkv.dkv_pack_zero_tail(self.desc, off, kp, vp, capacity_rows, stream)      # rows no block has filled
         return kp, vp, off
 
     def decode_attention(self, layer, q_new, out, lse_out=None, stream=None):
