@@ -357,7 +357,7 @@ def dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, 
                                               _ptr(vb_all), stride_layer, stride_seq, stride_head, _ptr(cu_seqlens),
                                               _ptr(counts), _ptr(out_all), _ptr(lse_all), _ptr(workspace),
                                               workspace.nbytes, _stream(stream)),
-           "dkv_decode_attention_layers", "dkv_pack_zero_tail")
+           "dkv_decode_attention_layers")
 
 
 def alloc_workspace(desc, device="cuda"):
