@@ -321,14 +321,14 @@ __device__ inline void stream_tile(int li, int ahead, int n_steps, int n_layers,
 // ------------------------------------------------------------------------------------------------------
 // Row statistics: one partial (max, sum of exp2) per layer, chunk and row, in the log2 domain:
 // y = c * x with c = softmax_scale * log2(e); partial = (max y, sum exp2(y - max y)).
-// grid = (chunk upper bound over all S keys, Hkv). A workgroup owns one chunk of one (sequence, KV head) and
-// takes it through all n_layers layers of the launch: the geometry is the same for every layer, and while the
+// grid = (chunk upper bound over all S keys, Hkv, shares of layers_each layers). A workgroup owns one chunk of one
+// (sequence, KV head) and takes it through the layers of its share (all of the launch, where the chunks fill the device): the geometry is the same for every layer, and while the
 // last two steps of a layer run, the first two key tiles and the Q block of the next layer are already being
 // fetched, so that only the first layer pays for a cold start.
 // ------------------------------------------------------------------------------------------------------
 template <int RS, int KS>
-__global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int chunk, int n_layers, ScoreLayers src,
-                                                                 int64_t stride_token_b, int64_t stride_head_b,
+__global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int chunk, int n_layers, int layers_each,
+                                                                 ScoreLayers src, int64_t stride_token_b, int64_t stride_head_b,
                                                                  const int32_t* __restrict__ cu,
                                                                  float* __restrict__ partials,
                                                                  int64_t partials_stride_layer) {
@@ -343,6 +343,8 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
   int seq, c, nc, begin, S, first_full, n_full;
   if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, 0, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
   const int head = blockIdx.y;
+  const int first_layer = blockIdx.z * layers_each;      // the layers of the call this workgroup takes its chunk through
+  if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rs = wave % RS, ks = wave / RS;
   const int c0 = c * chunk;
@@ -369,11 +371,11 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
   int k_layer;
   const char* k_ptr;
   {
-    const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[0] + k_off, stride_b, 0, len - 1);
-    const typename PieceVec<QS::kPieces>::type q0 = load_q_pieces<RS, KS>(src.q[0] + q_off, p.rows);
-    const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[0] + k_off, stride_b, TL::kKeys, len - 1);
+    const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, 0, len - 1);
+    const typename PieceVec<QS::kPieces>::type q0 = load_q_pieces<RS, KS>(src.q[first_layer] + q_off, p.rows);
+    const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, TL::kKeys, len - 1);
     int l2, t2;
-    stream_tile(0, 2, n_steps, n_layers, l2, t2);
+    stream_tile(first_layer, 2, n_steps, n_layers, l2, t2);
     ld[0] = load_tile<RS, KS>(src.k[l2] + k_off, stride_b, t2 * TL::kKeys, len - 1);   // stored by the first step
     k_layer = l2;
     k_ptr = src.k[l2] + k_off;
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
   // before a layer's last one fetches the next layer's Q block into LDS; the last step, which has nothing of its
   // own layer left to multiply, takes that Q as its operand for the next layer's tile 0, and is followed by the
   // layer's epilogue - so the matrix pipe, the vector ALU and the loads never pause between layers.
-  int li = 0, it = 0;                               // layer of the call and step within it (uniform over the workgroup)
+  int li = first_layer, it = 0;                     // layer of the call and step within it (uniform over the workgroup)
   float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.0f, 0.0f};
   auto step = [&](auto buffer, floatx16 (&a)[2], floatx16 (&b)[2]) {
     constexpr int kBuf = decltype(buffer)::value;   // buffer of this step's tile
@@ -513,7 +515,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
 
 // ------------------------------------------------------------------------------------------------------
 // Scores: a[s] = row_scale * sum_rows exp2(c * x[row, s] - lse2[row]) over the chunk's outputs plus the pooling
-// halo, max-pooled over the prefix. grid = (chunk upper bound over the S' prefix outputs, Hkv).
+// halo, max-pooled over the prefix. grid = (chunk upper bound over the S' prefix outputs, Hkv, shares of the layers).
 // ------------------------------------------------------------------------------------------------------
 // Column sums of one row slab in the emit kernel: the chunk's outputs, the pooling halo and two tiles of slack
 // (the last step computes a tile past the range).
@@ -609,8 +611,8 @@ constexpr int kMaxChunk = 4096;
 // (supplied by the caller, natural log, single-layer launches) or are merged here from the chunk partials
 // (single-layer launches).
 template <int RS, int KS>
-__global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int chunk, int n_layers, ScoreLayers src,
-                                                                int64_t stride_token_b, int64_t stride_head_b,
+__global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int chunk, int n_layers, int layers_each,
+                                                                ScoreLayers src, int64_t stride_token_b, int64_t stride_head_b,
                                                                 const int32_t* __restrict__ cu,
                                                                 const float* __restrict__ partials,
                                                                 const float* __restrict__ lse_rows,
@@ -635,6 +637,8 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   int seq, c, nc, begin, S, first_full, n_full;
   if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, p.w, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
   const int head = blockIdx.y;
+  const int first_layer = blockIdx.z * layers_each;          // as in the statistics kernel
+  if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rs = wave % RS, ks = wave / RS;
   const int prefix = S - p.w;                                // > 0 here
@@ -667,13 +671,13 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   int k_layer;                    // layer and K pointer of the tiles being fetched (see the statistics kernel)
   const char* k_ptr;
   {
-    const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[0] + k_off, stride_b, emit_tile(n_iter, 0) * TL::kKeys, len - 1);
+    const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 0) * TL::kKeys, len - 1);
     typename PieceVec<QS::kPieces>::type q0;
-    if (QS::kEmitViaLds) q0 = load_q_pieces<RS, KS>(src.q[0] + q_off, p.rows);
-    else load_q_frags(src.q[0] + q_off, rs, p.rows, qf);
-    const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[0] + k_off, stride_b, emit_tile(n_iter, 1) * TL::kKeys, len - 1);
+    if (QS::kEmitViaLds) q0 = load_q_pieces<RS, KS>(src.q[first_layer] + q_off, p.rows);
+    else load_q_frags(src.q[first_layer] + q_off, rs, p.rows, qf);
+    const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 1) * TL::kKeys, len - 1);
     int l2, t2;
-    stream_tile(0, 2, n_steps, n_layers, l2, t2);
+    stream_tile(first_layer, 2, n_steps, n_layers, l2, t2);
     ld[0] = load_tile<RS, KS>(src.k[l2] + k_off, stride_b, emit_tile(n_iter, t2) * TL::kKeys, len - 1);   // stored by the first step
     k_layer = l2;
     k_ptr = src.k[l2] + k_off;
@@ -683,7 +687,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   }
   // ---- lse2[row] of the first layer
   if (lse_rows != nullptr) {
-    if (tid < kRows) lse_s[0][tid] = lse_row[0];
+    if (tid < kRows) lse_s[first_layer & 1][tid] = lse_row[first_layer * lse_rows_stride_layer];
   } else if (lse_in != nullptr) {
     if (tid < kRows)   // padding rows get +inf: exp2(x - inf) = 0
       lse_s[0][tid] = tid < p.rows ? lse_in[((int64_t)seq * p.Hq + (int64_t)head * p.G) * p.w + tid] * kLog2e : INFINITY;
@@ -707,7 +711,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   // by the layer's epilogue. Loads that a step consumes itself are issued before the tile's, which stay in flight
   // past the end of the step (loads return in order). Prefix keys are visible to every window row: no mask;
   // columns past the computed range are discarded in the epilogue. Fixed summation order per column.
-  int li = 0, it = 0;                                          // layer of the call and step within it (uniform over the workgroup)
+  int li = first_layer, it = 0;                                // layer of the call and step within it (uniform over the workgroup)
   auto step = [&](auto buffer, floatx16 (&a)[2], floatx16 (&b)[2]) {
     constexpr int kBuf = decltype(buffer)::value;              // buffer of this step's tile
     if (li >= n_layers) return;                                // the padding step of an odd stream
@@ -953,10 +957,23 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     src.q[i] = static_cast<const uint16_t*>(q_layers[i]);
     src.k[i] = static_cast<const char*>(k_layers[i]);
   }
-  const int grid_x = p.total_tokens / chunk + p.n_seqs;      // upper bound on chunks over all sequences
+  // Chunks of a single sequence, an upper bound on the chunks over several. (Workgroups that find no chunk cost more than
+  // themselves: with one empty one beside 16 or 32 the dispatcher put two full ones on one compute unit.)
+  const int grid_x = p.n_seqs == 1 ? (p.total_tokens + chunk - 1) / chunk : p.total_tokens / chunk + p.n_seqs;
+  // Short prompts: the chunks of all heads do not fill the device, and a workgroup that walks all layers of the call leaves
+  // the rest idle. The layers are then dealt out to blockIdx.z, as many shares as bring the workgroups closest to one per
+  // compute unit (a few too many run behind the others, at half the length or less); the results do not depend on it.
+  // Scoring of 16 layers, us, one share / dealt out: 8 heads, 128 rows, 1024 tokens 121 / 33, 2048 123 / 50, 4096 127 / 80 (at
+  // 8192 tokens the chunks fill the device); 4 heads, 224 rows, 8192 tokens 203 / 119; four prompts of 300 to 1500 tokens
+  // 138 / 81. One layer per call and long prompts: the grid alone, 0 to 10 % less time.
+  const int groups = grid_x * p.Hkv, cus = device_cus();
+  int shares = (cus + groups / 2) / groups;
+  shares = shares < 1 ? 1 : (shares > n_layers ? n_layers : shares);
+  const int layers_each = (n_layers + shares - 1) / shares;
+  shares = (n_layers + layers_each - 1) / layers_each;
   if (phases & kPhaseStats)
-    launch(DKV_KERNEL_SCORE_STATS, (score_stats_mfma<RS, KS>), dim3(grid_x, p.Hkv), dim3(TL::kThreads), lds_stats, st, p, chunk,
-           n_layers, src, k_stride_token * 2, k_stride_head * 2, cu, partials, partials_stride_layer);
+    launch(DKV_KERNEL_SCORE_STATS, (score_stats_mfma<RS, KS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_stats, st, p, chunk,
+           n_layers, layers_each, src, k_stride_token * 2, k_stride_head * 2, cu, partials, partials_stride_layer);
   if (phases & kPhaseEmit) {
     // The emit kernel takes the layers of the call from the last to the first: the statistics kernel has just
     // streamed them first to last, so the last layers are the ones the memory-side cache still holds.
@@ -984,8 +1001,8 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     // all layers); a single layer recomputes the halo keys inside the emit kernel, which is cheaper than a launch.
     float* edges = n_layers > 1 && p.half > 0 ? reinterpret_cast<float*>(ws + wl.edges) : nullptr;
     const int64_t edges_stride_layer = (int64_t)wl.edges_layer_bytes / (int64_t)sizeof(float);
-    launch(DKV_KERNEL_SCORE_EMIT, (score_emit_mfma<RS, KS>), dim3(grid_x, p.Hkv), dim3(TL::kThreads), lds_emit, st, p, chunk,
-           n_layers, rev, k_stride_token * 2, k_stride_head * 2, cu, static_cast<const float*>(partials),
+    launch(DKV_KERNEL_SCORE_EMIT, (score_emit_mfma<RS, KS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_emit, st, p, chunk,
+           n_layers, layers_each, rev, k_stride_token * 2, k_stride_head * 2, cu, static_cast<const float*>(partials),
            lse_rows ? static_cast<const float*>(lse_rows) + last * lse_rows_stride_layer : nullptr, -lse_rows_stride_layer,
            lse_in, scores + last * scores_stride_layer, scores_stride_head, -scores_stride_layer, edges, edges_stride_layer);
     if (edges != nullptr)
