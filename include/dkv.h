@@ -169,7 +169,7 @@ size_t dkv_static_scratch_limit(void);   /* host only: bytes of the fixed array 
  * dkv_score_window (Eq. 1-2) for the n_layers consecutive layers [layer_begin, layer_begin + n_layers) in one call,
  * for a caller that holds the window queries and the keys of a few layers (see dkv_select_topk_layers): a layer's
  * scores depend on that layer's Q and K only. One launch per sweep covers all the layers; a workgroup takes its
- * chunk of keys through the layers one after the other and fetches the next layer's first tiles while it finishes
+ * chunk of keys through the layers (short prompts: through a share of them) one after the other and fetches the next layer's first tiles while it finishes
  * the current one, so the start-up cost of a launch is paid once per call instead of once per layer. Results are
  * identical to n_layers dkv_score_window calls.
  * h_q_layers, h_k_layers  HOST arrays of n_layers DEVICE pointers (Q_win and K of layer layer_begin + i), all with the

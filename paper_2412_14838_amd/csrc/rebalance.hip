@@ -25,8 +25,9 @@
 // of the top-digit histogram: T[u] holds the layers that are new to update u (T[0] additionally the kept
 // history), so update u's top-digit histogram is T[0] + ... + T[u]; the next call folds T[1..] into T[0] before
 // it starts. The scans read every layer once per call, however many updates cover it: the updates whose
-// thresholds agree in the digits found so far form a class (see class_of below), a workgroup keeps its chunk of
-// scores in registers, takes it through the classes (usually one) and stores what it finds once per class.
+// thresholds agree in the digits found so far form a class (see class_of below), a workgroup keeps its chunks of
+// scores in registers and takes them (scan 2: the few it has collected) through the classes, and stores what it finds
+// once per class. Scan 1 usually has one class; a further one reads its chunks again.
 #include "dkv_internal.h"
 
 namespace dkv {
