@@ -8,6 +8,8 @@
 // the nine products are taken, all but those below 2^-24 of the whole: per 16 elements six MFMAs of 32 cycles instead
 // of the eight of 64 cycles that the fp32 form needs. Scores differ from float64 ones by 3.4e-7 (2-norm; 4.0e-7 with
 // the fp32 multiply-adds of the vector ALU).
+// The split, and sums of products in the matrix pipe's own order, end before the range of the elements does: what they
+// leave without a number is taken again as fp32 multiply-adds (see logit_fma).
 //
 // Measured, both sweeps of a call, 128 rows, one MI355X: fp32, 8 layers of 8192 tokens, 8 heads of 128: 215 us (2270 us on
 // the vector ALU, score_generic.hip); bf16, 16 layers of 16384 tokens, 8 heads of 64: 131 us = 4.1 TB/s (1690 us). Bound:
@@ -179,7 +181,8 @@ __device__ inline void load_some(Slot<G>& slot, const Pending<G>& pend, int from
   }
 }
 
-// x as three bf16 terms, two elements at a time: hi + mid + lo == x up to 2^-25 of it.
+// x as three bf16 terms, two elements at a time: hi + mid + lo == x, from 2^-110 (below it the smallest bits of lo are
+// lost) to where hi rounds to infinity (3.396e38).
 __device__ inline uint32_t pack_bf16(float a, float b) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   bf16x2 v;
@@ -379,6 +382,45 @@ __device__ inline void load_rest(Slot<G>& other, const Pending<G>& pend, int j) 
   load_some<G>(other, pend, from + j * n / G::kSteps, from + (j + 1) * n / G::kSteps);
 }
 
+// Logits past the range of the products above. A split leaves NaN where an element is infinite or rounds to it, products
+// of opposite sign can meet as inf - inf where multiply-adds one after the other stay on the side that overflowed first,
+// and exp2(c * x - y), with c * x unrounded and y the rounded maximum or normaliser, is off by |y| 2^-25 octaves. None of
+// that shows for logits of ordinary size; all of it ends as a sum of exponentials that is no number or as a |y| past
+// kMaxExponent. Such sums are taken again from the elements: a wavefront's statistics, the column sums of the keys. Keys
+// filled with the type's lowest value or with -inf then have no weight, as in the definition, one of several logits of
+// 10^7 takes all of it, and logits of +inf or NaN leave no number in their (sequence, KV head).
+constexpr float kMaxExponent = 8192.0f;     // logits of 5700
+
+// Infinite or NaN (by its bits: the compiler may assume that there are no NaNs).
+__device__ inline bool no_number(float v) {
+  uint32_t u = __float_as_uint(v);
+  asm volatile("" : "+v"(u));
+  return (u & 0x7f800000u) == 0x7f800000u;
+}
+
+// c * (one logit), as fp32 multiply-adds in the order of the elements; rounded before anything is subtracted from it.
+template <typename E, int D>
+__device__ inline float logit_fma(const char* __restrict__ q, const char* __restrict__ k, float c) {
+  float acc = 0.0f;
+#pragma unroll 1
+  for (int j = 0; j < D * E::kBytes; j += 16) {
+    const uint4 a = *reinterpret_cast<const uint4*>(q + j), b = *reinterpret_cast<const uint4*>(k + j);
+    const uint32_t u[4] = {a.x, a.y, a.z, a.w}, v[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (E::kBytes == 4) {
+        acc = fmaf(__uint_as_float(u[i]), __uint_as_float(v[i]), acc);
+      } else {
+        acc = fmaf(__uint_as_float(u[i] << 16), __uint_as_float(v[i] << 16), acc);
+        acc = fmaf(__uint_as_float(u[i] & 0xffff0000u), __uint_as_float(v[i] & 0xffff0000u), acc);
+      }
+    }
+  }
+  float y = acc * c;
+  asm volatile("" : "+v"(y));
+  return y;
+}
+
 // The lower and the upper half-wavefront's value of every lane pair (l, l + 32), in both lanes.
 __device__ inline void both_halves(float v, float& lower, float& upper) {
   const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -503,6 +545,7 @@ __global__ __launch_bounds__(kThreads) void score_stats_tiles(Params p, int n_la
     const int lim_all = prefix_rel < cur.len ? prefix_rel : cur.len;
     const int key0 = tile_key(S * G::kTiles, walk.wave);
     const bool masked = tile_key(S * G::kTiles + G::kTiles - 1, walk.wave) + 31 >= lim_all;   // a key of the stage is in the window or past the chunk
+    float l_all = 0.0f, m_large = 0.0f;                     // no number if one of the sums is none; the largest maximum
     // a quarter of the slices finds the maximum of row tile t's logits `x`, the others take the exponentials
     all_row_tiles<G, true>(qrow, plane, k, other, walk.pend, row_tiles, [&](auto more, floatx16 (&x)[G::kTiles], floatx16 (&y)[G::kTiles], int t) {
       constexpr int J = G::kSteps, JM = J / 4, V = G::kTiles * 16;
@@ -540,8 +583,34 @@ __global__ __launch_bounds__(kThreads) void score_stats_tiles(Params p, int n_la
       float l_lo, l_hi;
       both_halves((s0 + s1) + (s2 + s3), l_lo, l_hi);
       const float l = fmaf(old.y, fast_exp2(old.x - m_use), l_lo + l_hi);
+      l_all += l;
+      m_large = fmaxf(m_large, fabsf(m_use));
       if (lane < 32) mine[t * 32] = make_float2(m, l);
     });
+    if (__builtin_expect(__any(no_number(l_all) || m_large > kMaxExponent), 0)) {   // this wavefront's keys so far, from the elements
+      int lane = threadIdx.x & 63;
+      asm volatile("" : "+v"(lane));               // nothing of this is computed ahead (see load_q)
+      const char* __restrict__ q0 = q_base<E>(src, cur, p);
+      const char* __restrict__ k0 = key_base(src, cur, stride_token_b, stride_head_b);
+#pragma unroll 1
+      for (int t = 0; t < row_tiles; ++t) {
+        const int r = t * 32 + (lane & 31), row = r < p.rows ? r : p.rows - 1;
+        int limit = prefix_rel + r % p.w;           // as above
+        limit = limit < cur.len ? limit : cur.len - 1;
+        float m = -INFINITY, l = 0.0f;
+#pragma unroll 1
+        for (int i = 0; i < (S + 1) * G::kTiles * 16; ++i) {         // the half-wavefronts take half of a tile's keys each
+          const int key = tile_key(i / 16, walk.wave) + 16 * (lane >> 5) + i % 16;
+          if (key <= limit)
+            merge_pair(m, l, make_float2(logit_fma<E, D>(q0 + (int64_t)row * D * E::kBytes, k0 + (int64_t)key * stride_token_b, cexp), 1.0f));
+        }
+        float m_lo, m_hi, l_lo, l_hi;
+        both_halves(m, m_lo, m_hi);
+        both_halves(l, l_lo, l_hi);
+        merge_pair(m_lo, l_lo, make_float2(m_hi, l_hi));
+        if (lane < 32) mine[t * 32] = make_float2(m_lo, l_lo);
+      }
+    }
     // Q of the next task (loads return in order: it arrives right behind the other slot's keys, which the next stage
     // needs anyway), then the first of the keys that take this slot
     constexpr bool kLast = S == G::kPerTask - 1;
@@ -663,6 +732,8 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
   float* __restrict__ part = lse_s + 256;                                             // [kChunk + kMaxHalo], key c0 - half first
   float* __restrict__ halo_s = part + kChunk + kMaxHalo;                              // [2][8 row tiles][64] (HALO)
   float2* __restrict__ mstage = reinterpret_cast<float2*>(halo_s);                    // [kThreads] (single-layer merge)
+  int* __restrict__ large_rows = reinterpret_cast<int*>(halo_s + 2 * 8 * 64);         // [4] a normaliser of 64 rows past kMaxExponent
+  int* __restrict__ no_sums = large_rows + 4;                                         // [kWaves + 16] a wavefront's, a halo unit's sums hold no number
   const int tid = threadIdx.x, lane = tid & 63;
   Walk<E, D, NT> walk(p, src, cu, n_layers, stride_token_b, stride_head_b);
   if (walk.task >= walk.n_tasks) return;
@@ -680,16 +751,19 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
         : lse_in + ((int64_t)t.seq * p.Hq + (int64_t)t.head * p.G) * p.w;
     return src_row[tid < p.rows ? tid : p.rows - 1];
   };
-  auto store_normaliser = [&](float v) {
-    if (tid < 256) lse_s[tid] = tid < p.rows ? (from_rows ? v : v * kLog2e) : INFINITY;
+  auto put_normaliser = [&](float v) {                           // v: log2 domain, all threads
+    const bool large = __any(tid < p.rows && fabsf(v) > kMaxExponent);
+    if (tid < 256) lse_s[tid] = tid < p.rows ? v : INFINITY;
+    if (tid < 256 && lane == 0) large_rows[wave] = large;
   };
+  auto store_normaliser = [&](float v) { put_normaliser(from_rows ? v : v * kLog2e); };
   const bool merge_here = HALO && lse_rows == nullptr && lse_in == nullptr;
   auto merge_normalisers = [&](const Task& t) {
     const int first = t.chunk_id - t.c0 / kChunk, n = (t.S + kChunk - 1) / kChunk;
     merge_chunks(reinterpret_cast<const float2*>(partials) + ((int64_t)first * p.Hkv + t.head) * p.rows_pad, n, p.rows_pad,
                  (uint32_t)(p.Hkv * p.rows_pad), mstage);
     lds_barrier();
-    if (tid < p.rows_pad) lse_s[tid] = combine_groups(mstage, p.rows_pad, tid, p.rows);
+    put_normaliser(tid < p.rows ? combine_groups(mstage, p.rows_pad, tid, p.rows) : 0.0f);
     lds_barrier();                                             // mstage and halo_s share their place
   };
   // Halo units: one row tile of one tile of halo keys (the `half` before the chunk, then the `half` behind it); the halves
@@ -720,7 +794,19 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
       s2 += fast_exp2(fmaf(acc[0][4 * i + 2], cexp, -lz.z));
       s3 += fast_exp2(fmaf(acc[0][4 * i + 3], cexp, -lz.w));
     }
-    halo_s[(kt * 8 + t) * 64 + lane] = (s0 + s1) + (s2 + s3);
+    const float sum = (s0 + s1) + (s2 + s3);
+    halo_s[(kt * 8 + t) * 64 + lane] = sum;
+    const bool none = __any(no_number(sum));
+    if (lane == 0) no_sums[kWaves + unit] = none;
+  };
+  // Column sum of a key from the elements.
+  auto column_fma = [&](const Task& t, int key) {
+    const char* __restrict__ qr = q_base<E>(src, t, p);
+    const char* __restrict__ kk = key_base(src, t, stride_token_b, stride_head_b) + (int64_t)key * stride_token_b;
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int r = 0; r < p.rows; ++r, qr += D * E::kBytes) sum += fast_exp2(logit_fma<E, D>(qr, kk, cexp) - lse_s[r]);
+    return sum * p.row_scale;
   };
   {
     QBlock<G> q;
@@ -751,6 +837,7 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     const int prefix = cur.S - p.w;
     int len = prefix - cur.c0;                               // prefix keys of the chunk (none: only the guard is written)
     len = len < cur.len ? len : cur.len;
+    const int large = large_rows[lane & 3];                  // read here: the next task's are written behind the last barrier
     // column sums of all keys of the stage; those past the prefix are not used
     float col[G::kTiles];
 #pragma unroll
@@ -782,12 +869,16 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
 #pragma unroll
       for (int c = 0; c < T; ++c) col[c] += (sum[c][0] + sum[c][1]) + (sum[c][2] + sum[c][3]);
     });
+    bool none = false;
 #pragma unroll
     for (int c = 0; c < G::kTiles; ++c) {
       float lo, hi;
       both_halves(col[c], lo, hi);
       if (lane < 32) part[half + tile_key(S * G::kTiles + c, wave) + lane] = (lo + hi) * p.row_scale;
+      none |= no_number(lo + hi);
     }
+    none = __any(none);
+    if (lane == 0 && (S == 0 || none)) no_sums[wave] = none;
     if (HALO && kLast)
       for (int u = wave + kWaves; u < halo_units; u += kWaves) {
         Slot<H> kh;
@@ -805,6 +896,8 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     walk.template slot_used<SLOT, S>();
     if (!kLast) return;
     lds_barrier();
+    // checked when the outputs are ready: the flag arrives with the sums they are made of
+    int sums_to_check = no_sums[lane < kWaves + halo_units ? lane : 0] | (large << 1);
     if (HALO && half > 0) {
       if (tid < 2 * half && len > 0) {
         const int kt = tid >> 5, l = tid & 31;
@@ -825,16 +918,13 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     const int first = HALO && cur.c0 > 0 ? -half : 0;
     int last = HALO && len == kChunk ? kChunk + half - 1 : len - 1;
     last = last < prefix - cur.c0 - 1 ? last : prefix - cur.c0 - 1;
-    if (!HALO && tid < 2 * half && len > 0) {                // [0, half): the first column sums, [half, 2 half): the last
-      const int i = tid < half ? tid : len - 2 * half + tid;
-      edges[cur.layer * edges_stride_layer + ((int64_t)cur.chunk_id * p.Hkv + cur.head) * kMaxHalo + tid] =
-          i >= 0 && i < len ? part[half + i] : -INFINITY;
-    }
+    constexpr int kOut = (kChunk + kThreads - 1) / kThreads;
+    float pooled[kOut];
+    for (;;) {
 #pragma unroll
-    for (int u = 0; u < (kChunk + kThreads - 1) / kThreads; ++u) {
-      const int i = tid + u * kThreads;
-      if (i < cur.len && prefix > 0) {
-        float m = -INFINITY;                                 // the guard over the window slots
+      for (int u = 0; u < kOut; ++u) {
+        const int i = tid + u * kThreads;
+        float m = -INFINITY;                                   // the guard over the window slots
         if (i < len) {
           m = part[half + i];
           for (int o = 1; o <= half; ++o) {
@@ -842,8 +932,31 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
             m = fmaxf(m, fmaxf(lo, hi));
           }
         }
-        out[i] = m;
+        pooled[u] = m;
       }
+      if (__builtin_expect(!__any(sums_to_check != 0), 1)) break;
+      const bool all = __any((sums_to_check & 2) != 0);        // uniform over the workgroup, as is the branch
+      sums_to_check = 0;
+      lds_barrier();
+      int i0 = threadIdx.x;
+      asm volatile("" : "+v"(i0));                             // nothing of this is computed ahead (see load_q)
+#pragma unroll 1
+      for (int i = i0; i < kChunk + 2 * half; i += kThreads) { // the chunk's keys, then the halo
+        const int e = i - kChunk, key = e < 0 ? i : (e < half ? e - half : kChunk + e - half);
+        const bool there = e < 0 ? i < len : HALO && len > 0 && (e < half ? cur.c0 > 0 : cur.c0 + key < prefix);
+        if (there && (all || no_number(part[half + key]))) part[half + key] = column_fma(cur, key);
+      }
+      lds_barrier();
+    }
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+      const int i = tid + u * kThreads;
+      if (i < cur.len && prefix > 0) out[i] = pooled[u];
+    }
+    if (!HALO && tid < 2 * half && len > 0) {                // [0, half): the first column sums, [half, 2 half): the last
+      const int i = tid < half ? tid : len - 2 * half + tid;
+      edges[cur.layer * edges_stride_layer + ((int64_t)cur.chunk_id * p.Hkv + cur.head) * kMaxHalo + tid] =
+          i >= 0 && i < len ? part[half + i] : -INFINITY;
     }
     if (has_next) {
       store_q<G>(qnext, smem, row_tiles);
@@ -951,7 +1064,7 @@ static hipError_t launch_tiles_t(const Params& p, int phases, int n_layers, cons
   const int row_tiles = (p.rows + 31) / 32;
   const size_t q_bytes = (size_t)G::kTerms * row_tiles * 32 * G::kQRow;
   const size_t lds_stats = q_bytes + (size_t)kWaves * row_tiles * 32 * sizeof(float2);
-  const size_t lds_emit = q_bytes + (256 + chunk + kMaxHalo + 2 * 8 * 64) * sizeof(float);
+  const size_t lds_emit = q_bytes + (256 + chunk + kMaxHalo + 2 * 8 * 64 + 4 + kWaves + 16) * sizeof(float);
   static bool attr_stats = false, attr_emit = false, attr_halo = false;
   hipError_t e = allow_lds(&score_stats_tiles<E, D, NT>, attr_stats);
   if (e == hipSuccess) e = allow_lds(&score_emit_tiles<E, D, NT, false>, attr_emit);
