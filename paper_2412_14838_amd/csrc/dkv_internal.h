@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include <atomic>
+#include <initializer_list>
 #include "../../include/dkv.h"
 
 namespace dkv {
@@ -128,6 +129,25 @@ inline void launch(int kernel_id, Kernel kernel, dim3 grid, dim3 block, size_t l
     }
   }
   hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, args...);
+}
+
+// Dynamic LDS past the default: a launch may ask for up to `bytes` of it once these kernels have been given it, which holds
+// for the device it was done on. `given` (one per call site, devices 0 .. 63 as bits) keeps track; on further devices, and
+// where two threads meet, it is done again.
+struct KernelLds {
+  const void* kernel;
+  int bytes;
+};
+inline hipError_t allow_lds(std::atomic<uint64_t>& given, std::initializer_list<KernelLds> kernels) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? uint64_t(1) << dev : 0;
+  if (given.load(std::memory_order_acquire) & bit) return hipSuccess;
+  for (const KernelLds& k : kernels)
+    if ((e = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes)) != hipSuccess) return e;
+  given.fetch_or(bit, std::memory_order_release);
+  return hipSuccess;
 }
 
 // Host-side descriptor validation shared by every entry point. Returns DKV_OK or a negative status.

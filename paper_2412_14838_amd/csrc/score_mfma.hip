@@ -942,16 +942,10 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   const size_t lds_stats = 2 * TL::kTileBytes + (size_t)QStage<RS, KS>::kBytes + stat_bytes;
   const size_t lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(chunk) * sizeof(float) +
                           (size_t)QStage<RS, KS>::kBytes;   // the Q staging area serves the next layer in every variant
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_stats_mfma<RS, KS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_stats);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_emit_mfma<RS, KS>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static std::atomic<uint64_t> given{0};
+  const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_mfma<RS, KS>), (int)lds_stats},
+                                         {reinterpret_cast<const void*>(&score_emit_mfma<RS, KS>), kLdsBudget}});
+  if (e != hipSuccess) return e;
   ScoreLayers src{};
   for (int i = 0; i < n_layers && (phases & (kPhaseStats | kPhaseEmit)); ++i) {
     src.q[i] = static_cast<const uint16_t*>(q_layers[i]);

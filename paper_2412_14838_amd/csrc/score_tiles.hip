@@ -1040,15 +1040,7 @@ static int pick_tiles(const Params& p, int cus) {
   return best;
 }
 
-constexpr size_t kMaxLds = 160 * 1024;
-
-template <typename Kernel>
-static hipError_t allow_lds(Kernel kernel, bool& done) {
-  if (done) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-  done = e == hipSuccess;
-  return e;
-}
+constexpr int kMaxLds = 160 * 1024;
 
 template <typename E, int D, int NT>
 static hipError_t launch_tiles_t(const Params& p, int phases, int n_layers, const void* const* q_layers,
@@ -1065,10 +1057,10 @@ static hipError_t launch_tiles_t(const Params& p, int phases, int n_layers, cons
   const size_t q_bytes = (size_t)G::kTerms * row_tiles * 32 * G::kQRow;
   const size_t lds_stats = q_bytes + (size_t)kWaves * row_tiles * 32 * sizeof(float2);
   const size_t lds_emit = q_bytes + (256 + chunk + kMaxHalo + 2 * 8 * 64 + 4 + kWaves + 16) * sizeof(float);
-  static bool attr_stats = false, attr_emit = false, attr_halo = false;
-  hipError_t e = allow_lds(&score_stats_tiles<E, D, NT>, attr_stats);
-  if (e == hipSuccess) e = allow_lds(&score_emit_tiles<E, D, NT, false>, attr_emit);
-  if (e == hipSuccess) e = allow_lds(&score_emit_tiles<E, D, NT, true>, attr_halo);
+  static std::atomic<uint64_t> given{0};
+  const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_tiles<E, D, NT>), kMaxLds},
+                                         {reinterpret_cast<const void*>(&score_emit_tiles<E, D, NT, false>), kMaxLds},
+                                         {reinterpret_cast<const void*>(&score_emit_tiles<E, D, NT, true>), kMaxLds}});
   if (e != hipSuccess) return e;
   TileLayers src{};
   for (int i = 0; i < n_layers && (phases & (kPhaseStats | kPhaseEmit)); ++i) {

@@ -517,20 +517,15 @@ hipError_t launch_select(const Params& p, int layer, int n_layers, const float* 
                          int64_t scores_stride_layer, const int32_t* cu, int32_t* idx_out, int64_t idx_stride_layer,
                          int32_t* counts, char* ws, const WorkspaceLayout& wl, hipStream_t st) {
   const size_t lds = 2048 * sizeof(u64) + (size_t)kRadixBins * kHistCopies * sizeof(int);
-  static bool attr_set = false;
-  if (!attr_set) {
-    for (const void* f : {reinterpret_cast<const void*>(&select_topk_kernel<kSelDirect, 32>),
-                          reinterpret_cast<const void*>(&select_topk_kernel<kSelDirect, 16>),
-                          reinterpret_cast<const void*>(&select_topk_kernel<kSelDirect, 8>),
-                          reinterpret_cast<const void*>(&select_topk_kernel<kSelSegments, 32>),
-                          reinterpret_cast<const void*>(&select_topk_kernel<kSelMerge, 32>),
-                          reinterpret_cast<const void*>(&select_topk_kernel<kSelMerge, 16>),
-                          reinterpret_cast<const void*>(&select_topk_kernel<kSelMerge, 8>)}) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    attr_set = true;
-  }
+  static std::atomic<uint64_t> given{0};
+  const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&select_topk_kernel<kSelDirect, 32>), (int)lds},
+                                         {reinterpret_cast<const void*>(&select_topk_kernel<kSelDirect, 16>), (int)lds},
+                                         {reinterpret_cast<const void*>(&select_topk_kernel<kSelDirect, 8>), (int)lds},
+                                         {reinterpret_cast<const void*>(&select_topk_kernel<kSelSegments, 32>), (int)lds},
+                                         {reinterpret_cast<const void*>(&select_topk_kernel<kSelMerge, 32>), (int)lds},
+                                         {reinterpret_cast<const void*>(&select_topk_kernel<kSelMerge, 16>), (int)lds},
+                                         {reinterpret_cast<const void*>(&select_topk_kernel<kSelMerge, 8>), (int)lds}});
+  if (e != hipSuccess) return e;
   SelectCandidates cand{};
   if (wl.select_segments <= 1) {      // every row fits the registers of one workgroup
     // the fewest registers per thread that hold the longest row the descriptor admits
