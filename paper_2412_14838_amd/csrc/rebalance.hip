@@ -13,7 +13,7 @@
 //   scan1   histograms the middle digit of the elements that share digit 0 and counts, per layer, the elements
 //           whose digit 0 is larger (they are above T).
 //   pick1   digit 1 of T from that histogram.
-//   scan2   the same one digit down, over the few elements that reach the upper digits of the thresholds: histograms the
+//   scan2   the same one digit down, over the few elements that share or reach the thresholds' upper digits: histograms the
 //           last digit (per layer and in total), counts per layer the elements that share digit 0 and have a larger
 //           middle digit.
 //   final   one workgroup per sequence: digit 2, then cnt_i = #{> T in layer i} + the share of the elements
@@ -44,7 +44,7 @@ constexpr int kHeadsPerGroup = 4;
 constexpr int kHeadThreads = 256;
 constexpr int kPassThreads = kHeadsPerGroup * kHeadThreads;
 constexpr int kPassChunk = 8192;     // prefix positions of a head per workgroup
-constexpr int kListCap = 4096;       // elements scan 2 collects (its threshold is reached by 1 to 3 % of a workgroup's 32768)
+constexpr int kListCap = 7168;       // elements scan 2 collects of a workgroup's 32768: long prompts have 1 to 3 % of them, a salient layer with half its rows kept 12 %
 constexpr int kLowBins = 1024;       // the last digit has 10 bits
 constexpr uint32_t kHeaderMagic = 0x646b7631u;
 
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
   __shared__ int list_size;
   int seq, c, begin, len;
   if (!find_chunk(cu, n_seqs, kPassChunk, w, blockIdx.x, seq, c, begin, len)) return;
-  const int head = blockIdx.y * kHeadsPerGroup + threadIdx.x / kHeadThreads, layer = blockIdx.z;
+  const int head = blockIdx.y * kHeadsPerGroup + __builtin_amdgcn_readfirstlane(threadIdx.x / kHeadThreads), layer = blockIdx.z;
   const int first_update = first_update_of(layer, layers_done, interval);   // < n_updates by the grid
   const int n = len - w;
   const int i0 = c * kPassChunk;
@@ -396,19 +396,24 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
   // p lies in (key, end): PASS 1 any larger top digit, PASS 2 a larger middle digit under the same top digit.
   constexpr int SH = PASS == 1 ? 21 : 10;
   auto bin_of = [](uint32_t u) { return PASS == 1 ? ((u >> 10) & (uint32_t)(kRadixBins - 1)) : (u & (uint32_t)(kLowBins - 1)); };
-  // Scan 2 looks at the elements that reach the lowest of the thresholds' prefixes: one or two in a hundred. They are
-  // collected first (list, any order), and the classes are taken through the list instead of through every element. With
-  // too many of them (long plateaus of equal scores at the threshold) the classes go through all elements, read again.
+  // Scan 2 looks at the elements between the lowest of the thresholds' prefixes and the end of the highest one's top digit
+  // (a quarter of an octave): what lies above is known from scan 1. They are collected first (list, any order), and the
+  // classes are taken through the list instead of through every element. With too many of them (long plateaus of equal
+  // scores at the threshold) the classes go through all elements, read again.
   int n_listed = 0;
   if constexpr (PASS == 2) {
-    uint32_t lowest = key_of[cls_update[0]];
-    for (int r = 1; r < classes; ++r) lowest = key_of[cls_update[r]] < lowest ? key_of[cls_update[r]] : lowest;
-    const uint32_t bound = lowest << 10;
-    if (lowest != 0u) {                                       // else everything reaches it, the zeros outside the chunk too
+    uint32_t lowest = key_of[cls_update[0]], highest = lowest;
+    for (int r = 1; r < classes; ++r) {
+      const uint32_t key = key_of[cls_update[r]];
+      lowest = key < lowest ? key : lowest;
+      highest = key > highest ? key : highest;
+    }
+    const uint32_t bound = lowest << 10, span = (((highest >> 11) + 1u) << 21) - bound;   // modulo 2^32, as the differences below
+    if (lowest != 0u) {                                       // else the zeros outside the chunk would be among them
       int mine = 0;
 #pragma unroll
       for (int j = 0; j < NV; ++j)
-        mine += (cv.v[j].x >= bound) + (cv.v[j].y >= bound) + (cv.v[j].z >= bound) + (cv.v[j].w >= bound);
+        mine += (cv.v[j].x - bound < span) + (cv.v[j].y - bound < span) + (cv.v[j].z - bound < span) + (cv.v[j].w - bound < span);
       const int incl = wave_prefix_sum(mine);
       int base = 0;
       if ((threadIdx.x & 63) == 63 && incl) base = atomicAdd(&list_size, incl);
@@ -418,10 +423,10 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
       if (n_listed <= kListCap) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-          if (cv.v[j].x >= bound) list[slot++] = cv.v[j].x;
-          if (cv.v[j].y >= bound) list[slot++] = cv.v[j].y;
-          if (cv.v[j].z >= bound) list[slot++] = cv.v[j].z;
-          if (cv.v[j].w >= bound) list[slot++] = cv.v[j].w;
+          if (cv.v[j].x - bound < span) list[slot++] = cv.v[j].x;
+          if (cv.v[j].y - bound < span) list[slot++] = cv.v[j].y;
+          if (cv.v[j].z - bound < span) list[slot++] = cv.v[j].z;
+          if (cv.v[j].w - bound < span) list[slot++] = cv.v[j].w;
           __builtin_amdgcn_sched_barrier(0);                  // vector by vector: side by side they take registers that cost occupancy
         }
       }
@@ -437,20 +442,54 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
 #pragma unroll
     for (int r = 0; r < ROUND; ++r) mine[r] = 0;
   };
-  // element by element, for the in_round classes from c0 on
-  auto take = [&](uint32_t u, int c0, int in_round) {
+  // an element of the list, for all classes
+  auto take = [&](uint32_t u) {
     const uint32_t pq = u >> SH;
 #pragma unroll
     for (int r = 0; r < ROUND; ++r) {
-      if (r >= in_round) break;
-      const uint32_t key = key_of[cls_update[c0 + r]];
-      mine[r] += pq > key && (PASS == 1 || pq >> 11 == key >> 11);
+      if (r >= classes) break;
+      const uint32_t key = key_of[cls_update[r]];
+      mine[r] += pq > key && pq >> 11 == key >> 11;
       if (pq == key) atomicAdd(&h[r * BINS + bin_of(u)], 1);
     }
   };
-  auto take_all = [&](int c0, int in_round) {
-    const uint32_t* __restrict__ row = reinterpret_cast<const uint32_t*>(scores_all) + e_lo;
-    for (int i = threadIdx.x & (kHeadThreads - 1); i < i1 - i0; i += kHeadThreads) take(row[i], c0, in_round);
+  // The elements of `part` for one class: the histogram hr; returns this thread's elements above the class's key.
+  auto take_vectors = [&](const auto& part, uint32_t key, int* __restrict__ hr) {
+    int higher = 0;
+#pragma unroll
+    for (int j = 0; j < (int)(sizeof(part.v) / sizeof(part.v[0])); ++j) {
+      const uint4 v = part.v[j];
+      const uint32_t p0 = v.x >> SH, p1 = v.y >> SH, p2 = v.z >> SH, p3 = v.w >> SH;
+      if (PASS == 1) {
+        higher += (p0 > key) + (p1 > key) + (p2 > key) + (p3 > key);
+      } else {
+        const uint32_t span = 2047u - (key & 2047u);                   // of the larger middle digits under the same top digit
+        higher += (p0 - key - 1u < span) + (p1 - key - 1u < span) + (p2 - key - 1u < span) + (p3 - key - 1u < span);
+      }
+      if (p0 == key || p1 == key || p2 == key || p3 == key) {           // one branch per vector
+        if (p0 == key) atomicAdd(&hr[bin_of(v.x)], 1);
+        if (p1 == key) atomicAdd(&hr[bin_of(v.y)], 1);
+        if (p2 == key) atomicAdd(&hr[bin_of(v.z)], 1);
+        if (p3 == key) atomicAdd(&hr[bin_of(v.w)], 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);                      // as above
+    }
+    if (part.outside && key == 0u) atomicAdd(&hr[0], -part.outside);    // the zeros outside the chunk
+    return higher;
+  };
+  // All elements of the chunk, read again in halves: kept from class to class, the elements, their digits or their
+  // addresses would cost occupancy.
+  auto take_again = [&](uint32_t key, int* __restrict__ hr) {
+    constexpr int kHalf = kPassChunk / 2;
+    int higher = 0;
+#pragma unroll 1
+    for (int from = 0; from < i1 - i0; from += kHalf) {
+      ChunkVectors<kHalf / 4 / kHeadThreads + 1> part;
+      const int64_t e = e_lo + from;
+      load_chunk(scores_all, (int64_t)L * Hkv * total_tokens, e, e + (i1 - i0 - from < kHalf ? i1 - i0 - from : kHalf), part);
+      higher += take_vectors(part, key, hr);
+    }
+    return higher;
   };
   auto finish = [&](int c0, int in_round) {
 #pragma unroll
@@ -481,32 +520,22 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
     static_assert(ROUND >= DKV_MAX_UPDATES, "all classes in one round");
     start(classes);
     if (n_listed <= kListCap) {
-      for (int i = threadIdx.x; i < n_listed; i += kPassThreads) take(list[i], 0, classes);
+      for (int i = threadIdx.x; i < n_listed; i += kPassThreads) take(list[i]);
     } else {
-      take_all(0, classes);
+      for (int r = 0; r < classes; ++r) {
+        const int m = wave_sum(take_again(key_of[cls_update[r]], h + r * BINS));
+        if ((threadIdx.x & 63) == 0 && m) atomicAdd(&n_above[r], m);
+      }
     }
     finish(0, classes);
   } else {
     start(1);
-    const uint32_t key = key_of[cls_update[0]];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const uint32_t p0 = cv.v[j].x >> SH, p1 = cv.v[j].y >> SH, p2 = cv.v[j].z >> SH, p3 = cv.v[j].w >> SH;
-      mine[0] += (p0 > key) + (p1 > key) + (p2 > key) + (p3 > key);
-      if (p0 == key || p1 == key || p2 == key || p3 == key) {           // one branch per vector
-        if (p0 == key) atomicAdd(&h[bin_of(cv.v[j].x)], 1);
-        if (p1 == key) atomicAdd(&h[bin_of(cv.v[j].y)], 1);
-        if (p2 == key) atomicAdd(&h[bin_of(cv.v[j].z)], 1);
-        if (p3 == key) atomicAdd(&h[bin_of(cv.v[j].w)], 1);
-      }
-      __builtin_amdgcn_sched_barrier(0);                      // as above
-    }
-    if (cv.outside && key == 0u) atomicAdd(&h[0], -cv.outside);         // the zeros outside the chunk
+    mine[0] = take_vectors(cv, key_of[cls_update[0]], h);
     finish(0, 1);
     for (int c0 = 1; c0 < classes; ++c0) {                    // updates whose thresholds lie in other top digits: rare
       __syncthreads();                                        // h and n_above are reused
       start(1);
-      take_all(c0, 1);
+      mine[0] = take_again(key_of[cls_update[c0]], h);
       finish(c0, 1);
     }
   }

@@ -52,3 +52,54 @@ def test_update_scans_match_the_oracle(Hkv, seqlens, kind):
                 cnt, _, Zp = O.update_buffer_length([A[i][:, cu[s]:cu[s] + pre] for i in range(l)], cfg.layer_max, cfg.mean_budget, cfg.L)
                 assert np.array_equal(hits[slot, s, :l], cnt), (batch, l, s)
                 assert np.array_equal(budgets[slot, s, :l], np.minimum(Zp, 2**31 - 1)), (batch, l, s)
+
+
+def _check_updates(cfg, A, done):
+    for batch in (False, True):
+        comp = Compressor(cfg, keep_cache=False)
+        comp.scores.copy_(torch.from_numpy(A))
+        comp.select_layers(0, cfg.L)
+        if batch:
+            comp.rebalance_batch(done[0], len(done))
+        else:
+            for l in done:
+                comp.rebalance(l)
+        torch.cuda.synchronize()
+        hits, budgets = comp.hits_all.cpu().numpy(), comp.budgets_all.cpu().numpy()
+        cu = cfg.cu_seqlens
+        for slot, l in enumerate(done):
+            for s in range(cfg.n_seqs):
+                pre = cfg.seqlens[s] - cfg.w
+                cnt, _, Zp = O.update_buffer_length([A[i][:, cu[s]:cu[s] + pre] for i in range(l)], cfg.layer_max, cfg.mean_budget, cfg.L)
+                assert np.array_equal(hits[slot, s, :l], cnt), (batch, l, s)
+                assert np.array_equal(budgets[slot, s, :l], np.minimum(Zp, 2**31 - 1)), (batch, l, s)
+
+
+@pytest.mark.parametrize("sharing", [7168, 7169])
+def test_as_many_elements_at_the_threshold_as_the_last_scan_collects(sharing):
+    cfg = W.Workload("cap", L=2, Hq=4, Hkv=4, d=64, seqlens=(8192 + 8,), dtype="bf16", w=8, P=7, mean_budget=900, layer_max=1800,
+                     interval=1, seed=1)
+    rng = np.random.default_rng(sharing)
+    A = np.full((cfg.L, cfg.Hkv, cfg.total_tokens), -np.inf, np.float32)
+    for l in range(cfg.L):
+        row = rng.uniform(0.1, 0.5, 4 * 8192).astype(np.float32)
+        where = rng.permutation(4 * 8192)
+        # one value of the upper 22 bits, all of the last digit; above them some that the scan before has counted
+        row[where[:sharing]] = (np.uint32(0x3F800400) + rng.integers(0, 1024, sharing).astype(np.uint32)).view(np.float32)
+        row[where[sharing:sharing + 200]] = 3.0
+        A[l, :, :8192] = row.reshape(4, 8192)
+    _check_updates(cfg, A, (1, 2))
+
+
+def test_scores_on_the_borders_of_the_digits():
+    cfg = W.Workload("borders", L=6, Hq=5, Hkv=5, d=64, seqlens=(9000, 77, 300), dtype="bf16", w=8, P=7, mean_budget=40, layer_max=160,
+                     interval=2, seed=1)
+    rng = np.random.default_rng(3)
+    top, mid = np.uint32(0x3F800000 >> 21), np.uint32(700)
+    at = (top << np.uint32(21)) | (mid << np.uint32(10))
+    values = np.array([top << 21, (top << 21) - 1, ((top + 1) << 21) - 1, (top + 1) << 21, at, at - 1, at + 1023, at + 1024, 1, 0], np.uint32)
+    for most_common in range(len(values)):                     # the thresholds move through the borders
+        p = np.full(len(values), 0.004)
+        p[most_common] = 1 - p.sum() + p[most_common]
+        A = values[rng.choice(len(values), (cfg.L, cfg.Hkv, cfg.total_tokens), p=p)].view(np.float32)
+        _check_updates(cfg, A, (2, 4, 6))
