@@ -33,18 +33,27 @@
 namespace dkv {
 
 constexpr int kFinalThreads = 1024;
-constexpr int kHist0Copies = 4;      // interleaved LDS copies of the top-digit histogram (every element lands there)
-// Workgroups of the three passes over the scores: four heads of one chunk of prefix positions in one layer, 256 threads to
-// a head. Heads of a layer share every histogram, and a workgroup's fixed work - its histogram cleared, read back and added
-// to the global one, where all workgroups of a sequence meet in the same 2048 words - is paid once for all four. Registers
-// are kept below 64, so that two workgroups fit a compute unit. Measured, us per call, one head to a workgroup / four: scans
-// 1 and 2 of a single update over up to 32 layers of 8 x 32736 positions 35 / 18.5 (average), of eight updates in one call
-// 43 / 24, of eight updates over 2048 ragged rows 93 / 54; top digit 12.8 / 11.3 and 24.6 / 20 for the last two.
-constexpr int kHeadsPerGroup = 4;
-constexpr int kHeadThreads = 256;
-constexpr int kPassThreads = kHeadsPerGroup * kHeadThreads;
-constexpr int kPassChunk = 8192;     // prefix positions of a head per workgroup
-constexpr int kListCap = 7168;       // elements scan 2 collects of a workgroup's 32768: long prompts have 1 to 3 % of them, a salient layer with half its rows kept 12 %
+// Workgroups of the three passes over the scores: some heads of one chunk of prefix positions in one layer, 32 elements to a
+// thread. Heads of a layer share every histogram, and a workgroup's fixed work - its sequence found, its histogram cleared,
+// read back and added to the global one, where all workgroups of a sequence meet in the same 2048 words - is paid once for
+// all of them. Registers are kept below 64, so that 32 wavefronts fit a compute unit. Long rows: four heads of 8192
+// positions. Measured, us per call, one head of 8192 to a workgroup / four: scans 1 and 2 of a single update over up to 32
+// layers of 8 x 32736 positions 35 / 18.5 (average), of eight updates in one call 43 / 24, of eight updates over 2048 ragged
+// rows 93 / 54; top digit 12.8 / 11.3 and 24.6 / 20 for the last two. Rows that do not fill such a workgroup leave most of
+// its 1024 threads idle, and few heads do; two heads of 4096 positions then. One update over all layers, us, one head of
+// 8192 / four of 8192 / two of 4096: 16 layers of 1024 tokens, 1 head 21.4 / 22.5 / 21.6, 8 heads 24.1 / 23.6 / 22.6; of 8192
+// tokens 25.8 / 22.5 / 22.8 and 28.9 / 24.9 / 25.5; of 16384 26.4 / 23.2 / 23.4 and 33.0 / 25.9 / 30.0; 8 layers of 64 x 300
+// tokens, 2 heads 63 / 103 / 45, 8 heads 153 / 154 / 90; of 8 x 6000 tokens 27.8 / 27.4 / 25.0 and 32.5 / 29.4 / 28.7.
+template <int HEADS, int HEAD_THREADS>
+struct PassShape {
+  static constexpr int kHeads = HEADS, kHeadThreads = HEAD_THREADS, kThreads = HEADS * HEAD_THREADS;
+  static constexpr int kChunk = 32 * HEAD_THREADS;         // prefix positions of a head per workgroup
+  static constexpr int kHist0Copies = kThreads / 256 < 2 ? 2 : 4;   // interleaved LDS copies of the top-digit histogram (every element lands there)
+  // elements scan 2 collects of the workgroup's: long prompts have 1 to 3 % of them, a salient layer with half its rows kept 12 %
+  static constexpr int kListCap = HEADS * kChunk * 7 / 32;
+};
+using LongRows = PassShape<4, 256>;
+using ShortRows = PassShape<2, 128>;
 constexpr int kLowBins = 1024;       // the last digit has 10 bits
 constexpr uint32_t kHeaderMagic = 0x646b7631u;
 
@@ -98,7 +107,7 @@ struct ChunkVectors {
 };
 
 // n_elems: elements of the whole score tensor; its last, partial vector (if any) is read element by element.
-template <int NV>
+template <int kHeadThreads, int NV>
 __device__ inline void load_chunk(const float* __restrict__ scores_all, int64_t n_elems, int64_t e_lo, int64_t e_hi,
                                   ChunkVectors<NV>& cv) {
   const uint32_t* __restrict__ base = reinterpret_cast<const uint32_t*>(scores_all);
@@ -204,26 +213,28 @@ __device__ inline int global_k(const int32_t* __restrict__ cu, int seq, int w, i
 
 // Top-digit histogram of the layers not yet counted. grid = (chunk upper bound, groups of heads, layers_done).
 // layers_done: of the call's first update; layers at or past it belong to the later updates' slots.
-__global__ __launch_bounds__(kPassThreads, 8) void rebalance_hist0_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
+template <typename Shape>
+__global__ __launch_bounds__(Shape::kThreads, 8) void rebalance_hist0_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
                                                               int layers_done, int interval,
                                                               const float* __restrict__ scores_all,
                                                               const int32_t* __restrict__ cu,
                                                               const int32_t* __restrict__ header, uint32_t epoch,
                                                               int32_t* __restrict__ tot0, int64_t tot0_words) {
+  constexpr int kHist0Copies = Shape::kHist0Copies;
   __shared__ int h[kRadixBins * kHist0Copies];
-  const int head = blockIdx.y * kHeadsPerGroup + threadIdx.x / kHeadThreads, layer = blockIdx.z;
+  const int head = blockIdx.y * Shape::kHeads + threadIdx.x / Shape::kHeadThreads, layer = blockIdx.z;
   if (layer < layers_already_counted(header, scores_all, layers_done, interval, n_seqs, total_tokens, epoch)) return;
   const int slot = layer < layers_done ? 0 : 1 + (layer - layers_done) / interval;
   int seq, c, begin, len;
-  if (!find_chunk(cu, n_seqs, kPassChunk, w, blockIdx.x, seq, c, begin, len)) return;
+  if (!find_chunk(cu, n_seqs, Shape::kChunk, w, blockIdx.x, seq, c, begin, len)) return;
   const int n = len - w;
-  const int i0 = c * kPassChunk;
-  const int i1 = head >= Hkv ? i0 : (i0 + kPassChunk < n ? i0 + kPassChunk : n);
-  constexpr int NV = kPassChunk / 4 / kHeadThreads + 1;
+  const int i0 = c * Shape::kChunk;
+  const int i1 = head >= Hkv ? i0 : (i0 + Shape::kChunk < n ? i0 + Shape::kChunk : n);
+  constexpr int NV = Shape::kChunk / 4 / Shape::kHeadThreads + 1;
   ChunkVectors<NV> cv;
   const int64_t e_lo = ((int64_t)layer * Hkv + head) * total_tokens + begin + i0;
-  load_chunk<NV>(scores_all, (int64_t)L * Hkv * total_tokens, e_lo, e_lo + (i1 - i0), cv);
-  for (int b = threadIdx.x; b < kRadixBins * kHist0Copies; b += kPassThreads) h[b] = 0;
+  load_chunk<Shape::kHeadThreads>(scores_all, (int64_t)L * Hkv * total_tokens, e_lo, e_lo + (i1 - i0), cv);
+  for (int b = threadIdx.x; b < kRadixBins * kHist0Copies; b += Shape::kThreads) h[b] = 0;
   __syncthreads();
   int* __restrict__ hc = h + (threadIdx.x & (kHist0Copies - 1));
   // Scores crowd into a few top digits (a quarter of an octave each) and pooling repeats values along a row, so a
@@ -251,7 +262,7 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_hist0_kernel(int n_
   if (run) atomicAdd(&hc[run_digit * kHist0Copies], run);
   __syncthreads();
   int32_t* __restrict__ g = tot0 + slot * tot0_words + (int64_t)seq * kRadixBins;
-  for (int b = threadIdx.x; b < kRadixBins; b += kPassThreads) {
+  for (int b = threadIdx.x; b < kRadixBins; b += Shape::kThreads) {
     int v = 0;
 #pragma unroll
     for (int c2 = 0; c2 < kHist0Copies; ++c2) v += h[b * kHist0Copies + c2];
@@ -332,8 +343,8 @@ __global__ __launch_bounds__(kFinalThreads) void rebalance_pick_kernel(int n_seq
 // from the histogram the kernel before completed (the top digit from tot0, the middle digit from tot1: 8 KB from
 // the L2, while its scores are on their way), and the sequence's first workgroup records it in `picks` for the
 // kernels behind.
-template <int PASS, bool PICKS_HERE>
-__global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
+template <typename Shape, int PASS, bool PICKS_HERE>
+__global__ __launch_bounds__(Shape::kThreads, PASS == 1 || PICKS_HERE || Shape::kThreads == 1024 ? 8 : 4) void rebalance_scan_kernel(int n_seqs, int Hkv, int w, int L, int total_tokens,
                                                              int layers_done, int interval, int n_updates,
                                                              int mean_budget, const int32_t* __restrict__ tot0,
                                                              const float* __restrict__ scores_all,
@@ -345,35 +356,35 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
   constexpr int BINS = PASS == 1 ? kRadixBins : kLowBins;
   // classes taken through the chunk together: PASS 1 usually has one (the top digit of T rarely moves between the
   // updates of a call), PASS 2 often one per update (the middle digit does), and its histograms are small
-  constexpr int ROUND = PASS == 1 ? 1 : DKV_MAX_UPDATES;
+  constexpr int ROUND = PASS == 1 || PICKS_HERE ? 1 : DKV_MAX_UPDATES;
   __shared__ int h[ROUND * BINS];
   __shared__ uint32_t key_of[DKV_MAX_UPDATES];        // the digits of the updates' thresholds found so far
   __shared__ int cls_update[DKV_MAX_UPDATES];         // the classes of the updates that cover this layer (first members)
   __shared__ int n_cls;
   __shared__ int n_above[ROUND];
-  __shared__ uint32_t list[PASS == 2 ? kListCap : 1];
+  __shared__ uint32_t list[PASS == 2 ? Shape::kListCap : 1];
   __shared__ int list_size;
   int seq, c, begin, len;
-  if (!find_chunk(cu, n_seqs, kPassChunk, w, blockIdx.x, seq, c, begin, len)) return;
-  const int head = blockIdx.y * kHeadsPerGroup + __builtin_amdgcn_readfirstlane(threadIdx.x / kHeadThreads), layer = blockIdx.z;
+  if (!find_chunk(cu, n_seqs, Shape::kChunk, w, blockIdx.x, seq, c, begin, len)) return;
+  const int head = blockIdx.y * Shape::kHeads + __builtin_amdgcn_readfirstlane(threadIdx.x / Shape::kHeadThreads), layer = blockIdx.z;
   const int first_update = first_update_of(layer, layers_done, interval);   // < n_updates by the grid
   const int n = len - w;
-  const int i0 = c * kPassChunk;
-  const int i1 = head >= Hkv ? i0 : (i0 + kPassChunk < n ? i0 + kPassChunk : n);
-  constexpr int NV = kPassChunk / 4 / kHeadThreads + 1;
+  const int i0 = c * Shape::kChunk;
+  const int i1 = head >= Hkv ? i0 : (i0 + Shape::kChunk < n ? i0 + Shape::kChunk : n);
+  constexpr int NV = Shape::kChunk / 4 / Shape::kHeadThreads + 1;
   ChunkVectors<NV> cv;
   const int64_t e_lo = ((int64_t)layer * Hkv + head) * total_tokens + begin + i0;
-  load_chunk<NV>(scores_all, (int64_t)L * Hkv * total_tokens, e_lo, e_lo + (i1 - i0), cv);
+  load_chunk<Shape::kHeadThreads>(scores_all, (int64_t)L * Hkv * total_tokens, e_lo, e_lo + (i1 - i0), cv);
   if (PICKS_HERE) {                                      // n_updates == 1: update 0, class 0, slot 0
-    __shared__ int pick_scratch[kPassThreads / 64];
+    __shared__ int pick_scratch[Shape::kThreads / 64];
     __shared__ int pick_sh[2];
     int32_t* __restrict__ pk = picks + (int64_t)seq * 4;
-    const Bins<kPassThreads, kRadixBins> bins = load_bins<kPassThreads, kRadixBins>(
+    const Bins<Shape::kThreads, kRadixBins> bins = load_bins<Shape::kThreads, kRadixBins>(
         PASS == 1 ? tot0 + (int64_t)seq * kRadixBins : tot1 + (int64_t)seq * DKV_MAX_UPDATES * kRadixBins);
     const int rem = PASS == 1 ? global_k(cu, seq, w, Hkv, mean_budget, layers_done) : pk[1];
     const int d_top = PASS == 1 ? 0 : pk[0];
     int digit, left;
-    pick_digit<kPassThreads, kRadixBins>(bins, rem, pick_scratch, pick_sh, digit, left);
+    pick_digit<Shape::kThreads, kRadixBins>(bins, rem, pick_scratch, pick_sh, digit, left);
     if (threadIdx.x == 0) {
       key_of[0] = PASS == 1 ? (uint32_t)digit : (((uint32_t)d_top << 11) | (uint32_t)digit);
       if (c == 0 && blockIdx.y == 0 && layer == 0) { pk[2 * (PASS - 1)] = digit; pk[2 * (PASS - 1) + 1] = left; }
@@ -420,7 +431,7 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
       int slot = __builtin_amdgcn_readlane(base, 63) + incl - mine;
       __syncthreads();
       n_listed = list_size;
-      if (n_listed <= kListCap) {
+      if (n_listed <= Shape::kListCap) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
           if (cv.v[j].x - bound < span) list[slot++] = cv.v[j].x;
@@ -431,12 +442,12 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
         }
       }
     } else {
-      n_listed = kListCap + 1;
+      n_listed = Shape::kListCap + 1;
     }
   }
   int mine[ROUND];
   auto start = [&](int in_round) {
-    for (int b = threadIdx.x; b < in_round * BINS; b += kPassThreads) h[b] = 0;
+    for (int b = threadIdx.x; b < in_round * BINS; b += Shape::kThreads) h[b] = 0;
     if (threadIdx.x < ROUND) n_above[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
@@ -480,13 +491,13 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
   // All elements of the chunk, read again in halves: kept from class to class, the elements, their digits or their
   // addresses would cost occupancy.
   auto take_again = [&](uint32_t key, int* __restrict__ hr) {
-    constexpr int kHalf = kPassChunk / 2;
+    constexpr int kHalf = Shape::kChunk / 2;
     int higher = 0;
 #pragma unroll 1
     for (int from = 0; from < i1 - i0; from += kHalf) {
-      ChunkVectors<kHalf / 4 / kHeadThreads + 1> part;
+      ChunkVectors<kHalf / 4 / Shape::kHeadThreads + 1> part;
       const int64_t e = e_lo + from;
-      load_chunk(scores_all, (int64_t)L * Hkv * total_tokens, e, e + (i1 - i0 - from < kHalf ? i1 - i0 - from : kHalf), part);
+      load_chunk<Shape::kHeadThreads>(scores_all, (int64_t)L * Hkv * total_tokens, e, e + (i1 - i0 - from < kHalf ? i1 - i0 - from : kHalf), part);
       higher += take_vectors(part, key, hr);
     }
     return higher;
@@ -504,7 +515,7 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
       const int64_t cls = (int64_t)cls_update[c0 + r] * always_words;   // the class's block
       if (threadIdx.x == 0 && n_above[r])
         atomicAdd(&above[cls + ((int64_t)(PASS - 1) * n_seqs + seq) * L + layer], n_above[r]);
-      for (int b = threadIdx.x; b < BINS; b += kPassThreads) {
+      for (int b = threadIdx.x; b < BINS; b += Shape::kThreads) {
         const int v = h[r * BINS + b];
         if (!v) continue;
         if (PASS == 1) {
@@ -517,10 +528,10 @@ __global__ __launch_bounds__(kPassThreads, 8) void rebalance_scan_kernel(int n_s
     }
   };
   if constexpr (PASS == 2) {
-    static_assert(ROUND >= DKV_MAX_UPDATES, "all classes in one round");
+    static_assert(ROUND >= (PICKS_HERE ? 1 : DKV_MAX_UPDATES), "all classes in one round");
     start(classes);
-    if (n_listed <= kListCap) {
-      for (int i = threadIdx.x; i < n_listed; i += kPassThreads) take(list[i]);
+    if (n_listed <= Shape::kListCap) {
+      for (int i = threadIdx.x; i < n_listed; i += Shape::kThreads) take(list[i]);
     } else {
       for (int r = 0; r < classes; ++r) {
         const int m = wave_sum(take_again(key_of[cls_update[r]], h + r * BINS));
@@ -664,7 +675,8 @@ __global__ __launch_bounds__(kFinalThreads) void rebalance_final_kernel(
 
 // layers_done: of the first update; update u of the n_updates covers layers [0, layers_done + u * interval).
 // budgets_out / hits_out (may be null): update u writes its block out_stride_update ints after update u - 1's.
-hipError_t launch_rebalance(const Params& p, int layers_done, int n_updates, uint32_t epoch, const float* scores_all,
+template <typename Shape>
+static hipError_t launch_rebalance_t(const Params& p, int layers_done, int n_updates, uint32_t epoch, const float* scores_all,
                             const int32_t* cu, int32_t* counts, int32_t* budgets_out, int32_t* hits_out,
                             int64_t out_stride_update, char* ws, const WorkspaceLayout& wl, hipStream_t st) {
   int32_t* header = reinterpret_cast<int32_t*>(ws + wl.header);
@@ -684,27 +696,27 @@ hipError_t launch_rebalance(const Params& p, int layers_done, int n_updates, uin
          reinterpret_cast<uint32_t*>(tot1), clear_words, reinterpret_cast<uint32_t*>(tot0), (size_t)tot0_words, header,
          scores_all, layers_done, p.interval, p.n_seqs, p.total_tokens, epoch, picks, n_updates * p.n_seqs * 4);
   const int last_done = layers_done + (n_updates - 1) * p.interval;
-  const int head_groups = (p.Hkv + kHeadsPerGroup - 1) / kHeadsPerGroup;
-  const dim3 grid(p.total_tokens / kPassChunk + p.n_seqs, head_groups, last_done);
-  launch(DKV_KERNEL_REBALANCE_HIST, rebalance_hist0_kernel, grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+  const int head_groups = (p.Hkv + Shape::kHeads - 1) / Shape::kHeads;
+  const dim3 grid(p.total_tokens / Shape::kChunk + p.n_seqs, head_groups, last_done);
+  launch(DKV_KERNEL_REBALANCE_HIST, rebalance_hist0_kernel<Shape>, grid, dim3(Shape::kThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
          p.total_tokens, layers_done, p.interval, scores_all, cu, header, epoch, tot0, tot0_words);
   const dim3 grid_pick(p.n_seqs, n_updates);
   if (n_updates == 1) {     // the scans pick their digits themselves: two launches less
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<1, true>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<Shape, 1, true>), grid, dim3(Shape::kThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<2, true>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<Shape, 2, true>), grid, dim3(Shape::kThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
   } else {
     launch(DKV_KERNEL_REBALANCE_PICK, rebalance_pick_kernel<0>, grid_pick, dim3(kFinalThreads), 0, st, p.n_seqs, p.w, p.Hkv,
            p.mean_budget, layers_done, p.interval, cu, tot0, tot0_words, tot1, always_words, picks);
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<1, false>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<Shape, 1, false>), grid, dim3(Shape::kThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
     launch(DKV_KERNEL_REBALANCE_PICK, rebalance_pick_kernel<1>, grid_pick, dim3(kFinalThreads), 0, st, p.n_seqs, p.w, p.Hkv,
            p.mean_budget, layers_done, p.interval, cu, tot0, tot0_words, tot1, always_words, picks);
-    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<2, false>), grid, dim3(kPassThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
+    launch(DKV_KERNEL_REBALANCE_SCAN, (rebalance_scan_kernel<Shape, 2, false>), grid, dim3(Shape::kThreads), 0, st, p.n_seqs, p.Hkv, p.w, p.L,
            p.total_tokens, layers_done, p.interval, n_updates, p.mean_budget, tot0, scores_all, cu, picks, tot1, tot2, hist2,
            above, always_words);
   }
@@ -712,6 +724,17 @@ hipError_t launch_rebalance(const Params& p, int layers_done, int n_updates, uin
          p.n_seqs, p.L, layers_done, p.interval, p.w, p.Hkv, p.mean_budget, p.layer_max, p.total_tokens, scores_all, cu,
          picks, tot2, hist2, above, always_words, header, epoch, counts, budgets_out, hits_out, out_stride_update);
   return hipGetLastError();
+}
+
+hipError_t launch_rebalance(const Params& p, int layers_done, int n_updates, uint32_t epoch, const float* scores_all,
+                            const int32_t* cu, int32_t* counts, int32_t* budgets_out, int32_t* hits_out,
+                            int64_t out_stride_update, char* ws, const WorkspaceLayout& wl, hipStream_t st) {
+  // by the mean length: a workgroup of the long shape that holds a short row costs as much as one that is full
+  if ((int64_t)p.total_tokens > (int64_t)LongRows::kChunk * p.n_seqs)
+    return launch_rebalance_t<LongRows>(p, layers_done, n_updates, epoch, scores_all, cu, counts, budgets_out, hits_out,
+                                        out_stride_update, ws, wl, st);
+  return launch_rebalance_t<ShortRows>(p, layers_done, n_updates, epoch, scores_all, cu, counts, budgets_out, hits_out,
+                                       out_stride_update, ws, wl, st);
 }
 
 }  // namespace dkv

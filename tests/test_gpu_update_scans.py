@@ -70,24 +70,36 @@ def _check_updates(cfg, A, done):
         for slot, l in enumerate(done):
             for s in range(cfg.n_seqs):
                 pre = cfg.seqlens[s] - cfg.w
+                if pre <= 0:
+                    continue
                 cnt, _, Zp = O.update_buffer_length([A[i][:, cu[s]:cu[s] + pre] for i in range(l)], cfg.layer_max, cfg.mean_budget, cfg.L)
                 assert np.array_equal(hits[slot, s, :l], cnt), (batch, l, s)
                 assert np.array_equal(budgets[slot, s, :l], np.minimum(Zp, 2**31 - 1)), (batch, l, s)
 
 
-@pytest.mark.parametrize("sharing", [7168, 7169])
-def test_as_many_elements_at_the_threshold_as_the_last_scan_collects(sharing):
-    cfg = W.Workload("cap", L=2, Hq=4, Hkv=4, d=64, seqlens=(8192 + 8,), dtype="bf16", w=8, P=7, mean_budget=900, layer_max=1800,
+# workgroups of four heads of 8192 positions (the mean length is more) and of two heads of 4096
+@pytest.mark.parametrize("kind", ["smooth", "plateau", "zeros", "scaled"])
+@pytest.mark.parametrize("Hkv,seqlens", [(6, (8193 + 8,)), (1, (16385 + 8,)), (2, (9, 24600)), (3, (4095 + 8, 4096 + 8, 4097 + 8)),
+                                         (1, (8192,)), (8, tuple(30 + 11 * i for i in range(40)))])
+def test_both_shapes_of_workgroups(Hkv, seqlens, kind):
+    cfg = W.Workload("shapes", L=4, Hq=Hkv, Hkv=Hkv, d=64, seqlens=seqlens, dtype="bf16", w=8, P=7, mean_budget=40, layer_max=160,
+                     interval=2, seed=1)
+    _check_updates(cfg, _scores(kind, cfg, np.random.default_rng(11 * Hkv + len(kind))), (2, 4))
+
+
+@pytest.mark.parametrize("Hkv,chunk,sharing", [(4, 8192, 7168), (4, 8192, 7169), (2, 4096, 1792), (2, 4096, 1793)])
+def test_as_many_elements_at_the_threshold_as_the_last_scan_collects(Hkv, chunk, sharing):
+    cfg = W.Workload("cap", L=2, Hq=Hkv, Hkv=Hkv, d=64, seqlens=(chunk + 8,), dtype="bf16", w=8, P=7, mean_budget=sharing // 8, layer_max=1800,
                      interval=1, seed=1)
     rng = np.random.default_rng(sharing)
     A = np.full((cfg.L, cfg.Hkv, cfg.total_tokens), -np.inf, np.float32)
     for l in range(cfg.L):
-        row = rng.uniform(0.1, 0.5, 4 * 8192).astype(np.float32)
-        where = rng.permutation(4 * 8192)
+        row = rng.uniform(0.1, 0.5, Hkv * chunk).astype(np.float32)
+        where = rng.permutation(Hkv * chunk)
         # one value of the upper 22 bits, all of the last digit; above them some that the scan before has counted
         row[where[:sharing]] = (np.uint32(0x3F800400) + rng.integers(0, 1024, sharing).astype(np.uint32)).view(np.float32)
-        row[where[sharing:sharing + 200]] = 3.0
-        A[l, :, :8192] = row.reshape(4, 8192)
+        row[where[sharing:sharing + 50]] = 3.0
+        A[l, :, :chunk] = row.reshape(Hkv, chunk)
     _check_updates(cfg, A, (1, 2))
 
 
