@@ -213,29 +213,6 @@ hipError_t launch_select_recent(const Params& p, int layer, int n_sink, const in
 // Device helpers
 // ----------------------------------------------------------------------------------------------
 #if defined(__HIPCC__)
-// Maps a linear chunk index to (sequence, chunk within the sequence) when every sequence is cut into
-// chunks of `chunk` items and `window_off` is subtracted from each length first (0: all S keys,
-// w: the S' prefix positions). Returns false for indices past the last chunk (grids are sized by an
-// upper bound). A sequence whose item count is 0 owns no chunk.
-__device__ inline bool find_chunk(const int32_t* __restrict__ cu, int n_seqs, int chunk, int window_off, int b,
-                                  int& seq, int& c, int& seq_begin, int& seq_len) {
-  int begin = cu[0];
-  for (int s = 0; s < n_seqs; ++s) {
-    const int end = cu[s + 1];
-    const int len = end - begin;
-    int items = len - window_off;
-    items = items > 0 ? items : 0;
-    const int n = (items + chunk - 1) / chunk;
-    if (b < n) {
-      seq = s; c = b; seq_begin = begin; seq_len = len;
-      return true;
-    }
-    b -= n;
-    begin = end;
-  }
-  return false;
-}
-
 // ---- wavefront and workgroup prefix sums on DPP moves (a few cycles each; a shuffle through LDS costs a round trip
 // per step). All of these must be called by every lane of the wavefront (workgroup), outside divergent branches.
 
@@ -254,6 +231,51 @@ __device__ inline int wave_prefix_sum(int v) {
   v = dpp_add_from<0x142, 0xa>(v);   // row_bcast:15: rows 1 and 3 add the total of the row before
   v = dpp_add_from<0x143, 0xc>(v);   // row_bcast:31: rows 2 and 3 add the total of the first two
   return v;
+}
+
+// Maps a linear chunk index to (sequence, chunk within the sequence) when every sequence is cut into
+// chunks of `chunk` items and `window_off` is subtracted from each length first (0: all S keys,
+// w: the S' prefix positions). Returns false for indices past the last chunk (grids are sized by an
+// upper bound). A sequence whose item count is 0 owns no chunk. Called by whole wavefronts, b the same for all lanes: in
+// larger batches every lane counts the chunks of one sequence (one after the other they are a chain of loads, 256 of
+// which kept the workgroups of the update's passes 3 to 4 times as long as their work did).
+__device__ inline bool find_chunk(const int32_t* __restrict__ cu, int n_seqs, int chunk, int window_off, int b,
+                                  int& seq, int& c, int& seq_begin, int& seq_len) {
+  if (n_seqs > 8) {
+    for (int s0 = 0; s0 < n_seqs; s0 += 64) {
+      const int s = s0 + (int)(threadIdx.x & 63);
+      const int begin = s < n_seqs ? cu[s] : 0, len = s < n_seqs ? cu[s + 1] - begin : 0;
+      int items = len - window_off;
+      items = items > 0 ? items : 0;
+      const int n = (items + chunk - 1) / chunk;
+      const int incl = wave_prefix_sum(n), total = __builtin_amdgcn_readlane(incl, 63);
+      if (b < total) {
+        const int lane = __builtin_ctzll(__ballot(incl > b));
+        seq = s0 + lane;
+        c = b - (__builtin_amdgcn_readlane(incl, lane) - __builtin_amdgcn_readlane(n, lane));
+        seq_begin = __builtin_amdgcn_readlane(begin, lane);
+        seq_len = __builtin_amdgcn_readlane(len, lane);
+        return true;
+      }
+      b -= total;
+    }
+    return false;
+  }
+  int begin = cu[0];
+  for (int s = 0; s < n_seqs; ++s) {
+    const int end = cu[s + 1];
+    const int len = end - begin;
+    int items = len - window_off;
+    items = items > 0 ? items : 0;
+    const int n = (items + chunk - 1) / chunk;
+    if (b < n) {
+      seq = s; c = b; seq_begin = begin; seq_len = len;
+      return true;
+    }
+    b -= n;
+    begin = end;
+  }
+  return false;
 }
 
 // Sum over the 16 lanes of a row; every lane of the row gets it.
