@@ -280,6 +280,32 @@ __device__ inline bool find_chunk2(const int32_t* __restrict__ cu, int n_seqs, i
     n_full = (total_tokens + chunk - 1) / chunk;
     return b < n;
   }
+  if (n_seqs > 8) {                      // by the lanes of the wavefront, as in find_chunk
+    int full0 = 0;
+    for (int s0 = 0; s0 < n_seqs; s0 += 64) {
+      const int s = s0 + (int)(threadIdx.x & 63);
+      const int at = s < n_seqs ? cu[s] : 0, len = s < n_seqs ? cu[s + 1] - at : 0;
+      const int nf = (len + chunk - 1) / chunk;
+      int items = len - window_off;
+      items = items > 0 ? items : 0;
+      const int n = (items + chunk - 1) / chunk;
+      const int incl = wave_prefix_sum(n), incl_full = wave_prefix_sum(nf), total = __builtin_amdgcn_readlane(incl, 63);
+      if (b < total) {
+        const int lane = __builtin_ctzll(__ballot(incl > b));
+        nc = __builtin_amdgcn_readlane(n, lane);
+        n_full = __builtin_amdgcn_readlane(nf, lane);
+        seq = s0 + lane;
+        c = b - (__builtin_amdgcn_readlane(incl, lane) - nc);
+        first_full = full0 + __builtin_amdgcn_readlane(incl_full, lane) - n_full;
+        seq_begin = __builtin_amdgcn_readlane(at, lane);
+        seq_len = __builtin_amdgcn_readlane(len, lane);
+        return true;
+      }
+      b -= total;
+      full0 += __builtin_amdgcn_readlane(incl_full, 63);
+    }
+    return false;
+  }
   int begin = cu[0];
   int full = 0;
   for (int s = 0; s < n_seqs; ++s) {
