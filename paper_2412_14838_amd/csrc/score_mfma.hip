@@ -927,6 +927,8 @@ bool score_mfma_supported(const Params& p, int dtype, int64_t k_stride_token) {
 // device holds one workgroup per compute unit, so the chunk is the multiple of the tile that minimises
 // rounds x (fixed + streaming): as few rounds of workgroups as possible, and within that the shortest chunk.
 // The number of chunks is exact for one sequence and an upper bound (one ragged tail per sequence) otherwise.
+constexpr double kFixedUs = 6.0, kUsPerKey = 0.0102;         // measured: 1.3 us per 128-key step of a full device
+
 template <int RS, int KS>
 static int pick_chunk(const Params& p, int cus) {
   using TL = Tile<RS, KS>;
@@ -934,15 +936,34 @@ static int pick_chunk(const Params& p, int cus) {
   int max_chunk = (int)((kLdsBudget - lds_fixed) / (emit_slabs<RS>() * (long long)sizeof(float))) - kMaxHalo - 2 * TL::kKeys;
   max_chunk = max_chunk / TL::kKeys * TL::kKeys;
   if (max_chunk > kMaxChunk) max_chunk = kMaxChunk;
-  const double fixed_us = 6.0, us_per_key = 0.0102;          // measured: 1.3 us per 128-key step of a full device
   int best = 256;
   double best_cost = 1e30;
   for (int chunk = 256; chunk <= max_chunk; chunk += TL::kKeys) {
     if (chunk % TL::kKeys) continue;
     const long long chunks = p.n_seqs == 1 ? (p.total_tokens + chunk - 1) / chunk : p.total_tokens / chunk + p.n_seqs;
     const long long rounds = (chunks * p.Hkv + cus - 1) / cus;
-    const double cost = rounds * (fixed_us + chunk * us_per_key);
+    const double cost = rounds * (kFixedUs + chunk * kUsPerKey);
     if (cost < best_cost - 1e-9) { best_cost = cost; best = chunk; }
+  }
+  return best;
+}
+
+// Shares into which the layers of a call are dealt. Short prompts: the chunks of all heads (`groups` workgroups to a share) do
+// not fill the device, and a workgroup that walks all layers leaves the rest idle. By the same cost as the chunk: rounds x
+// (fixed + streaming of a share's layers); the results do not depend on it.
+// Scoring of 16 layers, us, one share / dealt out: 8 heads, 128 rows, 1024 tokens 121 / 33, 2048 123 / 50, 4096 127 / 80 (at
+// 8192 tokens the chunks fill the device); 4 heads, 224 rows, 8192 tokens 203 / 119; four prompts of 300 to 1500 tokens
+// 138 / 81. A second round of workgroups, few as they may be, takes as long as the first: 8 heads, 128 rows, 5000 tokens (160
+// workgroups to a share), 4 layers 43.3 in one share, 46.9 in two, 16 layers 129 in one, 130 in two, 104 in five.
+static int pick_shares(int groups, int n_layers, int chunk, int cus) {
+  int best = 1;
+  double best_cost = 1e30;
+  for (int shares = 1; shares <= n_layers; ++shares) {
+    const int each = (n_layers + shares - 1) / shares;
+    if ((n_layers + each - 1) / each != shares) continue;    // the last share would be empty
+    const long long rounds = ((long long)groups * shares + cus - 1) / cus;
+    const double cost = rounds * (kFixedUs + (double)each * chunk * kUsPerKey);
+    if (cost < best_cost - 1e-9) { best_cost = cost; best = shares; }
   }
   return best;
 }
@@ -980,17 +1001,8 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   // Chunks of a single sequence, an upper bound on the chunks over several. (Workgroups that find no chunk cost more than
   // themselves: with one empty one beside 16 or 32 the dispatcher put two full ones on one compute unit.)
   const int grid_x = p.n_seqs == 1 ? (p.total_tokens + chunk - 1) / chunk : p.total_tokens / chunk + p.n_seqs;
-  // Short prompts: the chunks of all heads do not fill the device, and a workgroup that walks all layers of the call leaves
-  // the rest idle. The layers are then dealt out to blockIdx.z, as many shares as bring the workgroups closest to one per
-  // compute unit (a few too many run behind the others, at half the length or less); the results do not depend on it.
-  // Scoring of 16 layers, us, one share / dealt out: 8 heads, 128 rows, 1024 tokens 121 / 33, 2048 123 / 50, 4096 127 / 80 (at
-  // 8192 tokens the chunks fill the device); 4 heads, 224 rows, 8192 tokens 203 / 119; four prompts of 300 to 1500 tokens
-  // 138 / 81. One layer per call and long prompts: the grid alone, 0 to 10 % less time.
-  const int groups = grid_x * p.Hkv, cus = device_cus();
-  int shares = (cus + groups / 2) / groups;
-  shares = shares < 1 ? 1 : (shares > n_layers ? n_layers : shares);
+  const int shares = pick_shares(grid_x * p.Hkv, n_layers, chunk, device_cus());
   const int layers_each = (n_layers + shares - 1) / shares;
-  shares = (n_layers + layers_each - 1) / layers_each;
   if (phases & kPhaseStats)
     launch(DKV_KERNEL_SCORE_STATS, (score_stats_mfma<RS, KS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_stats, st, p, chunk,
            n_layers, layers_each, src, k_stride_token * 2, k_stride_head * 2, cu, partials, partials_stride_layer);
