@@ -36,3 +36,23 @@ def test_tail_of_the_packed_cache_is_zero(d, dtype):
         end = max(o for o in off if o <= capacity)
         for raw, done in zip(pack(capacity, False)[:2], pack(capacity, True)[:2]):
             assert torch.equal(raw[:end], done[:end]) and (raw[end:] == 7).all() and (done[end:] == 0).all(), capacity
+
+
+@pytest.mark.parametrize("n_seqs,L", [(1, 1), (64, 1), (13, 5), (1300, 4)])
+def test_first_block_left_out_among_many(n_seqs, L):
+    """The tail starts at the last offset within the capacity, whatever the number of blocks (one, 64, 65, thousands)."""
+    cfg = W.Workload("many", L=L, Hq=1, Hkv=1, d=64, seqlens=(30,) * n_seqs, dtype="bf16", w=16, P=7, mean_budget=4, layer_max=8,
+                     interval=1, seed=1)
+    desc = dkv.desc_from_workload(cfg)
+    gen = torch.Generator().manual_seed(n_seqs)
+    off = torch.cat([torch.zeros(1, dtype=torch.int64), torch.randint(1, 4, (n_seqs * L,), generator=gen).cumsum(0)])
+    dev = off.cuda()
+    total, n = int(off[-1]), n_seqs * L
+    for b in sorted({0, 1, n // 64, n // 2, n - 1, n} & set(range(n + 1))):
+        for capacity in sorted({max(int(off[b]) + x, 1) for x in (-1, 0, 1)} | {total + 9}):
+            k, v = (torch.full((capacity, cfg.d), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+            dkv.dkv_pack_zero_tail(desc, dev, k, v, capacity)
+            torch.cuda.synchronize()
+            end = int(off[off <= capacity].max())
+            for t in (k, v):
+                assert (t[:end] == 7).all() and (t[end:] == 0).all(), (b, capacity)
