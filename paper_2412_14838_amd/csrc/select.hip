@@ -12,7 +12,7 @@
 // the digit passes, us: 8 rows of 32736 positions (one layer) 26 -> 15, of 8160 9.6 -> 6.4; 256 rows of 32736 37 -> 21; 2048
 // rows of 4064 to 16352 102 -> 69; 16 rows of 992 7.7 -> 5.0.
 // Short path (the same rows, where the upper-tail path gives up): after two digits the elements that can still win are the
-// ones above those 22 bits plus the few that share them; when they fit (4096), steps 1-2 stop there, all of them
+// ones above those 22 bits plus the few that share them; when they fit (4096, few of them sharing the digits), steps 1-2 stop there, all of them
 // become keys, step 3 orders them and writes the first k. The result is the same list bit for bit.
 // Prefix sums and reductions over the workgroup go through DPP moves (see dkv_internal.h).
 //
@@ -35,6 +35,12 @@ constexpr int kSelResident = kSelPerThread * kSelThreads;      // 32768 position
 static_assert(kSelResident == kSelectSegment, "the workspace is sized for segments of what one workgroup holds");
 
 constexpr int kShortCap = 4096;                                // candidates the short path orders (see below)
+// ... of which share the threshold's bin or upper digits: each is compared with all others there, so more of them, mostly equal
+// scores, are better off with the third digit and the pick in position order. The line is k, between these two. us, 8 rows
+// of 8192 with that many equal scores at the threshold, compared / picked: k 128, 512 18.8 / 13, 1024 58 / 14, 3500 409 / 18;
+// k 512, 512 19.5 / 17, 1024 59 / 17; k 1024, 512 23 / 29, 1024 61 / 29; k 2048, 512 50 / 76.
+constexpr int kShareLow = 384, kShareHigh = 768;
+__device__ inline int share_cap(int k) { return k < kShareLow ? kShareLow : (k < kShareHigh ? k : kShareHigh); }
 constexpr int kTailBits = 12, kTailBins = 1 << kTailBits;      // bins of the upper-tail path (see below)
 static_assert(kTailBins == 4 * kSelThreads && DKV_MAX_LAYER_MAX <= 2 * kSelThreads, "four bins per thread; k is at most two elements per thread");
 constexpr int kOrderPerThread = kShortCap / kSelThreads;       // keys a thread takes through the ordering step
@@ -173,7 +179,8 @@ __global__ __launch_bounds__(kSelThreads) void select_topk_kernel(int Hkv, int w
     // are counted - about a quarter of a long row - in kTailBins equal steps between the two. The scan over the bins gives
     // every bin its place in the result; the elements of the threshold's bin and above go there in any order and are
     // ranked inside their bin by counting, so that selection and ordering share the histogram. Rows whose threshold bin
-    // holds too many (long plateaus of equal scores) or whose winners include zeros take the digit passes below. The list is the same bit for bit.
+    // holds too many (plateaus of equal scores; the largest score shared by all threads is seen before anything is counted)
+    // or whose winners include zeros take the digit passes below. The list is the same bit for bit.
     // What bounds it: the fixed chain of passes and barriers of one workgroup per row.
     if (n <= RES) {
       int2* __restrict__ bins = reinterpret_cast<int2*>(sel_smem);                 // [kTailBins] two copies of a count; then (first place, next place)
@@ -199,53 +206,56 @@ __global__ __launch_bounds__(kSelThreads) void select_topk_kernel(int Hkv, int w
         lo = tail_lo[i] < lo ? tail_lo[i] : lo;
         hi = tail_hi[i] > hi ? tail_hi[i] : hi;
       }
-      lo = lo > 1u ? lo : 1u;                                                      // zeros are not counted: places past the row hold some
-      const uint32_t range = hi > lo ? hi - lo : 0u;
-      const int shift = range < (uint32_t)kTailBins ? 0 : (32 - __builtin_clz(range)) - kTailBits;   // (range >> shift) < kTailBins
-      int* __restrict__ counts_of = reinterpret_cast<int*>(bins) + (lane & 1);
-#pragma unroll
-      for (int j = 0; j < PER; ++j)
-        if (v[j] >= lo) atomicAdd(&counts_of[2 * ((v[j] - lo) >> shift)], 1);
-      __syncthreads();
-      const int4 a = mine4[0], b = mine4[1];
-      const int c0 = a.x + a.y, c1 = a.z + a.w, c2 = b.x + b.y, c3 = b.z + b.w;    // ascending bins
-      const int p3 = block_exclusive_scan(c0 + c1 + c2 + c3, scratch), p2 = p3 + c3, p1 = p2 + c2, p0 = p1 + c1, end = p0 + c0;
-      mine4[0] = make_int4(p0, p0, p1, p1);
-      mine4[1] = make_int4(p2, p2, p3, p3);
-      if (p3 < k && k <= end) {                                                    // one thread; none if zeros are among the winners
-        const int q = k <= p2 ? 3 : (k <= p1 ? 2 : (k <= p0 ? 1 : 0));
-        picked[0] = kTailBins - 4 - 4 * tid + q;
-        picked[1] = q == 3 ? p2 : (q == 2 ? p1 : (q == 1 ? p0 : end));
-      }
-      __syncthreads();
-      const int m = picked[1];
-      if (m <= kShortCap) {
-        const uint32_t bound = lo + ((uint32_t)picked[0] << shift);
-        uint32_t lo2 = lo;
-        asm volatile("" : "+v"(lo2));                                              // the bins are computed again: kept from the counting they cost a register each
+      if (hi > lo || n <= kSelThreads) {                                           // else at least 1024 elements share the largest score
+        lo = lo > 1u ? lo : 1u;                                                      // zeros are not counted: places past the row hold some
+        const uint32_t range = hi > lo ? hi - lo : 0u;
+        const int shift = range < (uint32_t)kTailBins ? 0 : (32 - __builtin_clz(range)) - kTailBits;   // (range >> shift) < kTailBins
+        int* __restrict__ counts_of = reinterpret_cast<int*>(bins) + (lane & 1);
 #pragma unroll
         for (int j = 0; j < PER; ++j)
-          if (v[j] >= bound) sorted[atomicAdd(&bins[(v[j] - lo2) >> shift].y, 1)] = make_key(v[j], j * kSelThreads + tid);
+          if (v[j] >= lo) atomicAdd(&counts_of[2 * ((v[j] - lo) >> shift)], 1);
         __syncthreads();
-#pragma unroll
-        for (int c = 0; c < kOrderPerThread; ++c) {
-          const int j = tid + c * kSelThreads;
-          if (j < m) {
-            const u64 key = sorted[j];
-            const int2 span = bins[(~(uint32_t)(key >> 32) - lo) >> shift];        // the bin's places
-            int rank = span.x;
-            for (int i = span.x; i < span.y; i += 4) {                             // four reads in flight (the places behind the last bin are there)
-              const u64 k0 = sorted[i], k1 = sorted[i + 1], k2 = sorted[i + 2], k3 = sorted[i + 3];
-              rank += (k0 < key ? 1 : 0) + (i + 1 < span.y && k1 < key ? 1 : 0) + (i + 2 < span.y && k2 < key ? 1 : 0) +
-                      (i + 3 < span.y && k3 < key ? 1 : 0);
-            }
-            if (rank < k) out[rank] = MODE == kSelMerge ? cand.pos[cand_row + (uint32_t)key] : (int32_t)(uint32_t)key;
-          }
+        const int4 a = mine4[0], b = mine4[1];
+        const int c0 = a.x + a.y, c1 = a.z + a.w, c2 = b.x + b.y, c3 = b.z + b.w;    // ascending bins
+        const int p3 = block_exclusive_scan(c0 + c1 + c2 + c3, scratch), p2 = p3 + c3, p1 = p2 + c2, p0 = p1 + c1, end = p0 + c0;
+        mine4[0] = make_int4(p0, p0, p1, p1);
+        mine4[1] = make_int4(p2, p2, p3, p3);
+        if (p3 < k && k <= end) {                                                    // one thread; none if zeros are among the winners
+          const int q = k <= p2 ? 3 : (k <= p1 ? 2 : (k <= p0 ? 1 : 0));
+          picked[0] = kTailBins - 4 - 4 * tid + q;
+          const int places = q == 3 ? p2 : (q == 2 ? p1 : (q == 1 ? p0 : end));
+          if (places - (q == 3 ? p3 : (q == 2 ? p2 : (q == 1 ? p1 : p0))) <= share_cap(k)) picked[1] = places;   // else left as it is: too many
         }
-        for (int j = k + tid; j < layer_max; j += kSelThreads) out[j] = -1;
-        return;
+        __syncthreads();
+        const int m = picked[1];
+        if (m <= kShortCap) {
+          const uint32_t bound = lo + ((uint32_t)picked[0] << shift);
+          uint32_t lo2 = lo;
+          asm volatile("" : "+v"(lo2));                                              // the bins are computed again: kept from the counting they cost a register each
+#pragma unroll
+          for (int j = 0; j < PER; ++j)
+            if (v[j] >= bound) sorted[atomicAdd(&bins[(v[j] - lo2) >> shift].y, 1)] = make_key(v[j], j * kSelThreads + tid);
+          __syncthreads();
+#pragma unroll
+          for (int c = 0; c < kOrderPerThread; ++c) {
+            const int j = tid + c * kSelThreads;
+            if (j < m) {
+              const u64 key = sorted[j];
+              const int2 span = bins[(~(uint32_t)(key >> 32) - lo) >> shift];        // the bin's places
+              int rank = span.x;
+              for (int i = span.x; i < span.y; i += 4) {                             // four reads in flight (the places behind the last bin are there)
+                const u64 k0 = sorted[i], k1 = sorted[i + 1], k2 = sorted[i + 2], k3 = sorted[i + 3];
+                rank += (k0 < key ? 1 : 0) + (i + 1 < span.y && k1 < key ? 1 : 0) + (i + 2 < span.y && k2 < key ? 1 : 0) +
+                        (i + 3 < span.y && k3 < key ? 1 : 0);
+              }
+              if (rank < k) out[rank] = MODE == kSelMerge ? cand.pos[cand_row + (uint32_t)key] : (int32_t)(uint32_t)key;
+            }
+          }
+          for (int j = k + tid; j < layer_max; j += kSelThreads) out[j] = -1;
+          return;
+        }
+        __syncthreads();                                                             // the digit passes reuse the bins and picked
       }
-      __syncthreads();                                                             // the digit passes reuse the bins and picked
     }
   }
 
@@ -317,7 +327,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk_kernel(int Hkv, int w
   // collide on the LDS banks more than 8 copies of a few hot 11-bit digits collide on their addresses.)
   const int sure = k - rem;
   const int m_short = sure + picked[2];
-  const bool short_path = MODE != kSelSegments && n <= RES && m_short <= kShortCap;
+  const bool short_path = MODE != kSelSegments && n <= RES && m_short <= kShortCap && picked[2] <= share_cap(k);
   int m_keys = k;                                     // keys the ordering step sorts
   const u64* order_src = keys;
   if (short_path) {
