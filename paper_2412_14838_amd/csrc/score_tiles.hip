@@ -34,6 +34,7 @@ namespace dkv {
 constexpr int kWaves = 8;             // wavefronts per workgroup
 constexpr int kThreads = kWaves * 64;
 constexpr int kTileRow = kWaves * 32; // keys of one tile of every wavefront: a chunk is a whole number of these
+static_assert(kTileRow >= kMfmaMinChunk && kTileRow >= kGenericKeys, "the workspace is sized for chunks of so many keys");
 
 // Q and K of the layers one launch covers (kernel argument, indexed by the layer's place in the launch).
 struct TileLayers {
@@ -134,7 +135,7 @@ struct Geo {
   static constexpr int kEnd = kSlots == 2 ? (3 * kLoads + 7) / 8 : 0, kFirst = (kLoads - kEnd + 1) / 2;
   static constexpr int kQRow = D * 2 + 16;                     // bytes per row and term of Q in LDS (16 of padding: conflict-free 16-byte reads)
   static constexpr int kQPieces = D * E::kBytes / 16;          // 16-byte pieces per row of Q in memory
-  static constexpr int kMaxRows = kTerms * D > 256 ? 128 : 256;   // three terms of 128 rows of 128 elements are what LDS takes
+  static constexpr int kMaxRows = kTerms * D > 256 ? 128 : 256;   // 8 pieces of Q a thread, as at head size 64 (in LDS three terms of 160 rows of 128 elements would fit)
   static constexpr int kQLoads = kMaxRows * kQPieces / kThreads;  // pieces per thread of the widest Q block
   static_assert(kPerTask <= 2 && (kTerms == 1 || NT == 1), "a task is one or two stages, and one of one tile for split elements");
 };
@@ -1011,8 +1012,8 @@ __global__ __launch_bounds__(64) void score_fix_borders_tiles(Params p, int chun
   out[s] = fmaxf(out[s], m);
 }
 
-// Offsets of key rows inside a chunk (at most 1024 rows) are formed in 32 bits; Q has to fit LDS. What does not takes
-// the vector-ALU kernels.
+// Offsets of key rows inside a chunk (at most 1024 rows) are formed in 32 bits; Q has to fit LDS whole (see kMaxRows: fp32 at
+// head size 128 up to 128 rows). What does not takes the vector-ALU kernels.
 bool score_tiles_supported(const Params& p, int dtype, int64_t k_stride_token) {
   const int64_t stride_b = k_stride_token * (dtype == DKV_BF16 ? 2 : 4);
   if (stride_b * 1024 >= ((int64_t)1 << 32) || 2 * p.half > kMaxHalo || p.rows > 256) return false;

@@ -338,7 +338,8 @@ def test_fixed_pattern_schedules_match_the_oracle_and_validate(lib):
 
 def test_score_path_and_the_token_stride_limit(lib):
     """The matrix-core kernels form key-row offsets in 32 bits: a token stride whose product with the largest row
-    index of a chunk would pass 2^32 bytes must take the vector-ALU kernels (dkv_score_path tells which)."""
+    index of a chunk would pass 2^32 bytes must take the vector-ALU kernels (dkv_score_path is 1 for the kernels that stream
+    bf16 keys of head size 128 and 0 for all others)."""
     bf = _good(head_dim=128, dtype=dkv.DKV_BF16, n_q_heads=8, n_kv_heads=2, window=32)
     assert lib.dkv_score_path(C.byref(bf), 128) == 1
     assert lib.dkv_score_path(C.byref(bf), 8 * 128) == 1                   # token-major, 8 KV heads
@@ -346,7 +347,7 @@ def test_score_path_and_the_token_stride_limit(lib):
     assert lib.dkv_score_path(C.byref(bf), limit_elems // 8 * 8) == 1
     assert lib.dkv_score_path(C.byref(bf), (limit_elems // 8 + 1) * 8) == 0
     assert lib.dkv_score_path(C.byref(bf), 1 << 22) == 0
-    assert lib.dkv_score_path(C.byref(_good()), 64) == 0                   # fp32: vector ALU
+    assert lib.dkv_score_path(C.byref(_good()), 64) == 0                   # fp32: keys in registers
     assert lib.dkv_score_path(C.byref(_good(head_dim=64, dtype=dkv.DKV_BF16)), 64) == 0
     assert lib.dkv_score_path(C.byref(bf), 100) == dkv.DKV_ERR_INVALID_ARG  # rows overlap
     assert lib.dkv_score_path(None, 128) == dkv.DKV_ERR_INVALID_ARG

@@ -39,7 +39,7 @@ CASES = {
     "pool15": small_cfg("pool15", P=15, seqlens=(900,)),
     "pool63": small_cfg("pool63", P=63, seqlens=(2300, 70)),                     # the widest pooling window
     "rows256": small_cfg("rows256", Hq=16, Hkv=2, seqlens=(1300, 300)),         # G * w = 256: the most score rows
-    "small_f32_d128": small_cfg("f32_d128", dtype="f32", seqlens=(900, 40, 300)),   # fp32 at head size 128 (vector ALU)
+    "small_f32_d128": small_cfg("f32_d128", dtype="f32", seqlens=(900, 40, 300)),   # fp32 at head size 128
 }
 
 
