@@ -387,7 +387,7 @@ __device__ inline void load_rest(Slot<G>& other, const Pending<G>& pend, int j) 
 // of opposite sign can meet as inf - inf where multiply-adds one after the other stay on the side that overflowed first,
 // and exp2(c * x - y), with c * x unrounded and y the rounded maximum or normaliser, is off by |y| 2^-25 octaves. None of
 // that shows for logits of ordinary size; all of it ends as a sum of exponentials that is no number or as a |y| past
-// kMaxExponent. Such sums are taken again from the elements: a wavefront's statistics, the column sums of the keys. Keys
+// kMaxExponent. Such sums are taken again from the elements: a row's statistics of a chunk, a key's column sum. Keys
 // filled with the type's lowest value or with -inf then have no weight, as in the definition, one of several logits of
 // 10^7 takes all of it, and logits of +inf or NaN leave no number in their (sequence, KV head).
 constexpr float kMaxExponent = 8192.0f;     // logits of 5700
@@ -546,7 +546,6 @@ __global__ __launch_bounds__(kThreads) void score_stats_tiles(Params p, int n_la
     const int lim_all = prefix_rel < cur.len ? prefix_rel : cur.len;
     const int key0 = tile_key(S * G::kTiles, walk.wave);
     const bool masked = tile_key(S * G::kTiles + G::kTiles - 1, walk.wave) + 31 >= lim_all;   // a key of the stage is in the window or past the chunk
-    float l_all = 0.0f, m_large = 0.0f;                     // no number if one of the sums is none; the largest maximum
     // a quarter of the slices finds the maximum of row tile t's logits `x`, the others take the exponentials
     all_row_tiles<G, true>(qrow, plane, k, other, walk.pend, row_tiles, [&](auto more, floatx16 (&x)[G::kTiles], floatx16 (&y)[G::kTiles], int t) {
       constexpr int J = G::kSteps, JM = J / 4, V = G::kTiles * 16;
@@ -584,34 +583,8 @@ __global__ __launch_bounds__(kThreads) void score_stats_tiles(Params p, int n_la
       float l_lo, l_hi;
       both_halves((s0 + s1) + (s2 + s3), l_lo, l_hi);
       const float l = fmaf(old.y, fast_exp2(old.x - m_use), l_lo + l_hi);
-      l_all += l;
-      m_large = fmaxf(m_large, fabsf(m_use));
       if (lane < 32) mine[t * 32] = make_float2(m, l);
     });
-    if (__builtin_expect(__any(no_number(l_all) || m_large > kMaxExponent), 0)) {   // this wavefront's keys so far, from the elements
-      int lane = threadIdx.x & 63;
-      asm volatile("" : "+v"(lane));               // nothing of this is computed ahead (see load_q)
-      const char* __restrict__ q0 = q_base<E>(src, cur, p);
-      const char* __restrict__ k0 = key_base(src, cur, stride_token_b, stride_head_b);
-#pragma unroll 1
-      for (int t = 0; t < row_tiles; ++t) {
-        const int r = t * 32 + (lane & 31), row = r < p.rows ? r : p.rows - 1;
-        int limit = prefix_rel + r % p.w;           // as above
-        limit = limit < cur.len ? limit : cur.len - 1;
-        float m = -INFINITY, l = 0.0f;
-#pragma unroll 1
-        for (int i = 0; i < (S + 1) * G::kTiles * 16; ++i) {         // the half-wavefronts take half of a tile's keys each
-          const int key = tile_key(i / 16, walk.wave) + 16 * (lane >> 5) + i % 16;
-          if (key <= limit)
-            merge_pair(m, l, make_float2(logit_fma<E, D>(q0 + (int64_t)row * D * E::kBytes, k0 + (int64_t)key * stride_token_b, cexp), 1.0f));
-        }
-        float m_lo, m_hi, l_lo, l_hi;
-        both_halves(m, m_lo, m_hi);
-        both_halves(l, l_lo, l_hi);
-        merge_pair(m_lo, l_lo, make_float2(m_hi, l_hi));
-        if (lane < 32) mine[t * 32] = make_float2(m_lo, l_lo);
-      }
-    }
     // Q of the next task (loads return in order: it arrives right behind the other slot's keys, which the next stage
     // needs anyway), then the first of the keys that take this slot
     constexpr bool kLast = S == G::kPerTask - 1;
@@ -621,24 +594,40 @@ __global__ __launch_bounds__(kThreads) void score_stats_tiles(Params p, int n_la
     walk.template slot_used<SLOT, S>();
     if (!kLast) return;
     lds_barrier();
-    if ((int)threadIdx.x < p.rows) {               // the wavefronts' statistics in a fixed order
-      const int r = threadIdx.x;
-      float M = -INFINITY;
+    const int r = threadIdx.x;
+    float M = -INFINITY, L = 0.0f;
+    float2* __restrict__ part = reinterpret_cast<float2*>(partials + cur.layer * partials_stride_layer) +
+                                ((int64_t)cur.chunk_id * p.Hkv + cur.head) * p.rows_pad;
+    if (r < p.rows) {                              // the wavefronts' statistics in a fixed order
 #pragma unroll
       for (int q = 0; q < kWaves; ++q) M = fmaxf(M, stat[q * row_tiles * 32 + r].x);
       const float Mu = M == -INFINITY ? 0.0f : M;
-      float L = 0.0f;
 #pragma unroll
       for (int q = 0; q < kWaves; ++q) {
         const float2 v = stat[q * row_tiles * 32 + r];
         L = fmaf(v.y, fast_exp2(v.x - Mu), L);
       }
-      float2* __restrict__ part = reinterpret_cast<float2*>(partials + cur.layer * partials_stride_layer);
-      part[((int64_t)cur.chunk_id * p.Hkv + cur.head) * p.rows_pad + r] = make_float2(M, L);
+      part[r] = make_float2(M, L);
     }
     if (has_next) {
       store_q<G>(qnext, smem, row_tiles);
       lds_barrier();
+    }
+    // behind the barrier, where no other wavefront waits for it: rows of the chunk again, from the elements
+    const bool again = no_number(L) || (M != -INFINITY && fabsf(M) > kMaxExponent);
+    if (__builtin_expect(__any(again), 0)) {
+      const Task t = walk.find(walk.task);         // (the current one: found again, its fields need no registers until here)
+      if (again) {
+        const char* __restrict__ qr = q_base<E>(src, t, p) + (int64_t)r * D * E::kBytes;
+        const char* __restrict__ kk = key_base(src, t, stride_token_b, stride_head_b);
+        const int limit = t.S - p.w - t.c0 + r % p.w, n = limit < t.len ? limit + 1 : t.len;
+        M = -INFINITY;
+        L = 0.0f;
+#pragma unroll 1
+        for (int key = 0; key < n; ++key, kk += stride_token_b) merge_pair(M, L, make_float2(logit_fma<E, D>(qr, kk, cexp), 1.0f));
+        part = reinterpret_cast<float2*>(partials + t.layer * partials_stride_layer) + ((int64_t)t.chunk_id * p.Hkv + t.head) * p.rows_pad;
+        part[r] = make_float2(M, L);
+      }
     }
     walk.advance();
   });
@@ -733,8 +722,7 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
   float* __restrict__ part = lse_s + 256;                                             // [kChunk + kMaxHalo], key c0 - half first
   float* __restrict__ halo_s = part + kChunk + kMaxHalo;                              // [2][8 row tiles][64] (HALO)
   float2* __restrict__ mstage = reinterpret_cast<float2*>(halo_s);                    // [kThreads] (single-layer merge)
-  int* __restrict__ large_rows = reinterpret_cast<int*>(halo_s + 2 * 8 * 64);         // [4] a normaliser of 64 rows past kMaxExponent
-  int* __restrict__ no_sums = large_rows + 4;                                         // [kWaves + 16] a wavefront's, a halo unit's sums hold no number
+  float* __restrict__ lse_all = halo_s + 2 * 8 * 64;                                  // [256] the normalisers as they are
   const int tid = threadIdx.x, lane = tid & 63;
   Walk<E, D, NT> walk(p, src, cu, n_layers, stride_token_b, stride_head_b);
   if (walk.task >= walk.n_tasks) return;
@@ -752,10 +740,12 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
         : lse_in + ((int64_t)t.seq * p.Hq + (int64_t)t.head * p.G) * p.w;
     return src_row[tid < p.rows ? tid : p.rows - 1];
   };
-  auto put_normaliser = [&](float v) {                           // v: log2 domain, all threads
-    const bool large = __any(tid < p.rows && fabsf(v) > kMaxExponent);
-    if (tid < 256) lse_s[tid] = tid < p.rows ? v : INFINITY;
-    if (tid < 256 && lane == 0) large_rows[wave] = large;
+  // lse_s: -inf in the place of normalisers past kMaxExponent, which makes every sum over their rows infinite
+  auto put_normaliser = [&](float v) {                           // v: log2 domain
+    if (tid < 256) {
+      lse_s[tid] = tid < p.rows ? (fabsf(v) > kMaxExponent ? -INFINITY : v) : INFINITY;
+      lse_all[tid] = v;
+    }
   };
   auto store_normaliser = [&](float v) { put_normaliser(from_rows ? v : v * kLog2e); };
   const bool merge_here = HALO && lse_rows == nullptr && lse_in == nullptr;
@@ -764,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     merge_chunks(reinterpret_cast<const float2*>(partials) + ((int64_t)first * p.Hkv + t.head) * p.rows_pad, n, p.rows_pad,
                  (uint32_t)(p.Hkv * p.rows_pad), mstage);
     lds_barrier();
-    put_normaliser(tid < p.rows ? combine_groups(mstage, p.rows_pad, tid, p.rows) : 0.0f);
+    put_normaliser(tid < p.rows ? combine_groups(mstage, p.rows_pad, tid, p.rows) : INFINITY);
     lds_barrier();                                             // mstage and halo_s share their place
   };
   // Halo units: one row tile of one tile of halo keys (the `half` before the chunk, then the `half` behind it); the halves
@@ -795,10 +785,7 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
       s2 += fast_exp2(fmaf(acc[0][4 * i + 2], cexp, -lz.z));
       s3 += fast_exp2(fmaf(acc[0][4 * i + 3], cexp, -lz.w));
     }
-    const float sum = (s0 + s1) + (s2 + s3);
-    halo_s[(kt * 8 + t) * 64 + lane] = sum;
-    const bool none = __any(no_number(sum));
-    if (lane == 0) no_sums[kWaves + unit] = none;
+    halo_s[(kt * 8 + t) * 64 + lane] = (s0 + s1) + (s2 + s3);
   };
   // Column sum of a key from the elements.
   auto column_fma = [&](const Task& t, int key) {
@@ -806,8 +793,8 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     const char* __restrict__ kk = key_base(src, t, stride_token_b, stride_head_b) + (int64_t)key * stride_token_b;
     float sum = 0.0f;
 #pragma unroll 1
-    for (int r = 0; r < p.rows; ++r, qr += D * E::kBytes) sum += fast_exp2(logit_fma<E, D>(qr, kk, cexp) - lse_s[r]);
-    return sum * p.row_scale;
+    for (int r = 0; r < p.rows; ++r, qr += D * E::kBytes) sum += fast_exp2(logit_fma<E, D>(qr, kk, cexp) - lse_all[r]);
+    return sum;
   };
   {
     QBlock<G> q;
@@ -838,7 +825,6 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     const int prefix = cur.S - p.w;
     int len = prefix - cur.c0;                               // prefix keys of the chunk (none: only the guard is written)
     len = len < cur.len ? len : cur.len;
-    const int large = large_rows[lane & 3];                  // read here: the next task's are written behind the last barrier
     // column sums of all keys of the stage; those past the prefix are not used
     float col[G::kTiles];
 #pragma unroll
@@ -870,16 +856,26 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
 #pragma unroll
       for (int c = 0; c < T; ++c) col[c] += (sum[c][0] + sum[c][1]) + (sum[c][2] + sum[c][3]);
     });
+    float sums[G::kTiles];
     bool none = false;
 #pragma unroll
     for (int c = 0; c < G::kTiles; ++c) {
       float lo, hi;
       both_halves(col[c], lo, hi);
-      if (lane < 32) part[half + tile_key(S * G::kTiles + c, wave) + lane] = (lo + hi) * p.row_scale;
-      none |= no_number(lo + hi);
+      sums[c] = lo + hi;
+      none |= no_number(sums[c]);
     }
-    none = __any(none);
-    if (lane == 0 && (S == 0 || none)) no_sums[wave] = none;
+    if (__builtin_expect(__any(none), 0)) {
+#pragma unroll 1
+      for (int c = 0; c < G::kTiles; ++c) {
+        const int key = tile_key(S * G::kTiles + c, wave) + (lane & 31);
+        const float had = c == 0 ? sums[0] : sums[G::kTiles - 1];
+        if (key < len && no_number(had)) (c == 0 ? sums[0] : sums[G::kTiles - 1]) = column_fma(cur, key);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < G::kTiles; ++c)
+      if (lane < 32) part[half + tile_key(S * G::kTiles + c, wave) + lane] = sums[c] * p.row_scale;
     if (HALO && kLast)
       for (int u = wave + kWaves; u < halo_units; u += kWaves) {
         Slot<H> kh;
@@ -897,8 +893,6 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     walk.template slot_used<SLOT, S>();
     if (!kLast) return;
     lds_barrier();
-    // checked when the outputs are ready: the flag arrives with the sums they are made of
-    int sums_to_check = no_sums[lane < kWaves + halo_units ? lane : 0] | (large << 1);
     if (HALO && half > 0) {
       if (tid < 2 * half && len > 0) {
         const int kt = tid >> 5, l = tid & 31;
@@ -909,7 +903,9 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
         }
         const int key = tid < half ? tid - half : kChunk + tid - half;
         const bool in = tid < half ? cur.c0 > 0 : cur.c0 + key < prefix;   // c0 is 0 or at least a chunk, longer than half
-        part[half + key] = in ? (lo + hi) * p.row_scale : -INFINITY;
+        float sum = lo + hi;
+        if (__builtin_expect(in && no_number(sum), 0)) sum = column_fma(cur, key);
+        part[half + key] = in ? sum * p.row_scale : -INFINITY;
       }
       lds_barrier();
     }
@@ -919,13 +915,16 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     const int first = HALO && cur.c0 > 0 ? -half : 0;
     int last = HALO && len == kChunk ? kChunk + half - 1 : len - 1;
     last = last < prefix - cur.c0 - 1 ? last : prefix - cur.c0 - 1;
-    constexpr int kOut = (kChunk + kThreads - 1) / kThreads;
-    float pooled[kOut];
-    for (;;) {
+    if (!HALO && tid < 2 * half && len > 0) {                // [0, half): the first column sums, [half, 2 half): the last
+      const int i = tid < half ? tid : len - 2 * half + tid;
+      edges[cur.layer * edges_stride_layer + ((int64_t)cur.chunk_id * p.Hkv + cur.head) * kMaxHalo + tid] =
+          i >= 0 && i < len ? part[half + i] : -INFINITY;
+    }
 #pragma unroll
-      for (int u = 0; u < kOut; ++u) {
-        const int i = tid + u * kThreads;
-        float m = -INFINITY;                                   // the guard over the window slots
+    for (int u = 0; u < (kChunk + kThreads - 1) / kThreads; ++u) {
+      const int i = tid + u * kThreads;
+      if (i < cur.len && prefix > 0) {
+        float m = -INFINITY;                                 // the guard over the window slots
         if (i < len) {
           m = part[half + i];
           for (int o = 1; o <= half; ++o) {
@@ -933,31 +932,8 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
             m = fmaxf(m, fmaxf(lo, hi));
           }
         }
-        pooled[u] = m;
+        out[i] = m;
       }
-      if (__builtin_expect(!__any(sums_to_check != 0), 1)) break;
-      const bool all = __any((sums_to_check & 2) != 0);        // uniform over the workgroup, as is the branch
-      sums_to_check = 0;
-      lds_barrier();
-      int i0 = threadIdx.x;
-      asm volatile("" : "+v"(i0));                             // nothing of this is computed ahead (see load_q)
-#pragma unroll 1
-      for (int i = i0; i < kChunk + 2 * half; i += kThreads) { // the chunk's keys, then the halo
-        const int e = i - kChunk, key = e < 0 ? i : (e < half ? e - half : kChunk + e - half);
-        const bool there = e < 0 ? i < len : HALO && len > 0 && (e < half ? cur.c0 > 0 : cur.c0 + key < prefix);
-        if (there && (all || no_number(part[half + key]))) part[half + key] = column_fma(cur, key);
-      }
-      lds_barrier();
-    }
-#pragma unroll
-    for (int u = 0; u < kOut; ++u) {
-      const int i = tid + u * kThreads;
-      if (i < cur.len && prefix > 0) out[i] = pooled[u];
-    }
-    if (!HALO && tid < 2 * half && len > 0) {                // [0, half): the first column sums, [half, 2 half): the last
-      const int i = tid < half ? tid : len - 2 * half + tid;
-      edges[cur.layer * edges_stride_layer + ((int64_t)cur.chunk_id * p.Hkv + cur.head) * kMaxHalo + tid] =
-          i >= 0 && i < len ? part[half + i] : -INFINITY;
     }
     if (has_next) {
       store_q<G>(qnext, smem, row_tiles);
@@ -1057,7 +1033,7 @@ static hipError_t launch_tiles_t(const Params& p, int phases, int n_layers, cons
   const int row_tiles = (p.rows + 31) / 32;
   const size_t q_bytes = (size_t)G::kTerms * row_tiles * 32 * G::kQRow;
   const size_t lds_stats = q_bytes + (size_t)kWaves * row_tiles * 32 * sizeof(float2);
-  const size_t lds_emit = q_bytes + (256 + chunk + kMaxHalo + 2 * 8 * 64 + 4 + kWaves + 16) * sizeof(float);
+  const size_t lds_emit = q_bytes + (256 + chunk + kMaxHalo + 2 * 8 * 64 + 256) * sizeof(float);
   static std::atomic<uint64_t> given{0};
   const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_tiles<E, D, NT>), kMaxLds},
                                          {reinterpret_cast<const void*>(&score_emit_tiles<E, D, NT, false>), kMaxLds},
