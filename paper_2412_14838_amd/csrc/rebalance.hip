@@ -423,8 +423,13 @@ __global__ __launch_bounds__(Shape::kThreads, PASS == 1 || PICKS_HERE || Shape::
     if (lowest != 0u) {                                       // else the zeros outside the chunk would be among them
       int mine = 0;
 #pragma unroll
-      for (int j = 0; j < NV; ++j)
-        mine += (cv.v[j].x - bound < span) + (cv.v[j].y - bound < span) + (cv.v[j].z - bound < span) + (cv.v[j].w - bound < span);
+      for (int j = 0; j < NV; ++j) {                           // in place: what overflows the list is read again
+        cv.v[j].x -= bound;
+        cv.v[j].y -= bound;
+        cv.v[j].z -= bound;
+        cv.v[j].w -= bound;
+        mine += (cv.v[j].x < span) + (cv.v[j].y < span) + (cv.v[j].z < span) + (cv.v[j].w < span);
+      }
       const int incl = wave_prefix_sum(mine);
       int base = 0;
       if ((threadIdx.x & 63) == 63 && incl) base = atomicAdd(&list_size, incl);
@@ -434,10 +439,10 @@ __global__ __launch_bounds__(Shape::kThreads, PASS == 1 || PICKS_HERE || Shape::
       if (n_listed <= Shape::kListCap) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-          if (cv.v[j].x - bound < span) list[slot++] = cv.v[j].x;
-          if (cv.v[j].y - bound < span) list[slot++] = cv.v[j].y;
-          if (cv.v[j].z - bound < span) list[slot++] = cv.v[j].z;
-          if (cv.v[j].w - bound < span) list[slot++] = cv.v[j].w;
+          if (cv.v[j].x < span) list[slot++] = cv.v[j].x + bound;
+          if (cv.v[j].y < span) list[slot++] = cv.v[j].y + bound;
+          if (cv.v[j].z < span) list[slot++] = cv.v[j].z + bound;
+          if (cv.v[j].w < span) list[slot++] = cv.v[j].w + bound;
           __builtin_amdgcn_sched_barrier(0);                  // vector by vector: side by side they take registers that cost occupancy
         }
       }
