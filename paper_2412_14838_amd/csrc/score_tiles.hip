@@ -390,6 +390,8 @@ __device__ inline void load_rest(Slot<G>& other, const Pending<G>& pend, int j) 
 // kMaxExponent. Such sums are taken again from the elements: a row's statistics of a chunk, a key's column sum. Keys
 // filled with the type's lowest value or with -inf then have no weight, as in the definition, one of several logits of
 // 10^7 takes all of it, and logits of +inf or NaN leave no number in their (sequence, KV head).
+// What that costs, us for 2 layers of 8192 fp32 keys of 128, 8 heads, 128 rows: 74 without, 1060 with one key in 100 of -inf
+// (all rows of its chunk), 1390 with NaN in every row; the vector ALU took 570 for any.
 constexpr float kMaxExponent = 8192.0f;     // logits of 5700
 
 // Infinite or NaN (by its bits: the compiler may assume that there are no NaNs).
@@ -399,27 +401,52 @@ __device__ inline bool no_number(float v) {
   return (u & 0x7f800000u) == 0x7f800000u;
 }
 
-// c * (one logit), as fp32 multiply-adds in the order of the elements; rounded before anything is subtracted from it.
+// y[i] = c * (logit of row i and this lane's key), as fp32 multiply-adds in the order of the elements; rounded before anything
+// is subtracted from it. q: the first of eight rows, of which `rows` are there (the last one repeated for the others).
+constexpr int kFmaRows = 8;
 template <typename E, int D>
-__device__ inline float logit_fma(const char* __restrict__ q, const char* __restrict__ k, float c) {
-  float acc = 0.0f;
-#pragma unroll 1
-  for (int j = 0; j < D * E::kBytes; j += 16) {
-    const uint4 a = *reinterpret_cast<const uint4*>(q + j), b = *reinterpret_cast<const uint4*>(k + j);
-    const uint32_t u[4] = {a.x, a.y, a.z, a.w}, v[4] = {b.x, b.y, b.z, b.w};
+__device__ __forceinline__ void logits_fma(const char* __restrict__ q, int rows, const char* __restrict__ k, float c, float (&y)[kFmaRows]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if constexpr (E::kBytes == 4) {
-        acc = fmaf(__uint_as_float(u[i]), __uint_as_float(v[i]), acc);
-      } else {
-        acc = fmaf(__uint_as_float(u[i] << 16), __uint_as_float(v[i] << 16), acc);
-        acc = fmaf(__uint_as_float(u[i] & 0xffff0000u), __uint_as_float(v[i] & 0xffff0000u), acc);
+  for (int i = 0; i < kFmaRows; ++i) y[i] = 0.0f;
+#pragma unroll 4
+  for (int j = 0; j < D * E::kBytes; j += 16) {
+    const uint4 b = *reinterpret_cast<const uint4*>(k + j);
+    const uint32_t v[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < kFmaRows; ++i) {
+      const uint4 a = *reinterpret_cast<const uint4*>(q + (i < rows ? i : rows - 1) * (D * E::kBytes) + j);
+      const uint32_t u[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (E::kBytes == 4) {
+          y[i] = fmaf(__uint_as_float(u[e]), __uint_as_float(v[e]), y[i]);
+        } else {
+          y[i] = fmaf(__uint_as_float(u[e] << 16), __uint_as_float(v[e] << 16), y[i]);
+          y[i] = fmaf(__uint_as_float(u[e] & 0xffff0000u), __uint_as_float(v[e] & 0xffff0000u), y[i]);
+        }
       }
     }
   }
-  float y = acc * c;
-  asm volatile("" : "+v"(y));
-  return y;
+#pragma unroll
+  for (int i = 0; i < kFmaRows; ++i) {
+    y[i] *= c;
+    asm volatile("" : "+v"(y[i]));
+  }
+}
+
+// Column sum of a key from the elements: rows of q against the key at k, normalisers lse (log2 domain).
+template <typename E, int D>
+__device__ __forceinline__ float column_fma(const char* __restrict__ q, int rows, const char* __restrict__ k, float c,
+                                            const float* __restrict__ lse) {
+  float sum = 0.0f, y[kFmaRows];
+#pragma unroll 1
+  for (int r0 = 0; r0 < rows; r0 += kFmaRows) {
+    logits_fma<E, D>(q + (int64_t)r0 * D * E::kBytes, rows - r0, k, c, y);
+#pragma unroll
+    for (int i = 0; i < kFmaRows; ++i)
+      if (r0 + i < rows) sum += fast_exp2(y[i] - lse[r0 + i]);
+  }
+  return sum;
 }
 
 // The lower and the upper half-wavefront's value of every lane pair (l, l + 32), in both lanes.
@@ -617,16 +644,34 @@ __global__ __launch_bounds__(kThreads) void score_stats_tiles(Params p, int n_la
     const bool again = no_number(L) || (M != -INFINITY && fabsf(M) > kMaxExponent);
     if (__builtin_expect(__any(again), 0)) {
       const Task t = walk.find(walk.task);         // (the current one: found again, its fields need no registers until here)
-      if (again) {
-        const char* __restrict__ qr = q_base<E>(src, t, p) + (int64_t)r * D * E::kBytes;
-        const char* __restrict__ kk = key_base(src, t, stride_token_b, stride_head_b);
-        const int limit = t.S - p.w - t.c0 + r % p.w, n = limit < t.len ? limit + 1 : t.len;
-        M = -INFINITY;
-        L = 0.0f;
+      const char* __restrict__ k0 = key_base(src, t, stride_token_b, stride_head_b);
+      part = reinterpret_cast<float2*>(partials + t.layer * partials_stride_layer) + ((int64_t)t.chunk_id * p.Hkv + t.head) * p.rows_pad;
+      const unsigned long long which = __ballot(again);
 #pragma unroll 1
-        for (int key = 0; key < n; ++key, kk += stride_token_b) merge_pair(M, L, make_float2(logit_fma<E, D>(qr, kk, cexp), 1.0f));
-        part = reinterpret_cast<float2*>(partials + t.layer * partials_stride_layer) + ((int64_t)t.chunk_id * p.Hkv + t.head) * p.rows_pad;
-        part[r] = make_float2(M, L);
+      for (int g = 0; g < 64; g += kFmaRows) {     // eight of this wavefront's rows at a time, a key to a lane
+        if (!(which >> g & ((1u << kFmaRows) - 1u))) continue;
+        const int r0 = walk.wave * 64 + g;
+        float m[kFmaRows], l[kFmaRows], y[kFmaRows];
+#pragma unroll
+        for (int i = 0; i < kFmaRows; ++i) { m[i] = -INFINITY; l[i] = 0.0f; }
+#pragma unroll 1
+        for (int key0 = 0; key0 < t.len; key0 += 64) {
+          const int key = key0 + lane;
+          logits_fma<E, D>(q_base<E>(src, t, p) + (int64_t)r0 * D * E::kBytes, p.rows - r0,
+                           k0 + (int64_t)(key < t.len ? key : t.len - 1) * stride_token_b, cexp, y);
+#pragma unroll
+          for (int i = 0; i < kFmaRows; ++i)
+            if (key < t.len && key <= t.S - p.w - t.c0 + (r0 + i) % p.w) merge_pair(m[i], l[i], make_float2(y[i], 1.0f));
+        }
+#pragma unroll
+        for (int i = 0; i < kFmaRows; ++i) {
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) {
+            const float2 other = make_float2(__shfl_xor(m[i], o), __shfl_xor(l[i], o));
+            merge_pair(m[i], l[i], other);
+          }
+          if (lane == 0 && (which >> (g + i) & 1u)) part[r0 + i] = make_float2(m[i], l[i]);
+        }
       }
     }
     walk.advance();
@@ -787,14 +832,9 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
     }
     halo_s[(kt * 8 + t) * 64 + lane] = (s0 + s1) + (s2 + s3);
   };
-  // Column sum of a key from the elements.
-  auto column_fma = [&](const Task& t, int key) {
-    const char* __restrict__ qr = q_base<E>(src, t, p);
-    const char* __restrict__ kk = key_base(src, t, stride_token_b, stride_head_b) + (int64_t)key * stride_token_b;
-    float sum = 0.0f;
-#pragma unroll 1
-    for (int r = 0; r < p.rows; ++r, qr += D * E::kBytes) sum += fast_exp2(logit_fma<E, D>(qr, kk, cexp) - lse_all[r]);
-    return sum;
+  auto take_again = [&](const Task& t, int key) __attribute__((always_inline)) {   // a key's sum
+    return column_fma<E, D>(q_base<E>(src, t, p), p.rows, key_base(src, t, stride_token_b, stride_head_b) + (int64_t)key * stride_token_b,
+                            cexp, lse_all);
   };
   {
     QBlock<G> q;
@@ -870,7 +910,7 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
       for (int c = 0; c < G::kTiles; ++c) {
         const int key = tile_key(S * G::kTiles + c, wave) + (lane & 31);
         const float had = c == 0 ? sums[0] : sums[G::kTiles - 1];
-        if (key < len && no_number(had)) (c == 0 ? sums[0] : sums[G::kTiles - 1]) = column_fma(cur, key);
+        if (key < len && no_number(had)) (c == 0 ? sums[0] : sums[G::kTiles - 1]) = take_again(cur, key);
       }
     }
 #pragma unroll
@@ -904,7 +944,7 @@ __global__ __launch_bounds__(kThreads) void score_emit_tiles(Params p, int n_lay
         const int key = tid < half ? tid - half : kChunk + tid - half;
         const bool in = tid < half ? cur.c0 > 0 : cur.c0 + key < prefix;   // c0 is 0 or at least a chunk, longer than half
         float sum = lo + hi;
-        if (__builtin_expect(in && no_number(sum), 0)) sum = column_fma(cur, key);
+        if (__builtin_expect(in && no_number(sum), 0)) sum = take_again(cur, key);
         part[half + key] = in ? sum * p.row_scale : -INFINITY;
       }
       lds_barrier();
