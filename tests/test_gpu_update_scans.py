@@ -80,7 +80,8 @@ def _check_updates(cfg, A, done):
 # workgroups of four heads of 8192 positions (the mean length is more) and of two heads of 4096
 @pytest.mark.parametrize("kind", ["smooth", "plateau", "zeros", "scaled"])
 @pytest.mark.parametrize("Hkv,seqlens", [(6, (8193 + 8,)), (1, (16385 + 8,)), (2, (9, 24600)), (3, (4095 + 8, 4096 + 8, 4097 + 8)),
-                                         (1, (8192,)), (8, tuple(30 + 11 * i for i in range(40)))])
+                                         (1, (8192,)), (8, tuple(30 + 11 * i for i in range(40))),
+                                         (2, tuple((5 * i) % 61 + (3000 if i % 50 == 0 else 1) for i in range(150)))])
 def test_both_shapes_of_workgroups(Hkv, seqlens, kind):
     cfg = W.Workload("shapes", L=4, Hq=Hkv, Hkv=Hkv, d=64, seqlens=seqlens, dtype="bf16", w=8, P=7, mean_budget=40, layer_max=160,
                      interval=2, seed=1)
