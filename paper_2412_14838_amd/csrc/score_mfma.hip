@@ -11,7 +11,7 @@
 //                 small kernel of its own when a call covers several layers;
 //   emit kernel:  S_tile = Q . K_tile^T (rows as M, keys as N: a lane holds ONE key and 16 rows, so the sum over
 //                 the rows is an in-lane reduction), p = exp2(S * c - lse2[row]), window/group sum, max-pool,
-//                 write.
+//                 write. Here for more than 128 rows and for short chunks; score_waves.h has the other one.
 // Both use v_mfma_f32_32x32x16_bf16 with the whole Q block of the wavefront resident in registers and K tiles
 // staged through LDS (coalesced 16-byte global loads, padded rows, 16-byte LDS reads in MFMA operand layout).
 // The MFMAs of one tile are issued in the same step as the exponentials of the tile before it (two accumulator
@@ -913,6 +913,10 @@ __global__ __launch_bounds__(256) void score_lse_mfma(Params p, int chunk, int t
   }
 }
 
+}  // namespace dkv
+#include "score_waves.h"
+namespace dkv {
+
 // load_tile() forms the byte offset of a key row inside a chunk in 32 bits (a 24-bit multiply): the largest row
 // index it can see (the chunk, the pooling halo and two tiles of slack) times the token stride must stay below
 // 2^32, and the stride itself below 2^24. Longer strides take the vector-ALU kernels.
@@ -987,11 +991,29 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   const int64_t partials_stride_layer = (int64_t)wl.partials_layer_bytes / (int64_t)sizeof(float);
   const size_t stat_bytes = (size_t)KS * RS * 64 * sizeof(float2);               // the final [KS][RS * 64] partials
   const size_t lds_stats = 2 * TL::kTileBytes + (size_t)QStage<RS, KS>::kBytes + stat_bytes;
-  const size_t lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(chunk) * sizeof(float) +
-                          (size_t)QStage<RS, KS>::kBytes;   // the Q staging area serves the next layer in every variant
+  // The kernel that writes the scores: score_waves.h has the rule.
+  void (*emit_kernel)(Params, int, int, int, ScoreLayers, int64_t, int64_t, const int32_t*, const float*, const float*, int64_t,
+                      const float*, float*, int64_t, int64_t, float*, int64_t) = nullptr;
+  int emit_threads = TL::kThreads;
+  size_t lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(chunk) * sizeof(float) +
+                    (size_t)QStage<RS, KS>::kBytes;         // the Q staging area serves the next layer in every variant
+  const void *emit_a = nullptr, *emit_b = nullptr;          // those this call's number of rows may take
+  if constexpr (RS > 1) {
+    emit_kernel = &score_emit_mfma<RS, KS>;
+    emit_a = emit_b = reinterpret_cast<const void*>(emit_kernel);
+  }
+  if constexpr (RS <= 2) {
+    emit_b = reinterpret_cast<const void*>(&score_emit_waves<2 * RS>);
+    if (RS == 1) emit_a = emit_b;
+    if (RS == 1 || chunk >= kWvMinChunk) {
+      emit_kernel = &score_emit_waves<2 * RS>;
+      emit_threads = kWvThreads;
+      lds_emit = wv_lds_emit<2 * RS>(chunk);
+    }
+  }
   static std::atomic<uint64_t> given{0};
   const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_mfma<RS, KS>), (int)lds_stats},
-                                         {reinterpret_cast<const void*>(&score_emit_mfma<RS, KS>), kLdsBudget}});
+                                         {emit_a, kLdsBudget}, {emit_b, kLdsBudget}});
   if (e != hipSuccess) return e;
   ScoreLayers src{};
   for (int i = 0; i < n_layers && (phases & (kPhaseStats | kPhaseEmit)); ++i) {
@@ -1033,7 +1055,7 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     // all layers); a single layer recomputes the halo keys inside the emit kernel, which is cheaper than a launch.
     float* edges = n_layers > 1 && p.half > 0 ? reinterpret_cast<float*>(ws + wl.edges) : nullptr;
     const int64_t edges_stride_layer = (int64_t)wl.edges_layer_bytes / (int64_t)sizeof(float);
-    launch(DKV_KERNEL_SCORE_EMIT, (score_emit_mfma<RS, KS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_emit, st, p, chunk,
+    launch(DKV_KERNEL_SCORE_EMIT, emit_kernel, dim3(grid_x, p.Hkv, shares), dim3(emit_threads), lds_emit, st, p, chunk,
            n_layers, layers_each, rev, k_stride_token * 2, k_stride_head * 2, cu, static_cast<const float*>(partials),
            lse_rows ? static_cast<const float*>(lse_rows) + last * lse_rows_stride_layer : nullptr, -lse_rows_stride_layer,
            lse_in, scores + last * scores_stride_layer, scores_stride_head, -scores_stride_layer, edges, edges_stride_layer);

@@ -1,0 +1,453 @@
+// The second scoring sweep for up to 128 score rows (G * ws) per KV head: bf16, head size 128. Included by score_mfma.hip,
+// whose helpers (chunks, merges, layers of a launch) it uses; the mathematics of the two sweeps is described there.
+//
+// A wavefront owns tiles of 32 keys and multiplies them with ALL score rows, whose Q block stays in its registers (128
+// rows: 128 of 256). Its keys go from global memory straight into its own piece of LDS (global_load_lds, 16 bytes a lane)
+// and from there into registers in MFMA operand layout; no other wavefront touches them, so the wavefronts of a workgroup
+// need no barrier between the tiles, only three per layer. A ring of three half tiles (32 keys x 64 of the head's
+// dimensions, 4 KB) per wavefront is in flight. The eight wavefronts take neighbouring tiles, 64 KB of consecutive keys per
+// round. A row of a half tile is 128 bytes, one cache line; its 16-byte pieces lie in LDS with bits 1 to 3 of the row
+// folded into their place, which makes the reads (32 rows, the same piece) free of bank conflicts; the loads fold the
+// same bits into the address they read from.
+// A unit of work is 32 keys x 32 rows: its 8 MFMAs go out among the exponentials of the unit before it (two accumulators),
+// across the ends of tiles and layers. Row tiles are unrolled, so that Q's registers have fixed names; in a layer's last
+// tile the next layer's rows replace them one row tile at a time. Sums are taken in the order of score_emit_mfma: the
+// scores are the same bits, whichever kernel writes them.
+//
+// What bounds it: up to 64 rows, the stream of keys (32 layers of 8 heads x 32768 keys in 370 us, 5.8 TB/s; a plain read 346). At
+// 128 rows the issue of vector and matrix instructions: an exponential takes the SIMD 8 cycles, a plain instruction 4, an
+// MFMA 8 to 10 of issue, and a second wavefront adds little to that: 320 cycles a unit at least, at a clock that falls to
+// 1.5 GHz while memory streams as well.
+// Against score_emit_mfma (key tiles shared by all wavefronts, a barrier every 128 keys), us, before / after:
+//   32 layers, 8 heads, 32768 keys: 64 rows 409 / 370, 128 rows 470 / 420 (with the keys in the L2: 357 / 212, 375 / 311)
+//   16 layers in one call, per layer, 8 heads: 65536 keys, 128 rows 29.5 / 24.8; five prompts of 4000 to 15000 keys, 64 rows
+//   21.6 / 17.7, 128 rows 23.0 / 19.2; 8192 keys, 64 rows 3.74 / 3.20
+//   one layer, 8 heads: 64 rows, 2048 keys 8.7 / 7.3, 16384 11.0 / 8.1, 65536 27.0 / 22.5; 128 rows, 32768 keys 18.6 / 15.9
+// At 65 to 128 rows a wavefront's tile takes four units, and what a layer costs beside them shows when there are few tiles:
+// below kWvMinChunk keys to a chunk score_emit_mfma stays (16 layers in one call, 8 heads of 128 rows, 8192 keys, both sweeps per
+// layer: 8.35 there, 8.96 here; one layer 18.4 and 17.8).
+// The first sweep done the same way was not better at 128 rows (32 layers of 32768 keys 417 / 419, one layer of 8192 9.6 / 10.1),
+// and its sums come out in another order.
+#pragma once
+
+namespace dkv {
+
+constexpr int kWvWaves = 8, kWvThreads = 64 * kWvWaves;
+constexpr int kWvRing = 3, kWvHalfBytes = 4096;                    // half tiles in flight per wavefront
+constexpr int kWvMinChunk = 1024;
+constexpr int kWvRingBytes = kWvWaves * kWvRing * kWvHalfBytes;
+
+// Row tiles of 32 for a call (2 or 4: an even number keeps the accumulators' roles fixed).
+__host__ __device__ constexpr int wv_rows(int nrt) { return nrt * 32; }
+constexpr int kWvMergeBytes = kWvThreads * (int)sizeof(float2);    // at most; merges of chunk partials share the place of the column sums
+__host__ __device__ inline int wv_sums_bytes(int chunk) {          // column sums of a chunk: its outputs, the pooling halo, the last tile's rest
+  const int b = (chunk + kMaxHalo + 32) * (int)sizeof(float);
+  return b > kWvMergeBytes ? b : kWvMergeBytes;
+}
+template <int NRT> inline size_t wv_lds_emit(int chunk) {
+  return kWvRingBytes + wv_rows(NRT) * 256 + 2 * wv_rows(NRT) * sizeof(float) + wv_sums_bytes(chunk);
+}
+
+__device__ inline uint32_t lds_address(const void* p) {
+  return (uint32_t)(size_t)(__attribute__((address_space(3))) const char*)p;
+}
+
+// The lane, counted anew: where it is needed once per tile or layer it is not worth a register in between.
+__device__ inline int lane_again() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+// 16 (4) bytes per lane from base + off straight to LDS: lane l's land at lds + 16 l (4 l). Written as assembly because the
+// compiler would put a wait for ALL loads in front of every LDS read that follows; there is no register result. Whoever
+// reads the data waits with wait_newer() first. Other loads and stores of the wavefront only make that wait longer
+// (they are counted in the same order). The base is copied inside: a vector instruction may have written it just before.
+__device__ inline void load_lds16(uint32_t lds, uint32_t off, const char* base) {
+  const char* b;
+  asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(b) : "s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ inline void load_lds4(uint32_t lds, uint32_t off, const char* base) {
+  const char* b;
+  asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %0" : "=&s"(b) : "s"(lds), "v"(off), "s"(base) : "memory");
+}
+// Four of the former, 1 KB apart in LDS.
+__device__ inline void load_lds16x4(uint32_t lds, uint32_t off0, uint32_t off1, uint32_t off2, uint32_t off3, const char* base) {
+  const char* b;
+  asm volatile(
+      "s_mov_b64 %0, %6\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %0\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %0\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %0"
+      : "=&s"(b)
+      : "s"(lds), "v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(base)
+      : "memory", "scc");
+}
+// Waits until at most `n` half tiles (of four loads each) asked for last are still in flight. n is uniform.
+__device__ inline void wait_newer(int n) {
+  if (n >= 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+  else if (n == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  else if (n == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// The keys of one wavefront as a stream of half tiles: of the tiles wave, wave + 8, ... of the chunk from the last to the first,
+// layer after layer. issue() asks for the next half, take() brings the oldest one into the operand registers.
+struct WaveKeys {
+  char* lds;                        // of the workgroup
+  uint32_t ring;                    // this wavefront's part of it
+  const char* const* k_layers;      // kernel argument
+  int64_t k_off;
+  const char* k_ptr;                // first key of the next tile to ask for
+  const char* k_layer;              // first key of the chunk in that tile's layer
+  uint32_t stride_b, off[4];        // of this lane's rows 8 i + lane / 8 and piece in a half tile
+  int len, wave, my_tiles;
+  int layer, row0, tiles_left, issue_slot, take_slot, issued, taken, total;   // row0, tiles_left: of the next tile to ask for, in its layer; slots in bytes
+  int spare;                        // the place of a half 1 that was taken waits for its refill
+  uint32_t read_off[4];             // LDS places of this lane's pieces (head dimensions 16 j .. + 15) within a half
+
+  __device__ void start(char* smem, const ScoreLayers& src, int64_t chunk_off, uint32_t stride, int chunk_len, int first_layer, int n_layers) {
+    const int lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lds = smem;
+    ring = (uint32_t)(wave * (kWvRing * kWvHalfBytes));
+    k_layers = src.k;
+    k_off = chunk_off;
+    stride_b = stride;
+    len = chunk_len;
+    const int tiles = (len + 31) >> 5;
+    my_tiles = tiles > wave ? (tiles - wave + kWvWaves - 1) / kWvWaves : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) off[i] = (uint32_t)(8 * i + (lane >> 3)) * stride_b + piece_off(lane, i);
+    layer = first_layer;
+    issue_slot = take_slot = issued = taken = 0;
+    row0 = first_key(0);
+    tiles_left = my_tiles;
+    spare = 0;
+    total = 2 * my_tiles * (n_layers - first_layer);
+    k_layer = src.k[first_layer] + k_off;
+    k_ptr = k_layer + (uint64_t)((uint32_t)first_key(0) * stride_b);
+    const int r = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read_off[j] = ring + (uint32_t)(r * 128 + (((2 * j + h) ^ ((r >> 1) & 7)) << 4));
+  }
+  // The piece that lands in place lane % 8 of row 8 i + lane / 8.
+  static __device__ uint32_t piece_off(int lane, int i) { return (uint32_t)((lane & 7) ^ ((lane >> 4) + 4 * (i & 1))) * 16u; }
+  __device__ int first_key(int t) const {            // of the wavefront's t-th tile, relative to the chunk
+    return ((my_tiles - 1 - t) * kWvWaves + wave) * 32;
+  }
+  // The next half: halves 0 and 1 in turns (the first three calls 0, 1, 0; then as refill() has them).
+  template <int H>
+  __device__ void issue() {
+    if (__builtin_expect(issued >= total, 0)) return;
+    const uint32_t place = lds_address(lds) + ring + (uint32_t)issue_slot;
+    if (__builtin_expect(row0 + 32 <= len, 1)) {
+      load_lds16x4(place, off[0], off[1], off[2], off[3], k_ptr + H * 128);
+    } else {                                         // rows past the chunk repeat its last one
+      const int lane = lane_again();
+      uint32_t last[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        int row = row0 + 8 * i + (lane >> 3);
+        row = row < len ? row : len - 1;
+        last[i] = __umul24((uint32_t)row, stride_b) + piece_off(lane, i);
+      }
+      load_lds16x4(place, last[0], last[1], last[2], last[3], k_layer + H * 128);
+    }
+    ++issued;
+    issue_slot = issue_slot == (kWvRing - 1) * kWvHalfBytes ? 0 : issue_slot + kWvHalfBytes;
+    if (H == 1) {
+      row0 -= 32 * kWvWaves;
+      k_ptr -= (uint64_t)(256u * stride_b);
+      if (__builtin_expect(--tiles_left == 0, 0)) {      // the wavefront's last tile of a layer
+        tiles_left = my_tiles;
+        ++layer;
+        row0 = first_key(0);
+        if (issued < total) {
+          k_layer = k_layers[layer] + k_off;
+          k_ptr = k_layer + (uint64_t)((uint32_t)row0 * stride_b);
+        }
+      }
+    }
+  }
+  template <int H>
+  __device__ void take(bf16x8 (&kf)[8]) {
+    if (__builtin_expect(taken >= total, 0)) return;
+    if (H == 1) spare = 1;
+    const int newer = issued - taken - 1;            // in the middle of the stream: 2, then 1
+    if (__builtin_expect(newer == 2 - H, 1)) {
+      if (H == 0) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    } else {
+      wait_newer(newer);
+    }
+    const uint32_t at = (uint32_t)take_slot;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kf[4 * H + j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(lds + (at + read_off[j])));
+    ++taken;
+    take_slot = take_slot == (kWvRing - 1) * kWvHalfBytes ? 0 : take_slot + kWvHalfBytes;
+  }
+  // issue() once the reads of half H have arrived: its place is the one the next half, an other one, goes to. (That of half 1 is given away
+  // under the exponentials that follow, in the next tile or at the end of the layer, whichever comes first.)
+  template <int H>
+  __device__ void refill(const bf16x8 (&kf)[8]) {
+    if (H == 1) {
+      if (spare == 0) return;
+      spare = 0;
+    }
+    asm volatile("" ::"v"(kf[4 * H]), "v"(kf[4 * H + 1]), "v"(kf[4 * H + 2]), "v"(kf[4 * H + 3]) : "memory");
+    issue<1 - H>();
+  }
+};
+
+// Two wavefronts share a SIMD, and the older one wins whenever both could issue: it would run ahead and wait at the next
+// barrier. They have the higher priority in turns, the younger one in the first half of every tile.
+__device__ inline void take_turns(int mine) {
+  if (mine != 0) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
+
+// The Q block of a (sequence, head): kRows rows of 256 bytes in LDS, each wavefront fetches NRT * 4 of them (rows past p.rows
+// repeat the last one: their statistics are never used, and their normalisers are +inf).
+template <int NRT>
+__device__ inline void load_q_block(char* qbuf, const char* q_head, int rows, int wave) {
+  const int lane = lane_again();
+#pragma unroll
+  for (int i = 0; i < NRT; ++i) {
+    const int row = wave * (NRT * 4) + 4 * i + (lane >> 4);
+    const int src_row = row < rows ? row : rows - 1;
+    load_lds16(lds_address(qbuf) + (uint32_t)(wave * (NRT * 4) + 4 * i) * 256u,
+               (uint32_t)src_row * 256u + (uint32_t)((lane & 15) ^ (row & 15)) * 16u, q_head);
+  }
+}
+// Row tile t in operand layout; `at`: the places of this lane's pieces (head dimensions 16 j .. + 15) in row tile 0.
+struct QPlaces {
+  uint32_t at[4];                                  // the other four: ^ 128
+  __device__ QPlaces() {
+    const uint32_t r = threadIdx.x & 31, h = (threadIdx.x >> 5) & 1;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) at[j] = r * 256 + (((2 * j + h) ^ (r & 15)) << 4);
+  }
+};
+__device__ inline void read_q_tile(const char* qbuf, const QPlaces& q, int t, bf16x8 (&qf)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    uint32_t at = q.at[j & 3];
+    asm volatile("" : "+v"(at));                     // made anew: kept, the other four cost registers
+    qf[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qbuf + t * 8192 + (at ^ (32u * (j & 4)))));
+  }
+}
+
+// The lower half-wavefront's value ([0]) and the upper half's ([1]), in every lane.
+__device__ inline float2 both_halves(float v) {
+  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return make_float2(__uint_as_float(x[0]), __uint_as_float(x[1]));
+}
+
+// Scores, see score_emit_mfma (same arguments). The column sums of a chunk lie in LDS until its layer is done.
+template <int NRT>
+__global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chunk, int n_layers, int layers_each, ScoreLayers src,
+                                                               int64_t stride_token_b, int64_t stride_head_b,
+                                                               const int32_t* __restrict__ cu, const float* __restrict__ partials,
+                                                               const float* __restrict__ lse_rows, int64_t lse_rows_stride_layer,
+                                                               const float* __restrict__ lse_in, float* __restrict__ scores,
+                                                               int64_t scores_stride_head, int64_t scores_stride_layer,
+                                                               float* __restrict__ edges, int64_t edges_stride_layer) {
+  constexpr int kRows = wv_rows(NRT), RS = NRT / 2, KS = 4;                  // shape of the merge of chunk partials
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  char* qbuf = smem + kWvRingBytes;
+  float* lse_s = reinterpret_cast<float*>(qbuf + kRows * 256);           // [2][kRows] lse2 per row, by layer parity
+  float* sums = lse_s + 2 * kRows;                                      // column sums by key of the chunk
+
+  chunk = fitted_chunk(cu, p.n_seqs, chunk, Tile<NRT / 2, 4>::kKeys, gridDim.x);       // not longer than the host's: the LDS fits
+  const int half = p.half;
+  int seq, c, nc, begin, S, first_full, n_full;
+  if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, p.w, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
+  seq = __builtin_amdgcn_readfirstlane(seq);
+  begin = __builtin_amdgcn_readfirstlane(begin);
+  const int head = blockIdx.y;
+  const int first_layer = blockIdx.z * layers_each;
+  if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int prefix = __builtin_amdgcn_readfirstlane(S - p.w);            // > 0 here
+  const int o0 = __builtin_amdgcn_readfirstlane(c * chunk);              // outputs [o0, o1)
+  const int o1 = o0 + chunk < prefix ? o0 + chunk : prefix;
+  // keys [kbeg, kend): the outputs plus the pooling halo, inside the prefix - or, with `edges`, the outputs alone:
+  // then the pooled values next to a chunk border lack the neighbour's keys, the column sums of the first and the
+  // last `half` keys go to `edges`, and score_fix_borders completes those outputs afterwards
+  const int halo = edges != nullptr ? 0 : half;
+  const int kbeg = o0 - halo > 0 ? o0 - halo : 0;
+  const int kend = o1 + halo < prefix ? o1 + halo : prefix;
+  const int len = kend - kbeg;                                           // <= chunk + 2 * half
+  const float cexp = p.scale * kLog2e;
+  const int64_t q_off = ((int64_t)seq * p.Hq + (int64_t)head * p.G) * p.w * 256;
+  const float* __restrict__ lse_seq = lse_rows + ((int64_t)seq * p.Hkv + head) * p.rows_pad;     // (multi-layer launches)
+
+  // Tiles from the last to the first: what the statistics kernel, first to last, left in the caches
+  WaveKeys keys;
+  keys.start(smem, src, ((int64_t)begin + kbeg) * stride_token_b + (int64_t)head * stride_head_b, (uint32_t)stride_token_b, len,
+             first_layer, n_layers);
+  load_q_block<NRT>(qbuf, reinterpret_cast<const char*>(src.q[first_layer]) + q_off, p.rows, keys.wave);
+  int at_q = 0;
+  keys.issue<0>();
+  keys.issue<1>();
+  keys.issue<0>();
+  // ---- lse2[row] of the first layer; padding rows get +inf: exp2(x - inf) = 0
+  float* __restrict__ lse_first = lse_s + (first_layer & 1) * kRows;
+  if (lse_rows != nullptr) {
+    if (tid < kRows) lse_first[tid] = lse_seq[first_layer * lse_rows_stride_layer + tid];
+  } else if (lse_in != nullptr) {
+    if (tid < kRows)
+      lse_first[tid] = tid < p.rows ? lse_in[((int64_t)seq * p.Hq + (int64_t)head * p.G) * p.w + tid] * kLog2e : INFINITY;
+  } else {
+    float2* mstage = reinterpret_cast<float2*>(sums);
+    if (tid < KS * kRows)
+      merge_chunks<RS, KS>(reinterpret_cast<const float2*>(partials) + ((int64_t)first_full * p.Hkv + head) * p.rows_pad, n_full,
+                           (uint32_t)(p.Hkv * p.rows_pad), mstage);
+    lds_barrier();
+    if (tid < kRows) lse_first[tid] = combine_groups<RS, KS>(mstage, tid, p.rows);
+  }
+  // the normalisers of the next layer (the first kRows / 64 wavefronts) and its Q block
+  auto load_next = [&](int layer) {
+    if (keys.wave < kRows / 64)
+      load_lds4(lds_address(lse_s + (layer & 1) * kRows + keys.wave * 64), (uint32_t)lane_again() * 4u,
+                reinterpret_cast<const char*>(lse_seq + layer * lse_rows_stride_layer + keys.wave * 64));
+    load_q_block<NRT>(qbuf, reinterpret_cast<const char*>(src.q[layer]) + q_off, p.rows, keys.wave);
+    at_q = keys.issued;
+  };
+  wait_newer(keys.issued - at_q);
+  lds_barrier();
+  bf16x8 qf[NRT][8], kf[8];
+  const QPlaces q_places;
+#pragma unroll
+  for (int t = 0; t < NRT; ++t) read_q_tile(qbuf, q_places, t, qf[t]);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) kf[j] = qf[0][j];
+  keys.take<0>(kf);
+  keys.take<1>(kf);
+  if (first_layer + 1 < n_layers) {
+    lds_barrier();                                                       // every wavefront has its Q: the block's place is free
+    load_next(first_layer + 1);
+  }
+  keys.refill<0>(kf);
+
+  floatx16 acc[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[1][e] = 0.0f;
+  float4 lz[4] = {};                                                     // normalisers of a unit's rows, read from LDS a unit ahead
+  int row0 = -1;                                                         // first key of the tile whose exponentials are taken; none yet
+  const float* __restrict__ lse_cur = nullptr;                           // of the layer: + 32 * (row tile) + 8 * (e / 4) + e % 4
+  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, slab = 0.0f;         // slab: of the first 64 rows
+  auto unit = [&](auto rt_c, auto mul_c) {
+    constexpr int RT = decltype(rt_c)::value, PT = (RT + NRT - 1) % NRT;
+    constexpr bool MUL = decltype(mul_c)::value;
+    floatx16& cur = acc[RT & 1];
+    floatx16& a = acc[(RT & 1) ^ 1];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (RT == 0 && j == 2) keys.refill<1>(kf);
+      if (MUL) {
+        if (j == 0) {
+          floatx16 zero;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) zero[e] = 0.0f;
+          cur = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[RT][j], kf[j], zero, 0, 0, 0);
+        } else {
+          cur = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[RT][j], kf[j], cur, 0, 0, 0);
+        }
+      }
+      if ((j & 1) == 0) {
+        s0 += fast_exp2(fmaf(a[2 * j], cexp, -lz[j >> 1].x));
+        s1 += fast_exp2(fmaf(a[2 * j + 1], cexp, -lz[j >> 1].y));
+      } else {
+        s2 += fast_exp2(fmaf(a[2 * j], cexp, -lz[j >> 1].z));
+        s3 += fast_exp2(fmaf(a[2 * j + 1], cexp, -lz[j >> 1].w));
+        lz[j >> 1] = *reinterpret_cast<const float4*>(lse_cur + RT * 32 + 8 * (j >> 1));     // of the next unit
+      }
+      if (MUL && RT == NRT - 1 && j == 4) keys.take<0>(kf);
+      asm volatile("" : "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3));       // an anchor: without it the exponentials sink below all MFMAs
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (MUL && RT == NRT - 1) {
+      keys.take<1>(kf);
+      keys.refill<0>(kf);
+    }
+    if (PT & 1) {                                                      // 64 rows, summed up as score_emit_mfma does: the same bits
+      const float2 x = both_halves((s0 + s1) + (s2 + s3));
+      s0 = s1 = s2 = s3 = 0.0f;
+      if (PT == NRT - 1) {                                             // the tile's last rows: its column sums are complete
+        const float sum = NRT == 2 ? x.x + x.y : slab + (x.x + x.y);
+        const int lane = lane_again();
+        if (row0 >= 0 && lane < 32) sums[row0 + lane] = row0 + lane < len ? sum * p.row_scale : -INFINITY;
+      } else {
+        slab = x.x + x.y;
+      }
+    }
+  };
+  // A layer's end, behind the first unit of the next one (no loops around global memory instructions: keys are in flight)
+  auto pool_layer = [&](int li) {
+    lds_barrier();                                                       // all column sums are in LDS; every wavefront has the next layer's Q
+    if (li + 2 < n_layers) load_next(li + 2);
+    const int tid = keys.wave * 64 + lane_again();
+    if (edges != nullptr && tid < 2 * half) {                            // [0, half): the first column sums, [half, 2 half): the last
+      const int i = tid < half ? tid : len - 2 * half + tid;
+      edges[li * edges_stride_layer + ((int64_t)blockIdx.x * p.Hkv + head) * kMaxHalo + tid] =
+          i >= 0 && i < len ? sums[i] : -INFINITY;
+    }
+    // max-pool, window [i - half, i + half] cut to [0, len): an index clamped to the range stays inside the window, and
+    // taking an element twice does not change a maximum
+    float* __restrict__ out = scores + li * scores_stride_layer + (int64_t)head * scores_stride_head + begin;
+    auto pool = [&](int s0, bool two) {                                    // outputs s0 and, with `two`, s0 + kWvThreads
+      const int i0 = s0 - kbeg, i1 = i0 + (two ? kWvThreads : 0);
+      float m0 = sums[i0], m1 = sums[i1];
+      for (int o = 1; o <= half; ++o) {
+        const float a0 = sums[i0 - o > 0 ? i0 - o : 0], b0 = sums[i0 + o < len ? i0 + o : len - 1];
+        const float a1 = sums[i1 - o > 0 ? i1 - o : 0], b1 = sums[i1 + o < len ? i1 + o : len - 1];
+        m0 = fmaxf(m0, fmaxf(a0, b0));
+        m1 = fmaxf(m1, fmaxf(a1, b1));
+      }
+      out[s0] = m0;
+      if (two) out[s0 + kWvThreads] = m1;
+    };
+#pragma unroll
+    for (int u = 0; u < kMaxChunk / kWvThreads; u += 2) {
+      const int s = o0 + tid + u * kWvThreads;
+      if (s < o1) pool(s, s + kWvThreads < o1);
+    }
+    if (c == nc - 1 && tid < p.w) out[prefix + tid] = -INFINITY;         // guard over the window slots (w <= 256 <= threads)
+  };
+  for (int li = first_layer; li < n_layers; ++li) {
+    lse_cur = lse_s + (li & 1) * kRows + 4 * (lane_again() >> 5);
+    for (int k = 0; k < keys.my_tiles || k == 0; ++k) {
+      take_turns(keys.wave >> 2);
+      if (keys.my_tiles > 0) unit(std::integral_constant<int, 0>{}, std::true_type{});
+      if (k == 0 && li > first_layer) {
+        pool_layer(li - 1);
+        lds_barrier();                                                 // the column sums are read
+      }
+      row0 = keys.first_key(k);
+      const int turn_q = (li + 1 < n_layers) & (k + 1 >= keys.my_tiles);
+      if (turn_q) {                                                    // the layer's last tile: a row tile's Q gives way to the next layer's once it is used
+        wait_newer(keys.issued - at_q);
+        lds_barrier();
+        read_q_tile(qbuf, q_places, 0, qf[0]);
+      }
+      if (keys.my_tiles == 0) break;
+      if constexpr (NRT == 2) take_turns((keys.wave >> 2) ^ 1);
+      unit(std::integral_constant<int, 1>{}, std::true_type{});
+      if (turn_q) read_q_tile(qbuf, q_places, 1, qf[1]);
+      if constexpr (NRT == 4) {
+        take_turns((keys.wave >> 2) ^ 1);
+        unit(std::integral_constant<int, 2>{}, std::true_type{});
+        if (turn_q) read_q_tile(qbuf, q_places, 2, qf[2]);
+        unit(std::integral_constant<int, 3>{}, std::true_type{});
+        if (turn_q) read_q_tile(qbuf, q_places, 3, qf[3]);
+      }
+    }
+  }
+  if (keys.my_tiles > 0) unit(std::integral_constant<int, 0>{}, std::false_type{});
+  pool_layer(n_layers - 1);
+}
+
+}  // namespace dkv
