@@ -9,11 +9,13 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdkv.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 # packed fp32 VALU forms are switched off for all device code
 HIPCC_FLAGS = ["-O3", "-fno-honor-nans", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
@@ -47,6 +49,12 @@ def build(verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
+    # the Python binding of the stage calls (host code only), beside the library and linked to it
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"], "-o", BINDING,
+           os.path.join(CSRC, "binding.cpp"), "-L" + HERE, "-l:libdkv.so", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for binding.cpp:\n%s\n%s" % (r.stdout, r.stderr))
     if verbose:
         print("built", LIB)
     # the stand-alone measurement programs under tests/probes (not part of the library)

@@ -1,4 +1,4 @@
-"""Thin ctypes binding over libdkv.so (argument marshalling only; every step runs in the HIP kernels).
+"""Thin binding over libdkv.so (argument marshalling only, compiled for the stage calls; every step runs in the HIP kernels).
 
 The functions carry the names of the C ABI (include/dkv.h).  torch is used for device memory and streams
 only: tensors are passed as raw device pointers, the current torch stream as the hipStream_t.
@@ -110,6 +110,20 @@ def load() -> C.CDLL:
     return lib
 
 
+_binding = None
+
+
+def binding():
+    """The compiled stage calls (csrc/binding.cpp): the functions of the C ABI, for tensors, integers and a dkv_desc. Raises if
+    it is not built."""
+    global _binding
+    if _binding is None:
+        load()
+        from . import _binding as compiled
+        _binding = compiled
+    return _binding
+
+
 def make_desc(*, n_layers, n_q_heads, n_kv_heads, head_dim, window, pool_kernel, layer_max, mean_budget, interval,
               dtype, n_seqs, total_tokens, max_seq_len, softmax_scale=0.0, row_scale=0.0) -> dkv_desc:
     return dkv_desc(n_layers, n_q_heads, n_kv_heads, head_dim, window, pool_kernel, layer_max, mean_budget, interval,
@@ -132,10 +146,7 @@ def _ptr(t) -> Optional[int]:
 
 def layer_ptr(t, layer: int) -> int:
     """Address of t[layer], without the tensor (a view costs more than the rest of a call's marshalling)."""
-    n = t.shape[0]
-    if not -n <= layer < n:
-        raise IndexError("layer %d of a tensor of %d layers" % (layer, n))
-    return t.data_ptr() + int(layer if layer >= 0 else layer + n) * t.stride(0) * t.element_size()
+    return binding().layer_ptr(t, layer)
 
 
 def _stream(stream) -> Optional[int]:
@@ -161,6 +172,14 @@ def _torch():
 def _check(status: int, where: str) -> None:
     if status != DKV_OK:
         raise DkvError(status, where)
+
+
+def _same_layers(k_layers, *others) -> int:
+    n = len(k_layers)
+    for o in others:
+        if len(o) > n:
+            raise IndexError("%d tensors for %d layers" % (len(o), n))
+    return n
 
 
 def dkv_version() -> int:
@@ -196,17 +215,15 @@ def dkv_profile_end(capacity: int):
 
 def dkv_score_window(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                      workspace, stream=None) -> None:
-    _check(load().dkv_score_window(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head, _ptr(cu_seqlens),
-                                   _ptr(scores_out), scores_stride_head, _ptr(workspace),
-                                   workspace.nbytes, _stream(stream)), "dkv_score_window")
-
+    _check(binding().dkv_score_window(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
+                                      scores_stride_head, workspace, workspace.nbytes, stream), "dkv_score_window")
+                                      
 
 def dkv_score_window_static(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                             stream=None) -> None:
-    _check(load().dkv_score_window_static(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head,
-                                          _ptr(cu_seqlens), _ptr(scores_out), scores_stride_head, _stream(stream)),
-           "dkv_score_window_static")
-
+    _check(binding().dkv_score_window_static(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
+                                             scores_stride_head, stream), "dkv_score_window_static")
+                                             
 
 def dkv_static_scratch_limit() -> int:
     return int(load().dkv_static_scratch_limit())
@@ -220,145 +237,113 @@ def dkv_layer_budgets(desc, schedule, beta=4):
 
 
 def dkv_apply_budgets(desc, n_layers, budgets, counts, stream=None) -> None:
-    _check(load().dkv_apply_budgets(C.byref(desc), n_layers, _ptr(budgets), _ptr(counts), _stream(stream)),
-           "dkv_apply_budgets")
+    _check(binding().dkv_apply_budgets(desc, n_layers, budgets, counts, stream), "dkv_apply_budgets")
 
 
 def dkv_select_recent(desc, layer, n_sink, cu_seqlens, idx_out, counts, stream=None) -> None:
-    _check(load().dkv_select_recent(C.byref(desc), layer, n_sink, _ptr(cu_seqlens), _ptr(idx_out), _ptr(counts),
-                                    _stream(stream)), "dkv_select_recent")
+    _check(binding().dkv_select_recent(desc, layer, n_sink, cu_seqlens, idx_out, counts, stream), "dkv_select_recent")
 
 
 def dkv_score_window_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens, scores_all,
                             workspace, stream=None) -> None:
     """q_layers, k_layers: sequences of device tensors, one per layer of the call."""
-    n = len(k_layers)
-    qs = (C.c_void_p * n)(*[t.data_ptr() for t in q_layers])
-    ks = (C.c_void_p * n)(*[t.data_ptr() for t in k_layers])
-    _check(load().dkv_score_window_layers(C.byref(desc), layer_begin, n, qs, ks, k_stride_token, k_stride_head,
-                                          _ptr(cu_seqlens), _ptr(scores_all), _ptr(workspace),
-                                          workspace.nbytes, _stream(stream)),
-           "dkv_score_window_layers")
-
+    n = _same_layers(k_layers, q_layers)
+    _check(binding().dkv_score_window_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
+                                             cu_seqlens, scores_all, workspace, workspace.nbytes, stream), "dkv_score_window_layers")
+                                             
 
 def dkv_score_window_lse_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens,
                                 lse_layers, scores_all, workspace, stream=None) -> None:
     """q_layers, k_layers, lse_layers: sequences of device tensors, one per layer of the call."""
-    n = len(k_layers)
-    qs = (C.c_void_p * n)(*[t.data_ptr() for t in q_layers])
-    ks = (C.c_void_p * n)(*[t.data_ptr() for t in k_layers])
-    ls = (C.c_void_p * n)(*[t.data_ptr() for t in lse_layers])
-    _check(load().dkv_score_window_lse_layers(C.byref(desc), layer_begin, n, qs, ks, k_stride_token, k_stride_head,
-                                              _ptr(cu_seqlens), ls, _ptr(scores_all), _ptr(workspace),
-                                              workspace.nbytes, _stream(stream)),
-           "dkv_score_window_lse_layers")
-
+    n = _same_layers(k_layers, q_layers, lse_layers)
+    _check(binding().dkv_score_window_lse_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
+                                                 cu_seqlens, lse_layers, scores_all, workspace, workspace.nbytes, stream), "dkv_score_window_lse_layers")
+                                                 
 
 def dkv_score_window_stats(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                            workspace, stream=None) -> None:
-    _check(load().dkv_score_window_stats(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head,
-                                         _ptr(cu_seqlens), _ptr(scores_out), scores_stride_head, _ptr(workspace),
-                                         workspace.nbytes, _stream(stream)),
-           "dkv_score_window_stats")
-
+    _check(binding().dkv_score_window_stats(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
+                                            scores_stride_head, workspace, workspace.nbytes, stream), "dkv_score_window_stats")
+                                            
 
 def dkv_score_window_emit(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                           workspace, stream=None) -> None:
-    _check(load().dkv_score_window_emit(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head,
-                                        _ptr(cu_seqlens), _ptr(scores_out), scores_stride_head, _ptr(workspace),
-                                        workspace.nbytes, _stream(stream)),
-           "dkv_score_window_emit")
-
+    _check(binding().dkv_score_window_emit(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
+                                           scores_stride_head, workspace, workspace.nbytes, stream), "dkv_score_window_emit")
+                                           
 
 def dkv_score_window_lse(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, lse, scores_out, scores_stride_head,
                          stream=None) -> None:
-    _check(load().dkv_score_window_lse(C.byref(desc), _ptr(q_win), _ptr(k), k_stride_token, k_stride_head,
-                                       _ptr(cu_seqlens), _ptr(lse), _ptr(scores_out), scores_stride_head,
-                                       _stream(stream)), "dkv_score_window_lse")
-
+    _check(binding().dkv_score_window_lse(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, lse, scores_out,
+                                          scores_stride_head, stream), "dkv_score_window_lse")
+                                          
 
 def dkv_row_lse(desc, k_stride_token, cu_seqlens, lse_out, workspace, stream=None) -> None:
-    _check(load().dkv_row_lse(C.byref(desc), k_stride_token, _ptr(cu_seqlens), _ptr(lse_out), _ptr(workspace),
-                              workspace.nbytes, _stream(stream)), "dkv_row_lse")
-
+    _check(binding().dkv_row_lse(desc, k_stride_token, cu_seqlens, lse_out, workspace, workspace.nbytes, stream),
+                                 "dkv_row_lse")
+                                 
 
 def dkv_select_topk(desc, layer, scores, scores_stride_head, cu_seqlens, idx_out, counts, workspace,
                     stream=None) -> None:
-    _check(load().dkv_select_topk(C.byref(desc), layer, _ptr(scores), scores_stride_head, _ptr(cu_seqlens),
-                                  _ptr(idx_out), _ptr(counts), _ptr(workspace),
-                                  workspace.nbytes, _stream(stream)), "dkv_select_topk")
-
+    _check(binding().dkv_select_topk(desc, layer, scores, scores_stride_head, cu_seqlens, idx_out, counts, workspace,
+                                     workspace.nbytes, stream), "dkv_select_topk")
+                                     
 
 def dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, idx_all, counts, workspace,
                            stream=None) -> None:
-    _check(load().dkv_select_topk_layers(C.byref(desc), layer_begin, n_layers, _ptr(scores_all), _ptr(cu_seqlens),
-                                         _ptr(idx_all), _ptr(counts), _ptr(workspace),
-                                         workspace.nbytes, _stream(stream)),
-           "dkv_select_topk_layers")
-
+    _check(binding().dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, idx_all, counts, workspace,
+                                            workspace.nbytes, stream), "dkv_select_topk_layers")
+                                            
 
 def dkv_gather_kv_layers(desc, layer_begin, k_layers, v_layers, stride_token, stride_head, cu_seqlens, idx_all, counts,
                          k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream=None) -> None:
     """k_layers, v_layers: sequences of device tensors, one per layer of the call."""
-    n = len(k_layers)
-    ks = (C.c_void_p * n)(*[t.data_ptr() for t in k_layers])
-    vs = (C.c_void_p * n)(*[t.data_ptr() for t in v_layers])
-    _check(load().dkv_gather_kv_layers(C.byref(desc), layer_begin, n, ks, vs, stride_token, stride_head,
-                                       _ptr(cu_seqlens), _ptr(idx_all), _ptr(counts), _ptr(k_out_all), _ptr(v_out_all),
-                                       out_stride_layer, out_stride_seq, out_stride_head, _stream(stream)),
-           "dkv_gather_kv_layers")
-
+    n = _same_layers(k_layers, v_layers)
+    _check(binding().dkv_gather_kv_layers(desc, layer_begin, n, k_layers, v_layers, stride_token, stride_head, cu_seqlens,
+                                          idx_all, counts, k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream),
+                                          "dkv_gather_kv_layers")
+                                          
 
 def dkv_rebalance(desc, layers_done, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out, workspace,
                   stream=None) -> None:
-    _check(load().dkv_rebalance(C.byref(desc), layers_done, epoch, _ptr(scores_all), _ptr(cu_seqlens), _ptr(counts),
-                                _ptr(budgets_out), _ptr(hits_out), _ptr(workspace),
-                                workspace.nbytes, _stream(stream)), "dkv_rebalance")
-
+    _check(binding().dkv_rebalance(desc, layers_done, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out,
+                                   workspace, workspace.nbytes, stream), "dkv_rebalance")
+                                   
 
 def dkv_rebalance_batch(desc, layers_done, n_updates, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out,
                         out_stride_update, workspace, stream=None) -> None:
-    _check(load().dkv_rebalance_batch(C.byref(desc), layers_done, n_updates, epoch, _ptr(scores_all), _ptr(cu_seqlens),
-                                      _ptr(counts), _ptr(budgets_out), _ptr(hits_out), out_stride_update,
-                                      _ptr(workspace), workspace.nbytes,
-                                      _stream(stream)), "dkv_rebalance_batch")
-
+    _check(binding().dkv_rebalance_batch(desc, layers_done, n_updates, epoch, scores_all, cu_seqlens, counts, budgets_out,
+                                         hits_out, out_stride_update, workspace, workspace.nbytes, stream), "dkv_rebalance_batch")
+                                         
 
 def dkv_gather_kv(desc, layer, k, v, stride_token, stride_head, cu_seqlens, idx, counts, k_out, v_out, out_stride_seq,
                   out_stride_head, stream=None) -> None:
-    _check(load().dkv_gather_kv(C.byref(desc), layer, _ptr(k), _ptr(v), stride_token, stride_head, _ptr(cu_seqlens),
-                                _ptr(idx), _ptr(counts), _ptr(k_out), _ptr(v_out), out_stride_seq, out_stride_head,
-                                _stream(stream)), "dkv_gather_kv")
-
+    _check(binding().dkv_gather_kv(desc, layer, k, v, stride_token, stride_head, cu_seqlens, idx, counts, k_out, v_out,
+                                   out_stride_seq, out_stride_head, stream), "dkv_gather_kv")
+                                   
 
 def dkv_pack_cache(desc, cu_seqlens, counts, kb_all, vb_all, stride_layer, stride_seq, stride_head, k_packed, v_packed,
                    capacity_rows, row_offsets, stream=None) -> None:
-    _check(load().dkv_pack_cache(C.byref(desc), _ptr(cu_seqlens), _ptr(counts), _ptr(kb_all), _ptr(vb_all),
-                                 stride_layer, stride_seq, stride_head, _ptr(k_packed), _ptr(v_packed), capacity_rows,
-                                 _ptr(row_offsets), _stream(stream)), "dkv_pack_cache")
-
+    _check(binding().dkv_pack_cache(desc, cu_seqlens, counts, kb_all, vb_all, stride_layer, stride_seq, stride_head,
+                                    k_packed, v_packed, capacity_rows, row_offsets, stream), "dkv_pack_cache")
+                                    
 
 def dkv_pack_zero_tail(desc, row_offsets, k_packed, v_packed, capacity_rows, stream=None) -> None:
-    _check(load().dkv_pack_zero_tail(C.byref(desc), _ptr(row_offsets), _ptr(k_packed), _ptr(v_packed), capacity_rows,
-                                     _stream(stream)), "dkv_pack_zero_tail")
+    _check(binding().dkv_pack_zero_tail(desc, row_offsets, k_packed, v_packed, capacity_rows, stream), "dkv_pack_zero_tail")
 
 
 def dkv_decode_attention(desc, layer, q_new, kb, vb, stride_seq, stride_head, cu_seqlens, counts, out, lse_out, workspace,
                          stream=None) -> None:
-    _check(load().dkv_decode_attention(C.byref(desc), layer, _ptr(q_new), _ptr(kb), _ptr(vb), stride_seq, stride_head,
-                                       _ptr(cu_seqlens), _ptr(counts), _ptr(out), _ptr(lse_out), _ptr(workspace),
-                                       workspace.nbytes, _stream(stream)),
-           "dkv_decode_attention")
-
+    _check(binding().dkv_decode_attention(desc, layer, q_new, kb, vb, stride_seq, stride_head, cu_seqlens, counts, out,
+                                          lse_out, workspace, workspace.nbytes, stream), "dkv_decode_attention")
+                                          
 
 def dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, vb_all, stride_layer, stride_seq,
                                 stride_head, cu_seqlens, counts, out_all, lse_all, workspace, stream=None) -> None:
-    _check(load().dkv_decode_attention_layers(C.byref(desc), layer_begin, n_layers, _ptr(q_new_all), _ptr(kb_all),
-                                              _ptr(vb_all), stride_layer, stride_seq, stride_head, _ptr(cu_seqlens),
-                                              _ptr(counts), _ptr(out_all), _ptr(lse_all), _ptr(workspace),
-                                              workspace.nbytes, _stream(stream)),
-           "dkv_decode_attention_layers")
-
+    _check(binding().dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, vb_all, stride_layer,
+                                                 stride_seq, stride_head, cu_seqlens, counts, out_all, lse_all, workspace, workspace.nbytes, stream),
+                                                 "dkv_decode_attention_layers")
+                                                 
 
 def alloc_workspace(desc, device="cuda"):
     """Allocate (torch) the workspace the stage calls need."""

@@ -1,0 +1,56 @@
+"""The compiled stage calls take what the functions of the C ABI take, and refuse the rest. Calls that the library refuses on the
+host: nothing is launched."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_14838_amd import dkv
+
+
+def _desc(**kw):
+    a = dict(n_layers=4, n_q_heads=4, n_kv_heads=2, head_dim=128, window=16, pool_kernel=7, layer_max=64, mean_budget=16, interval=2,
+             dtype=dkv.DKV_BF16, n_seqs=1, total_tokens=300, max_seq_len=300)
+    a.update(kw)
+    return dkv.dkv_desc(**a)
+
+
+def test_arguments_arrive_as_through_ctypes():
+    """Every argument of a call in turn off by one step into what the library refuses: the same status as the plain C call's."""
+    t = torch.zeros(4096, dtype=torch.uint8)
+    at = t.data_ptr()
+    good = [3, t, at, t, 80 * 128, 80 * 128, t, t, t, None, t, 1 << 40, 64]
+    for i, bad in ((0, 4), (0, -1), (0, np.int64(9)), (1, None), (2, None), (2, at + 8), (3, None), (4, -1), (5, 127), (6, None), (7, None),
+                   (8, None), (10, None), (11, 16)):
+        a = list(good)
+        a[i] = bad
+        plain = [x.data_ptr() if isinstance(x, torch.Tensor) else (int(x) if isinstance(x, np.int64) else x) for x in a]
+        d = _desc()
+        want = dkv.load().dkv_decode_attention(C.byref(d), *plain)
+        assert want < 0 and dkv.binding().dkv_decode_attention(d, *a) == want, (i, bad)
+
+
+def test_what_is_no_argument_is_refused():
+    t = torch.zeros(64, dtype=torch.uint8)
+    b = dkv.binding()
+    good = [_desc(), 1, t, t, 64]
+    for i, bad in ((0, None), (0, b"short"), (1, 1.0), (1, "1"), (2, "x"), (2, 1.5), (4, object())):
+        a = list(good)
+        a[i] = bad
+        with pytest.raises((TypeError, AttributeError)):
+            b.dkv_apply_budgets(*a)
+    with pytest.raises(TypeError):
+        b.dkv_apply_budgets(*good[:-1])
+
+
+def test_layers_of_a_call():
+    t, d = torch.zeros(4096, dtype=torch.uint8), _desc()
+    strides = (128, 300 * 128)
+    with pytest.raises(dkv.DkvError) as e:                                # fewer queries than keys: null pointers, as ever
+        dkv.dkv_score_window_layers(d, 0, [t], [t, t], *strides, t, t, t, 64)
+    assert e.value.status == dkv.DKV_ERR_INVALID_ARG
+    with pytest.raises(IndexError):
+        dkv.dkv_score_window_layers(d, 0, [t, t, t], [t, t], *strides, t, t, t, 64)
+    with pytest.raises(dkv.DkvError):
+        dkv.dkv_score_window_layers(d, 0, [t] * 40, [t] * 40, *strides, t, t, t, 64)
