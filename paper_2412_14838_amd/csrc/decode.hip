@@ -12,6 +12,7 @@
 //                   whole rows, all loads of the slab are in flight together); the dot products are summed over
 //                   those lanes by DPP, the softmax weights stay in registers, and each group of lanes leaves
 //                   (m, l, acc) of its own rows in LDS, where the workgroup merges them;
+//                   (bf16 calls that are small enough take one kernel for both steps: decode_one_kernel)
 //   merge kernel:   out = sum_s acc_s exp(m_s - M) / sum_s l_s exp(m_s - M), lse = M + log(sum ...).
 // All sums in fp32.
 #include "dkv_internal.h"
@@ -225,6 +226,73 @@ __device__ inline uint32_t pack_bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
+// The softmax of a 32-row tile per head, from its logits as the MFMA leaves them (lane: head lane % 32, rows
+// 8 (i / 4) + 4 (lane / 32) + i % 4): maximum in units of log 2, sum, and P as two bf16 operands per step of 16 rows.
+struct TileWeights {
+  float m, l;
+  uint4 hi[2], lo[2];
+};
+__device__ inline TileWeights tile_weights(floatx16 sc, int rows_left, float scale2) {
+  TileWeights t;
+  const int half = (threadIdx.x >> 5) & 1;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int row = 8 * (i >> 2) + 4 * half + (i & 3);
+    sc[i] = row < rows_left ? sc[i] * scale2 : -INFINITY;
+    mx = fmaxf(mx, sc[i]);
+  }
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  const float m_finite = fmaxf(mx, -3.0e38f);           // a wavefront without rows: 2^(-inf - m_finite) = 0, not NaN
+  float lsum = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    sc[i] = __builtin_amdgcn_exp2f(sc[i] - m_finite);
+    lsum += sc[i];
+  }
+  lsum += __shfl_xor(lsum, 32);
+  t.m = mx;
+  t.l = lsum;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = sc[8 * s + 2 * e], b = sc[8 * s + 2 * e + 1];
+      hi[e] = pack_bf16_pair(a, b);
+      lo[e] = pack_bf16_pair(a - __uint_as_float(hi[e] << 16), b - __uint_as_float(hi[e] & 0xffff0000u));
+    }
+    t.hi[s] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    t.lo[s] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+  }
+  return t;
+}
+
+// Unnormalised output of the tile in 32 head-dim columns (lane: column lane % 32, heads 8 (i / 4) + 4 (lane / 32) + i % 4);
+// `column`: this lane's column of the staged rows of V, VSTRIDE bytes apart.
+template <int VSTRIDE>
+__device__ inline floatx16 tile_output(const char* __restrict__ column, const TileWeights& t) {
+  const int half = (threadIdx.x >> 5) & 1;
+  floatx16 oc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) oc[i] = 0.0f;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    uint32_t vv[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {                       // rows of the contraction slots 2 e and 2 e + 1 of step s
+      const int row_a = 8 * (2 * s + (2 * e) / 4) + 4 * half + (2 * e) % 4;
+      const uint32_t a = *reinterpret_cast<const uint16_t*>(column + row_a * VSTRIDE);
+      const uint32_t b = *reinterpret_cast<const uint16_t*>(column + (row_a + 1) * VSTRIDE);
+      vv[e] = a | (b << 16);
+    }
+    const bf16x8 vop = __builtin_bit_cast(bf16x8, make_uint4(vv[0], vv[1], vv[2], vv[3]));
+    oc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, t.hi[s]), vop, oc, 0, 0, 0);
+    oc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, t.lo[s]), vop, oc, 0, 0, 0);
+  }
+  return oc;
+}
+
 template <int D>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_mfma_kernel(int w, int layer_max, int L, int layer, int Hq,
                                                                           int Hkv, int n_seqs, int G, float scale,
@@ -306,62 +374,14 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_mfma_kernel(int w,
 #pragma unroll
   for (int ds = 0; ds < DS; ++ds)
     sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ds]), __builtin_bit_cast(bf16x8, qb[ds]), sc, 0, 0, 0);
-  // this lane: head `col`, rows 8 (i / 4) + 4 half + i % 4 of the wavefront; in units of log 2
   const float scale2 = scale * 1.4426950408889634f;
-  float mx = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int row = 8 * (i >> 2) + 4 * half + (i & 3);
-    sc[i] = row < rows_left ? sc[i] * scale2 : -INFINITY;
-    mx = fmaxf(mx, sc[i]);
-  }
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
-  const float m_finite = fmaxf(mx, -3.0e38f);           // a wavefront without rows: 2^(-inf - m_finite) = 0, not NaN
-  float lsum = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    sc[i] = __builtin_amdgcn_exp2f(sc[i] - m_finite);
-    lsum += sc[i];
-  }
-  lsum += __shfl_xor(lsum, 32);
-  if (half == 0 && col < GMAX) { m_s[wave][col] = mx; l_s[wave][col] = lsum; }
-
-  // ---- P as two bf16 operands per step of 16 rows
-  uint4 p_hi[2], p_lo[2];
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    uint32_t hi[4], lo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = sc[8 * s + 2 * e], b = sc[8 * s + 2 * e + 1];
-      hi[e] = pack_bf16_pair(a, b);
-      lo[e] = pack_bf16_pair(a - __uint_as_float(hi[e] << 16), b - __uint_as_float(hi[e] & 0xffff0000u));
-    }
-    p_hi[s] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    p_lo[s] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-  }
+  const TileWeights tw = tile_weights(sc, rows_left, scale2);
+  if (half == 0 && col < GMAX) { m_s[wave][col] = tw.m; l_s[wave][col] = tw.l; }
 
   // ---- output: heads x head-dim columns; B = V read column-wise from the staged rows (this wavefront's own stores)
   floatx16 oc[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oc[dt][i] = 0.0f;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      uint32_t vv[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {                     // rows of the contraction slots 2 e and 2 e + 1 of step s
-        const int row_a = 8 * (2 * s + (2 * e) / 4) + 4 * half + (2 * e) % 4;
-        const uint32_t a = *reinterpret_cast<const uint16_t*>(my_stage + row_a * VSTRIDE + (dt * 32 + col) * 2);
-        const uint32_t b = *reinterpret_cast<const uint16_t*>(my_stage + (row_a + 1) * VSTRIDE + (dt * 32 + col) * 2);
-        vv[e] = a | (b << 16);
-      }
-      const bf16x8 vop = __builtin_bit_cast(bf16x8, make_uint4(vv[0], vv[1], vv[2], vv[3]));
-      oc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, p_hi[s]), vop, oc[dt], 0, 0, 0);
-      oc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, p_lo[s]), vop, oc[dt], 0, 0, 0);
-    }
-  }
+  for (int dt = 0; dt < DT; ++dt) oc[dt] = tile_output<VSTRIDE>(my_stage + (dt * 32 + col) * 2, tw);
   // this lane: column dt * 32 + col, heads 8 (i / 4) + 4 half + i % 4. The staged V is spent (the wavefront's LDS
   // accesses complete in order): its place takes the wavefront's outputs [head][D]
   float* __restrict__ my_out = reinterpret_cast<float*>(my_stage);
@@ -440,6 +460,187 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(int w, int layer_max, i
   if (lse_out && j == 0) lse_out[(int64_t)seq * Hq + g] = used > 0 && Lsum > 0.0f ? M + __logf(Lsum) : -INFINITY;
 }
 
+// ------------------------------------------------------------------------------------------------------
+// Both steps in one launch, for bf16 calls whose workgroups fit the device at once (a decoder's call per layer): a launch
+// costs 4 to 5 us behind another, the whole layer's rows (2 MB) less. A workgroup of 16 wavefronts owns 32 columns of
+// the output of one (KV head, sequence, layer): it takes ALL rows of the block, 32 per wavefront and turn, so that nothing has
+// to be merged across workgroups. The logits are computed once per column group (4 or 2 times; the workgroups of a head sit
+// on one XCD where Hkv * n_seqs is a multiple of 8 and find K in its L2); V is read once. The loads of a wavefront's next
+// rows are in flight under the softmax of the present ones. Per tile of 32 rows (max, sum, output) go to LDS and are
+// merged there, four tiles to a slab and then the slabs, in the two kernels' own order: the same bits.
+// What bounds it: the launch, one memory latency and the merges (5 us up to 256 rows), and from there the vector ALU: a turn
+// of 512 rows takes the compute unit 3.3 us, four tiles of ~450 instructions to a SIMD.
+// ------------------------------------------------------------------------------------------------------
+constexpr int kDecOneThreads = 1024, kDecOneWaves = kDecOneThreads / 64;
+constexpr int kDecOneVStride = 32 * 2 + 16;             // bytes per staged row of V
+constexpr int kDecOneKStride = 64 * 2 + 16;             // and of 64 columns of K
+constexpr int kDecOneWaveStage = 32 * kDecOneKStride;   // a wavefront's K, half a head at a time, and then its V
+constexpr int kDecOneStage = kDecOneWaves * kDecOneWaveStage;
+constexpr int kDecOneTiles = 4;                         // tiles per slab
+constexpr int kDecOneLds = 152 * 1024;                  // what a call may ask for
+constexpr int kDecOneMaxRows = 640;                     // window + mean budget up to which a call takes this kernel
+
+__host__ __device__ constexpr size_t decode_one_lds(int n_slabs, int G) {
+  return kDecOneStage + (size_t)n_slabs * G * (kDecOneTiles * (32 + 2) + 3) * sizeof(float) + 2 * G * sizeof(float);
+}
+
+// One kernel or two: the workgroups have to fit the device at once, and the rows of a layer, which only the device knows, are
+// expected to be the mean that the updates leave. One layer of one sequence under graph replay, us, two kernels / one, bf16,
+// d = 128, 8 heads of 4: 232 rows 8.4 / 5.9, 288 8.7 / 6.8, 544 9.3 / 8.1, 1056 9.2 / 11.7, 2080 10.0 / 18.1 (so a layer far
+// above the mean loses less than the others win: both are straight lines in the rows, which cross near 700); 8 sequences:
+// 288 10.1 / 7.7, 544 12.4 / 9.8, 1056 15.0 / 14.7; d = 64: 288 7.5 / 5.7, 544 7.9 / 6.9, 1056 7.3 / 9.0.
+inline bool decode_one_fits(const Params& p, int n_layers, int n_slabs) {
+  return (long long)p.Hkv * p.n_seqs * n_layers * (p.d / 32) <= device_cus() && p.w + p.mean_budget <= kDecOneMaxRows &&
+         decode_one_lds(n_slabs, p.G) <= (size_t)kDecOneLds;
+}
+
+template <int D>
+__global__ __launch_bounds__(kDecOneThreads) void decode_one_kernel(int w, int layer_max, int L, int layer, int Hq, int Hkv,
+                                                                    int n_seqs, int G, int n_slabs, float scale,
+                                                                    DecodeLayerStrides ls_, const uint16_t* __restrict__ q_new,
+                                                                    const uint16_t* __restrict__ kb,
+                                                                    const uint16_t* __restrict__ vb, int64_t stride_seq,
+                                                                    int64_t stride_head, const int32_t* __restrict__ cu,
+                                                                    const int32_t* __restrict__ counts,
+                                                                    float* __restrict__ out, float* __restrict__ lse_out) {
+  constexpr int DS = D / 16, TILES = kDecOneTiles, VSTRIDE = kDecOneVStride, KSTRIDE = kDecOneKStride;
+  static_assert(decode_slab_rows(2) == 32 * TILES && kDecodeMaxGroup <= kDecOneWaves, "");
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  float* __restrict__ acc_t = reinterpret_cast<float*>(smem + kDecOneStage);       // [tile][G][32]
+  float* __restrict__ m_t = acc_t + n_slabs * TILES * G * 32;                      // [tile][G]
+  float* __restrict__ l_t = m_t + n_slabs * TILES * G;
+  float* __restrict__ m_s = l_t + n_slabs * TILES * G;                             // [slab][G]
+  float* __restrict__ l_s = m_s + n_slabs * G;
+  float* __restrict__ factor = l_s + n_slabs * G;                                  // [slab][G]
+  float* __restrict__ red = factor + n_slabs * G;                                  // [G] max, [G] sum
+  const int tid = threadIdx.x, split = blockIdx.y;
+  const int head = blockIdx.x % Hkv, seq = (blockIdx.x / Hkv) % n_seqs, lz = blockIdx.x / (Hkv * n_seqs);
+  layer += lz;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, col = lane & 31, half = lane >> 5;
+  // Q in operand layout: needs no counts, goes out first
+  const uint16_t* __restrict__ q_head = q_new + lz * ls_.q + ((int64_t)seq * Hq + (int64_t)head * G) * D;
+  uint4 qb[DS];
+#pragma unroll
+  for (int ds = 0; ds < DS; ++ds) {
+    qb[ds] = make_uint4(0, 0, 0, 0);
+    if (col < G) qb[ds] = *reinterpret_cast<const uint4*>(q_head + (int64_t)col * D + ds * 16 + half * 8);
+  }
+  const int S = cu[seq + 1] - cu[seq];
+  const int wq = S < w ? S : w;
+  int n = counts[seq * L + layer];
+  n = n < 0 ? 0 : (n < layer_max ? n : layer_max);
+  const int R = wq + n;
+  const int used = (R + 32 * TILES - 1) / (32 * TILES);                            // <= n_slabs
+  const uint16_t* __restrict__ kblock = kb + lz * ls_.cache + (int64_t)seq * stride_seq + (int64_t)head * stride_head;
+  const uint16_t* __restrict__ vblock = vb + lz * ls_.cache + (int64_t)seq * stride_seq + (int64_t)head * stride_head + split * 32;
+  char* __restrict__ my_stage = smem + wave * kDecOneWaveStage;
+  const float scale2 = scale * 1.4426950408889634f;
+  const int vrow = lane >> 2, vpiece = lane & 3;                                   // this lane's piece of V: rows vrow and vrow + 16
+
+  // K comes in whole cache lines, 8 rows x 64 columns per load, and gets its operand layout in LDS: a lane per row straight
+  // from memory takes the address unit 64 cycles a load, 640 a tile (a turn of 16 tiles 4.3 us).
+  const int krow = lane >> 3, kpiece = lane & 7;
+
+  uint4 kreg[DS], vreg[2];
+  auto load_k = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = t * 32 + 8 * i + krow;
+      const bool ok = row < R;
+      const int64_t off = ok ? (int64_t)cache_slot(row, w, wq) * D + kpiece * 8 : 0;
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h) {
+        kreg[4 * h + i] = make_uint4(0, 0, 0, 0);
+        if (ok) kreg[4 * h + i] = *reinterpret_cast<const uint4*>(kblock + off + h * 64);
+      }
+    }
+  };
+  auto load_v = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = t * 32 + 16 * i + vrow;
+      vreg[i] = make_uint4(0, 0, 0, 0);                 // rows past the block's last: zeros (their weights are zero too)
+      if (row < R) vreg[i] = *reinterpret_cast<const uint4*>(vblock + (int64_t)cache_slot(row, w, wq) * D + vpiece * 8);
+    }
+  };
+  load_k(wave);
+  load_v(wave);
+  for (int t = wave; t < used * TILES; t += kDecOneWaves) {
+    floatx16 sc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sc[i] = 0.0f;
+    // (a wavefront's LDS accesses complete in order: its area is written again right behind the reads)
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(my_stage + (8 * i + krow) * KSTRIDE + kpiece * 16) = kreg[4 * h + i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(my_stage + col * KSTRIDE + (2 * j + half) * 16)),
+            __builtin_bit_cast(bf16x8, qb[4 * h + j]), sc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<uint4*>(my_stage + (16 * i + vrow) * VSTRIDE + vpiece * 16) = vreg[i];
+    load_k(t + kDecOneWaves);                           // past the block's rows: nothing is read
+    load_v(t + kDecOneWaves);
+    const TileWeights tw = tile_weights(sc, R - t * 32, scale2);
+    if (half == 0 && col < G) { m_t[t * G + col] = tw.m; l_t[t * G + col] = tw.l; }
+    const floatx16 oc = tile_output<VSTRIDE>(my_stage + col * 2, tw);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {                       // heads below kDecodeMaxGroup
+      const int hd = 8 * (i >> 2) + 4 * half + (i & 3);
+      if (hd < G) acc_t[(t * G + hd) * 32 + col] = oc[i];
+    }
+  }
+  __syncthreads();
+  // ---- the slabs' results, each in the place of its first tile's (read by this thread alone)
+  for (int i = tid; i < used * G * 32; i += kDecOneThreads) {
+    const int j = i & 31, sg = i >> 5, s = sg / G, g = sg - s * G;
+    float M = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < TILES; ++u) M = fmaxf(M, m_t[(s * TILES + u) * G + g]);   // finite: the slab's first row is valid
+    float a = 0.0f, lt = 0.0f;
+#pragma unroll
+    for (int u = 0; u < TILES; ++u) {
+      const int at = (s * TILES + u) * G + g;
+      const float f = __builtin_amdgcn_exp2f(m_t[at] - M);
+      a = fmaf(acc_t[at * 32 + j], f, a);
+      lt = fmaf(l_t[at], f, lt);
+    }
+    acc_t[(s * TILES * G + g) * 32 + j] = a;
+    if (j == 0) { m_s[sg] = M * 0.6931471805599453f; l_s[sg] = lt; }
+  }
+  __syncthreads();
+  // ---- a wavefront per query head: maximum over the slabs, their weights and the sum, as in decode_merge_kernel
+  if (wave < G) {
+    const int g = wave;
+    float M = -INFINITY;
+    for (int s = lane; s < used; s += 64) M = fmaxf(M, m_s[s * G + g]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    float Lsum = 0.0f;
+    for (int s = lane; s < used; s += 64) {
+      const float f = __expf(m_s[s * G + g] - M);
+      factor[s * G + g] = f;
+      Lsum += l_s[s * G + g] * f;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) Lsum += __shfl_xor(Lsum, o);
+    if (lane == 0) { red[g] = M; red[G + g] = Lsum; }
+  }
+  __syncthreads();
+  if (tid < G * 32) {
+    const int g = tid >> 5, j = tid & 31;
+    float acc = 0.0f;
+    for (int s = 0; s < used; ++s) acc = fmaf(acc_t[(s * TILES * G + g) * 32 + j], factor[s * G + g], acc);
+    const float M = red[g], Lsum = red[G + g];
+    const int64_t row = (int64_t)seq * Hq + (int64_t)head * G + g;
+    out[lz * ls_.out + row * D + split * 32 + j] = used > 0 && Lsum > 0.0f ? acc / Lsum : 0.0f;
+    if (lse_out && split == 0 && j == 0) lse_out[lz * ls_.lse + row] = used > 0 && Lsum > 0.0f ? M + __logf(Lsum) : -INFINITY;
+  }
+}
+
 template <typename T, int D>
 static hipError_t launch_decode_t(const Params& p, int layer, int n_layers, const void* q_new, const void* kb,
                                   const void* vb, int64_t stride_layer, int64_t stride_seq, int64_t stride_head,
@@ -455,6 +656,16 @@ static hipError_t launch_decode_t(const Params& p, int layer, int n_layers, cons
   ls.lse = (int64_t)p.n_seqs * p.Hq;
   const dim3 grid_partial(p.Hkv * p.n_seqs * n_layers, n_slabs);
   if constexpr (sizeof(T) == 2) {
+    if (decode_one_fits(p, n_layers, n_slabs)) {
+      static std::atomic<uint64_t> given{0};
+      const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&decode_one_kernel<D>), kDecOneLds}});
+      if (e != hipSuccess) return e;
+      launch(DKV_KERNEL_DECODE, (decode_one_kernel<D>), dim3(p.Hkv * p.n_seqs * n_layers, D / 32), dim3(kDecOneThreads),
+             decode_one_lds(n_slabs, p.G), st, p.w, p.layer_max, p.L, layer, p.Hq, p.Hkv, p.n_seqs, p.G, n_slabs, p.scale, ls,
+             static_cast<const uint16_t*>(q_new), static_cast<const uint16_t*>(kb), static_cast<const uint16_t*>(vb), stride_seq,
+             stride_head, cu, counts, out, lse_out);
+      return hipGetLastError();
+    }
     launch(DKV_KERNEL_DECODE, (decode_partial_mfma_kernel<D>), grid_partial, dim3(kDecThreads), 0,
            st, p.w, p.layer_max, p.L, layer, p.Hq, p.Hkv, p.n_seqs, p.G, p.scale, ls, static_cast<const uint16_t*>(q_new),
            static_cast<const uint16_t*>(kb), static_cast<const uint16_t*>(vb), stride_seq, stride_head, cu, counts, partial);

@@ -131,6 +131,17 @@ inline void launch(int kernel_id, Kernel kernel, dim3 grid, dim3 block, size_t l
   hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, args...);
 }
 
+inline int device_cus() {
+  static int cus = 0;
+  if (cus == 0) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+      cus = 256;
+  }
+  return cus;
+}
+
 // Dynamic LDS past the default: a launch may ask for up to `bytes` of it once these kernels have been given it, which holds
 // for the device it was done on. `given` (one per call site, devices 0 .. 63 as bits) keeps track; on further devices, and
 // where two threads meet, it is done again.

@@ -33,15 +33,4 @@ __device__ inline void merge_pair(float& M, float& Lsum, const float2 v) {
 // log2 domain the emit kernels read: lse_rows [layer][seq][head][rows_pad].
 void launch_import_lse(const Params& p, int n_layers, const float* const* lse_layers, float* lse_rows, hipStream_t st);
 
-inline int device_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-      cus = 256;
-  }
-  return cus;
-}
-
 }  // namespace dkv
