@@ -469,7 +469,7 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(int w, int layer_max, i
 // rows are in flight under the softmax of the present ones. Per tile of 32 rows (max, sum, output) go to LDS and are
 // merged there, four tiles to a slab and then the slabs, in the two kernels' own order: the same bits.
 // What bounds it: the launch, one memory latency and the merges (5 us up to 256 rows), and from there the vector ALU: a turn
-// of 512 rows takes the compute unit 3.3 us, four tiles of ~450 instructions to a SIMD.
+// of 512 rows takes the compute unit about 3 us, four tiles of ~400 instructions to a SIMD.
 // ------------------------------------------------------------------------------------------------------
 constexpr int kDecOneThreads = 1024, kDecOneWaves = kDecOneThreads / 64;
 constexpr int kDecOneVStride = 32 * 2 + 16;             // bytes per staged row of V
@@ -486,9 +486,9 @@ __host__ __device__ constexpr size_t decode_one_lds(int n_slabs, int G) {
 
 // One kernel or two: the workgroups have to fit the device at once, and the rows of a layer, which only the device knows, are
 // expected to be the mean that the updates leave. One layer of one sequence under graph replay, us, two kernels / one, bf16,
-// d = 128, 8 heads of 4: 232 rows 8.4 / 5.9, 288 8.7 / 6.8, 544 9.3 / 8.1, 1056 9.2 / 11.7, 2080 10.0 / 18.1 (so a layer far
-// above the mean loses less than the others win: both are straight lines in the rows, which cross near 700); 8 sequences:
-// 288 10.1 / 7.7, 544 12.4 / 9.8, 1056 15.0 / 14.7; d = 64: 288 7.5 / 5.7, 544 7.9 / 6.9, 1056 7.3 / 9.0.
+// d = 128, 8 heads of 4: 232 rows 8.4 / 5.7, 288 8.7 / 6.5, 544 9.3 / 7.8, 1056 9.2 / 11.2, 2080 10.0 / 17.6 (so a layer far
+// above the mean loses less than the others win: both are straight lines in the rows, which cross near 750); 8 sequences:
+// 288 10.1 / 7.5, 544 12.4 / 9.1, 1056 15.0 / 14.1; d = 64: 288 7.5 / 5.6, 544 7.9 / 6.5, 1056 7.3 / 8.6.
 inline bool decode_one_fits(const Params& p, int n_layers, int n_slabs) {
   return (long long)p.Hkv * p.n_seqs * n_layers * (p.d / 32) <= device_cus() && p.w + p.mean_budget <= kDecOneMaxRows &&
          decode_one_lds(n_slabs, p.G) <= (size_t)kDecOneLds;
@@ -541,17 +541,21 @@ __global__ __launch_bounds__(kDecOneThreads) void decode_one_kernel(int w, int l
   // from memory takes the address unit 64 cycles a load, 640 a tile (a turn of 16 tiles 4.3 us).
   const int krow = lane >> 3, kpiece = lane & 7;
 
-  uint4 kreg[DS], vreg[2];
-  auto load_k = [&](int t) {
+  // each as ONE vector value: plain arrays would be demoted to scratch memory across the loop
+  typedef uint32_t KPieces __attribute__((ext_vector_type(4 * DS)));
+  typedef uint32_t VPieces __attribute__((ext_vector_type(8)));
+  KPieces kreg = 0;
+  VPieces vreg = 0;
+  auto load_k = [&](int t) {                            // rows past the block's repeat its last one: their logits are masked
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = t * 32 + 8 * i + krow;
-      const bool ok = row < R;
-      const int64_t off = ok ? (int64_t)cache_slot(row, w, wq) * D + kpiece * 8 : 0;
+      const uint32_t off = (uint32_t)cache_slot(row < R ? row : R - 1, w, wq) * D + kpiece * 8;
 #pragma unroll
       for (int h = 0; h < D / 64; ++h) {
-        kreg[4 * h + i] = make_uint4(0, 0, 0, 0);
-        if (ok) kreg[4 * h + i] = *reinterpret_cast<const uint4*>(kblock + off + h * 64);
+        const uint4 v = *reinterpret_cast<const uint4*>(kblock + (off + h * 64));
+        const int e = 4 * (4 * h + i);
+        kreg[e] = v.x; kreg[e + 1] = v.y; kreg[e + 2] = v.z; kreg[e + 3] = v.w;
       }
     }
   };
@@ -559,12 +563,15 @@ __global__ __launch_bounds__(kDecOneThreads) void decode_one_kernel(int w, int l
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int row = t * 32 + 16 * i + vrow;
-      vreg[i] = make_uint4(0, 0, 0, 0);                 // rows past the block's last: zeros (their weights are zero too)
-      if (row < R) vreg[i] = *reinterpret_cast<const uint4*>(vblock + (int64_t)cache_slot(row, w, wq) * D + vpiece * 8);
+      uint4 v = make_uint4(0, 0, 0, 0);                 // rows past the block's last: zeros (their weights are zero too)
+      if (row < R) v = *reinterpret_cast<const uint4*>(vblock + ((uint32_t)cache_slot(row, w, wq) * D + vpiece * 8));
+      vreg[4 * i] = v.x; vreg[4 * i + 1] = v.y; vreg[4 * i + 2] = v.z; vreg[4 * i + 3] = v.w;
     }
   };
-  load_k(wave);
-  load_v(wave);
+  if (wave < used * TILES) {
+    load_k(wave);
+    load_v(wave);
+  }
   for (int t = wave; t < used * TILES; t += kDecOneWaves) {
     floatx16 sc;
 #pragma unroll
@@ -573,7 +580,11 @@ __global__ __launch_bounds__(kDecOneThreads) void decode_one_kernel(int w, int l
 #pragma unroll
     for (int h = 0; h < D / 64; ++h) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(my_stage + (8 * i + krow) * KSTRIDE + kpiece * 16) = kreg[4 * h + i];
+      for (int i = 0; i < 4; ++i) {
+        const int e = 4 * (4 * h + i);
+        *reinterpret_cast<uint4*>(my_stage + (8 * i + krow) * KSTRIDE + kpiece * 16) =
+            make_uint4(kreg[e], kreg[e + 1], kreg[e + 2], kreg[e + 3]);
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -581,9 +592,13 @@ __global__ __launch_bounds__(kDecOneThreads) void decode_one_kernel(int w, int l
             __builtin_bit_cast(bf16x8, qb[4 * h + j]), sc, 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) *reinterpret_cast<uint4*>(my_stage + (16 * i + vrow) * VSTRIDE + vpiece * 16) = vreg[i];
-    load_k(t + kDecOneWaves);                           // past the block's rows: nothing is read
-    load_v(t + kDecOneWaves);
+    for (int i = 0; i < 2; ++i)
+      *reinterpret_cast<uint4*>(my_stage + (16 * i + vrow) * VSTRIDE + vpiece * 16) =
+          make_uint4(vreg[4 * i], vreg[4 * i + 1], vreg[4 * i + 2], vreg[4 * i + 3]);
+    if (t + kDecOneWaves < used * TILES) {
+      load_k(t + kDecOneWaves);
+      load_v(t + kDecOneWaves);
+    }
     const TileWeights tw = tile_weights(sc, R - t * 32, scale2);
     if (half == 0 && col < G) { m_t[t * G + col] = tw.m; l_t[t * G + col] = tw.l; }
     const floatx16 oc = tile_output<VSTRIDE>(my_stage + col * 2, tw);
