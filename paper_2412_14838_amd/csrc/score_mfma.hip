@@ -45,7 +45,8 @@ struct Tile {
 
 // The Q block of one (sequence, KV head) - up to RS * 64 rows of 128 - goes through LDS once per workgroup
 // (every row is needed by KS wavefronts): load_q_pieces() fetches kQPieces 16-byte pieces per thread (rows past
-// `rows` are zero), store_q_pieces() puts them into `qbuf` in the padded row layout of the key tiles, and after a
+// `rows` repeat the last one: their statistics are never used and their normalisers are +inf; zeros would make a NaN of
+// an infinite element of a key), store_q_pieces() puts them into `qbuf` in the padded row layout of the key tiles, and after a
 // barrier read_q_frags() gives each wavefront the fragments of its 64 rows in MFMA operand layout:
 // qf[t][j] = 8 consecutive head-dim elements (16 j + 8 (lane / 32) ..) of row rs * 64 + t * 32 + lane % 32.
 template <int N> struct PieceVec;
@@ -73,8 +74,8 @@ __device__ inline typename PieceVec<QStage<RS, KS>::kPieces>::type load_q_pieces
 #pragma unroll
   for (int i = 0; i < QStage<RS, KS>::kPieces; ++i) {
     const uint32_t pc = t + i * (RS * KS * 64);                // piece pc of the block: row pc / 16, 16 bytes at pc * 16
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if ((int)(pc >> 4) < rows) v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + pc * 16u);
+    const uint32_t row = pc >> 4, src_row = row < (uint32_t)rows ? row : (uint32_t)rows - 1u;
+    const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + src_row * 256u + (pc & 15u) * 16u);
     reg[4 * i] = v.x; reg[4 * i + 1] = v.y; reg[4 * i + 2] = v.z; reg[4 * i + 3] = v.w;
   }
   return reg;
@@ -101,8 +102,8 @@ __device__ inline typename PieceVec<QStage<RS, KS>::kPartPieces>::type load_q_pa
 #pragma unroll
   for (int i = 0; i < QStage<RS, KS>::kPartPieces; ++i) {
     const uint32_t pc = t + (uint32_t)(part * QStage<RS, KS>::kPartPieces + i) * (RS * KS * 64);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if ((int)(pc >> 4) < rows) v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + pc * 16u);
+    const uint32_t row = pc >> 4, src_row = row < (uint32_t)rows ? row : (uint32_t)rows - 1u;
+    const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + src_row * 256u + (pc & 15u) * 16u);
     reg[4 * i] = v.x; reg[4 * i + 1] = v.y; reg[4 * i + 2] = v.z; reg[4 * i + 3] = v.w;
   }
   return reg;
@@ -134,13 +135,11 @@ __device__ inline void load_q_frags(const uint16_t* __restrict__ q_head, int rs,
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const int r = rs * 64 + t * 32 + (lane & 31);
+    int r = rs * 64 + t * 32 + (lane & 31);
+    r = r < rows ? r : rows - 1;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (r < rows) v = *reinterpret_cast<const uint4*>(q_head + (int64_t)r * 128 + j * 16 + (lane >> 5) * 8);
-      qf[t][j] = __builtin_bit_cast(bf16x8, v);
-    }
+    for (int j = 0; j < 8; ++j)
+      qf[t][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(q_head + (int64_t)r * 128 + j * 16 + (lane >> 5) * 8));
   }
 }
 

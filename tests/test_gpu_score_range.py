@@ -115,3 +115,64 @@ def test_infinite_logits_and_nan_stay_in_their_head(d):
             ref = O.score_window(data["q_win"][s], data["k"][:, b:b + cfg.seqlens[s]], cfg.P)[h]
             assert (np.abs(got[h, b:b + n] - ref) <= RTOL * ref).all()
         assert np.isnan(got[1, 600:600 + 300 - cfg.w]).all()
+
+
+# bf16 at head size 128: the kernels that stream their keys through LDS, at numbers of rows (3 or 6 query heads x window) that leave
+# some of their 64, 128 or 256 rows over. P = 1: a pooling window of several keys would hide a key without a number.
+ROWS_128 = {"36_rows": (2, 3, 12, (700, 262, 300)), "72_rows": (2, 3, 24, (700, 262, 300)), "72_rows_long_chunks": (32, 3, 24, (8200,)),
+            "144_rows": (2, 6, 24, (700, 262, 300))}
+
+
+def _cfg_128(rows, L, seed):
+    Hkv, G, w, seqlens = ROWS_128[rows]
+    return W.Workload("range128", L=L, Hq=G * Hkv, Hkv=Hkv, d=128, seqlens=seqlens, dtype="bf16", w=w, P=1, mean_budget=32, layer_max=64,
+                      interval=1, seed=seed)
+
+
+@pytest.mark.parametrize("rows", list(ROWS_128))
+@pytest.mark.parametrize("kind", ["lowest_key", "minus_inf_element", "minus_inf_key", "large_k"])
+def test_bf16_scores_at_the_end_of_the_range_at_head_size_128(kind, rows):
+    cfg = _cfg_128(rows, 2, 43)
+    data = [W.make_layer(cfg, l, with_v=False) for l in range(cfg.L)]
+    for x in data:
+        _place(kind, cfg, x, LARGEST["bf16"])
+        x["q_win"] = W.round_to_bf16(x["q_win"])               # what the device will hold
+    dev = [to_device(cfg, x) for x in data]
+    one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
+    for l in range(cfg.L):
+        one.score(l, dev[l]["q_win"], dev[l]["k"])
+    many.score_layers(0, [x["q_win"] for x in dev], [x["k"] for x in dev])
+    torch.cuda.synchronize()
+    cu = cfg.cu_seqlens
+    for l in range(cfg.L):
+        got = one.scores[l].cpu().numpy()
+        for s in range(cfg.n_seqs):
+            n = cfg.seqlens[s] - cfg.w
+            ref = O.score_window(data[l]["q_win"][s], data[l]["k"][:, cu[s]:cu[s + 1]], cfg.P)
+            off = np.abs(got[:, cu[s]:cu[s] + n] - ref)
+            assert np.isfinite(off).all() and (off <= RTOL * ref).all(), (l, s, off.max())
+            assert np.isneginf(got[:, cu[s] + n:cu[s + 1]]).all()
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+
+
+@pytest.mark.parametrize("rows", list(ROWS_128))
+def test_bf16_infinite_logits_and_nan_stay_in_their_head_at_head_size_128(rows):
+    cfg = _cfg_128(rows, 1, 44)
+    clean = W.make_layer(cfg, 0, with_v=False)
+    s = cfg.n_seqs - 1                                         # the last sequence, head 1
+    cu, at = cfg.cu_seqlens, int(cfg.cu_seqlens[s])
+    for bad in (np.inf, np.nan):
+        data = {"q_win": np.abs(clean["q_win"]), "k": clean["k"].copy()}
+        data["k"][1, at + 20, 7] = bad
+        dev, comp = to_device(cfg, data), Compressor(cfg, keep_cache=False)
+        comp.score(0, dev["q_win"], dev["k"])
+        torch.cuda.synchronize()
+        got = comp.scores[0].cpu().numpy()
+        for q in range(cfg.n_seqs):
+            n = cfg.seqlens[q] - cfg.w
+            with np.errstate(invalid="ignore"):
+                ref = O.score_window(data["q_win"][q], data["k"][:, cu[q]:cu[q + 1]], cfg.P)
+            for h in range(cfg.Hkv):
+                if (q, h) != (s, 1):
+                    assert (np.abs(got[h, cu[q]:cu[q] + n] - ref[h]) <= RTOL * ref[h]).all(), (q, h)
+        assert np.isnan(got[1, at:at + cfg.seqlens[s] - cfg.w]).all()
