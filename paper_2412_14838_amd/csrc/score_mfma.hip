@@ -351,6 +351,11 @@ __device__ inline void stream_tile(int li, int ahead, int n_steps, int n_layers,
 // last two steps of a layer run, the first two key tiles and the Q block of the next layer are already being
 // fetched, so that only the first layer pays for a cold start.
 // ------------------------------------------------------------------------------------------------------
+// What a running maximum of logits (log2 domain) starts from. Below it a fused multiply-add minus the rounded maximum leaves up to
+// 2^7 of rounding, whose exponential is infinite: keys of the type's lowest value would leave no number in the rows that see nothing
+// else in a chunk. As it is such keys have no weight.
+constexpr float kLowestMax = -4294967296.0f;
+
 template <int RS, int KS>
 __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int chunk, int n_layers, int layers_each,
                                                                  ScoreLayers src, int64_t stride_token_b, int64_t stride_head_b,
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
   // own layer left to multiply, takes that Q as its operand for the next layer's tile 0, and is followed by the
   // layer's epilogue - so the matrix pipe, the vector ALU and the loads never pause between layers.
   int li = first_layer, it = 0;                     // layer of the call and step within it (uniform over the workgroup)
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.0f, 0.0f};
+  float m_run[2] = {kLowestMax, kLowestMax}, l_run[2] = {0.0f, 0.0f};
   auto step = [&](auto buffer, floatx16 (&a)[2], floatx16 (&b)[2]) {
     constexpr int kBuf = decltype(buffer)::value;   // buffer of this step's tile
     if (li >= n_layers) return;                     // the padding step of an odd stream
@@ -457,10 +462,9 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
         float mx = fmaxf(a[t][0], a[t][1]);
 #pragma unroll
         for (int i = 2; i < 16; i += 2) mx = fmaxf(mx, fmaxf(a[t][i], a[t][i + 1]));
-        const float m_new = fmaxf(m_run[t], mx * cexp);
-        m_use[t] = m_new == -INFINITY ? 0.0f : m_new;
+        m_use[t] = fmaxf(m_run[t], mx * cexp);
         l_run[t] *= fast_exp2(m_run[t] - m_use[t]);
-        m_run[t] = m_new;
+        m_run[t] = m_use[t];
         s0 = s1 = s2 = s3 = 0.0f;
       }
       s0 += fast_exp2(fmaf(a[t][e], cexp, -m_use[t]));
@@ -506,10 +510,9 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
     for (int t = 0; t < 2; ++t) {
       const float m2 = __shfl_xor(m_run[t], 32), l2 = __shfl_xor(l_run[t], 32);
       const float M = fmaxf(m_run[t], m2);
-      const float Mu = M == -INFINITY ? 0.0f : M;
-      const float Lsum = fmaf(l_run[t], fast_exp2(m_run[t] - Mu), l2 * fast_exp2(m2 - Mu));   // spelled out: both copies of this code round alike
+      const float Lsum = fmaf(l_run[t], fast_exp2(m_run[t] - M), l2 * fast_exp2(m2 - M));   // spelled out: both copies of this code round alike
       if (lane < 32) stat[ks * (RS * 64) + rs * 64 + t * 32 + lane] = make_float2(M, Lsum);
-      m_run[t] = -INFINITY;
+      m_run[t] = kLowestMax;
       l_run[t] = 0.0f;
     }
     lds_barrier();
@@ -517,15 +520,14 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
                                 (((int64_t)blockIdx.x) * p.Hkv + head) * p.rows_pad;
     if (tid < RS * 64) {                            // no loop around memory instructions: key tiles are in flight
       const int r = tid;
-      float M = -INFINITY;
+      float M = kLowestMax;
 #pragma unroll
       for (int q = 0; q < KS; ++q) M = fmaxf(M, stat[q * (RS * 64) + r].x);
-      const float Mu = M == -INFINITY ? 0.0f : M;
       float Lsum = 0.0f;
 #pragma unroll
       for (int q = 0; q < KS; ++q) {
         const float2 v = stat[q * (RS * 64) + r];
-        Lsum = fmaf(v.y, fast_exp2(v.x - Mu), Lsum);
+        Lsum = fmaf(v.y, fast_exp2(v.x - M), Lsum);
       }
       part[r] = make_float2(M, Lsum);
     }

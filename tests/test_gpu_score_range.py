@@ -130,12 +130,16 @@ def _cfg_128(rows, L, seed):
 
 
 @pytest.mark.parametrize("rows", list(ROWS_128))
-@pytest.mark.parametrize("kind", ["lowest_key", "minus_inf_element", "minus_inf_key", "large_k"])
+@pytest.mark.parametrize("kind", ["lowest_element", "lowest_run", "lowest_key", "minus_inf_element", "minus_inf_key", "large_k"])
 def test_bf16_scores_at_the_end_of_the_range_at_head_size_128(kind, rows):
     cfg = _cfg_128(rows, 2, 43)
     data = [W.make_layer(cfg, l, with_v=False) for l in range(cfg.L)]
     for x in data:
         _place(kind, cfg, x, LARGEST["bf16"])
+        if kind == "lowest_run":                               # logits of -1e36 to -1e38 in all keys of some chunks, finite ones
+            x["q_win"][:, :cfg.G, :, 5] = 0.125 * (1 + np.arange(cfg.w) % 7)
+            for b, e in zip(cfg.cu_seqlens, cfg.cu_seqlens[1:]):
+                x["k"][0, b + 256:e - cfg.w, 5] = -LARGEST["bf16"]
         x["q_win"] = W.round_to_bf16(x["q_win"])               # what the device will hold
     dev = [to_device(cfg, x) for x in data]
     one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
