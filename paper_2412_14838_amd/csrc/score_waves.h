@@ -65,11 +65,11 @@ __device__ inline int lane_again() {
 // (they are counted in the same order). The base is copied inside: a vector instruction may have written it just before.
 __device__ inline void load_lds16(uint32_t lds, uint32_t off, const char* base) {
   const char* b;
-  asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(b) : "s"(lds), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(b) : "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 __device__ inline void load_lds4(uint32_t lds, uint32_t off, const char* base) {
   const char* b;
-  asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %0" : "=&s"(b) : "s"(lds), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %0" : "=&s"(b) : "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 // Four of the former, 1 KB apart in LDS.
 __device__ inline void load_lds16x4(uint32_t lds, uint32_t off0, uint32_t off1, uint32_t off2, uint32_t off3, const char* base) {
@@ -81,7 +81,7 @@ __device__ inline void load_lds16x4(uint32_t lds, uint32_t off0, uint32_t off1, 
       "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %0"
       : "=&s"(b)
       : "s"(lds), "v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(base)
-      : "memory", "scc");
+      : "memory", "scc", "m0");
 }
 // Waits until at most `n` half tiles (of four loads each) asked for last are still in flight. n is uniform.
 __device__ inline void wait_newer(int n) {
