@@ -131,14 +131,14 @@ inline void launch(int kernel_id, Kernel kernel, dim3 grid, dim3 block, size_t l
   hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, args...);
 }
 
+// Compute units of the current device (devices 0 .. 63 are asked once, whichever thread comes first).
 inline int device_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-      cus = 256;
-  }
+  static std::atomic<int> known[64];
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
+  if (dev < 64 && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  if (dev < 64) known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 
