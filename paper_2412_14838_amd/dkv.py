@@ -174,12 +174,16 @@ def _check(status: int, where: str) -> None:
         raise DkvError(status, where)
 
 
-def _same_layers(k_layers, *others) -> int:
+def _layers(k_layers, *others):
+    """The number of layers, and the other tensors of each (any iterable, at most as many) as sequences."""
     n = len(k_layers)
+    out = [n]
     for o in others:
+        o = o if hasattr(o, "__len__") else tuple(o)
         if len(o) > n:
             raise IndexError("%d tensors for %d layers" % (len(o), n))
-    return n
+        out.append(o)
+    return out
 
 
 def dkv_version() -> int:
@@ -247,7 +251,7 @@ def dkv_select_recent(desc, layer, n_sink, cu_seqlens, idx_out, counts, stream=N
 def dkv_score_window_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens, scores_all,
                             workspace, stream=None) -> None:
     """q_layers, k_layers: sequences of device tensors, one per layer of the call."""
-    n = _same_layers(k_layers, q_layers)
+    n, q_layers = _layers(k_layers, q_layers)
     _check(binding().dkv_score_window_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
                                              cu_seqlens, scores_all, workspace, workspace.nbytes, stream), "dkv_score_window_layers")
                                              
@@ -255,7 +259,7 @@ def dkv_score_window_layers(desc, layer_begin, q_layers, k_layers, k_stride_toke
 def dkv_score_window_lse_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens,
                                 lse_layers, scores_all, workspace, stream=None) -> None:
     """q_layers, k_layers, lse_layers: sequences of device tensors, one per layer of the call."""
-    n = _same_layers(k_layers, q_layers, lse_layers)
+    n, q_layers, lse_layers = _layers(k_layers, q_layers, lse_layers)
     _check(binding().dkv_score_window_lse_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
                                                  cu_seqlens, lse_layers, scores_all, workspace, workspace.nbytes, stream), "dkv_score_window_lse_layers")
                                                  
@@ -298,7 +302,7 @@ def dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, 
 def dkv_gather_kv_layers(desc, layer_begin, k_layers, v_layers, stride_token, stride_head, cu_seqlens, idx_all, counts,
                          k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream=None) -> None:
     """k_layers, v_layers: sequences of device tensors, one per layer of the call."""
-    n = _same_layers(k_layers, v_layers)
+    n, v_layers = _layers(k_layers, v_layers)
     _check(binding().dkv_gather_kv_layers(desc, layer_begin, n, k_layers, v_layers, stride_token, stride_head, cu_seqlens,
                                           idx_all, counts, k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream),
                                           "dkv_gather_kv_layers")

@@ -54,3 +54,19 @@ def test_layers_of_a_call():
         dkv.dkv_score_window_layers(d, 0, [t, t, t], [t, t], *strides, t, t, t, 64)
     with pytest.raises(dkv.DkvError):
         dkv.dkv_score_window_layers(d, 0, [t] * 40, [t] * 40, *strides, t, t, t, 64)
+
+
+def test_layers_may_come_from_any_iterable():
+    """As ctypes took them: what is no sequence is read once. The status is that of a call the library refuses (32 layers of 4)."""
+    t, d = torch.zeros(4096, dtype=torch.uint8), _desc()
+    out = (128, 300 * 128, t, t, t, t, t)
+    for make in (lambda n: (t for _ in range(n)), lambda n: map(lambda _: t, range(n)), lambda n: iter([t] * n), lambda n: dict.fromkeys(range(n), t).values(),
+                 lambda n: torch.zeros(n, 4096, dtype=torch.uint8)):
+        for call in (lambda q, k: dkv.dkv_score_window_layers(d, 0, q, k, *out[:5], stream=64),
+                     lambda q, k: dkv.dkv_score_window_lse_layers(d, 0, q, k, *out[:3], make(32), t, t, stream=64),
+                     lambda q, k: dkv.dkv_gather_kv_layers(d, 0, k, q, *out, 1 << 20, 1 << 18, 1 << 16, stream=64)):
+            with pytest.raises(dkv.DkvError) as e:
+                call(make(32), [t] * 32)
+            assert e.value.status == dkv.DKV_ERR_INVALID_ARG
+    with pytest.raises(IndexError):
+        dkv.dkv_score_window_layers(d, 0, (t for _ in range(3)), [t, t], *out[:5], stream=64)
