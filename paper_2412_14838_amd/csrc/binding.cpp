@@ -20,6 +20,7 @@ namespace {
 
 PyObject *s_data_ptr, *s_cuda_stream, *s_shape, *s_stride, *s_element_size, *s_zero;
 PyObject *current_device, *current_raw_stream;      // torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
+PyObject* desc_type;                                // dkv.dkv_desc, see use_desc
 
 // The conversions return false with a Python error set.
 bool to_address(PyObject* o, uintptr_t& out) {
@@ -132,8 +133,9 @@ struct Arg<const dkv_desc*> {
   const dkv_desc* value;
   Py_buffer view{};
   bool take(PyObject* o, bool) {
-    if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
-    if (view.len != (Py_ssize_t)sizeof(dkv_desc)) {
+    const int is_desc = desc_type == nullptr ? 0 : PyObject_IsInstance(o, desc_type);
+    if (is_desc < 0 || (is_desc == 1 && PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0)) return false;
+    if (is_desc == 0 || view.len < (Py_ssize_t)sizeof(dkv_desc)) {
       PyErr_SetString(PyExc_TypeError, "a dkv_desc is required");
       return false;
     }
@@ -204,6 +206,19 @@ PyObject* layer_ptr(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return PyLong_FromUnsignedLongLong(at + (unsigned long long)((layer >= 0 ? layer : layer + layers) * stride * size));
 }
 
+// use_desc(type): the ctypes structure (and its subclasses) that a descriptor has to be.
+PyObject* use_desc(PyObject*, PyObject* type) {
+  if (!PyType_Check(type)) {
+    PyErr_SetString(PyExc_TypeError, "a type is required");
+    return nullptr;
+  }
+  Py_INCREF(type);
+  PyObject* before = desc_type;
+  desc_type = type;
+  Py_XDECREF(before);
+  Py_RETURN_NONE;
+}
+
 #define DKV_CALL(NAME) \
   { #NAME, (PyCFunction)(void (*)(void))&Call<&NAME, decltype(&NAME)>::call, METH_FASTCALL, nullptr }
 
@@ -214,6 +229,7 @@ PyMethodDef methods[] = {
     DKV_CALL(dkv_gather_kv), DKV_CALL(dkv_gather_kv_layers), DKV_CALL(dkv_pack_cache), DKV_CALL(dkv_pack_zero_tail),
     DKV_CALL(dkv_decode_attention), DKV_CALL(dkv_decode_attention_layers), DKV_CALL(dkv_apply_budgets), DKV_CALL(dkv_select_recent),
     {"layer_ptr", (PyCFunction)(void (*)(void))&layer_ptr, METH_FASTCALL, nullptr},
+    {"use_desc", use_desc, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -120,6 +120,7 @@ def binding():
     if _binding is None:
         load()
         from . import _binding as compiled
+        compiled.use_desc(dkv_desc)
         _binding = compiled
     return _binding
 

@@ -70,3 +70,23 @@ def test_layers_may_come_from_any_iterable():
             assert e.value.status == dkv.DKV_ERR_INVALID_ARG
     with pytest.raises(IndexError):
         dkv.dkv_score_window_layers(d, 0, (t for _ in range(3)), [t, t], *out[:5], stream=64)
+
+
+def test_a_descriptor_is_a_dkv_desc():
+    """Bytes and other structures of its size are none, as through ctypes; a structure derived from it is one."""
+    class Other(C.Structure):
+        _fields_ = [("words", C.c_int32 * 15)]
+
+    class Longer(dkv.dkv_desc):
+        _fields_ = [("more", C.c_int32)]
+
+    t, good = torch.zeros(64, dtype=torch.uint8), _desc()
+    assert C.sizeof(Other) == C.sizeof(good)
+    for bad in (bytes(good), bytearray(bytes(good)), memoryview(bytes(good)), np.frombuffer(bytes(good), np.int32), Other.from_buffer_copy(bytes(good))):
+        with pytest.raises(TypeError):
+            dkv.dkv_apply_budgets(bad, 5, t, t, 64)
+    longer = Longer(*[getattr(good, name) for name, _ in dkv.dkv_desc._fields_], 7)
+    for d in (good, longer):
+        with pytest.raises(dkv.DkvError) as e:                            # 5 layers of 4
+            dkv.dkv_apply_budgets(d, 5, t, t, 64)
+        assert e.value.status == dkv.DKV_ERR_INVALID_ARG
