@@ -2,7 +2,7 @@
 //
 // A decoder calls once per layer and token, and its calls are as long as their preparation on the host: 12.3 us a call
 // through ctypes against 10 us of the two kernels it launches. Here the conversions are generated from the functions' own
-// types: a pointer takes None, an address or whatever has data_ptr(), an array of pointers a sequence of those, the last
+// types: a pointer takes None, an address or whatever has data_ptr(), an array of pointers a sequence of the latter, the last
 // parameter of every call is its stream. The GIL is given up around the call, as ctypes does.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -23,19 +23,22 @@ PyObject *current_device, *current_raw_stream;      // torch.cuda.current_device
 PyObject* desc_type;                                // dkv.dkv_desc, see use_desc
 
 // The conversions return false with a Python error set.
+bool tensor_address(PyObject* o, uintptr_t& out) {
+  PyObject* v = PyObject_CallMethodNoArgs(o, s_data_ptr);
+  if (v == nullptr) return false;
+  out = (uintptr_t)PyLong_AsUnsignedLongLongMask(v);
+  Py_DECREF(v);
+  return !PyErr_Occurred();
+}
+
+// A tensor, None or an address: a plain int (True is none).
 bool to_address(PyObject* o, uintptr_t& out) {
   if (o == Py_None) {
     out = 0;
     return true;
   }
-  if (PyLong_Check(o)) {
-    out = (uintptr_t)PyLong_AsUnsignedLongLongMask(o);
-    return !PyErr_Occurred();
-  }
-  PyObject* v = PyObject_CallMethodNoArgs(o, s_data_ptr);
-  if (v == nullptr) return false;
-  out = (uintptr_t)PyLong_AsUnsignedLongLongMask(v);
-  Py_DECREF(v);
+  if (!PyLong_CheckExact(o)) return tensor_address(o, out);
+  out = (uintptr_t)PyLong_AsUnsignedLongLongMask(o);
   return !PyErr_Occurred();
 }
 
@@ -119,7 +122,7 @@ struct Arg<T* const*> {
     bool ok = true;
     for (Py_ssize_t i = 0; ok && i < n; ++i) {
       uintptr_t v = 0;
-      ok = to_address(PySequence_Fast_GET_ITEM(seq, i), v);
+      ok = tensor_address(PySequence_Fast_GET_ITEM(seq, i), v);
       kept[(size_t)i] = reinterpret_cast<T*>(v);
     }
     Py_DECREF(seq);

@@ -90,3 +90,20 @@ def test_a_descriptor_is_a_dkv_desc():
         with pytest.raises(dkv.DkvError) as e:                            # 5 layers of 4
             dkv.dkv_apply_budgets(d, 5, t, t, 64)
         assert e.value.status == dkv.DKV_ERR_INVALID_ARG
+
+
+class _Address(int):
+    pass
+
+
+def test_what_is_no_tensor_is_refused():
+    """An address is a plain int, and the tensors of several layers are tensors: None and addresses among them are refused."""
+    t, d = torch.zeros(4096, dtype=torch.uint8), _desc()
+    for bad in (True, False, _Address(t.data_ptr()), np.int64(t.data_ptr())):
+        with pytest.raises(AttributeError):
+            dkv.dkv_apply_budgets(d, 5, bad, t, 64)
+    for bad in (None, t.data_ptr(), True):
+        with pytest.raises(AttributeError):
+            dkv.dkv_score_window_layers(d, 0, [t, bad], [t, t], 128, 300 * 128, t, t, t, 64)
+        with pytest.raises(AttributeError):
+            dkv.dkv_score_window_layers(d, 0, [t, t], [bad, t], 128, 300 * 128, t, t, t, 64)
