@@ -120,9 +120,12 @@ struct Arg<T* const*> {
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
     kept.assign((size_t)(n > DKV_MAX_SELECT_LAYERS ? n : DKV_MAX_SELECT_LAYERS), nullptr);   // a shorter one than the call's layers: null pointers
     bool ok = true;
-    for (Py_ssize_t i = 0; ok && i < n; ++i) {
+    for (Py_ssize_t i = 0; ok && i < n && i < PySequence_Fast_GET_SIZE(seq); ++i) {      // data_ptr() may change a list
+      PyObject* item = PySequence_Fast_GET_ITEM(seq, i);
+      Py_INCREF(item);
       uintptr_t v = 0;
-      ok = tensor_address(PySequence_Fast_GET_ITEM(seq, i), v);
+      ok = tensor_address(item, v);
+      Py_DECREF(item);
       kept[(size_t)i] = reinterpret_cast<T*>(v);
     }
     Py_DECREF(seq);

@@ -107,3 +107,22 @@ def test_what_is_no_tensor_is_refused():
             dkv.dkv_score_window_layers(d, 0, [t, bad], [t, t], 128, 300 * 128, t, t, t, 64)
         with pytest.raises(AttributeError):
             dkv.dkv_score_window_layers(d, 0, [t, t], [bad, t], 128, 300 * 128, t, t, t, 64)
+
+
+def test_a_list_may_change_while_it_is_read():
+    """data_ptr() is Python code for what is no plain tensor: the list it empties is not read past its end."""
+    t, d = torch.zeros(4096, dtype=torch.uint8), _desc()
+
+    class Emptying:
+        def __init__(self, of):
+            self.of = of
+
+        def data_ptr(self):
+            self.of.clear()
+            return t.data_ptr()
+
+    layers = []
+    layers += [Emptying(layers)] + [t] * 3
+    with pytest.raises(dkv.DkvError) as e:                                # the three others are null pointers
+        dkv.dkv_score_window_layers(d, 0, layers, [t] * 4, 128, 300 * 128, t, t, t, 64)
+    assert e.value.status == dkv.DKV_ERR_INVALID_ARG and layers == []
