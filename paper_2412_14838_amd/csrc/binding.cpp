@@ -12,7 +12,6 @@
 #include <tuple>
 #include <type_traits>
 #include <utility>
-#include <vector>
 
 #include "../../include/dkv.h"
 
@@ -113,23 +112,21 @@ struct Arg<T*> {
 template <typename T>
 struct Arg<T* const*> {
   T* const* value;
-  std::vector<T*> kept;
+  T* kept[DKV_MAX_SELECT_LAYERS] = {};             // fewer tensors than the call's layers: null pointers; more: no call takes them
   bool take(PyObject* o, bool) {
     PyObject* seq = PySequence_Fast(o, "a sequence of tensors is required");
     if (seq == nullptr) return false;
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    kept.assign((size_t)(n > DKV_MAX_SELECT_LAYERS ? n : DKV_MAX_SELECT_LAYERS), nullptr);   // a shorter one than the call's layers: null pointers
     bool ok = true;
-    for (Py_ssize_t i = 0; ok && i < n && i < PySequence_Fast_GET_SIZE(seq); ++i) {      // data_ptr() may change a list
+    for (Py_ssize_t i = 0; ok && i < DKV_MAX_SELECT_LAYERS && i < PySequence_Fast_GET_SIZE(seq); ++i) {      // data_ptr() may change a list
       PyObject* item = PySequence_Fast_GET_ITEM(seq, i);
       Py_INCREF(item);
       uintptr_t v = 0;
       ok = tensor_address(item, v);
       Py_DECREF(item);
-      kept[(size_t)i] = reinterpret_cast<T*>(v);
+      kept[i] = reinterpret_cast<T*>(v);
     }
     Py_DECREF(seq);
-    value = kept.data();
+    value = kept;
     return ok;
   }
 };

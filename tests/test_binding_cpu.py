@@ -1,12 +1,17 @@
 """The compiled stage calls take what the functions of the C ABI take, and refuse the rest. Calls that the library refuses on the
 host: nothing is launched."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2412_14838_amd import dkv
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _desc(**kw):
@@ -126,3 +131,23 @@ def test_a_list_may_change_while_it_is_read():
     with pytest.raises(dkv.DkvError) as e:                                # the three others are null pointers
         dkv.dkv_score_window_layers(d, 0, layers, [t] * 4, 128, 300 * 128, t, t, t, 64)
     assert e.value.status == dkv.DKV_ERR_INVALID_ARG and layers == []
+
+
+def test_no_cpp_exception_reaches_python():
+    """A list that would not fit memory a second time: the call refuses it (more layers than one takes), the process goes on."""
+    program = r"""
+import resource, torch
+from paper_2412_14838_amd import dkv
+from tests.test_binding_cpu import _desc
+t = torch.zeros(4096, dtype=torch.uint8)
+dkv.binding()
+layers = [t] * 40000000                                                   # 320 MB
+size = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (size + (64 << 20), resource.RLIM_INFINITY))
+try:
+    dkv.dkv_score_window_layers(_desc(), 0, layers, layers, 128, 300 * 128, t, t, t, 64)
+except dkv.DkvError as e:
+    print("refused", e.status)
+"""
+    run = subprocess.run([sys.executable, "-c", program], capture_output=True, text=True, cwd=ROOT, timeout=300)
+    assert run.returncode == 0 and run.stdout.split() == ["refused", str(dkv.DKV_ERR_INVALID_ARG)], (run.returncode, run.stderr[-500:])
