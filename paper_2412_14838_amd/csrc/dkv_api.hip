@@ -245,7 +245,7 @@ int dkv_score_window_layers(const dkv_desc* desc, int32_t layer_begin, int32_t n
   if (st != DKV_OK) return st;
   if (!scores_all) return DKV_ERR_INVALID_ARG;
   if (n_layers < 1 || n_layers > DKV_MAX_SELECT_LAYERS) return DKV_ERR_INVALID_ARG;
-  if (layer_begin < 0 || layer_begin + n_layers > desc->n_layers) return DKV_ERR_INVALID_ARG;
+  if (layer_begin < 0 || layer_begin > desc->n_layers - n_layers) return DKV_ERR_INVALID_ARG;
   const int64_t stride_layer = (int64_t)desc->n_kv_heads * desc->total_tokens;
   return score_window_phases(kPhaseStats | kPhaseEmit, desc, n_layers, h_q_layers, h_k_layers, k_stride_token,
                              k_stride_head, cu_seqlens, scores_all + layer_begin * stride_layer, desc->total_tokens,
@@ -282,7 +282,7 @@ int dkv_score_window_lse_layers(const dkv_desc* desc, int32_t layer_begin, int32
   if (st != DKV_OK) return st;
   if (!scores_all || !h_lse_layers) return DKV_ERR_INVALID_ARG;
   if (n_layers < 1 || n_layers > DKV_MAX_SELECT_LAYERS) return DKV_ERR_INVALID_ARG;
-  if (layer_begin < 0 || layer_begin + n_layers > desc->n_layers) return DKV_ERR_INVALID_ARG;
+  if (layer_begin < 0 || layer_begin > desc->n_layers - n_layers) return DKV_ERR_INVALID_ARG;
   const int64_t stride_layer = (int64_t)desc->n_kv_heads * desc->total_tokens;
   return score_window_phases(kPhaseEmit, desc, n_layers, h_q_layers, h_k_layers, k_stride_token, k_stride_head,
                              cu_seqlens, scores_all + layer_begin * stride_layer, desc->total_tokens, stride_layer,
@@ -320,7 +320,7 @@ int dkv_select_topk_layers(const dkv_desc* desc, int32_t layer_begin, int32_t n_
   if (st != DKV_OK) return st;
   if (!scores_all || !cu_seqlens || !idx_all || !counts) return DKV_ERR_INVALID_ARG;
   if (n_layers < 1 || n_layers > DKV_MAX_SELECT_LAYERS) return DKV_ERR_INVALID_ARG;
-  if (layer_begin < 0 || layer_begin + n_layers > desc->n_layers) return DKV_ERR_INVALID_ARG;
+  if (layer_begin < 0 || layer_begin > desc->n_layers - n_layers) return DKV_ERR_INVALID_ARG;
   WorkspaceLayout wl;
   st = check_workspace(*desc, workspace, workspace_bytes, wl);
   if (st != DKV_OK) return st;
@@ -394,7 +394,7 @@ int dkv_gather_kv_layers(const dkv_desc* desc, int32_t layer_begin, int32_t n_la
   if (!h_k_layers || !h_v_layers || !cu_seqlens || !idx_all || !counts || !k_out_all || !v_out_all)
     return DKV_ERR_INVALID_ARG;
   if (n_layers < 1 || n_layers > DKV_MAX_SELECT_LAYERS) return DKV_ERR_INVALID_ARG;
-  if (layer_begin < 0 || layer_begin + n_layers > desc->n_layers) return DKV_ERR_INVALID_ARG;
+  if (layer_begin < 0 || layer_begin > desc->n_layers - n_layers) return DKV_ERR_INVALID_ARG;
   for (int i = 0; i < n_layers; ++i)
     if (!h_k_layers[i] || !h_v_layers[i] || !aligned16(h_k_layers[i]) || !aligned16(h_v_layers[i]))
       return DKV_ERR_INVALID_ARG;
@@ -481,7 +481,7 @@ int dkv_decode_attention_layers(const dkv_desc* desc, int32_t layer_begin, int32
   if (st != DKV_OK) return st;
   if (!q_new_all || !kb_all || !vb_all || !cu_seqlens || !counts || !out_all) return DKV_ERR_INVALID_ARG;
   if (n_layers < 1 || n_layers > DKV_MAX_SELECT_LAYERS) return DKV_ERR_INVALID_ARG;
-  if (layer_begin < 0 || layer_begin + n_layers > desc->n_layers) return DKV_ERR_INVALID_ARG;
+  if (layer_begin < 0 || layer_begin > desc->n_layers - n_layers) return DKV_ERR_INVALID_ARG;
   if (!aligned16(kb_all) || !aligned16(vb_all)) return DKV_ERR_INVALID_ARG;
   if (desc->n_q_heads / desc->n_kv_heads > DKV_MAX_DECODE_GROUP) return DKV_ERR_UNSUPPORTED;
   const int64_t elt = desc->dtype == DKV_BF16 ? 2 : 4;

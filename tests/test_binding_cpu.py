@@ -151,3 +151,19 @@ except dkv.DkvError as e:
 """
     run = subprocess.run([sys.executable, "-c", program], capture_output=True, text=True, cwd=ROOT, timeout=300)
     assert run.returncode == 0 and run.stdout.split() == ["refused", str(dkv.DKV_ERR_INVALID_ARG)], (run.returncode, run.stderr[-500:])
+
+
+@pytest.mark.parametrize("layer", [2 ** 31 - 1, 2 ** 31 - 2, 4])
+def test_layers_past_the_model_are_refused(layer):
+    """Also where the first layer and their number add up past 2^31. Refused on the host: nothing is launched."""
+    t, d = torch.zeros(4096 + 256, dtype=torch.uint8), _desc()
+    t = t[-t.data_ptr() % 256:]                                           # as a workspace is aligned
+    lib, at, room, ptrs = dkv.load(), t.data_ptr(), 1 << 40, (C.c_void_p * 2)(t.data_ptr(), t.data_ptr())
+    block = 80 * 128
+    for status in (
+            lib.dkv_score_window_layers(C.byref(d), layer, 2, ptrs, ptrs, 128, 300 * 128, at, at, at, room, 64),
+            lib.dkv_score_window_lse_layers(C.byref(d), layer, 2, ptrs, ptrs, 128, 300 * 128, at, ptrs, at, at, room, 64),
+            lib.dkv_select_topk_layers(C.byref(d), layer, 2, at, at, at, at, at, room, 64),
+            lib.dkv_gather_kv_layers(C.byref(d), layer, 2, ptrs, ptrs, 128, 300 * 128, at, at, at, at, at, 4 * block, 2 * block, block, 64),
+            lib.dkv_decode_attention_layers(C.byref(d), layer, 2, at, at, at, 4 * block, 2 * block, block, at, at, at, None, at, room, 64)):
+        assert status == dkv.DKV_ERR_INVALID_ARG
