@@ -478,19 +478,28 @@ constexpr int kDecOneWaveStage = 32 * kDecOneKStride;   // a wavefront's K, half
 constexpr int kDecOneStage = kDecOneWaves * kDecOneWaveStage;
 constexpr int kDecOneTiles = 4;                         // tiles per slab
 constexpr int kDecOneLds = 152 * 1024;                  // what a call may ask for
-constexpr int kDecOneMaxRows = 640;                     // window + mean budget up to which a call takes this kernel
+constexpr int kDecOneMaxRows = 640;                     // rows to expect up to which a call takes this kernel
 
 __host__ __device__ constexpr size_t decode_one_lds(int n_slabs, int G) {
   return kDecOneStage + (size_t)n_slabs * G * (kDecOneTiles * (32 + 2) + 3) * sizeof(float) + 2 * G * sizeof(float);
 }
 
-// One kernel or two: the workgroups have to fit the device at once, and the rows of a layer, which only the device knows, are
-// expected to be the mean that the updates leave. One layer of one sequence under graph replay, us, two kernels / one, bf16,
-// d = 128, 8 heads of 4: 232 rows 8.4 / 5.7, 288 8.7 / 6.5, 544 9.3 / 7.8, 1056 9.2 / 11.2, 2080 10.0 / 17.6 (so a layer far
-// above the mean loses less than the others win: both are straight lines in the rows, which cross near 750); 8 sequences:
-// 288 10.1 / 7.5, 544 12.4 / 9.1, 1056 15.0 / 14.1; d = 64: 288 7.5 / 5.6, 544 7.9 / 6.5, 1056 7.3 / 8.6.
+// One kernel or two: the workgroups have to fit the device at once, and the rows to expect are few. How many rows a layer holds
+// only the device knows; the descriptor says what layers keep on average, and none keeps more than layer_max. One kernel's time is a
+// straight line in the rows, that of two hardly rises (more slabs are more workgroups), so over the layers of a model the mean is what
+// counts: a layer far above it loses what several below it win. One layer under graph replay, us, two kernels / one, by rows:
+//                               64        232        288        544        640        768       1056       1568       2080
+//   8 heads of 4, d = 128   7.4 / 5.0  8.3 / 5.6  8.7 / 6.4  9.2 / 7.7  9.3 / 7.8  9.5 / 8.3  8.5 / 10.6 9.6 / 14.0 8.8 / 16.8
+//   8 of 1                  6.6 / 4.9  7.4 / 5.4  7.5 / 6.2  7.7 / 7.3  7.7 / 7.3  7.8 / 7.9  7.5 / 10.0 7.9 / 12.9 8.1 / 15.6
+//   8 of 8                  7.8 / 5.2  8.8 / 6.0  9.1 / 6.8  9.7 / 8.2  9.7 / 8.3 10.0 / 9.0  9.0 / 11.5 10.2 / 15.2 9.4 / 18.3
+//   8 of 16                 8.7 / 6.0  9.6 / 7.0  9.9 / 7.9 10.5 / 9.7 10.5 / 9.8 11.0 / 11.0
+//   8 of 4, d = 64          6.5 / 4.4  7.1 / 5.0  7.5 / 5.6  7.9 / 6.7  8.0 / 6.6  8.2 / 7.1  7.2 / 8.8  8.4 / 11.5 7.6 / 13.9
+//   8 of 16, d = 64         7.1 / 5.0  7.7 / 5.7  8.0 / 6.5  8.7 / 8.0  8.6 / 8.1  8.9 / 8.9
+//   4 of 7, 8 sequences     8.0 / 5.3  8.9 / 6.1  9.3 / 6.8  9.9 / 8.3  9.9 / 8.3 10.4 / 9.0 10.5 / 11.5 13.1 / 15.3 13.9 / 18.6
+//   8 of 4, 8 sequences     7.7 / 5.2  8.7 / 5.8  9.0 / 6.7 10.8 / 7.9 11.6 / 8.0 12.0 / 8.6 13.1 / 12.0 17.7 / 16.3 19.2 / 20.0
 inline bool decode_one_fits(const Params& p, int n_layers, int n_slabs) {
-  return (long long)p.Hkv * p.n_seqs * n_layers * (p.d / 32) <= device_cus() && p.w + p.mean_budget <= kDecOneMaxRows &&
+  const int expected = p.w + (p.mean_budget < p.layer_max ? p.mean_budget : p.layer_max);
+  return (long long)p.Hkv * p.n_seqs * n_layers * (p.d / 32) <= device_cus() && expected <= kDecOneMaxRows &&
          decode_one_lds(n_slabs, p.G) <= (size_t)kDecOneLds;
 }
 
