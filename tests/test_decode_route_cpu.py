@@ -34,7 +34,7 @@ CASES = [                                                    # Hkv, G, d, w, mea
     ((8, 4, 128, 32, 2 ** 31 - 1, 2048, 1, BF16), 2), ((8, 4, 128, 32, 2 ** 31 - 1, 600, 1, BF16), 1),
     ((8, 4, 128, 32, 128, 512, 8, BF16), 1), ((8, 4, 128, 32, 128, 512, 9, BF16), 2),        # workgroups: 256, 288 of 256
     ((8, 4, 64, 32, 128, 512, 16, BF16), 1), ((8, 4, 64, 32, 128, 512, 17, BF16), 2),
-    ((8, 16, 128, 16, 128, 1008, 1, BF16), 1), ((8, 16, 128, 16, 128, 1009, 1, BF16), 2),    # LDS: 8, 9 slabs of 16 heads
+    ((8, 16, 128, 16, 128, 1136, 1, BF16), 1), ((8, 16, 128, 16, 128, 1137, 1, BF16), 2),    # LDS: 9, 10 slabs of 16 heads
     ((8, 4, 128, 32, 128, 512, 1, F32), 2),
 ]
 
