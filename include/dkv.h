@@ -379,7 +379,11 @@ int dkv_pack_zero_tail(const dkv_desc* desc, const int64_t* row_offsets, void* k
  * Hq / Hkv must not exceed DKV_MAX_DECODE_GROUP. All sums in fp32 (for bf16 caches the products run on the matrix
  * cores: bf16 x bf16 is exact there, and the softmax weights enter as two bf16 terms, hi + lo, whose residue is
  * below 2^-17 of the weight). Two kernels (the cache rows are split over workgroups, then merged); the split
- * results live in the workspace.
+ * results live in the workspace. bf16 calls whose workgroups fit the device at once take one kernel instead, with the
+ * same bits and no use of the workspace, where the rows to expect are few: window + mean_budget, at most 640. It is the
+ * faster one for layers that keep mean_budget rows on average, and for layers of up to about 770 rows each; of 2000 rows it
+ * takes twice as long as the two. A caller whose layers keep more than its mean_budget (no updates, no preset budgets: all
+ * candidates) states what they keep in the descriptor of its decode calls.
  */
 int dkv_decode_attention(const dkv_desc* desc, int32_t layer, const void* q_new, const void* kb, const void* vb,
                          int64_t stride_seq, int64_t stride_head, const int32_t* cu_seqlens, const int32_t* counts,

@@ -1,13 +1,14 @@
-"""Which kernels a decode call takes: one, or the two of larger calls. The HIP calls go to stand-ins that count launches: no GPU is
-needed."""
+"""Which kernels a decode call takes (one, or the two of larger calls), and what the layer loop tells the library about the rows a
+layer keeps. The HIP calls go to stand-ins that count launches, the stage calls to recorders: no GPU is needed."""
 import json
 import shutil
 import subprocess
 import sys
 
 import pytest
+import torch
 
-from paper_2412_14838_amd import dkv
+from paper_2412_14838_amd import dkv, pipeline as P, workloads as W
 from test_two_devices_cpu import ROOT, UNITS_STAND_INS
 
 PROGRAM = r"""
@@ -48,3 +49,47 @@ def test_route_of_a_call(tmp_path):
                          cwd=ROOT, timeout=300)
     assert run.returncode == 0, run.stderr
     assert list(zip([c for c, _ in CASES], json.loads(run.stdout.strip().splitlines()[-1]))) == CASES
+
+
+def _compressor(monkeypatch, **kw):
+    seen = []
+    for name in ("score_window", "score_window_layers", "select_topk", "select_topk_layers", "gather_kv", "gather_kv_layers", "rebalance",
+                 "rebalance_batch", "apply_budgets", "select_recent"):
+        monkeypatch.setattr(dkv, "dkv_" + name, lambda *a, **k: None)
+    monkeypatch.setattr(dkv, "dkv_decode_attention", lambda desc, *a: seen.append((desc.mean_budget, desc.softmax_scale)))
+    monkeypatch.setattr(dkv, "dkv_decode_attention_layers", lambda desc, *a: seen.append((desc.mean_budget, desc.softmax_scale)))
+    cfg = W.Workload("route", L=6, Hq=4, Hkv=2, d=64, seqlens=(300, 70), dtype="bf16", w=16, P=7, mean_budget=10, layer_max=64, interval=4,
+                     seed=1)
+    comp = P.Compressor(cfg, device="cpu", **kw)
+    comp.desc.softmax_scale = 0.25                              # whatever the caller's descriptor says goes with every call
+    t = torch.zeros(1)
+
+    def expected():
+        del seen[:]
+        for l in range(6):
+            comp.decode_attention(l, t, t)
+        for l, n in ((0, 6), (0, 4), (4, 2), (3, 2)):
+            comp.decode_attention_layers(l, n, t, t)
+        assert {s for _, s in seen} == {0.25} and comp.desc.mean_budget == 10
+        return [r for r, _ in seen]
+
+    return comp, t, expected
+
+
+@pytest.mark.parametrize("group", [1, 4])
+def test_layers_no_update_has_cut_are_said_to_hold_all_candidates(monkeypatch, group):
+    comp, t, expected = _compressor(monkeypatch, group=group)
+    assert expected() == [10] * 10                              # counts of the caller's own: as the descriptor says
+    comp.run([(t, t, t)] * 6)                                   # one update, after four layers
+    assert expected() == [10, 10, 10, 10, 64, 64, 10 + 54 * 2 // 6, 10, 64, 10 + 54 // 2]
+    comp.select(1)
+    assert expected()[:4] == [10, 64, 10, 10]
+    comp.rebalance(4)
+    assert expected()[:6] == [10, 10, 10, 10, 64, 64]
+
+
+@pytest.mark.parametrize("schedule", ["fixed", "pyramid", "recent"])
+def test_preset_budgets_cut_every_layer(monkeypatch, schedule):
+    comp, t, expected = _compressor(monkeypatch, schedule=schedule)
+    comp.run([(t, t, t)] * 6)
+    assert expected() == [10] * 10
