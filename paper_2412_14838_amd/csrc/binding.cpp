@@ -174,6 +174,14 @@ struct Call<Fn, int (*)(T...)> {
   }
 };
 
+// address(t): the pointer that a call gets for t (None: a null pointer, as None).
+PyObject* address(PyObject*, PyObject* o) {
+  if (o == Py_None) Py_RETURN_NONE;
+  uintptr_t at;
+  if (!to_address(o, at)) return nullptr;
+  return PyLong_FromUnsignedLongLong(at);
+}
+
 // layer_ptr(t, layer): the address of t[layer], without the tensor.
 PyObject* layer_ptr(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n != 2) {
@@ -231,6 +239,7 @@ PyMethodDef methods[] = {
     DKV_CALL(dkv_select_topk), DKV_CALL(dkv_select_topk_layers), DKV_CALL(dkv_rebalance), DKV_CALL(dkv_rebalance_batch),
     DKV_CALL(dkv_gather_kv), DKV_CALL(dkv_gather_kv_layers), DKV_CALL(dkv_pack_cache), DKV_CALL(dkv_pack_zero_tail),
     DKV_CALL(dkv_decode_attention), DKV_CALL(dkv_decode_attention_layers), DKV_CALL(dkv_apply_budgets), DKV_CALL(dkv_select_recent),
+    {"address", address, METH_O, nullptr},
     {"layer_ptr", (PyCFunction)(void (*)(void))&layer_ptr, METH_FASTCALL, nullptr},
     {"use_desc", use_desc, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};

@@ -8,7 +8,6 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdkv.so")
@@ -18,11 +17,12 @@ DKV_MAX_SELECT_LAYERS = 32
 DKV_MAX_UPDATES = 8
 DKV_OK, DKV_ERR_INVALID_ARG, DKV_ERR_UNSUPPORTED, DKV_ERR_WORKSPACE, DKV_ERR_LAUNCH = 0, -1, -2, -3, -4
 
-EXPORTS = ("dkv_version", "dkv_status_string", "dkv_workspace_bytes", "dkv_profile_begin", "dkv_profile_end", "dkv_score_window",
-           "dkv_score_window_layers", "dkv_score_window_stats", "dkv_score_window_emit", "dkv_score_window_lse", "dkv_score_window_lse_layers", "dkv_row_lse", "dkv_select_topk", "dkv_select_topk_layers", "dkv_rebalance", "dkv_rebalance_batch",
-           "dkv_gather_kv", "dkv_gather_kv_layers", "dkv_pack_cache", "dkv_decode_attention", "dkv_layer_budgets",
-           "dkv_apply_budgets", "dkv_select_recent", "dkv_score_window_static", "dkv_static_scratch_limit", "dkv_score_path",
-           "dkv_decode_attention_layers", "dkv_pack_zero_tail")
+EXPORTS = ("dkv_version", "dkv_status_string", "dkv_workspace_bytes", "dkv_profile_begin", "dkv_profile_end",
+           "dkv_score_window", "dkv_score_window_layers", "dkv_score_window_stats", "dkv_score_window_emit",
+           "dkv_score_window_lse", "dkv_score_window_lse_layers", "dkv_row_lse", "dkv_select_topk", "dkv_select_topk_layers",
+           "dkv_rebalance", "dkv_rebalance_batch", "dkv_gather_kv", "dkv_gather_kv_layers", "dkv_pack_cache",
+           "dkv_decode_attention", "dkv_layer_budgets", "dkv_apply_budgets", "dkv_select_recent", "dkv_score_window_static",
+           "dkv_static_scratch_limit", "dkv_score_path", "dkv_decode_attention_layers", "dkv_pack_zero_tail")
 DKV_SCHEDULE_FIXED, DKV_SCHEDULE_PYRAMID = 0, 1
 
 
@@ -140,34 +140,14 @@ def desc_from_workload(cfg, **override) -> dkv_desc:
     return make_desc(**kw)
 
 
-def _ptr(t) -> Optional[int]:
-    """Device address of a tensor; None and addresses (ints) pass through."""
-    return t if t is None or t.__class__ is int else t.data_ptr()
+def _ptr(t):
+    """Device address of a tensor as the stage calls take it; None and addresses (ints) pass through."""
+    return binding().address(t)
 
 
 def layer_ptr(t, layer: int) -> int:
     """Address of t[layer], without the tensor (a view costs more than the rest of a call's marshalling)."""
     return binding().layer_ptr(t, layer)
-
-
-def _stream(stream) -> Optional[int]:
-    if stream is None:
-        # the address of torch.cuda.current_stream(), without the Stream object
-        return _torch()._C._cuda_getCurrentRawStream(_torch().cuda.current_device()) or None
-    if isinstance(stream, int):
-        return stream or None
-    return stream.cuda_stream or None
-
-
-_torch_module = None
-
-
-def _torch():
-    global _torch_module
-    if _torch_module is None:
-        import torch
-        _torch_module = torch
-    return _torch_module
 
 
 def _check(status: int, where: str) -> None:
@@ -222,13 +202,13 @@ def dkv_score_window(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, 
                      workspace, stream=None) -> None:
     _check(binding().dkv_score_window(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
                                       scores_stride_head, workspace, workspace.nbytes, stream), "dkv_score_window")
-                                      
+
 
 def dkv_score_window_static(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                             stream=None) -> None:
     _check(binding().dkv_score_window_static(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
                                              scores_stride_head, stream), "dkv_score_window_static")
-                                             
+
 
 def dkv_static_scratch_limit() -> int:
     return int(load().dkv_static_scratch_limit())
@@ -254,84 +234,88 @@ def dkv_score_window_layers(desc, layer_begin, q_layers, k_layers, k_stride_toke
     """q_layers, k_layers: sequences of device tensors, one per layer of the call."""
     n, q_layers = _layers(k_layers, q_layers)
     _check(binding().dkv_score_window_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
-                                             cu_seqlens, scores_all, workspace, workspace.nbytes, stream), "dkv_score_window_layers")
-                                             
+                                             cu_seqlens, scores_all, workspace, workspace.nbytes, stream),
+           "dkv_score_window_layers")
+
 
 def dkv_score_window_lse_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens,
                                 lse_layers, scores_all, workspace, stream=None) -> None:
     """q_layers, k_layers, lse_layers: sequences of device tensors, one per layer of the call."""
     n, q_layers, lse_layers = _layers(k_layers, q_layers, lse_layers)
     _check(binding().dkv_score_window_lse_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
-                                                 cu_seqlens, lse_layers, scores_all, workspace, workspace.nbytes, stream), "dkv_score_window_lse_layers")
-                                                 
+                                                 cu_seqlens, lse_layers, scores_all, workspace, workspace.nbytes, stream),
+           "dkv_score_window_lse_layers")
+
 
 def dkv_score_window_stats(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                            workspace, stream=None) -> None:
     _check(binding().dkv_score_window_stats(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
-                                            scores_stride_head, workspace, workspace.nbytes, stream), "dkv_score_window_stats")
-                                            
+                                            scores_stride_head, workspace, workspace.nbytes, stream),
+           "dkv_score_window_stats")
+
 
 def dkv_score_window_emit(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
                           workspace, stream=None) -> None:
     _check(binding().dkv_score_window_emit(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out,
                                            scores_stride_head, workspace, workspace.nbytes, stream), "dkv_score_window_emit")
-                                           
+
 
 def dkv_score_window_lse(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, lse, scores_out, scores_stride_head,
                          stream=None) -> None:
     _check(binding().dkv_score_window_lse(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, lse, scores_out,
                                           scores_stride_head, stream), "dkv_score_window_lse")
-                                          
+
 
 def dkv_row_lse(desc, k_stride_token, cu_seqlens, lse_out, workspace, stream=None) -> None:
     _check(binding().dkv_row_lse(desc, k_stride_token, cu_seqlens, lse_out, workspace, workspace.nbytes, stream),
-                                 "dkv_row_lse")
-                                 
+           "dkv_row_lse")
+
 
 def dkv_select_topk(desc, layer, scores, scores_stride_head, cu_seqlens, idx_out, counts, workspace,
                     stream=None) -> None:
     _check(binding().dkv_select_topk(desc, layer, scores, scores_stride_head, cu_seqlens, idx_out, counts, workspace,
                                      workspace.nbytes, stream), "dkv_select_topk")
-                                     
+
 
 def dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, idx_all, counts, workspace,
                            stream=None) -> None:
     _check(binding().dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, idx_all, counts, workspace,
                                             workspace.nbytes, stream), "dkv_select_topk_layers")
-                                            
+
 
 def dkv_gather_kv_layers(desc, layer_begin, k_layers, v_layers, stride_token, stride_head, cu_seqlens, idx_all, counts,
                          k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream=None) -> None:
     """k_layers, v_layers: sequences of device tensors, one per layer of the call."""
     n, v_layers = _layers(k_layers, v_layers)
     _check(binding().dkv_gather_kv_layers(desc, layer_begin, n, k_layers, v_layers, stride_token, stride_head, cu_seqlens,
-                                          idx_all, counts, k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream),
-                                          "dkv_gather_kv_layers")
-                                          
+                                          idx_all, counts, k_out_all, v_out_all, out_stride_layer, out_stride_seq,
+                                          out_stride_head, stream), "dkv_gather_kv_layers")
+
 
 def dkv_rebalance(desc, layers_done, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out, workspace,
                   stream=None) -> None:
     _check(binding().dkv_rebalance(desc, layers_done, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out,
                                    workspace, workspace.nbytes, stream), "dkv_rebalance")
-                                   
+
 
 def dkv_rebalance_batch(desc, layers_done, n_updates, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out,
                         out_stride_update, workspace, stream=None) -> None:
     _check(binding().dkv_rebalance_batch(desc, layers_done, n_updates, epoch, scores_all, cu_seqlens, counts, budgets_out,
-                                         hits_out, out_stride_update, workspace, workspace.nbytes, stream), "dkv_rebalance_batch")
-                                         
+                                         hits_out, out_stride_update, workspace, workspace.nbytes, stream),
+           "dkv_rebalance_batch")
+
 
 def dkv_gather_kv(desc, layer, k, v, stride_token, stride_head, cu_seqlens, idx, counts, k_out, v_out, out_stride_seq,
                   out_stride_head, stream=None) -> None:
     _check(binding().dkv_gather_kv(desc, layer, k, v, stride_token, stride_head, cu_seqlens, idx, counts, k_out, v_out,
                                    out_stride_seq, out_stride_head, stream), "dkv_gather_kv")
-                                   
+
 
 def dkv_pack_cache(desc, cu_seqlens, counts, kb_all, vb_all, stride_layer, stride_seq, stride_head, k_packed, v_packed,
                    capacity_rows, row_offsets, stream=None) -> None:
     _check(binding().dkv_pack_cache(desc, cu_seqlens, counts, kb_all, vb_all, stride_layer, stride_seq, stride_head,
                                     k_packed, v_packed, capacity_rows, row_offsets, stream), "dkv_pack_cache")
-                                    
+
 
 def dkv_pack_zero_tail(desc, row_offsets, k_packed, v_packed, capacity_rows, stream=None) -> None:
     _check(binding().dkv_pack_zero_tail(desc, row_offsets, k_packed, v_packed, capacity_rows, stream), "dkv_pack_zero_tail")
@@ -341,14 +325,14 @@ def dkv_decode_attention(desc, layer, q_new, kb, vb, stride_seq, stride_head, cu
                          stream=None) -> None:
     _check(binding().dkv_decode_attention(desc, layer, q_new, kb, vb, stride_seq, stride_head, cu_seqlens, counts, out,
                                           lse_out, workspace, workspace.nbytes, stream), "dkv_decode_attention")
-                                          
+
 
 def dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, vb_all, stride_layer, stride_seq,
                                 stride_head, cu_seqlens, counts, out_all, lse_all, workspace, stream=None) -> None:
     _check(binding().dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, kb_all, vb_all, stride_layer,
-                                                 stride_seq, stride_head, cu_seqlens, counts, out_all, lse_all, workspace, workspace.nbytes, stream),
-                                                 "dkv_decode_attention_layers")
-                                                 
+                                                 stride_seq, stride_head, cu_seqlens, counts, out_all, lse_all, workspace,
+                                                 workspace.nbytes, stream), "dkv_decode_attention_layers")
+
 
 def alloc_workspace(desc, device="cuda"):
     """Allocate (torch) the workspace the stage calls need."""

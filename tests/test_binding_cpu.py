@@ -2,6 +2,7 @@
 host: nothing is launched."""
 import ctypes as C
 import os
+import shutil
 import subprocess
 import sys
 
@@ -10,6 +11,7 @@ import pytest
 import torch
 
 from paper_2412_14838_amd import dkv
+from test_two_devices_cpu import STAND_INS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -136,9 +138,11 @@ def test_a_list_may_change_while_it_is_read():
 def test_no_cpp_exception_reaches_python():
     """A list that would not fit memory a second time: the call refuses it (more layers than one takes), the process goes on."""
     program = r"""
+import sys
+sys.path.insert(0, "tests")
 import resource, torch
 from paper_2412_14838_amd import dkv
-from tests.test_binding_cpu import _desc
+from test_binding_cpu import _desc
 t = torch.zeros(4096, dtype=torch.uint8)
 dkv.binding()
 layers = [t] * 40000000                                                   # 320 MB
@@ -167,3 +171,39 @@ def test_layers_past_the_model_are_refused(layer):
             lib.dkv_gather_kv_layers(C.byref(d), layer, 2, ptrs, ptrs, 128, 300 * 128, at, at, at, at, at, 4 * block, 2 * block, block, 64),
             lib.dkv_decode_attention_layers(C.byref(d), layer, 2, at, at, at, 4 * block, 2 * block, block, at, at, at, None, at, room, 64)):
         assert status == dkv.DKV_ERR_INVALID_ARG
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_stream_of_a_call(tmp_path):
+    """An address, an object with cuda_stream, or (None) torch's current stream at the time of the call: what the launch gets. The
+    HIP calls go to stand-ins."""
+    src, lib = tmp_path / "stand_ins.cpp", tmp_path / "libstand_ins.so"
+    launch = "int hipLaunchKernel(const void*, d3, d3, void**, size_t, void*) { return 0; }"
+    assert launch in STAND_INS
+    src.write_text(STAND_INS.replace(launch, "static void* launched_on; void* stand_in_stream() { return launched_on; }\n"
+                                     "int hipLaunchKernel(const void*, d3, d3, void**, size_t, void* s) { launched_on = s; return 0; }"))
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(lib), str(src)], check=True)
+    program = r"""
+import sys
+sys.path.insert(0, "tests")
+import ctypes as C, sys
+stand_ins = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+stand_ins.stand_in_stream.restype = C.c_void_p
+import torch
+from paper_2412_14838_amd import dkv
+from test_binding_cpu import _desc
+now = [0, 0x500]
+torch.cuda.current_device = lambda: now[0]
+torch._C._cuda_getCurrentRawStream = lambda device: now[1] + device
+class Stream:
+    cuda_stream = 0x700
+for stream in (0x300, 0, Stream()):
+    dkv.dkv_apply_budgets(_desc(), 2, 0x1000, 0x1000, stream)
+    print(stand_ins.stand_in_stream())
+for now[:] in ([0, 0x500], [3, 0x600], [0, 0]):
+    dkv.dkv_apply_budgets(_desc(), 2, 0x1000, 0x1000)
+    print(stand_ins.stand_in_stream())
+"""
+    run = subprocess.run([sys.executable, "-c", program, str(lib)], capture_output=True, text=True, cwd=ROOT, timeout=300)
+    assert run.returncode == 0, run.stderr[-800:]
+    assert run.stdout.split() == [str(x or None) for x in (0x300, 0, 0x700, 0x500, 0x603, 0)]
