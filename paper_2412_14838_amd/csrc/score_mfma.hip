@@ -549,9 +549,13 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
 template <int RS, int KS>
 __host__ __device__ inline int emit_part_stride(int chunk) { return chunk + kMaxHalo + 2 * Tile<RS, KS>::kKeys; }
 
-// Slabs of that size in LDS: one per row slab, and at least two (the second also holds the pooled outputs).
+// Slabs of that size in LDS: one per row slab, at least two (the second also holds the pooled outputs): one row slab has a kernel of
+// its own (score_waves.h).
 template <int RS>
-__host__ __device__ constexpr int emit_slabs() { return RS > 1 ? RS : 2; }
+__host__ __device__ constexpr int emit_slabs() {
+  static_assert(RS > 1, "");
+  return RS;
+}
 
 // Key tile that step `it` of the emit kernel works on (steps past the first tile repeat it: same values again).
 __device__ inline int emit_tile(int n_iter, int it) { return it < n_iter ? n_iter - 1 - it : 0; }
@@ -937,10 +941,13 @@ constexpr double kFixedUs = 6.0, kUsPerKey = 0.0102;         // measured: 1.3 us
 template <int RS, int KS>
 static int pick_chunk(const Params& p, int cus) {
   using TL = Tile<RS, KS>;
-  const long long lds_fixed = 2LL * TL::kTileBytes + QStage<RS, KS>::kBytes;
-  int max_chunk = (int)((kLdsBudget - lds_fixed) / (emit_slabs<RS>() * (long long)sizeof(float))) - kMaxHalo - 2 * TL::kKeys;
-  max_chunk = max_chunk / TL::kKeys * TL::kKeys;
-  if (max_chunk > kMaxChunk) max_chunk = kMaxChunk;
+  int max_chunk = kMaxChunk;                                 // which score_emit_waves always has the LDS for
+  if constexpr (RS > 1) {
+    const long long lds_fixed = 2LL * TL::kTileBytes + QStage<RS, KS>::kBytes;
+    max_chunk = (int)((kLdsBudget - lds_fixed) / (emit_slabs<RS>() * (long long)sizeof(float))) - kMaxHalo - 2 * TL::kKeys;
+    max_chunk = max_chunk / TL::kKeys * TL::kKeys;
+    if (max_chunk > kMaxChunk) max_chunk = kMaxChunk;
+  }
   int best = 256;
   double best_cost = 1e30;
   for (int chunk = 256; chunk <= max_chunk; chunk += TL::kKeys) {
@@ -996,16 +1003,18 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   void (*emit_kernel)(Params, int, int, int, ScoreLayers, int64_t, int64_t, const int32_t*, const float*, const float*, int64_t,
                       const float*, float*, int64_t, int64_t, float*, int64_t) = nullptr;
   int emit_threads = TL::kThreads;
-  size_t lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(chunk) * sizeof(float) +
-                    (size_t)QStage<RS, KS>::kBytes;         // the Q staging area serves the next layer in every variant
+  size_t lds_emit = 0;
   const void *emit_a = nullptr, *emit_b = nullptr;          // those this call's number of rows may take
   if constexpr (RS > 1) {
     emit_kernel = &score_emit_mfma<RS, KS>;
     emit_a = emit_b = reinterpret_cast<const void*>(emit_kernel);
+    lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(chunk) * sizeof(float) +
+               (size_t)QStage<RS, KS>::kBytes;              // the Q staging area serves the next layer in every variant
   }
   if constexpr (RS <= 2) {
     emit_b = reinterpret_cast<const void*>(&score_emit_waves<2 * RS>);
     if (RS == 1) emit_a = emit_b;
+    static_assert(wv_lds_emit<2 * RS>(kMaxChunk) <= kLdsBudget && kWvThreads % wv_rows(2 * RS) == 0, "");
     if (RS == 1 || chunk >= kWvMinChunk) {
       emit_kernel = &score_emit_waves<2 * RS>;
       emit_threads = kWvThreads;

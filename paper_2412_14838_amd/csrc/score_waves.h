@@ -23,9 +23,14 @@
 //   16 layers in one call, per layer, 8 heads: 65536 keys, 128 rows 29.5 / 24.8; five prompts of 4000 to 15000 keys, 64 rows
 //   21.6 / 17.7, 128 rows 23.0 / 19.2; 8192 keys, 64 rows 3.74 / 3.20
 //   one layer, 8 heads: 64 rows, 2048 keys 8.7 / 7.3, 16384 11.0 / 8.1, 65536 27.0 / 22.5; 128 rows, 32768 keys 18.6 / 15.9
-// At 65 to 128 rows a wavefront's tile takes four units, and what a layer costs beside them shows when there are few tiles:
-// below kWvMinChunk keys to a chunk score_emit_mfma stays (16 layers in one call, 8 heads of 128 rows, 8192 keys, both sweeps per
-// layer: 8.35 there, 8.96 here; one layer 18.4 and 17.8).
+// At 65 to 128 rows a wavefront's tile takes four units, and what a layer costs beside them shows when there are few tiles: where the
+// host's chunk is shorter than kWvMinChunk keys score_emit_mfma stays (16 layers in one call, 8 heads of 128 rows, 8192 keys, both sweeps
+// per layer: 8.35 there, 8.96 here; one layer 18.4 and 17.8). A batch's chunk may be cut to half of the host's on the device
+// (fitted_chunk): this kernel is the faster one there all the same, before / after, 8 heads: 96 rows, 32 prompts of 30 K keys together,
+// 640 of 1024 keys, one layer 32.6 / 31.8, four in one call 77.2 / 71.4; 128 rows, 16 prompts of 16 K, 768 of 1024, 15.6 / 14.2 and
+// 39.4 / 34.5; 16 prompts of 45 K, 896 of 1024, 35.2 / 33.4 and 101 / 92. Up to 64 rows it is taken always, also at one tile to a
+// wavefront (chunks of 256 keys): 64 rows, one layer of 300 keys 7.8 / 6.2, 8192 keys 8.6 / 6.8, eight layers in one call 31.2 / 27.1;
+// 64 prompts of 300 keys, eight layers 88 / 72; 8 rows, 200 prompts of 400 keys, one layer 121 / 95.
 // The first sweep done the same way was not better at 128 rows (32 layers of 32768 keys 417 / 419, one layer of 8192 9.6 / 10.1),
 // and its sums come out in another order.
 #pragma once
@@ -40,11 +45,11 @@ constexpr int kWvRingBytes = kWvWaves * kWvRing * kWvHalfBytes;
 // Row tiles of 32 for a call (2 or 4: an even number keeps the accumulators' roles fixed).
 __host__ __device__ constexpr int wv_rows(int nrt) { return nrt * 32; }
 constexpr int kWvMergeBytes = kWvThreads * (int)sizeof(float2);    // at most; merges of chunk partials share the place of the column sums
-__host__ __device__ inline int wv_sums_bytes(int chunk) {          // column sums of a chunk: its outputs, the pooling halo, the last tile's rest
+__host__ __device__ constexpr int wv_sums_bytes(int chunk) {          // column sums of a chunk: its outputs, the pooling halo, the last tile's rest
   const int b = (chunk + kMaxHalo + 32) * (int)sizeof(float);
   return b > kWvMergeBytes ? b : kWvMergeBytes;
 }
-template <int NRT> inline size_t wv_lds_emit(int chunk) {
+template <int NRT> constexpr size_t wv_lds_emit(int chunk) {
   return kWvRingBytes + wv_rows(NRT) * 256 + 2 * wv_rows(NRT) * sizeof(float) + wv_sums_bytes(chunk);
 }
 
