@@ -35,10 +35,14 @@ def test_one_kernel_gives_the_bits_of_two(dkv, Hkv, G, d, seqlens, w, layer_max)
     one = torch.full((L, cfg.n_seqs, cfg.Hq, d), float("nan"), device="cuda")
     one_lse = torch.full((L, cfg.n_seqs, cfg.Hq), float("nan"), device="cuda")
     two, two_lse = torch.full_like(one, float("nan")), torch.full_like(one_lse, float("nan"))
+    dkv.dkv_profile_begin(2 * L + 2)
     for l in range(L):
         comp.decode_attention(l, q[l], one[l], one_lse[l])
+    assert [name for name, _ in dkv.dkv_profile_end(2 * L + 2)] == ["decode"] * L            # one launch each
     assert L * cfg.n_seqs * Hkv * (d // 32) > 256            # more than the device's compute units: the other route
+    dkv.dkv_profile_begin(4)
     comp.decode_attention_layers(0, L, q, two, two_lse)
+    assert [name for name, _ in dkv.dkv_profile_end(4)] == ["decode"] * 2
     torch.cuda.synchronize()
     assert torch.equal(one, two) and torch.equal(one_lse, two_lse)
     kb = comp.kb.reshape(L, cfg.n_seqs, Hkv, -1, d).double()
