@@ -45,10 +45,13 @@ struct Tile {
 
 // The Q block of one (sequence, KV head) - up to RS * 64 rows of 128 - goes through LDS once per workgroup
 // (every row is needed by KS wavefronts): load_q_pieces() fetches kQPieces 16-byte pieces per thread (rows past
-// `rows` repeat the last one: their statistics are never used and their normalisers are +inf; zeros would make a NaN of
-// an infinite element of a key), store_q_pieces() puts them into `qbuf` in the padded row layout of the key tiles, and after a
+// `rows` are zero, or, with REPEAT, those of the last tile of 32 that has any repeat the last one: where their exponentials are
+// taken, against normalisers of +inf, a zero would make a NaN of an infinite element of a key; repeated rows keep the matrix pipe
+// busier than zeros, 1 % of the sweeps' time at 224 rows), store_q_pieces() puts them into `qbuf` in the padded row layout of the key tiles, and after a
 // barrier read_q_frags() gives each wavefront the fragments of its 64 rows in MFMA operand layout:
 // qf[t][j] = 8 consecutive head-dim elements (16 j + 8 (lane / 32) ..) of row rs * 64 + t * 32 + lane % 32.
+__host__ __device__ constexpr int tiled_rows(int rows) { return (rows + 31) / 32 * 32; }
+
 template <int N> struct PieceVec;
 template <> struct PieceVec<2> { typedef uint32_t type __attribute__((ext_vector_type(8))); };
 template <> struct PieceVec<4> { typedef uint32_t type __attribute__((ext_vector_type(16))); };
@@ -65,7 +68,7 @@ struct QStage {
   static constexpr int kPartPieces = kPieces / kParts;
 };
 
-template <int RS, int KS>
+template <int RS, int KS, bool REPEAT>
 __device__ inline typename PieceVec<QStage<RS, KS>::kPieces>::type load_q_pieces(const uint16_t* __restrict__ q_head,
                                                                                   int rows) {
   typename PieceVec<QStage<RS, KS>::kPieces>::type reg;
@@ -75,7 +78,9 @@ __device__ inline typename PieceVec<QStage<RS, KS>::kPieces>::type load_q_pieces
   for (int i = 0; i < QStage<RS, KS>::kPieces; ++i) {
     const uint32_t pc = t + i * (RS * KS * 64);                // piece pc of the block: row pc / 16, 16 bytes at pc * 16
     const uint32_t row = pc >> 4, src_row = row < (uint32_t)rows ? row : (uint32_t)rows - 1u;
-    const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + src_row * 256u + (pc & 15u) * 16u);
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row < (uint32_t)(REPEAT ? tiled_rows(rows) : rows))
+      v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + src_row * 256u + (pc & 15u) * 16u);
     reg[4 * i] = v.x; reg[4 * i + 1] = v.y; reg[4 * i + 2] = v.z; reg[4 * i + 3] = v.w;
   }
   return reg;
@@ -93,7 +98,7 @@ __device__ inline void store_q_pieces(char* __restrict__ qbuf, typename PieceVec
 
 // The same for one part of the block: pieces [part * kPartPieces, (part + 1) * kPartPieces) of every thread. The
 // kernels fetch the next layer's Q in QStage::kParts steps, at most 4 pieces (16 registers) at a time.
-template <int RS, int KS>
+template <int RS, int KS, bool REPEAT>
 __device__ inline typename PieceVec<QStage<RS, KS>::kPartPieces>::type load_q_part(const uint16_t* __restrict__ q_head,
                                                                                     int rows, int part) {
   typename PieceVec<QStage<RS, KS>::kPartPieces>::type reg;
@@ -103,7 +108,9 @@ __device__ inline typename PieceVec<QStage<RS, KS>::kPartPieces>::type load_q_pa
   for (int i = 0; i < QStage<RS, KS>::kPartPieces; ++i) {
     const uint32_t pc = t + (uint32_t)(part * QStage<RS, KS>::kPartPieces + i) * (RS * KS * 64);
     const uint32_t row = pc >> 4, src_row = row < (uint32_t)rows ? row : (uint32_t)rows - 1u;
-    const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + src_row * 256u + (pc & 15u) * 16u);
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row < (uint32_t)(REPEAT ? tiled_rows(rows) : rows))
+      v = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q_head) + src_row * 256u + (pc & 15u) * 16u);
     reg[4 * i] = v.x; reg[4 * i + 1] = v.y; reg[4 * i + 2] = v.z; reg[4 * i + 3] = v.w;
   }
   return reg;
@@ -135,11 +142,13 @@ __device__ inline void load_q_frags(const uint16_t* __restrict__ q_head, int rs,
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    int r = rs * 64 + t * 32 + (lane & 31);
-    r = r < rows ? r : rows - 1;
+    const int r = rs * 64 + t * 32 + (lane & 31), src_row = r < rows ? r : rows - 1;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      qf[t][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(q_head + (int64_t)r * 128 + j * 16 + (lane >> 5) * 8));
+    for (int j = 0; j < 8; ++j) {
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (r < tiled_rows(rows)) v = *reinterpret_cast<const uint4*>(q_head + (int64_t)src_row * 128 + j * 16 + (lane >> 5) * 8);
+      qf[t][j] = __builtin_bit_cast(bf16x8, v);
+    }
   }
 }
 
@@ -402,7 +411,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
   const char* k_ptr;
   {
     const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, 0, len - 1);
-    const typename PieceVec<QS::kPieces>::type q0 = load_q_pieces<RS, KS>(src.q[first_layer] + q_off, p.rows);
+    const typename PieceVec<QS::kPieces>::type q0 = load_q_pieces<RS, KS, false>(src.q[first_layer] + q_off, p.rows);
     const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, TL::kKeys, len - 1);
     int l2, t2;
     stream_tile(first_layer, 2, n_steps, n_layers, l2, t2);
@@ -437,7 +446,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
     const bool last = it + 1 == n_steps;
     typename PieceVec<QS::kPartPieces>::type qnext;  // local: no value is carried from step to step
     // issued before the tile's loads, which stay in flight past the end of the step (loads return in order)
-    if (fetch_q) qnext = load_q_part<RS, KS>(src.q[li + 1] + q_off, p.rows, q_part);
+    if (fetch_q) qnext = load_q_part<RS, KS, false>(src.q[li + 1] + q_off, p.rows, q_part);
     int la, ta;                                     // tile v + 3: issued in this step, stored to LDS in the next one
     stream_tile(li, it + 3, n_steps, n_layers, la, ta);
     if (la != k_layer) {
@@ -704,7 +713,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   {
     const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 0) * TL::kKeys, len - 1);
     typename PieceVec<QS::kPieces>::type q0;
-    if (QS::kEmitViaLds) q0 = load_q_pieces<RS, KS>(src.q[first_layer] + q_off, p.rows);
+    if (QS::kEmitViaLds) q0 = load_q_pieces<RS, KS, true>(src.q[first_layer] + q_off, p.rows);
     else load_q_frags(src.q[first_layer] + q_off, rs, p.rows, qf);
     const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 1) * TL::kKeys, len - 1);
     int l2, t2;
@@ -753,7 +762,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
     const bool fetch_lse = last && has_next && tid < kRows;    // multi-layer launches come with lse_rows
     typename PieceVec<QS::kPartPieces>::type qnext;            // local: no value is carried from step to step
     float lse_next;
-    if (fetch_q) qnext = load_q_part<RS, KS>(src.q[li + 1] + q_off, p.rows, q_part);
+    if (fetch_q) qnext = load_q_part<RS, KS, true>(src.q[li + 1] + q_off, p.rows, q_part);
     if (fetch_lse) lse_next = lse_row[(li + 1) * lse_rows_stride_layer];
     int la, ta;                                                // tile v + 3: issued in this step, stored to LDS in the next one
     stream_tile(li, it + 3, n_steps, n_layers, la, ta);
@@ -781,8 +790,8 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
       const char* __restrict__ next_tile = tiles + (kBuf ^ 1) * TL::kTileBytes + lane_tile;
       bf16x8 kfj = read_k_frag(next_tile, 0);
       // a wavefront whose 32 keys of this tile all lie past the computed range (the ragged tile of the pooling
-      // halo) has no exponentials to take: its column sums are never read
-      const bool live = wave_row0 < len;
+      // halo) has no exponentials to take: its column sums are never read. Nor has a row tile of padding alone.
+      const bool live[2] = {wave_row0 < len && rs * 64 < p.rows, wave_row0 < len && rs * 64 + 32 < p.rows};
 #pragma unroll
       for (int j = 0; j < 8; ++j) {   // two MFMAs of the next tile, then one eighth of the exponentials of this one
         __builtin_amdgcn_sched_barrier(0);
@@ -791,7 +800,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
         if (j == 0) ld[kBuf ^ 1] = load_tile<RS, KS>(k_ptr, stride_b, emit_tile(n_iter, ta) * TL::kKeys, len - 1);
         if (j == 2) store_tile<RS, KS>(tiles + kBuf * TL::kTileBytes, ld[kBuf]);   // the tile of step v + 2 (see the statistics kernel; measured best here)
         mfma_slice<false>(j, kfj, qf, b);
-        if (live) exps(j, lz);
+        if (live[j >> 2]) exps(j, lz);
         // pinned here (see the statistics kernel)
         asm volatile("" : "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3));
         lz = lz_next;
