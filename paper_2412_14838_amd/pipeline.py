@@ -67,7 +67,7 @@ class Compressor:
             self.kb = torch.zeros((L, cfg.n_seqs, Hkv, self.slots, d), dtype=self.tdtype, device=device)
             self.vb = torch.zeros_like(self.kb)
         self.ws = dkv.alloc_workspace(self.desc, device)
-        self._uncut = set()         # layers that hold all their candidates: selected, and no update or preset budget since
+        self._uncut = 0             # bit l: layer l holds all its candidates (selected, and no update or preset budget since)
         self.preset = None
         if schedule != "dynamic":
             kind = dkv.DKV_SCHEDULE_PYRAMID if schedule == "pyramid" else dkv.DKV_SCHEDULE_FIXED
@@ -103,9 +103,9 @@ class Compressor:
         dkv.dkv_row_lse(self.desc, st, self.cu, lse_out, self.ws, stream)
 
     def select(self, layer, stream=None):
-        self._uncut.add(layer)
         dkv.dkv_select_topk(self.desc, layer, dkv.layer_ptr(self.scores, layer), self.cfg.total_tokens, self.cu,
                             dkv.layer_ptr(self.idx, layer), self.counts, self.ws, stream)
+        self._uncut |= 1 << int(layer)
 
     def gather(self, layer, k, v, stride_token=None, stride_head=None, stream=None):
         d = self.cfg.d
@@ -116,9 +116,9 @@ class Compressor:
                           self.slots * d, stream)
 
     def select_layers(self, layer_begin, n_layers, stream=None):
-        self._uncut.update(range(layer_begin, layer_begin + n_layers))
         dkv.dkv_select_topk_layers(self.desc, layer_begin, n_layers, self.scores, self.cu, self.idx, self.counts,
                                    self.ws, stream)
+        self._uncut |= (1 << int(n_layers)) - 1 << int(layer_begin)
 
     def gather_layers(self, layer_begin, ks, vs, stride_token=None, stride_head=None, stream=None):
         d = self.cfg.d
@@ -144,7 +144,9 @@ class Compressor:
 
     def _decode_desc(self, layer_begin, n_layers):
         """The descriptor of a decode call: mean_budget is what its layers keep on average, as far as the host knows."""
-        uncut = sum(l in self._uncut for l in range(layer_begin, layer_begin + n_layers))
+        uncut = bin(self._uncut >> max(int(layer_begin), 0) & (1 << max(int(n_layers), 0)) - 1).count("1")
+        if uncut == 0:
+            return self.desc
         desc = dkv.dkv_desc.from_buffer_copy(self.desc)
         desc.mean_budget += (desc.layer_max - desc.mean_budget) * uncut // n_layers
         return desc
@@ -152,14 +154,14 @@ class Compressor:
     def decode_attention(self, layer, q_new, out, lse_out=None, stream=None):
         """Attention of one new token per sequence (q_new [n_seqs][Hq][d]) over layer `layer` of the compressed cache."""
         d = self.cfg.d
-        desc = self._decode_desc(layer, 1) if layer in self._uncut else self.desc
+        desc = self._decode_desc(layer, 1) if self._uncut else self.desc
         dkv.dkv_decode_attention(desc, layer, q_new, dkv.layer_ptr(self.kb, layer), dkv.layer_ptr(self.vb, layer),
                                  self.cfg.Hkv * self.slots * d, self.slots * d, self.cu, self.counts, out, lse_out, self.ws, stream)
 
     def decode_attention_layers(self, layer_begin, n_layers, q_new_all, out_all, lse_all=None, stream=None):
         """The same for n_layers consecutive layers in one call: q_new_all, out_all [n_layers][n_seqs][Hq][d]."""
         d = self.cfg.d
-        desc = self._decode_desc(layer_begin, n_layers) if self._uncut and n_layers > 0 else self.desc
+        desc = self._decode_desc(layer_begin, n_layers) if self._uncut else self.desc
         dkv.dkv_decode_attention_layers(desc, layer_begin, n_layers, q_new_all, self.kb, self.vb,
                                         self.cfg.n_seqs * self.cfg.Hkv * self.slots * d, self.cfg.Hkv * self.slots * d,
                                         self.slots * d, self.cu, self.counts, out_all, lse_all, self.ws, stream)
@@ -171,7 +173,7 @@ class Compressor:
         self._last_update = self._update_slot(layers_done)
         dkv.dkv_rebalance(self.desc, layers_done, self.epoch, self.scores, self.cu, self.counts, self.budgets,
                           self.hits, self.ws, stream)
-        self._uncut.difference_update(range(layers_done))
+        self._uncut &= -1 << int(layers_done)
 
     def rebalance_batch(self, layers_done, n_updates, stream=None):
         """The updates after layers_done, layers_done + interval, ... layers in one call."""
@@ -179,7 +181,7 @@ class Compressor:
         self._last_update = u0 + n_updates - 1
         dkv.dkv_rebalance_batch(self.desc, layers_done, n_updates, self.epoch, self.scores, self.cu, self.counts,
                                 self.budgets_all[u0], self.hits_all[u0], self.cfg.n_seqs * self.cfg.L, self.ws, stream)
-        self._uncut.difference_update(range(layers_done + (n_updates - 1) * self.cfg.interval))
+        self._uncut &= -1 << int(layers_done + (n_updates - 1) * self.cfg.interval)
 
     def step(self, layer, q_win, k, v, **strides):
         if layer == 0:
@@ -197,11 +199,11 @@ class Compressor:
 
     def apply_budgets(self, n_layers, stream=None):
         dkv.dkv_apply_budgets(self.desc, n_layers, self.preset, self.counts, stream)
-        self._uncut.difference_update(range(n_layers))
+        self._uncut &= -1 << int(n_layers)
 
     def select_recent(self, layer, stream=None):
-        self._uncut.add(layer)
         dkv.dkv_select_recent(self.desc, layer, self.n_sink, self.cu, dkv.layer_ptr(self.idx, layer), self.counts, stream)
+        self._uncut |= 1 << int(layer)
 
     def _step_preset(self, layer, q_win, k, v, **strides):
         # the comparison patterns: the layer's candidates, cut to the preset budget, then the compaction of what is left
