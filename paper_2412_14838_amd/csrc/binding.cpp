@@ -112,10 +112,12 @@ struct Arg<T*> {
 template <typename T>
 struct Arg<T* const*> {
   T* const* value;
-  T* kept[DKV_MAX_SELECT_LAYERS] = {};             // fewer tensors than the call's layers: null pointers; more: no call takes them
+  T* kept[DKV_MAX_SELECT_LAYERS] = {};             // fewer tensors than the call's layers: null pointers
+  Py_ssize_t n;                                    // what the sequence held
   bool take(PyObject* o, bool) {
     PyObject* seq = PySequence_Fast(o, "a sequence of tensors is required");
     if (seq == nullptr) return false;
+    n = PySequence_Fast_GET_SIZE(seq);
     bool ok = true;
     for (Py_ssize_t i = 0; ok && i < DKV_MAX_SELECT_LAYERS && i < PySequence_Fast_GET_SIZE(seq); ++i) {      // data_ptr() may change a list
       PyObject* item = PySequence_Fast_GET_ITEM(seq, i);
@@ -150,6 +152,22 @@ struct Arg<const dkv_desc*> {
   }
 };
 
+// Not more tensors than layers (the third argument of the calls that take several).
+template <typename A>
+bool fits(const A&, long long) {
+  return true;
+}
+template <typename T>
+bool fits(const Arg<T* const*>& a, long long layers) {
+  if (a.n <= layers) return true;
+  PyErr_Format(PyExc_IndexError, "%zd tensors for %lld layers", a.n, layers);
+  return false;
+}
+template <typename T>
+struct is_array_of_pointers : std::false_type {};
+template <typename T>
+struct is_array_of_pointers<T* const*> : std::true_type {};
+
 template <auto Fn, typename Signature>
 struct Call;
 
@@ -159,6 +177,8 @@ struct Call<Fn, int (*)(T...)> {
   static PyObject* with(PyObject* const* a, std::index_sequence<I...>) {
     std::tuple<Arg<T>...> args;
     if (!(std::get<I>(args).take(a[I], I + 1 == sizeof...(T)) && ...)) return nullptr;
+    if constexpr ((is_array_of_pointers<T>::value || ...))
+      if (!(fits(std::get<I>(args), std::get<2>(args).value) && ...)) return nullptr;
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = Fn(std::get<I>(args).value...);

@@ -155,18 +155,6 @@ def _check(status: int, where: str) -> None:
         raise DkvError(status, where)
 
 
-def _layers(k_layers, *others):
-    """The number of layers, and the other tensors of each (any iterable, at most as many) as sequences."""
-    n = len(k_layers)
-    out = [n]
-    for o in others:
-        o = o if hasattr(o, "__len__") else tuple(o)
-        if len(o) > n:
-            raise IndexError("%d tensors for %d layers" % (len(o), n))
-        out.append(o)
-    return out
-
-
 def dkv_version() -> int:
     return load().dkv_version()
 
@@ -231,20 +219,18 @@ def dkv_select_recent(desc, layer, n_sink, cu_seqlens, idx_out, counts, stream=N
 
 def dkv_score_window_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens, scores_all,
                             workspace, stream=None) -> None:
-    """q_layers, k_layers: sequences of device tensors, one per layer of the call."""
-    n, q_layers = _layers(k_layers, q_layers)
-    _check(binding().dkv_score_window_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
-                                             cu_seqlens, scores_all, workspace, workspace.nbytes, stream),
+    """k_layers: a sequence of device tensors, one per layer of the call; q_layers: any iterable of as many."""
+    _check(binding().dkv_score_window_layers(desc, layer_begin, len(k_layers), q_layers, k_layers, k_stride_token,
+                                             k_stride_head, cu_seqlens, scores_all, workspace, workspace.nbytes, stream),
            "dkv_score_window_layers")
 
 
 def dkv_score_window_lse_layers(desc, layer_begin, q_layers, k_layers, k_stride_token, k_stride_head, cu_seqlens,
                                 lse_layers, scores_all, workspace, stream=None) -> None:
-    """q_layers, k_layers, lse_layers: sequences of device tensors, one per layer of the call."""
-    n, q_layers, lse_layers = _layers(k_layers, q_layers, lse_layers)
-    _check(binding().dkv_score_window_lse_layers(desc, layer_begin, n, q_layers, k_layers, k_stride_token, k_stride_head,
-                                                 cu_seqlens, lse_layers, scores_all, workspace, workspace.nbytes, stream),
-           "dkv_score_window_lse_layers")
+    """k_layers: a sequence of device tensors, one per layer of the call; q_layers, lse_layers: any iterables of as many."""
+    _check(binding().dkv_score_window_lse_layers(desc, layer_begin, len(k_layers), q_layers, k_layers, k_stride_token,
+                                                 k_stride_head, cu_seqlens, lse_layers, scores_all, workspace,
+                                                 workspace.nbytes, stream), "dkv_score_window_lse_layers")
 
 
 def dkv_score_window_stats(desc, q_win, k, k_stride_token, k_stride_head, cu_seqlens, scores_out, scores_stride_head,
@@ -285,11 +271,10 @@ def dkv_select_topk_layers(desc, layer_begin, n_layers, scores_all, cu_seqlens, 
 
 def dkv_gather_kv_layers(desc, layer_begin, k_layers, v_layers, stride_token, stride_head, cu_seqlens, idx_all, counts,
                          k_out_all, v_out_all, out_stride_layer, out_stride_seq, out_stride_head, stream=None) -> None:
-    """k_layers, v_layers: sequences of device tensors, one per layer of the call."""
-    n, v_layers = _layers(k_layers, v_layers)
-    _check(binding().dkv_gather_kv_layers(desc, layer_begin, n, k_layers, v_layers, stride_token, stride_head, cu_seqlens,
-                                          idx_all, counts, k_out_all, v_out_all, out_stride_layer, out_stride_seq,
-                                          out_stride_head, stream), "dkv_gather_kv_layers")
+    """k_layers: a sequence of device tensors, one per layer of the call; v_layers: any iterable of as many."""
+    _check(binding().dkv_gather_kv_layers(desc, layer_begin, len(k_layers), k_layers, v_layers, stride_token, stride_head,
+                                          cu_seqlens, idx_all, counts, k_out_all, v_out_all, out_stride_layer,
+                                          out_stride_seq, out_stride_head, stream), "dkv_gather_kv_layers")
 
 
 def dkv_rebalance(desc, layers_done, epoch, scores_all, cu_seqlens, counts, budgets_out, hits_out, workspace,
