@@ -141,7 +141,8 @@ int dkv_profile_end(int32_t* kernel_ids_out /* host */, float* microseconds_out 
  *            sequence without a prefix has no candidates and its slots are left alone). Candidate scores are >= 0.
  * Accumulation is fp32 (bf16 products are exact in fp32). Two kernels are enqueued (row statistics, then scores).
  * Elements may be infinite: a logit of -inf has no weight; one of +inf or NaN leaves no number in the scores of its
- * (sequence, KV head) and touches no other.
+ * (sequence, KV head) and touches no other. bf16 at head_dim 128 sums its products in one pass: a logit whose products leave
+ * fp32's range on both sides has no number there, and logits of 1e6 and more are known to fp32's rounding of them only.
  */
 int dkv_score_window(const dkv_desc* desc, const void* q_win, const void* k, int64_t k_stride_token,
                      int64_t k_stride_head, const int32_t* cu_seqlens, float* scores_out,
