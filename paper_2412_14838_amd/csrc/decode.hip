@@ -469,7 +469,8 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(int w, int layer_max, i
 // rows are in flight under the softmax of the present ones. Per tile of 32 rows (max, sum, output) go to LDS and are
 // merged there, four tiles to a slab and then the slabs, in the two kernels' own order: the same bits.
 // What bounds it: the launch, one memory latency and the merges (5 us up to 256 rows), and from there the vector ALU: a turn
-// of 512 rows takes the compute unit about 3 us, four tiles of ~400 instructions to a SIMD.
+// of 512 rows takes the compute unit about 3 us, four tiles of ~400 instructions to a SIMD (counters at 544 rows on average: the
+// vector ALUs busy 43 % of the launch's time, its start and end included, the matrix pipes 9 %, wavefronts waiting 46 %).
 // ------------------------------------------------------------------------------------------------------
 constexpr int kDecOneThreads = 1024, kDecOneWaves = kDecOneThreads / 64;
 constexpr int kDecOneVStride = 32 * 2 + 16;             // bytes per staged row of V

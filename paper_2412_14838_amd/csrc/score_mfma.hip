@@ -945,7 +945,8 @@ bool score_mfma_supported(const Params& p, int dtype, int64_t k_stride_token) {
 // device holds one workgroup per compute unit, so the chunk is the multiple of the tile that minimises
 // rounds x (fixed + streaming): as few rounds of workgroups as possible, and within that the shortest chunk.
 // The number of chunks is exact for one sequence and an upper bound (one ragged tail per sequence) otherwise.
-constexpr double kFixedUs = 6.0, kUsPerKey = 0.0102;         // measured: 1.3 us per 128-key step of a full device
+// Measured: 1.3 us per 128-key step of a full device, of the sweeps with shared tiles (as the first one is for any number of rows).
+constexpr double kFixedUs = 6.0, kUsPerKey = 0.0102;
 
 template <int RS, int KS>
 static int pick_chunk(const Params& p, int cus) {
