@@ -352,6 +352,11 @@ __device__ inline void stream_tile(int li, int ahead, int n_steps, int n_layers,
   if (step >= n_steps) step = n_steps - 1;
 }
 
+// What a running maximum of logits (log2 domain) starts from. Below it a fused multiply-add minus the rounded maximum leaves up to
+// 2^7 of rounding, whose exponential is infinite: keys of the type's lowest value would leave no number in the rows that see nothing
+// else in a chunk. As it is such keys have no weight.
+constexpr float kLowestMax = -4294967296.0f;
+
 // ------------------------------------------------------------------------------------------------------
 // Row statistics: one partial (max, sum of exp2) per layer, chunk and row, in the log2 domain:
 // y = c * x with c = softmax_scale * log2(e); partial = (max y, sum exp2(y - max y)).
@@ -360,11 +365,6 @@ __device__ inline void stream_tile(int li, int ahead, int n_steps, int n_layers,
 // last two steps of a layer run, the first two key tiles and the Q block of the next layer are already being
 // fetched, so that only the first layer pays for a cold start.
 // ------------------------------------------------------------------------------------------------------
-// What a running maximum of logits (log2 domain) starts from. Below it a fused multiply-add minus the rounded maximum leaves up to
-// 2^7 of rounding, whose exponential is infinite: keys of the type's lowest value would leave no number in the rows that see nothing
-// else in a chunk. As it is such keys have no weight.
-constexpr float kLowestMax = -4294967296.0f;
-
 template <int RS, int KS>
 __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int chunk, int n_layers, int layers_each,
                                                                  ScoreLayers src, int64_t stride_token_b, int64_t stride_head_b,
