@@ -642,6 +642,28 @@ __global__ __launch_bounds__(256) void score_import_lse(Params p, LseLayers src,
     out[r] = r < p.rows ? in[r] * kLog2e : INFINITY;
 }
 
+// The layers of a call lie in ScoreLayers in the order the emit kernels take them; share z starts at place layers_each * z. With the first
+// sweep's cut (layers_each < 0: its negative) the shares follow each other. Else they go side by side, i-th place of share z is layer
+// n_shares * i + z, so that all start with the layers the memory-side cache still holds. Returns the workgroup's first place, n_layers
+// becomes the end of its places, and what belongs to layer 0 of the call is moved so that place * stride leads to its layer's.
+__device__ inline int take_share(int layers_each, int& n_layers, const float* __restrict__& lse_rows, int64_t& lse_rows_stride,
+                                 float* __restrict__& scores, int64_t& scores_stride, float* __restrict__& edges, int64_t& edges_stride) {
+  if (layers_each < 0) {
+    const int first = (int)blockIdx.z * -layers_each;
+    n_layers = first - layers_each < n_layers ? first - layers_each : n_layers;
+    return first;
+  }
+  const int z = blockIdx.z, shares = gridDim.z, first = z * layers_each, back = z - first * shares;
+  n_layers = first + (n_layers - z + shares - 1) / shares;
+  if (lse_rows != nullptr) lse_rows += back * lse_rows_stride;
+  scores += back * scores_stride;
+  if (edges != nullptr) edges += back * edges_stride;
+  lse_rows_stride *= shares;
+  scores_stride *= shares;
+  edges_stride *= shares;
+  return first;
+}
+
 // Outputs per thread of the emit kernel's epilogue (the chunk is at most kMaxChunk outputs).
 constexpr int kMaxChunk = 4096;
 
@@ -677,8 +699,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   int seq, c, nc, begin, S, first_full, n_full;
   if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, p.w, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
   const int head = blockIdx.y;
-  const int first_layer = blockIdx.z * layers_each;          // as in the statistics kernel
-  if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
+  const int first_layer = take_share(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rs = wave % RS, ks = wave / RS;
   const int prefix = S - p.w;                                // > 0 here
@@ -948,8 +969,9 @@ bool score_mfma_supported(const Params& p, int dtype, int64_t k_stride_token) {
 // Measured: 1.3 us per 128-key step of a full device, of the sweeps with shared tiles (as the first one is for any number of rows).
 constexpr double kFixedUs = 6.0, kUsPerKey = 0.0102;
 
+// The longest chunk whose column sums fit the LDS of the kernel that writes the scores.
 template <int RS, int KS>
-static int pick_chunk(const Params& p, int cus) {
+static int longest_chunk() {
   using TL = Tile<RS, KS>;
   int max_chunk = kMaxChunk;                                 // which score_emit_waves always has the LDS for
   if constexpr (RS > 1) {
@@ -958,12 +980,24 @@ static int pick_chunk(const Params& p, int cus) {
     max_chunk = max_chunk / TL::kKeys * TL::kKeys;
     if (max_chunk > kMaxChunk) max_chunk = kMaxChunk;
   }
+  return max_chunk;
+}
+
+// Workgroups of a head's chunks: exact for one sequence, an upper bound over several. (Workgroups that find no chunk cost more than
+// themselves: with one empty one beside 16 or 32 the dispatcher put two full ones on one compute unit.)
+static int chunk_groups(const Params& p, int chunk) {
+  return p.n_seqs == 1 ? (p.total_tokens + chunk - 1) / chunk : p.total_tokens / chunk + p.n_seqs;
+}
+
+template <int RS, int KS>
+static int pick_chunk(const Params& p, int cus) {
+  using TL = Tile<RS, KS>;
+  const int max_chunk = longest_chunk<RS, KS>();
   int best = 256;
   double best_cost = 1e30;
   for (int chunk = 256; chunk <= max_chunk; chunk += TL::kKeys) {
     if (chunk % TL::kKeys) continue;
-    const long long chunks = p.n_seqs == 1 ? (p.total_tokens + chunk - 1) / chunk : p.total_tokens / chunk + p.n_seqs;
-    const long long rounds = (chunks * p.Hkv + cus - 1) / cus;
+    const long long rounds = ((long long)chunk_groups(p, chunk) * p.Hkv + cus - 1) / cus;
     const double cost = rounds * (kFixedUs + chunk * kUsPerKey);
     if (cost < best_cost - 1e-9) { best_cost = cost; best = chunk; }
   }
@@ -990,6 +1024,34 @@ static int pick_shares(int groups, int n_layers, int chunk, int cus) {
   return best;
 }
 
+// The second sweep of a call over several layers cuts the keys anew: its sums do not depend on where. A longer chunk in more shares of
+// the layers is as much work for a workgroup in fewer layers, each of which has its end (kLayerUs: three barriers, pooling, the next
+// layer's Q; 4 to 5 K cycles of the 21 K that a layer of 1024 keys takes). Both sweeps / the second one alone, us, the first sweep's cut /
+// this one, 8 heads of 128 rows: 32 layers of 32768 keys 844 / 830, 426 / 407; 16 of 8192 126 / 114, 72 / 56; 4 heads of 224 rows, 28 layers of 32768 627 / 603, 329 / 307. While the keys of the whole call fit the
+// L2s (8 x 4 MB), a workgroup finds what the first sweep's workgroup in its place has left in its XCD's: 2 layers of 5000 keys 29.1 with
+// that one's cut, 30.0 with this one; 4 of 2048 19.7 and 20.0. Without a first sweep nothing is there to be found.
+// A batch keeps the first sweep's cut, fitted to its lengths: eight prompts of 4000 to 15000, 32 layers, whole pass 2625 with it, 2678 anew.
+constexpr int64_t kL2Bytes = 32 << 20;
+constexpr double kLayerUs = 1.3;
+
+template <int RS, int KS>
+static void pick_emit_cut(const Params& p, int n_layers, int cus, int& chunk, int& shares) {
+  const int max_chunk = longest_chunk<RS, KS>();
+  double best_cost = 1e30;
+  for (int c = 256; c <= max_chunk; c += 256) {
+    const long long groups = (long long)chunk_groups(p, c) * p.Hkv;
+    for (int each = n_layers, s = 1; each >= 1; ) {
+      const long long rounds = (groups * s + cus - 1) / cus;
+      const double cost = rounds * (kFixedUs + each * (kLayerUs + c * kUsPerKey));
+      // (more do not fit the kernels' argument)
+      if (each * s <= DKV_MAX_SELECT_LAYERS && cost < best_cost * (1.0 - 1e-9)) { best_cost = cost; chunk = c; shares = s; }
+      if (each == 1) break;
+      s = (n_layers + each - 2) / (each - 1);                  // the fewest shares of fewer layers each
+      each = (n_layers + s - 1) / s;
+    }
+  }
+}
+
 void launch_import_lse(const Params& p, int n_layers, const float* const* lse_layers, float* lse_rows, hipStream_t st) {
   LseLayers in{};
   for (int i = 0; i < n_layers; ++i) in.lse[i] = lse_layers[i];
@@ -1004,7 +1066,14 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
                                 const float* const* lse_layers,
                                 float* lse_out, hipStream_t st) {
   using TL = Tile<RS, KS>;
-  const int chunk = pick_chunk<RS, KS>(p, device_cus());
+  const int cus = device_cus(), chunk = pick_chunk<RS, KS>(p, cus), grid_x = chunk_groups(p, chunk);
+  const int shares = pick_shares(grid_x * p.Hkv, n_layers, chunk, cus), layers_each = (n_layers + shares - 1) / shares;
+  int emit_chunk = chunk, emit_shares = 1;
+  const bool in_l2 = lse_layers == nullptr && (int64_t)n_layers * p.Hkv * p.total_tokens * 256 <= kL2Bytes;
+  const bool same_cut = n_layers == 1 || p.n_seqs > 1 || in_l2;
+  if (same_cut) emit_shares = shares;
+  else pick_emit_cut<RS, KS>(p, n_layers, cus, emit_chunk, emit_shares);
+  const int emit_grid_x = chunk_groups(p, emit_chunk), emit_each = (n_layers + emit_shares - 1) / emit_shares;
   float* partials = ws ? reinterpret_cast<float*>(ws + wl.partials) : nullptr;   // no workspace: lse supplied
   const int64_t partials_stride_layer = (int64_t)wl.partials_layer_bytes / (int64_t)sizeof(float);
   const size_t stat_bytes = (size_t)KS * RS * 64 * sizeof(float2);               // the final [KS][RS * 64] partials
@@ -1018,17 +1087,17 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   if constexpr (RS > 1) {
     emit_kernel = &score_emit_mfma<RS, KS>;
     emit_a = emit_b = reinterpret_cast<const void*>(emit_kernel);
-    lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(chunk) * sizeof(float) +
+    lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(emit_chunk) * sizeof(float) +
                (size_t)QStage<RS, KS>::kBytes;              // the Q staging area serves the next layer in every variant
   }
   if constexpr (RS <= 2) {
     emit_b = reinterpret_cast<const void*>(&score_emit_waves<2 * RS>);
     if (RS == 1) emit_a = emit_b;
     static_assert(wv_lds_emit<2 * RS>(kMaxChunk) <= kLdsBudget && kWvThreads % wv_rows(2 * RS) == 0, "");
-    if (RS == 1 || chunk >= kWvMinChunk) {
+    if (RS == 1 || emit_chunk >= kWvMinChunk) {
       emit_kernel = &score_emit_waves<2 * RS>;
       emit_threads = kWvThreads;
-      lds_emit = wv_lds_emit<2 * RS>(chunk);
+      lds_emit = wv_lds_emit<2 * RS>(emit_chunk);
     }
   }
   static std::atomic<uint64_t> given{0};
@@ -1040,11 +1109,6 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     src.q[i] = static_cast<const uint16_t*>(q_layers[i]);
     src.k[i] = static_cast<const char*>(k_layers[i]);
   }
-  // Chunks of a single sequence, an upper bound on the chunks over several. (Workgroups that find no chunk cost more than
-  // themselves: with one empty one beside 16 or 32 the dispatcher put two full ones on one compute unit.)
-  const int grid_x = p.n_seqs == 1 ? (p.total_tokens + chunk - 1) / chunk : p.total_tokens / chunk + p.n_seqs;
-  const int shares = pick_shares(grid_x * p.Hkv, n_layers, chunk, device_cus());
-  const int layers_each = (n_layers + shares - 1) / shares;
   if (phases & kPhaseStats)
     launch(DKV_KERNEL_SCORE_STATS, (score_stats_mfma<RS, KS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_stats, st, p, chunk,
            n_layers, layers_each, src, k_stride_token * 2, k_stride_head * 2, cu, partials, partials_stride_layer);
@@ -1053,8 +1117,9 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     // streamed them first to last, so the last layers are the ones the memory-side cache still holds.
     ScoreLayers rev{};
     for (int i = 0; i < n_layers; ++i) {
-      rev.q[i] = src.q[n_layers - 1 - i];
-      rev.k[i] = src.k[n_layers - 1 - i];
+      const int place = same_cut ? i : i % emit_shares * emit_each + i / emit_shares;
+      rev.q[place] = src.q[n_layers - 1 - i];
+      rev.k[place] = src.k[n_layers - 1 - i];
     }
     const int last = n_layers - 1;
     // several layers: their row normalisers are merged from the chunk partials by a small kernel of its own
@@ -1075,12 +1140,12 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     // all layers); a single layer recomputes the halo keys inside the emit kernel, which is cheaper than a launch.
     float* edges = n_layers > 1 && p.half > 0 ? reinterpret_cast<float*>(ws + wl.edges) : nullptr;
     const int64_t edges_stride_layer = (int64_t)wl.edges_layer_bytes / (int64_t)sizeof(float);
-    launch(DKV_KERNEL_SCORE_EMIT, emit_kernel, dim3(grid_x, p.Hkv, shares), dim3(emit_threads), lds_emit, st, p, chunk,
-           n_layers, layers_each, rev, k_stride_token * 2, k_stride_head * 2, cu, static_cast<const float*>(partials),
+    launch(DKV_KERNEL_SCORE_EMIT, emit_kernel, dim3(emit_grid_x, p.Hkv, emit_shares), dim3(emit_threads), lds_emit, st, p, emit_chunk,
+           n_layers, same_cut ? -emit_each : emit_each, rev, k_stride_token * 2, k_stride_head * 2, cu, static_cast<const float*>(partials),
            lse_rows ? static_cast<const float*>(lse_rows) + last * lse_rows_stride_layer : nullptr, -lse_rows_stride_layer,
            lse_in, scores + last * scores_stride_layer, scores_stride_head, -scores_stride_layer, edges, edges_stride_layer);
     if (edges != nullptr)
-      launch(DKV_KERNEL_SCORE_BORDERS, score_fix_borders, dim3(grid_x, p.Hkv, n_layers), dim3(64), 0, st, p, chunk,
+      launch(DKV_KERNEL_SCORE_BORDERS, score_fix_borders, dim3(emit_grid_x, p.Hkv, n_layers), dim3(64), 0, st, p, emit_chunk,
              (int)TL::kKeys, cu,
              static_cast<const float*>(edges), edges_stride_layer, scores + last * scores_stride_layer, scores_stride_head,
              -scores_stride_layer);

@@ -271,8 +271,7 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
   seq = __builtin_amdgcn_readfirstlane(seq);
   begin = __builtin_amdgcn_readfirstlane(begin);
   const int head = blockIdx.y;
-  const int first_layer = blockIdx.z * layers_each;
-  if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
+  const int first_layer = take_share(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
   const int tid = threadIdx.x, lane = tid & 63;
   const int prefix = __builtin_amdgcn_readfirstlane(S - p.w);            // > 0 here
   const int o0 = __builtin_amdgcn_readfirstlane(c * chunk);              // outputs [o0, o1)
