@@ -334,10 +334,14 @@ __device__ inline bool find_chunk2(const int32_t* __restrict__ cu, int n_seqs, i
   return false;
 }
 
-// Q and K of the layers one launch covers (kernel argument, indexed by the layer's place in the launch).
+// Q and K of the layers one launch covers (kernel argument, indexed by the layer's place in the launch): of one layer, or of up to
+// DKV_MAX_SELECT_LAYERS. The kernels exist for both. A call per layer, as a model's forward pass makes it, hands over 16 bytes instead
+// of 512, and its kernels hold nothing of what goes on from layer to layer: 32 layers one by one, whole passes, us, 8192 tokens
+// 1194 / 1140, 32768 tokens 2186 / 2130, 1.6 to 1.7 a layer.
+template <int LAYERS>
 struct ScoreLayers {
-  const uint16_t* q[DKV_MAX_SELECT_LAYERS];
-  const char* k[DKV_MAX_SELECT_LAYERS];
+  const uint16_t* q[LAYERS];
+  const char* k[LAYERS];
 };
 
 // The tile `ahead` steps after the start of layer `li` in the stream of n_steps tiles per layer: its layer and
@@ -365,9 +369,9 @@ constexpr float kLowestMax = -4294967296.0f;
 // last two steps of a layer run, the first two key tiles and the Q block of the next layer are already being
 // fetched, so that only the first layer pays for a cold start.
 // ------------------------------------------------------------------------------------------------------
-template <int RS, int KS>
+template <int RS, int KS, int LAYERS>
 __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int chunk, int n_layers, int layers_each,
-                                                                 ScoreLayers src, int64_t stride_token_b, int64_t stride_head_b,
+                                                                 ScoreLayers<LAYERS> src, int64_t stride_token_b, int64_t stride_head_b,
                                                                  const int32_t* __restrict__ cu,
                                                                  float* __restrict__ partials,
                                                                  int64_t partials_stride_layer) {
@@ -382,8 +386,13 @@ __global__ __launch_bounds__(RS * KS * 64) void score_stats_mfma(Params p, int c
   int seq, c, nc, begin, S, first_full, n_full;
   if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, 0, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
   const int head = blockIdx.y;
-  const int first_layer = blockIdx.z * layers_each;      // the layers of the call this workgroup takes its chunk through
-  if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
+  int first_layer = 0;                                   // the layers of the call this workgroup takes its chunk through
+  if constexpr (LAYERS == 1) {
+    n_layers = 1;
+  } else {
+    first_layer = blockIdx.z * layers_each;
+    if (first_layer + layers_each < n_layers) n_layers = first_layer + layers_each;
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rs = wave % RS, ks = wave / RS;
   const int c0 = c * chunk;
@@ -646,8 +655,13 @@ __global__ __launch_bounds__(256) void score_import_lse(Params p, LseLayers src,
 // sweep's cut (layers_each < 0: its negative) the shares follow each other. Else they go side by side, i-th place of share z is layer
 // n_shares * i + z, so that all start with the layers the memory-side cache still holds. Returns the workgroup's first place, n_layers
 // becomes the end of its places, and what belongs to layer 0 of the call is moved so that place * stride leads to its layer's.
+template <int LAYERS>
 __device__ inline int take_share(int layers_each, int& n_layers, const float* __restrict__& lse_rows, int64_t& lse_rows_stride,
                                  float* __restrict__& scores, int64_t& scores_stride, float* __restrict__& edges, int64_t& edges_stride) {
+  if constexpr (LAYERS == 1) {
+    n_layers = 1;
+    return 0;
+  }
   if (layers_each < 0) {
     const int first = (int)blockIdx.z * -layers_each;
     n_layers = first - layers_each < n_layers ? first - layers_each : n_layers;
@@ -672,9 +686,9 @@ constexpr int kMaxChunk = 4096;
 // run. The row normalisers come from lse_rows (multi-layer launches, written by the merge kernel), from lse_in
 // (supplied by the caller, natural log, single-layer launches) or are merged here from the chunk partials
 // (single-layer launches).
-template <int RS, int KS>
+template <int RS, int KS, int LAYERS>
 __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int chunk, int n_layers, int layers_each,
-                                                                ScoreLayers src, int64_t stride_token_b, int64_t stride_head_b,
+                                                                ScoreLayers<LAYERS> src, int64_t stride_token_b, int64_t stride_head_b,
                                                                 const int32_t* __restrict__ cu,
                                                                 const float* __restrict__ partials,
                                                                 const float* __restrict__ lse_rows,
@@ -699,7 +713,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   int seq, c, nc, begin, S, first_full, n_full;
   if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, p.w, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
   const int head = blockIdx.y;
-  const int first_layer = take_share(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
+  const int first_layer = take_share<LAYERS>(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rs = wave % RS, ks = wave / RS;
   const int prefix = S - p.w;                                // > 0 here
@@ -1058,7 +1072,7 @@ void launch_import_lse(const Params& p, int n_layers, const float* const* lse_la
   launch(DKV_KERNEL_SCORE_MERGE, score_import_lse, dim3(p.n_seqs, p.Hkv, n_layers), dim3(256), 0, st, p, in, lse_rows);
 }
 
-template <int RS, int KS>
+template <int RS, int KS, int LAYERS>
 static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const void* const* q_layers,
                                 const void* const* k_layers, int64_t k_stride_token, int64_t k_stride_head,
                                 const int32_t* cu, float* scores, int64_t scores_stride_head,
@@ -1079,43 +1093,43 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   const size_t stat_bytes = (size_t)KS * RS * 64 * sizeof(float2);               // the final [KS][RS * 64] partials
   const size_t lds_stats = 2 * TL::kTileBytes + (size_t)QStage<RS, KS>::kBytes + stat_bytes;
   // The kernel that writes the scores: score_waves.h has the rule.
-  void (*emit_kernel)(Params, int, int, int, ScoreLayers, int64_t, int64_t, const int32_t*, const float*, const float*, int64_t,
+  void (*emit_kernel)(Params, int, int, int, ScoreLayers<LAYERS>, int64_t, int64_t, const int32_t*, const float*, const float*, int64_t,
                       const float*, float*, int64_t, int64_t, float*, int64_t) = nullptr;
   int emit_threads = TL::kThreads;
   size_t lds_emit = 0;
   const void *emit_a = nullptr, *emit_b = nullptr;          // those this call's number of rows may take
   if constexpr (RS > 1) {
-    emit_kernel = &score_emit_mfma<RS, KS>;
+    emit_kernel = &score_emit_mfma<RS, KS, LAYERS>;
     emit_a = emit_b = reinterpret_cast<const void*>(emit_kernel);
     lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(emit_chunk) * sizeof(float) +
                (size_t)QStage<RS, KS>::kBytes;              // the Q staging area serves the next layer in every variant
   }
   if constexpr (RS <= 2) {
-    emit_b = reinterpret_cast<const void*>(&score_emit_waves<2 * RS>);
+    emit_b = reinterpret_cast<const void*>(&score_emit_waves<2 * RS, LAYERS>);
     if (RS == 1) emit_a = emit_b;
     static_assert(wv_lds_emit<2 * RS>(kMaxChunk) <= kLdsBudget && kWvThreads % wv_rows(2 * RS) == 0, "");
     if (RS == 1 || emit_chunk >= kWvMinChunk) {
-      emit_kernel = &score_emit_waves<2 * RS>;
+      emit_kernel = &score_emit_waves<2 * RS, LAYERS>;
       emit_threads = kWvThreads;
       lds_emit = wv_lds_emit<2 * RS>(emit_chunk);
     }
   }
   static std::atomic<uint64_t> given{0};
-  const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_mfma<RS, KS>), (int)lds_stats},
+  const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_mfma<RS, KS, LAYERS>), (int)lds_stats},
                                          {emit_a, kLdsBudget}, {emit_b, kLdsBudget}});
   if (e != hipSuccess) return e;
-  ScoreLayers src{};
+  ScoreLayers<LAYERS> src{};
   for (int i = 0; i < n_layers && (phases & (kPhaseStats | kPhaseEmit)); ++i) {
     src.q[i] = static_cast<const uint16_t*>(q_layers[i]);
     src.k[i] = static_cast<const char*>(k_layers[i]);
   }
   if (phases & kPhaseStats)
-    launch(DKV_KERNEL_SCORE_STATS, (score_stats_mfma<RS, KS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_stats, st, p, chunk,
+    launch(DKV_KERNEL_SCORE_STATS, (score_stats_mfma<RS, KS, LAYERS>), dim3(grid_x, p.Hkv, shares), dim3(TL::kThreads), lds_stats, st, p, chunk,
            n_layers, layers_each, src, k_stride_token * 2, k_stride_head * 2, cu, partials, partials_stride_layer);
   if (phases & kPhaseEmit) {
     // The emit kernel takes the layers of the call from the last to the first: the statistics kernel has just
     // streamed them first to last, so the last layers are the ones the memory-side cache still holds.
-    ScoreLayers rev{};
+    ScoreLayers<LAYERS> rev{};
     for (int i = 0; i < n_layers; ++i) {
       const int place = same_cut ? i : i % emit_shares * emit_each + i / emit_shares;
       rev.q[place] = src.q[n_layers - 1 - i];
@@ -1161,14 +1175,14 @@ hipError_t launch_score_mfma(const Params& p, int phases, int n_layers, const vo
                              const int32_t* cu, float* scores, int64_t scores_stride_head, int64_t scores_stride_layer,
                              char* ws, const WorkspaceLayout& wl, const float* lse_in, const float* const* lse_layers,
                              float* lse_out, hipStream_t st) {
-  if (p.rows <= 64)
-    return launch_mfma_t<1, 4>(p, phases, n_layers, q_layers, k_layers, k_stride_token, k_stride_head, cu, scores,
-                               scores_stride_head, scores_stride_layer, ws, wl, lse_in, lse_layers, lse_out, st);
-  if (p.rows <= 128)
-    return launch_mfma_t<2, 4>(p, phases, n_layers, q_layers, k_layers, k_stride_token, k_stride_head, cu, scores,
-                               scores_stride_head, scores_stride_layer, ws, wl, lse_in, lse_layers, lse_out, st);
-  return launch_mfma_t<4, 2>(p, phases, n_layers, q_layers, k_layers, k_stride_token, k_stride_head, cu, scores,
-                             scores_stride_head, scores_stride_layer, ws, wl, lse_in, lse_layers, lse_out, st);
+  auto run = [&](auto launcher) {
+    return launcher(p, phases, n_layers, q_layers, k_layers, k_stride_token, k_stride_head, cu, scores, scores_stride_head,
+                    scores_stride_layer, ws, wl, lse_in, lse_layers, lse_out, st);
+  };
+  constexpr int kMany = DKV_MAX_SELECT_LAYERS;
+  if (p.rows <= 64) return n_layers == 1 ? run(launch_mfma_t<1, 4, 1>) : run(launch_mfma_t<1, 4, kMany>);
+  if (p.rows <= 128) return n_layers == 1 ? run(launch_mfma_t<2, 4, 1>) : run(launch_mfma_t<2, 4, kMany>);
+  return n_layers == 1 ? run(launch_mfma_t<4, 2, 1>) : run(launch_mfma_t<4, 2, kMany>);
 }
 
 }  // namespace dkv

@@ -111,7 +111,8 @@ struct WaveKeys {
   int spare;                        // the place of a half 1 that was taken waits for its refill
   uint32_t read_off[4];             // LDS places of this lane's pieces (head dimensions 16 j .. + 15) within a half
 
-  __device__ void start(char* smem, const ScoreLayers& src, int64_t chunk_off, uint32_t stride, int chunk_len, int first_layer, int n_layers) {
+  template <int LAYERS>
+  __device__ void start(char* smem, const ScoreLayers<LAYERS>& src, int64_t chunk_off, uint32_t stride, int chunk_len, int first_layer, int n_layers) {
     const int lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     lds = smem;
@@ -250,8 +251,8 @@ __device__ inline float2 both_halves(float v) {
 }
 
 // Scores, see score_emit_mfma (same arguments). The column sums of a chunk lie in LDS until its layer is done.
-template <int NRT>
-__global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chunk, int n_layers, int layers_each, ScoreLayers src,
+template <int NRT, int LAYERS>
+__global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chunk, int n_layers, int layers_each, ScoreLayers<LAYERS> src,
                                                                int64_t stride_token_b, int64_t stride_head_b,
                                                                const int32_t* __restrict__ cu, const float* __restrict__ partials,
                                                                const float* __restrict__ lse_rows, int64_t lse_rows_stride_layer,
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
   seq = __builtin_amdgcn_readfirstlane(seq);
   begin = __builtin_amdgcn_readfirstlane(begin);
   const int head = blockIdx.y;
-  const int first_layer = take_share(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
+  const int first_layer = take_share<LAYERS>(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
   const int tid = threadIdx.x, lane = tid & 63;
   const int prefix = __builtin_amdgcn_readfirstlane(S - p.w);            // > 0 here
   const int o0 = __builtin_amdgcn_readfirstlane(c * chunk);              // outputs [o0, o1)
