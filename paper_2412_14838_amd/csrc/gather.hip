@@ -4,19 +4,21 @@
 
 namespace dkv {
 
-// Source tensors of the layers one call covers (kernel argument, indexed by the layer's place in the call).
+// Source tensors of the layers one call covers (kernel argument, indexed by the layer's place in the call): one layer's, or those of up to
+// DKV_MAX_SELECT_LAYERS.
+template <int LAYERS>
 struct GatherSources {
-  const char* k[DKV_MAX_SELECT_LAYERS];
-  const char* v[DKV_MAX_SELECT_LAYERS];
+  const char* k[LAYERS];
+  const char* v[LAYERS];
 };
 
 // One workgroup copies ROWS = 256 / LANES row slots of one (layer, sequence, KV head); LANES lanes x 16 bytes = one
 // row. grid = (slot_blocks * n_seqs * layers of the call, Hkv), slot_blocks = ceil((w + layer_max) / ROWS): the
 // (sequence, layer) pair rides in x, whose range is 2^31, not in z, whose range is 65535.
-template <int LANES>
+template <int LANES, int LAYERS>
 __global__ __launch_bounds__(256) void gather_kernel(int w, int layer_max, int L, int layer0, int n_seqs, int row_bytes,
                                                      int slot_blocks,
-                                                     GatherSources src_layers,
+                                                     GatherSources<LAYERS> src_layers,
                                                      int64_t stride_token_b, int64_t stride_head_b,
                                                      const int32_t* __restrict__ cu, const int32_t* __restrict__ idx0,
                                                      int64_t idx_stride_layer,
@@ -25,7 +27,7 @@ __global__ __launch_bounds__(256) void gather_kernel(int w, int layer_max, int L
                                                      int64_t out_stride_seq_b, int64_t out_stride_head_b) {
   constexpr int ROWS = 256 / LANES;
   const int pair = blockIdx.x / slot_blocks, slot_block = blockIdx.x % slot_blocks;
-  const int seq = pair % n_seqs, lz = pair / n_seqs, head = blockIdx.y;
+  const int lz = LAYERS == 1 ? 0 : pair / n_seqs, seq = pair - lz * n_seqs, head = blockIdx.y;
   const int layer = layer0 + lz;
   const char* __restrict__ k = src_layers.k[lz];
   const char* __restrict__ v = src_layers.v[lz];
@@ -66,12 +68,11 @@ hipError_t launch_gather(const Params& p, int elt_bytes, int layer, int n_layers
   const int row_bytes = p.d * elt_bytes;          // 128, 256 or 512
   const int lanes = row_bytes / 16;               // 8, 16 or 32
   const int slots = p.w + p.layer_max;
-  GatherSources src{};
-  for (int i = 0; i < n_layers; ++i) {
-    src.k[i] = static_cast<const char*>(k_layers[i]);
-    src.v[i] = static_cast<const char*>(v_layers[i]);
-  }
-  auto go = [&](auto kernel, int LANES) {
+  auto go = [&](auto kernel, int LANES, auto src) {
+    for (int i = 0; i < n_layers; ++i) {
+      src.k[i] = static_cast<const char*>(k_layers[i]);
+      src.v[i] = static_cast<const char*>(v_layers[i]);
+    }
     const int rows = 256 / LANES;
     const int slot_blocks = (slots + rows - 1) / rows;
     dim3 grid(slot_blocks * p.n_seqs * n_layers, p.Hkv);
@@ -81,9 +82,13 @@ hipError_t launch_gather(const Params& p, int elt_bytes, int layer, int n_layers
            static_cast<char*>(k_out), static_cast<char*>(v_out), out_stride_layer * elt_bytes,
            out_stride_seq * elt_bytes, out_stride_head * elt_bytes);
   };
-  if (lanes <= 8) go(gather_kernel<8>, 8);
-  else if (lanes <= 16) go(gather_kernel<16>, 16);
-  else go(gather_kernel<32>, 32);
+  auto by_layers = [&](auto one, auto many, int LANES) {
+    if (n_layers == 1) go(one, LANES, GatherSources<1>{});
+    else go(many, LANES, GatherSources<DKV_MAX_SELECT_LAYERS>{});
+  };
+  if (lanes <= 8) by_layers(gather_kernel<8, 1>, gather_kernel<8, DKV_MAX_SELECT_LAYERS>, 8);
+  else if (lanes <= 16) by_layers(gather_kernel<16, 1>, gather_kernel<16, DKV_MAX_SELECT_LAYERS>, 16);
+  else by_layers(gather_kernel<32, 1>, gather_kernel<32, DKV_MAX_SELECT_LAYERS>, 32);
   return hipGetLastError();
 }
 
