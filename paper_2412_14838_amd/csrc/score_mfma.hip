@@ -1038,32 +1038,48 @@ static int pick_shares(int groups, int n_layers, int chunk, int cus) {
   return best;
 }
 
-// The second sweep of a call over several layers cuts the keys anew: its sums do not depend on where. A longer chunk in more shares of
-// the layers is as much work for a workgroup in fewer layers, each of which has its end (kLayerUs: three barriers, pooling, the next
-// layer's Q; 4 to 5 K cycles of the 21 K that a layer of 1024 keys takes). Both sweeps / the second one alone, us, the first sweep's cut /
-// this one, 8 heads of 128 rows: 32 layers of 32768 keys 844 / 830, 426 / 407; 16 of 8192 126 / 114, 72 / 56; 4 heads of 224 rows, 28 layers of 32768 627 / 603, 329 / 307. While the keys of the whole call fit the
-// L2s (8 x 4 MB), a workgroup finds what the first sweep's workgroup in its place has left in its XCD's: 2 layers of 5000 keys 29.1 with
-// that one's cut, 30.0 with this one; 4 of 2048 19.7 and 20.0. Without a first sweep nothing is there to be found.
-// A batch keeps the first sweep's cut, fitted to its lengths: eight prompts of 4000 to 15000, 32 layers, whole pass 2625 with it, 2678 anew.
+// The second sweep of a call over several layers may cut the keys anew: its sums do not depend on where. A longer chunk in more shares of
+// the layers is as much work for a workgroup in fewer layers, each of which has its end (layer_us: barriers, pooling, the next layer's Q;
+// 4 to 5 K of the 21 K cycles that a layer of 1024 keys and 128 rows takes). Against that stands what a workgroup finds in its XCD's L2
+// of what the first sweep's workgroup in its place read last, kFoundUs, or all of the keys where they fit the L2s (8 x 4 MB).
+// Both sweeps / the second one alone, us, the first sweep's cut / the new one, one sequence: 8 heads of 128 rows, 32 layers of 32768 keys
+// 844 / 830, 426 / 407, 16 of 8192 126 / 114, 72 / 56, 8 of 6000 75 / 66, 41 / 29; 224 rows, 4 heads, 28 of 32768 627 / 603, 329 / 307, 4 of
+// 12000 63 / 56, 36 / 28; 160 rows, 2 heads, 16 of 20000 155 / 130, 83 / 58; 64 rows, 2 heads, 32 of 9000 96 / 85, 52 / 37. Not taken: 8 heads
+// of 128 rows, 4 of 12000 50 / 53, 32 / 30; 2 of 5000 29.1 / 30.0; 64 rows, 4 of 16384 53 / 58, 32 / 33, 32 of 32768 715 / 719; 16 rows, 4 of 30000 84 / 92, 47 / 52.
+// A batch keeps the first sweep's cut, fitted to its lengths: eight prompts of 4000 to 15000, 32 layers, whole pass 2625, 2678 anew.
 constexpr int64_t kL2Bytes = 32 << 20;
-constexpr double kLayerUs = 1.3;
+constexpr double kFoundUs = 8.0;
+template <int RS> constexpr double layer_us() { return RS == 1 ? 0.8 : RS == 2 ? 1.3 : 3.0; }
 
+// True if the cut (chunk, shares: the first sweep's) has been changed.
 template <int RS, int KS>
-static void pick_emit_cut(const Params& p, int n_layers, int cus, int& chunk, int& shares) {
+static bool pick_emit_cut(const Params& p, int n_layers, bool first_sweep, int cus, int& chunk, int& shares) {
+  if (n_layers == 1 || p.n_seqs > 1) return false;
+  if (RS == 1 && chunk > 256) return false;                  // up to 64 rows: the stream of keys hides a layer's end behind two tiles a wavefront
+  if (first_sweep && (int64_t)n_layers * p.Hkv * p.total_tokens * 256 <= kL2Bytes) return false;
+  auto cost = [&](int c, int s, int each) {
+    const long long rounds = ((long long)chunk_groups(p, c) * p.Hkv * s + cus - 1) / cus;
+    return rounds * (kFixedUs + each * (layer_us<RS>() + c * kUsPerKey));
+  };
   const int max_chunk = longest_chunk<RS, KS>();
-  double best_cost = 1e30;
+  double best_cost = cost(chunk, shares, (n_layers + shares - 1) / shares);
+  best_cost = first_sweep ? best_cost - kFoundUs : best_cost * 0.97;
+  bool changed = false;
   for (int c = 256; c <= max_chunk; c += 256) {
-    const long long groups = (long long)chunk_groups(p, c) * p.Hkv;
     for (int each = n_layers, s = 1; each >= 1; ) {
-      const long long rounds = (groups * s + cus - 1) / cus;
-      const double cost = rounds * (kFixedUs + each * (kLayerUs + c * kUsPerKey));
-      // (more do not fit the kernels' argument)
-      if (each * s <= DKV_MAX_SELECT_LAYERS && cost < best_cost * (1.0 - 1e-9)) { best_cost = cost; chunk = c; shares = s; }
+      // (more places do not fit the kernels' argument)
+      if (each * s <= DKV_MAX_SELECT_LAYERS && cost(c, s, each) < best_cost * (1.0 - 1e-9)) {
+        best_cost = cost(c, s, each);
+        chunk = c;
+        shares = s;
+        changed = true;
+      }
       if (each == 1) break;
       s = (n_layers + each - 2) / (each - 1);                  // the fewest shares of fewer layers each
       each = (n_layers + s - 1) / s;
     }
   }
+  return changed;
 }
 
 void launch_import_lse(const Params& p, int n_layers, const float* const* lse_layers, float* lse_rows, hipStream_t st) {
@@ -1082,11 +1098,8 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   using TL = Tile<RS, KS>;
   const int cus = device_cus(), chunk = pick_chunk<RS, KS>(p, cus), grid_x = chunk_groups(p, chunk);
   const int shares = pick_shares(grid_x * p.Hkv, n_layers, chunk, cus), layers_each = (n_layers + shares - 1) / shares;
-  int emit_chunk = chunk, emit_shares = 1;
-  const bool in_l2 = lse_layers == nullptr && (int64_t)n_layers * p.Hkv * p.total_tokens * 256 <= kL2Bytes;
-  const bool same_cut = n_layers == 1 || p.n_seqs > 1 || in_l2;
-  if (same_cut) emit_shares = shares;
-  else pick_emit_cut<RS, KS>(p, n_layers, cus, emit_chunk, emit_shares);
+  int emit_chunk = chunk, emit_shares = shares;
+  const bool same_cut = !pick_emit_cut<RS, KS>(p, LAYERS == 1 ? 1 : n_layers, lse_layers == nullptr, cus, emit_chunk, emit_shares);
   const int emit_grid_x = chunk_groups(p, emit_chunk), emit_each = (n_layers + emit_shares - 1) / emit_shares;
   float* partials = ws ? reinterpret_cast<float*>(ws + wl.partials) : nullptr;   // no workspace: lse supplied
   const int64_t partials_stride_layer = (int64_t)wl.partials_layer_bytes / (int64_t)sizeof(float);
