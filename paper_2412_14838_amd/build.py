@@ -20,11 +20,14 @@ BINDING = os.path.join(HERE, "_binding.so")
 # packed fp32 VALU forms are switched off for all device code
 HIPCC_FLAGS = ["-O3", "-fno-honor-nans", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
                "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
+# kernels of more than 256 registers: results of matrix instructions in vector registers, where the exponentials read them
+# (by default they would go to accumulation registers and be copied from there, 16 instructions a unit of 8 products)
+SOURCE_FLAGS = {"score_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
-    cmd = ["hipcc", *HIPCC_FLAGS, "-c", src, "-o", obj]
+    cmd = ["hipcc", *HIPCC_FLAGS, *SOURCE_FLAGS.get(os.path.basename(src), []), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))

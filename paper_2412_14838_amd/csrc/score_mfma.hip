@@ -11,7 +11,7 @@
 //                 small kernel of its own when a call covers several layers;
 //   emit kernel:  S_tile = Q . K_tile^T (rows as M, keys as N: a lane holds ONE key and 16 rows, so the sum over
 //                 the rows is an in-lane reduction), p = exp2(S * c - lse2[row]), window/group sum, max-pool,
-//                 write. Here for more than 128 rows and for short chunks; score_waves.h has the other one.
+//                 write. Here for 65 to 128 rows in short chunks; score_waves.h has the one for all else.
 // Both use v_mfma_f32_32x32x16_bf16 with the whole Q block of the wavefront resident in registers and K tiles
 // staged through LDS (coalesced 16-byte global loads, padded rows, 16-byte LDS reads in MFMA operand layout).
 // The MFMAs of one tile are issued in the same step as the exponentials of the tile before it (two accumulator
@@ -595,6 +595,20 @@ __device__ inline void merge_chunks(const float2* __restrict__ psrc, int n_full,
   mstage[mgrp * kRows + mrow] = make_float2(M, Lsum);
 }
 
+// merge_chunks<4, 2> by 256 threads: both groups of a row by one thread, side by side, the same bits.
+__device__ inline void merge_chunks_both(const float2* __restrict__ psrc, int n_full, uint32_t chunk_step, float2* __restrict__ mstage) {
+  const uint32_t t0 = threadIdx.x;
+  float M[2] = {-INFINITY, -INFINITY}, Lsum[2] = {0.0f, 0.0f};
+#pragma unroll 4
+  for (int cc = 0; cc + 1 < n_full; cc += 2, psrc += 2 * chunk_step) {
+    merge_pair(M[0], Lsum[0], psrc[t0]);
+    merge_pair(M[1], Lsum[1], psrc[t0 + chunk_step]);
+  }
+  if (n_full & 1) merge_pair(M[0], Lsum[0], psrc[t0]);
+  mstage[t0] = make_float2(M[0], Lsum[0]);
+  mstage[256 + t0] = make_float2(M[1], Lsum[1]);
+}
+
 // lse2 of row `row` (< RS * 64) from the KS staged merges; padding rows get +inf: exp2(x - inf) = 0
 template <int RS, int KS>
 __device__ inline float combine_groups(const float2* __restrict__ mstage, int row, int rows) {
@@ -988,7 +1002,7 @@ template <int RS, int KS>
 static int longest_chunk() {
   using TL = Tile<RS, KS>;
   int max_chunk = kMaxChunk;                                 // which score_emit_waves always has the LDS for
-  if constexpr (RS > 1) {
+  if constexpr (RS == 2) {
     const long long lds_fixed = 2LL * TL::kTileBytes + QStage<RS, KS>::kBytes;
     max_chunk = (int)((kLdsBudget - lds_fixed) / (emit_slabs<RS>() * (long long)sizeof(float))) - kMaxHalo - 2 * TL::kKeys;
     max_chunk = max_chunk / TL::kKeys * TL::kKeys;
@@ -1108,28 +1122,42 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
   // The kernel that writes the scores: score_waves.h has the rule.
   void (*emit_kernel)(Params, int, int, int, ScoreLayers<LAYERS>, int64_t, int64_t, const int32_t*, const float*, const float*, int64_t,
                       const float*, float*, int64_t, int64_t, float*, int64_t) = nullptr;
-  int emit_threads = TL::kThreads;
+  int emit_threads = 0;
   size_t lds_emit = 0;
-  const void *emit_a = nullptr, *emit_b = nullptr;          // those this call's number of rows may take
-  if constexpr (RS > 1) {
-    emit_kernel = &score_emit_mfma<RS, KS, LAYERS>;
-    emit_a = emit_b = reinterpret_cast<const void*>(emit_kernel);
-    lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(emit_chunk) * sizeof(float) +
-               (size_t)QStage<RS, KS>::kBytes;              // the Q staging area serves the next layer in every variant
-  }
-  if constexpr (RS <= 2) {
-    emit_b = reinterpret_cast<const void*>(&score_emit_waves<2 * RS, LAYERS>);
-    if (RS == 1) emit_a = emit_b;
-    static_assert(wv_lds_emit<2 * RS>(kMaxChunk) <= kLdsBudget && kWvThreads % wv_rows(2 * RS) == 0, "");
-    if (RS == 1 || emit_chunk >= kWvMinChunk) {
-      emit_kernel = &score_emit_waves<2 * RS, LAYERS>;
-      emit_threads = kWvThreads;
-      lds_emit = wv_lds_emit<2 * RS>(emit_chunk);
-    }
-  }
+  auto waves = [&](auto nrt_c) {
+    constexpr int NRT = decltype(nrt_c)::value;
+    static_assert(wv_lds_emit<NRT>(kMaxChunk) <= kLdsBudget, "");
+    emit_kernel = &score_emit_waves<NRT, LAYERS>;
+    emit_threads = wv_threads(NRT);
+    lds_emit = wv_lds_emit<NRT>(emit_chunk);
+  };
   static std::atomic<uint64_t> given{0};
-  const hipError_t e = allow_lds(given, {{reinterpret_cast<const void*>(&score_stats_mfma<RS, KS, LAYERS>), (int)lds_stats},
-                                         {emit_a, kLdsBudget}, {emit_b, kLdsBudget}});
+  const void* stats_kernel = reinterpret_cast<const void*>(&score_stats_mfma<RS, KS, LAYERS>);
+  hipError_t e;
+  if constexpr (RS == 1) {
+    waves(std::integral_constant<int, 2>{});
+    e = allow_lds(given, {{stats_kernel, (int)lds_stats}, {reinterpret_cast<const void*>(emit_kernel), kLdsBudget}});
+  } else if constexpr (RS == 2) {
+    waves(std::integral_constant<int, 4>{});
+    e = allow_lds(given, {{stats_kernel, (int)lds_stats}, {reinterpret_cast<const void*>(emit_kernel), kLdsBudget},
+                          {reinterpret_cast<const void*>(&score_emit_mfma<RS, KS, LAYERS>), kLdsBudget}});
+    if (emit_chunk < kWvMinChunk) {
+      emit_kernel = &score_emit_mfma<RS, KS, LAYERS>;
+      emit_threads = TL::kThreads;
+      lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(emit_chunk) * sizeof(float) +
+                 (size_t)QStage<RS, KS>::kBytes;             // the Q staging area serves the next layer in every variant
+    }
+  } else {
+    if (p.rows <= 160) waves(std::integral_constant<int, 5>{});
+    else if (p.rows <= 192) waves(std::integral_constant<int, 6>{});
+    else if (p.rows <= 224) waves(std::integral_constant<int, 7>{});
+    else waves(std::integral_constant<int, 8>{});
+    e = allow_lds(given, {{stats_kernel, (int)lds_stats},
+                          {reinterpret_cast<const void*>(&score_emit_waves<5, LAYERS>), kLdsBudget},
+                          {reinterpret_cast<const void*>(&score_emit_waves<6, LAYERS>), kLdsBudget},
+                          {reinterpret_cast<const void*>(&score_emit_waves<7, LAYERS>), kLdsBudget},
+                          {reinterpret_cast<const void*>(&score_emit_waves<8, LAYERS>), kLdsBudget}});
+  }
   if (e != hipSuccess) return e;
   ScoreLayers<LAYERS> src{};
   for (int i = 0; i < n_layers && (phases & (kPhaseStats | kPhaseEmit)); ++i) {

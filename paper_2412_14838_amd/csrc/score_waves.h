@@ -1,12 +1,13 @@
-// The second scoring sweep for up to 128 score rows (G * ws) per KV head: bf16, head size 128. Included by score_mfma.hip,
+// The second scoring sweep: bf16, head size 128, up to 256 score rows (G * ws) per KV head. Included by score_mfma.hip,
 // whose helpers (chunks, merges, layers of a launch) it uses; the mathematics of the two sweeps is described there.
 //
 // A wavefront owns tiles of 32 keys and multiplies them with ALL score rows, whose Q block stays in its registers (128
-// rows: 128 of 256). Its keys go from global memory straight into its own piece of LDS (global_load_lds, 16 bytes a lane)
+// rows: 128 of 256; more: 32 for every 32 rows, accumulation registers, which matrix instructions read as an operand and nothing
+// else needs, so that a SIMD holds one wavefront of 512). Its keys go from global memory straight into its own piece of LDS (global_load_lds, 16 bytes a lane)
 // and from there into registers in MFMA operand layout; no other wavefront touches them, so the wavefronts of a workgroup
-// need no barrier between the tiles, only three per layer. A ring of three half tiles (32 keys x 64 of the head's
-// dimensions, 4 KB) per wavefront is in flight. The eight wavefronts take neighbouring tiles, 64 KB of consecutive keys per
-// round. A row of a half tile is 128 bytes, one cache line; its 16-byte pieces lie in LDS with bits 1 to 3 of the row
+// need no barrier between the tiles, only three per layer. A ring of three (four) half tiles (32 keys x 64 of the head's
+// dimensions, 4 KB) per wavefront is in flight. The eight (four) wavefronts take neighbouring tiles, 64 (32) KB of consecutive keys
+// per round. A row of a half tile is 128 bytes, one cache line; its 16-byte pieces lie in LDS with bits 1 to 3 of the row
 // folded into their place, which makes the reads (32 rows, the same piece) free of bank conflicts; the loads fold the
 // same bits into the address they read from.
 // A unit of work is 32 keys x 32 rows: its 8 MFMAs go out among the exponentials of the unit before it (two accumulators),
@@ -31,27 +32,50 @@
 // 39.4 / 34.5; 16 prompts of 45 K, 896 of 1024, 35.2 / 33.4 and 101 / 92. Up to 64 rows it is taken always, also at one tile to a
 // wavefront (chunks of 256 keys): 64 rows, one layer of 300 keys 7.8 / 6.2, 8192 keys 8.6 / 6.8, eight layers in one call 31.2 / 27.1;
 // 64 prompts of 300 keys, eight layers 88 / 72; 8 rows, 200 prompts of 400 keys, one layer 121 / 95.
+// 129 to 256 rows: nobody else is on the SIMD, and whatever the wavefront waits for shows: its matrix instructions and exponentials
+// alone take 366 cycles a unit (203 ns at the 1.8 GHz the chip holds under them), the kernel 630 (257 cycles of MFMAs, 277 of
+// vector instructions). A branch around the LDS reads of the next tile made the waits behind it, for reads of a unit ago, wait for those
+// too: 7 % of the time. One row tile more costs what it is, not as 64 rows more for everybody. Against score_emit_mfma, us, before / after,
+// with the cut of the keys that both could take: 28 layers of 4 heads x 32768 keys, 224 rows 307 / 274; 16 of 2 heads x 20000, 160 rows
+// 57 / 46; 32 of 8 heads x 8192, 256 rows 199 / 178; 8 of 4 heads x 4097, 192 rows 28 / 25; one layer, both sweeps: 4 heads x 300 keys, 224
+// rows 20.1 / 18.6, 32768 30.6 / 30.2. Its normalisers kept in registers and one load of a tile at a time were tried: the former spills, the
+// latter costs more instructions than it hides (329 us for 310 with four in a row).
 // The first sweep done the same way was not better at 128 rows (32 layers of 32768 keys 417 / 419, one layer of 8192 9.6 / 10.1),
 // and its sums come out in another order.
 #pragma once
 
 namespace dkv {
 
-constexpr int kWvWaves = 8, kWvThreads = 64 * kWvWaves;
-constexpr int kWvRing = 3, kWvHalfBytes = 4096;                    // half tiles in flight per wavefront
+constexpr int kWvHalfBytes = 4096;
 constexpr int kWvMinChunk = 1024;
-constexpr int kWvRingBytes = kWvWaves * kWvRing * kWvHalfBytes;
+constexpr int wv_waves(int nrt) { return nrt > 4 ? 4 : 8; }
+constexpr int wv_threads(int nrt) { return 64 * wv_waves(nrt); }
+constexpr int wv_ring(int nrt) { return nrt > 4 ? 4 : 3; }         // half tiles in flight per wavefront
+constexpr int wv_ring_bytes(int nrt) { return wv_waves(nrt) * wv_ring(nrt) * kWvHalfBytes; }
+// Shape of the merge of chunk partials: row slabs of 64, groups of chunks; keys per round of the wavefronts (the unit of chunks).
+constexpr int wv_slabs(int nrt) { return nrt > 4 ? 4 : nrt / 2; }
+constexpr int wv_groups(int nrt) { return nrt > 4 ? 2 : 4; }
 
-// Row tiles of 32 for a call (2 or 4: an even number keeps the accumulators' roles fixed).
+// Row tiles of 32 for a call (2, 4 or 5 to 8).
 __host__ __device__ constexpr int wv_rows(int nrt) { return nrt * 32; }
-constexpr int kWvMergeBytes = kWvThreads * (int)sizeof(float2);    // at most; merges of chunk partials share the place of the column sums
+__host__ __device__ constexpr int wv_lse_rows(int nrt) { return (nrt + 1) / 2 * 64; }   // whole wavefronts load them
+constexpr int kWvMergeBytes = 512 * (int)sizeof(float2);           // at most; merges of chunk partials share the place of the column sums
 __host__ __device__ constexpr int wv_sums_bytes(int chunk) {          // column sums of a chunk: its outputs, the pooling halo, the last tile's rest
   const int b = (chunk + kMaxHalo + 32) * (int)sizeof(float);
   return b > kWvMergeBytes ? b : kWvMergeBytes;
 }
 template <int NRT> constexpr size_t wv_lds_emit(int chunk) {
-  return kWvRingBytes + wv_rows(NRT) * 256 + 2 * wv_rows(NRT) * sizeof(float) + wv_sums_bytes(chunk);
+  return wv_ring_bytes(NRT) + wv_rows(NRT) * 256 + 2 * wv_lse_rows(NRT) * sizeof(float) + wv_sums_bytes(chunk);
 }
+template <int NRT> constexpr size_t wv_lds_stats() {
+  return wv_ring_bytes(NRT) + wv_rows(NRT) * 256 + 2 * wv_waves(NRT) * wv_rows(NRT) * sizeof(float2);
+}
+
+// f(0), f(1) .. f(N - 1) with the index as a constant.
+template <typename F, int... I>
+__device__ inline void unrolled(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ inline void unrolled(F&& f) { unrolled(f, std::make_integer_sequence<int, N>{}); }
 
 __device__ inline uint32_t lds_address(const void* p) {
   return (uint32_t)(size_t)(__attribute__((address_space(3))) const char*)p;
@@ -90,14 +114,16 @@ __device__ inline void load_lds16x4(uint32_t lds, uint32_t off0, uint32_t off1, 
 }
 // Waits until at most `n` half tiles (of four loads each) asked for last are still in flight. n is uniform.
 __device__ inline void wait_newer(int n) {
-  if (n >= 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+  if (n >= 4) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+  else if (n == 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
   else if (n == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
   else if (n == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The keys of one wavefront as a stream of half tiles: of the tiles wave, wave + 8, ... of the chunk from the last to the first,
-// layer after layer. issue() asks for the next half, take() brings the oldest one into the operand registers.
+// The keys of one wavefront as a stream of half tiles: of the tiles wave, wave + WAVES, ... of the chunk, first to last (FORWARD) or
+// last to first, layer after layer. issue() asks for the next half, take() brings the oldest one into the operand registers.
+template <int WAVES, int RING, bool FORWARD>
 struct WaveKeys {
   char* lds;                        // of the workgroup
   uint32_t ring;                    // this wavefront's part of it
@@ -116,13 +142,13 @@ struct WaveKeys {
     const int lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     lds = smem;
-    ring = (uint32_t)(wave * (kWvRing * kWvHalfBytes));
+    ring = (uint32_t)(wave * (RING * kWvHalfBytes));
     k_layers = src.k;
     k_off = chunk_off;
     stride_b = stride;
     len = chunk_len;
     const int tiles = (len + 31) >> 5;
-    my_tiles = tiles > wave ? (tiles - wave + kWvWaves - 1) / kWvWaves : 0;
+    my_tiles = tiles > wave ? (tiles - wave + WAVES - 1) / WAVES : 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) off[i] = (uint32_t)(8 * i + (lane >> 3)) * stride_b + piece_off(lane, i);
     layer = first_layer;
@@ -140,9 +166,16 @@ struct WaveKeys {
   // The piece that lands in place lane % 8 of row 8 i + lane / 8.
   static __device__ uint32_t piece_off(int lane, int i) { return (uint32_t)((lane & 7) ^ ((lane >> 4) + 4 * (i & 1))) * 16u; }
   __device__ int first_key(int t) const {            // of the wavefront's t-th tile, relative to the chunk
-    return ((my_tiles - 1 - t) * kWvWaves + wave) * 32;
+    return ((FORWARD ? t : my_tiles - 1 - t) * WAVES + wave) * 32;
   }
-  // The next half: halves 0 and 1 in turns (the first three calls 0, 1, 0; then as refill() has them).
+  // The first halves: as many as the ring holds.
+  __device__ void fill() {
+    issue<0>();
+    issue<1>();
+    issue<0>();
+    if (RING == 4) issue<1>();
+  }
+  // The next half: halves 0 and 1 in turns.
   template <int H>
   __device__ void issue() {
     if (__builtin_expect(issued >= total, 0)) return;
@@ -161,10 +194,15 @@ struct WaveKeys {
       load_lds16x4(place, last[0], last[1], last[2], last[3], k_layer + H * 128);
     }
     ++issued;
-    issue_slot = issue_slot == (kWvRing - 1) * kWvHalfBytes ? 0 : issue_slot + kWvHalfBytes;
+    issue_slot = issue_slot == (RING - 1) * kWvHalfBytes ? 0 : issue_slot + kWvHalfBytes;
     if (H == 1) {
-      row0 -= 32 * kWvWaves;
-      k_ptr -= (uint64_t)(256u * stride_b);
+      if (FORWARD) {
+        row0 += 32 * WAVES;
+        k_ptr += (uint64_t)(32u * WAVES * stride_b);
+      } else {
+        row0 -= 32 * WAVES;
+        k_ptr -= (uint64_t)(32u * WAVES * stride_b);
+      }
       if (__builtin_expect(--tiles_left == 0, 0)) {      // the wavefront's last tile of a layer
         tiles_left = my_tiles;
         ++layer;
@@ -178,11 +216,13 @@ struct WaveKeys {
   }
   template <int H>
   __device__ void take(bf16x8 (&kf)[8]) {
-    if (__builtin_expect(taken >= total, 0)) return;
+    // (A wavefront alone on its SIMD reads on past the end: a branch around these reads would have every wait behind it be for them.)
+    if (RING != 4 && __builtin_expect(taken >= total, 0)) return;
     if (H == 1) spare = 1;
-    const int newer = issued - taken - 1;            // in the middle of the stream: 2, then 1
-    if (__builtin_expect(newer == 2 - H, 1)) {
-      if (H == 0) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    const int newer = issued - taken - 1;            // in the middle of the stream: RING - 1, then RING - 2
+    if (__builtin_expect(newer == RING - 1 - H, 1)) {
+      if (RING - 1 - H == 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+      else if (RING - 1 - H == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     } else {
       wait_newer(newer);
@@ -191,9 +231,9 @@ struct WaveKeys {
 #pragma unroll
     for (int j = 0; j < 4; ++j) kf[4 * H + j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(lds + (at + read_off[j])));
     ++taken;
-    take_slot = take_slot == (kWvRing - 1) * kWvHalfBytes ? 0 : take_slot + kWvHalfBytes;
+    take_slot = take_slot == (RING - 1) * kWvHalfBytes ? 0 : take_slot + kWvHalfBytes;
   }
-  // issue() once the reads of half H have arrived: its place is the one the next half, an other one, goes to. (That of half 1 is given away
+  // issue() once the reads of half H have arrived: its place is the one the next half goes to. (That of half 1 is given away
   // under the exponentials that follow, in the next tile or at the end of the layer, whichever comes first.)
   template <int H>
   __device__ void refill(const bf16x8 (&kf)[8]) {
@@ -202,7 +242,7 @@ struct WaveKeys {
       spare = 0;
     }
     asm volatile("" ::"v"(kf[4 * H]), "v"(kf[4 * H + 1]), "v"(kf[4 * H + 2]), "v"(kf[4 * H + 3]) : "memory");
-    issue<1 - H>();
+    issue<(H + RING) & 1>();
   }
 };
 
@@ -213,16 +253,17 @@ __device__ inline void take_turns(int mine) {
   else __builtin_amdgcn_s_setprio(0);
 }
 
-// The Q block of a (sequence, head): kRows rows of 256 bytes in LDS, each wavefront fetches NRT * 4 of them (rows past p.rows
+// The Q block of a (sequence, head): kRows rows of 256 bytes in LDS, the wavefronts fetch equal shares of them (rows past p.rows
 // repeat the last one: their statistics are never used, and their normalisers are +inf).
 template <int NRT>
 __device__ inline void load_q_block(char* qbuf, const char* q_head, int rows, int wave) {
+  constexpr int kLoads = NRT * 8 / wv_waves(NRT);
   const int lane = lane_again();
 #pragma unroll
-  for (int i = 0; i < NRT; ++i) {
-    const int row = wave * (NRT * 4) + 4 * i + (lane >> 4);
+  for (int i = 0; i < kLoads; ++i) {
+    const int row = wave * (kLoads * 4) + 4 * i + (lane >> 4);
     const int src_row = row < rows ? row : rows - 1;
-    load_lds16(lds_address(qbuf) + (uint32_t)(wave * (NRT * 4) + 4 * i) * 256u,
+    load_lds16(lds_address(qbuf) + (uint32_t)(wave * (kLoads * 4) + 4 * i) * 256u,
                (uint32_t)src_row * 256u + (uint32_t)((lane & 15) ^ (row & 15)) * 16u, q_head);
   }
 }
@@ -244,6 +285,15 @@ __device__ inline void read_q_tile(const char* qbuf, const QPlaces& q, int t, bf
   }
 }
 
+// More than four row tiles: Q's registers are accumulation registers, which nothing but the matrix instructions reads. Left to
+// itself the compiler shares them out between both kinds and copies.
+template <int NRT>
+__device__ inline void keep_q_in(bf16x8 (&qf)[8]) {
+  if constexpr (NRT > 4)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) asm volatile("" : "+a"(qf[j]));
+}
+
 // The lower half-wavefront's value ([0]) and the upper half's ([1]), in every lane.
 __device__ inline float2 both_halves(float v) {
   const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -252,20 +302,20 @@ __device__ inline float2 both_halves(float v) {
 
 // Scores, see score_emit_mfma (same arguments). The column sums of a chunk lie in LDS until its layer is done.
 template <int NRT, int LAYERS>
-__global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chunk, int n_layers, int layers_each, ScoreLayers<LAYERS> src,
+__global__ __launch_bounds__(wv_threads(NRT)) void score_emit_waves(Params p, int chunk, int n_layers, int layers_each, ScoreLayers<LAYERS> src,
                                                                int64_t stride_token_b, int64_t stride_head_b,
                                                                const int32_t* __restrict__ cu, const float* __restrict__ partials,
                                                                const float* __restrict__ lse_rows, int64_t lse_rows_stride_layer,
                                                                const float* __restrict__ lse_in, float* __restrict__ scores,
                                                                int64_t scores_stride_head, int64_t scores_stride_layer,
                                                                float* __restrict__ edges, int64_t edges_stride_layer) {
-  constexpr int kRows = wv_rows(NRT), RS = NRT / 2, KS = 4;                  // shape of the merge of chunk partials
+  constexpr int kRows = wv_rows(NRT), kLse = wv_lse_rows(NRT), kWvThreads = wv_threads(NRT), RS = wv_slabs(NRT), KS = wv_groups(NRT);
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char* qbuf = smem + kWvRingBytes;
-  float* lse_s = reinterpret_cast<float*>(qbuf + kRows * 256);           // [2][kRows] lse2 per row, by layer parity
-  float* sums = lse_s + 2 * kRows;                                      // column sums by key of the chunk
+  char* qbuf = smem + wv_ring_bytes(NRT);
+  float* lse_s = reinterpret_cast<float*>(qbuf + kRows * 256);           // [2][kLse] lse2 per row, by layer parity
+  float* sums = lse_s + 2 * kLse;                                      // column sums by key of the chunk
 
-  chunk = fitted_chunk(cu, p.n_seqs, chunk, Tile<NRT / 2, 4>::kKeys, gridDim.x);       // not longer than the host's: the LDS fits
+  chunk = fitted_chunk(cu, p.n_seqs, chunk, Tile<RS, KS>::kKeys, gridDim.x);       // not longer than the host's: the LDS fits
   const int half = p.half;
   int seq, c, nc, begin, S, first_full, n_full;
   if (!find_chunk2(cu, p.n_seqs, p.total_tokens, chunk, p.w, blockIdx.x, seq, c, nc, begin, S, first_full, n_full)) return;
@@ -289,16 +339,14 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
   const float* __restrict__ lse_seq = lse_rows + ((int64_t)seq * p.Hkv + head) * p.rows_pad;     // (multi-layer launches)
 
   // Tiles from the last to the first: what the statistics kernel, first to last, left in the caches
-  WaveKeys keys;
+  WaveKeys<wv_waves(NRT), wv_ring(NRT), false> keys;
   keys.start(smem, src, ((int64_t)begin + kbeg) * stride_token_b + (int64_t)head * stride_head_b, (uint32_t)stride_token_b, len,
              first_layer, n_layers);
   load_q_block<NRT>(qbuf, reinterpret_cast<const char*>(src.q[first_layer]) + q_off, p.rows, keys.wave);
   int at_q = 0;
-  keys.issue<0>();
-  keys.issue<1>();
-  keys.issue<0>();
+  keys.fill();
   // ---- lse2[row] of the first layer; padding rows get +inf: exp2(x - inf) = 0
-  float* __restrict__ lse_first = lse_s + (first_layer & 1) * kRows;
+  float* __restrict__ lse_first = lse_s + (first_layer & 1) * kLse;
   if (lse_rows != nullptr) {
     if (tid < kRows) lse_first[tid] = lse_seq[first_layer * lse_rows_stride_layer + tid];
   } else if (lse_in != nullptr) {
@@ -306,16 +354,19 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
       lse_first[tid] = tid < p.rows ? lse_in[((int64_t)seq * p.Hq + (int64_t)head * p.G) * p.w + tid] * kLog2e : INFINITY;
   } else {
     float2* mstage = reinterpret_cast<float2*>(sums);
-    if (tid < KS * kRows)
-      merge_chunks<RS, KS>(reinterpret_cast<const float2*>(partials) + ((int64_t)first_full * p.Hkv + head) * p.rows_pad, n_full,
-                           (uint32_t)(p.Hkv * p.rows_pad), mstage);
+    const float2* psrc = reinterpret_cast<const float2*>(partials) + ((int64_t)first_full * p.Hkv + head) * p.rows_pad;
+    if constexpr (NRT <= 4) {
+      if (tid < KS * RS * 64) merge_chunks<RS, KS>(psrc, n_full, (uint32_t)(p.Hkv * p.rows_pad), mstage);
+    } else {
+      merge_chunks_both(psrc, n_full, (uint32_t)(p.Hkv * p.rows_pad), mstage);
+    }
     lds_barrier();
     if (tid < kRows) lse_first[tid] = combine_groups<RS, KS>(mstage, tid, p.rows);
   }
-  // the normalisers of the next layer (the first kRows / 64 wavefronts) and its Q block
+  // the normalisers of the next layer (the first kLse / 64 wavefronts) and its Q block
   auto load_next = [&](int layer) {
-    if (keys.wave < kRows / 64)
-      load_lds4(lds_address(lse_s + (layer & 1) * kRows + keys.wave * 64), (uint32_t)lane_again() * 4u,
+    if (keys.wave < kLse / 64)
+      load_lds4(lds_address(lse_s + (layer & 1) * kLse + keys.wave * 64), (uint32_t)lane_again() * 4u,
                 reinterpret_cast<const char*>(lse_seq + layer * lse_rows_stride_layer + keys.wave * 64));
     load_q_block<NRT>(qbuf, reinterpret_cast<const char*>(src.q[layer]) + q_off, p.rows, keys.wave);
     at_q = keys.issued;
@@ -328,30 +379,33 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
   for (int t = 0; t < NRT; ++t) read_q_tile(qbuf, q_places, t, qf[t]);
 #pragma unroll
   for (int j = 0; j < 8; ++j) kf[j] = qf[0][j];
-  keys.take<0>(kf);
-  keys.take<1>(kf);
+  keys.template take<0>(kf);
+  keys.template take<1>(kf);
   if (first_layer + 1 < n_layers) {
     lds_barrier();                                                       // every wavefront has its Q: the block's place is free
     load_next(first_layer + 1);
   }
-  keys.refill<0>(kf);
+  keys.template refill<0>(kf);
 
-  floatx16 acc[2];
+  constexpr int kAccs = NRT % 2 == 0 ? 2 : 3;                            // an odd number's last one has an accumulator of its own
+  floatx16 acc[kAccs];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[1][e] = 0.0f;
+  for (int e = 0; e < 16; ++e) acc[kAccs - 1][e] = 0.0f;
   float4 lz[4] = {};                                                     // normalisers of a unit's rows, read from LDS a unit ahead
   int row0 = -1;                                                         // first key of the tile whose exponentials are taken; none yet
   const float* __restrict__ lse_cur = nullptr;                           // of the layer: + 32 * (row tile) + 8 * (e / 4) + e % 4
-  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, slab = 0.0f;         // slab: of the first 64 rows
+  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, slab = 0.0f;         // slab: of the rows before
   auto unit = [&](auto rt_c, auto mul_c) {
     constexpr int RT = decltype(rt_c)::value, PT = (RT + NRT - 1) % NRT;
     constexpr bool MUL = decltype(mul_c)::value;
-    floatx16& cur = acc[RT & 1];
-    floatx16& a = acc[(RT & 1) ^ 1];
+    constexpr int kCur = RT == NRT - 1 ? kAccs - 1 : RT & 1, kPrev = PT == NRT - 1 ? kAccs - 1 : PT & 1;
+    floatx16& cur = acc[kCur];
+    floatx16& a = acc[kPrev];
+    if (MUL) keep_q_in<NRT>(qf[RT]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       __builtin_amdgcn_sched_barrier(0);
-      if (RT == 0 && j == 2) keys.refill<1>(kf);
+      if (RT == 0 && j == (NRT > 4 ? 6 : 2)) keys.template refill<1>(kf);
       if (MUL) {
         if (j == 0) {
           floatx16 zero;
@@ -370,23 +424,21 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
         s3 += fast_exp2(fmaf(a[2 * j + 1], cexp, -lz[j >> 1].w));
         lz[j >> 1] = *reinterpret_cast<const float4*>(lse_cur + RT * 32 + 8 * (j >> 1));     // of the next unit
       }
-      if (MUL && RT == NRT - 1 && j == 4) keys.take<0>(kf);
+      if (MUL && RT == NRT - 1 && j == 4) keys.template take<0>(kf);
       asm volatile("" : "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3));       // an anchor: without it the exponentials sink below all MFMAs
     }
     __builtin_amdgcn_sched_barrier(0);
     if (MUL && RT == NRT - 1) {
-      keys.take<1>(kf);
-      keys.refill<0>(kf);
+      keys.template take<1>(kf);
+      keys.template refill<0>(kf);
     }
-    if (PT & 1) {                                                      // 64 rows, summed up as score_emit_mfma does: the same bits
+    if ((PT & 1) || PT == NRT - 1) {                                   // 64 rows, summed up as score_emit_mfma does: the same bits
       const float2 x = both_halves((s0 + s1) + (s2 + s3));
       s0 = s1 = s2 = s3 = 0.0f;
+      slab = PT <= 1 ? x.x + x.y : slab + (x.x + x.y);
       if (PT == NRT - 1) {                                             // the tile's last rows: its column sums are complete
-        const float sum = NRT == 2 ? x.x + x.y : slab + (x.x + x.y);
         const int lane = lane_again();
-        if (row0 >= 0 && lane < 32) sums[row0 + lane] = row0 + lane < len ? sum * p.row_scale : -INFINITY;
-      } else {
-        slab = x.x + x.y;
+        if (row0 >= 0 && lane < 32) sums[row0 + lane] = row0 + lane < len ? slab * p.row_scale : -INFINITY;
       }
     }
   };
@@ -423,9 +475,9 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
     if (c == nc - 1 && tid < p.w) out[prefix + tid] = -INFINITY;         // guard over the window slots (w <= 256 <= threads)
   };
   for (int li = first_layer; li < n_layers; ++li) {
-    lse_cur = lse_s + (li & 1) * kRows + 4 * (lane_again() >> 5);
+    lse_cur = lse_s + (li & 1) * kLse + 4 * (lane_again() >> 5);
     for (int k = 0; k < keys.my_tiles || k == 0; ++k) {
-      take_turns(keys.wave >> 2);
+      if (NRT <= 4) take_turns(keys.wave >> 2);
       if (keys.my_tiles > 0) unit(std::integral_constant<int, 0>{}, std::true_type{});
       if (k == 0 && li > first_layer) {
         pool_layer(li - 1);
@@ -439,16 +491,12 @@ __global__ __launch_bounds__(kWvThreads) void score_emit_waves(Params p, int chu
         read_q_tile(qbuf, q_places, 0, qf[0]);
       }
       if (keys.my_tiles == 0) break;
-      if constexpr (NRT == 2) take_turns((keys.wave >> 2) ^ 1);
-      unit(std::integral_constant<int, 1>{}, std::true_type{});
-      if (turn_q) read_q_tile(qbuf, q_places, 1, qf[1]);
-      if constexpr (NRT == 4) {
-        take_turns((keys.wave >> 2) ^ 1);
-        unit(std::integral_constant<int, 2>{}, std::true_type{});
-        if (turn_q) read_q_tile(qbuf, q_places, 2, qf[2]);
-        unit(std::integral_constant<int, 3>{}, std::true_type{});
-        if (turn_q) read_q_tile(qbuf, q_places, 3, qf[3]);
-      }
+      unrolled<NRT - 1>([&](auto i) {
+        constexpr int RT = decltype(i)::value + 1;
+        if (NRT <= 4 && RT == NRT / 2) take_turns((keys.wave >> 2) ^ 1);
+        unit(std::integral_constant<int, RT>{}, std::true_type{});
+        if (turn_q) read_q_tile(qbuf, q_places, RT, qf[RT]);
+      });
     }
   }
   if (keys.my_tiles > 0) unit(std::integral_constant<int, 0>{}, std::false_type{});

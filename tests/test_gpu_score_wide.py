@@ -1,0 +1,38 @@
+"""Scores of 129 to 256 rows per KV head: every number of row tiles, partly filled ones, ends of tiles, chunks and rounds of wavefronts,
+wavefronts without keys, layers that follow each other in one call, batches. Against float64, with the bound of test_gpu_score_waves."""
+import pytest
+import torch
+
+from paper_2412_14838_amd.pipeline import Compressor
+from test_gpu_score_waves import _cfg, _check, _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq,Hkv,w", [(3, 1, 43), (10, 2, 32), (6, 1, 31), (14, 2, 32), (7, 1, 29), (9, 1, 25), (8, 1, 32), (8, 2, 64)])
+@pytest.mark.parametrize("seqlens", [(257,), (97, 290), (300, 66, 700, 65), (2100,), (4705,)])
+def test_rows_and_edges(Hq, Hkv, w, seqlens):
+    cfg = _cfg(Hq, Hkv, w, seqlens, L=3)
+    one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
+    layers = _inputs(cfg)
+    for l, (q, k) in enumerate(layers):
+        one.score(l, q, k)
+    many.score_layers(0, [x[0] for x in layers], [x[1] for x in layers])
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+    for l in (0, 2):
+        _check(cfg, many.scores[l], *layers[l])
+
+
+@pytest.mark.parametrize("Hq,Hkv,w,seqlens,L", [(28, 4, 32, (32768,), 3), (40, 8, 32, (16001,), 5), (16, 2, 32, (70000,), 4), (24, 4, 32, (9000, 20001), 2)])
+def test_long_chunks(Hq, Hkv, w, seqlens, L):
+    cfg = _cfg(Hq, Hkv, w, seqlens, L=L)
+    one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
+    layers = _inputs(cfg)
+    for l, (q, k) in enumerate(layers):
+        one.score(l, q, k)
+    many.score_layers(0, [x[0] for x in layers], [x[1] for x in layers])
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+    _check(cfg, many.scores[L - 1], *layers[L - 1])
+    k_tm = layers[1][1].transpose(0, 1).contiguous()                     # token-major
+    one.score(0, layers[1][0], k_tm, stride_token=cfg.Hkv * 128, stride_head=128)
+    assert torch.equal(one.scores[0].view(torch.int32), many.scores[1].view(torch.int32))
