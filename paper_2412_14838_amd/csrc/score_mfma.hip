@@ -59,8 +59,6 @@ template <> struct PieceVec<8> { typedef uint32_t type __attribute__((ext_vector
 
 template <int RS, int KS>
 struct QStage {
-  static constexpr bool kStatsViaLds = true;
-  static constexpr bool kEmitViaLds = KS >= 4;                    // else every wavefront loads its own fragments (first layer of a launch)
   static constexpr int kRows = RS * 64;
   static constexpr int kPieces = kRows * 16 / (RS * KS * 64);     // 16 / KS
   static constexpr int kBytes = kRows * kLdsRow;
@@ -133,22 +131,6 @@ __device__ inline void read_q_frags(const char* __restrict__ qbuf, int rs, bf16x
     const char* row = qbuf + (rs * 64 + t * 32 + (lane & 31)) * kLdsRow + (lane >> 5) * 16;
 #pragma unroll
     for (int j = 0; j < 8; ++j) qf[t][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + j * 32));
-  }
-}
-
-// The same fragments straight from global memory, every wavefront for itself: used by the emit kernel where only
-// two wavefronts share a row slab (KS = 2), for which the detour through LDS measured slower there.
-__device__ inline void load_q_frags(const uint16_t* __restrict__ q_head, int rs, int rows, bf16x8 (&qf)[2][8]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int r = rs * 64 + t * 32 + (lane & 31), src_row = r < rows ? r : rows - 1;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (r < tiled_rows(rows)) v = *reinterpret_cast<const uint4*>(q_head + (int64_t)src_row * 128 + j * 16 + (lane >> 5) * 8);
-      qf[t][j] = __builtin_bit_cast(bf16x8, v);
-    }
   }
 }
 
@@ -761,9 +743,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   const char* k_ptr;
   {
     const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 0) * TL::kKeys, len - 1);
-    typename PieceVec<QS::kPieces>::type q0;
-    if (QS::kEmitViaLds) q0 = load_q_pieces<RS, KS, true>(src.q[first_layer] + q_off, p.rows);
-    else load_q_frags(src.q[first_layer] + q_off, rs, p.rows, qf);
+    const typename PieceVec<QS::kPieces>::type q0 = load_q_pieces<RS, KS, true>(src.q[first_layer] + q_off, p.rows);
     const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 1) * TL::kKeys, len - 1);
     int l2, t2;
     stream_tile(first_layer, 2, n_steps, n_layers, l2, t2);
@@ -771,7 +751,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
     k_layer = l2;
     k_ptr = src.k[l2] + k_off;
     store_tile<RS, KS>(tiles, reg0);
-    if (QS::kEmitViaLds) store_q_pieces<RS, KS>(qbuf, q0);
+    store_q_pieces<RS, KS>(qbuf, q0);
     store_tile<RS, KS>(tiles + TL::kTileBytes, reg1);
   }
   // ---- lse2[row] of the first layer
@@ -788,7 +768,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   }
   floatx16 acc[2], nxt[2];
   lds_barrier();                                             // lse2 is complete, the first tile and Q are in place
-  if (QS::kEmitViaLds) read_q_frags(qbuf, rs, qf);
+  read_q_frags(qbuf, rs, qf);
   mfma_tile<false>(tiles + lane_tile, qf, acc);
   lds_barrier();                                             // buffer 0 is rewritten by the first step
 

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(wv_threads(NRT)) void score_emit_waves(Params p, in
   begin = __builtin_amdgcn_readfirstlane(begin);
   const int head = blockIdx.y;
   const int first_layer = take_share<LAYERS>(layers_each, n_layers, lse_rows, lse_rows_stride_layer, scores, scores_stride_layer, edges, edges_stride_layer);
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
   const int prefix = __builtin_amdgcn_readfirstlane(S - p.w);            // > 0 here
   const int o0 = __builtin_amdgcn_readfirstlane(c * chunk);              // outputs [o0, o1)
   const int o1 = o0 + chunk < prefix ? o0 + chunk : prefix;
