@@ -34,12 +34,12 @@
 // 64 prompts of 300 keys, eight layers 88 / 72; 8 rows, 200 prompts of 400 keys, one layer 121 / 95.
 // 129 to 256 rows: nobody else is on the SIMD, and whatever the wavefront waits for shows: its matrix instructions and exponentials
 // alone take 366 cycles a unit (203 ns at the 1.8 GHz the chip holds under them), the kernel 630 (257 cycles of MFMAs, 277 of
-// vector instructions). A branch around the LDS reads of the next tile made the waits behind it, for reads of a unit ago, wait for those
-// too: 7 % of the time. One row tile more costs what it is, not as 64 rows more for everybody. Against score_emit_mfma, us, before / after,
-// with the cut of the keys that both could take: 28 layers of 4 heads x 32768 keys, 224 rows 307 / 274; 16 of 2 heads x 20000, 160 rows
-// 57 / 46; 32 of 8 heads x 8192, 256 rows 199 / 178; 8 of 4 heads x 4097, 192 rows 28 / 25; one layer, both sweeps: 4 heads x 300 keys, 224
-// rows 20.1 / 18.6, 32768 30.6 / 30.2. Its normalisers kept in registers and one load of a tile at a time were tried: the former spills, the
-// latter costs more instructions than it hides (329 us for 310 with four in a row).
+// vector instructions). A branch around the LDS reads of the next tile would have the waits behind it, for reads of a unit ago, wait for
+// those too (7 layers of 4 heads x 131072 keys, 224 rows 280 / 275). One row tile more costs what it is, not as 64 rows more for everybody.
+// Against score_emit_mfma, us, before / after: 28 layers of 4 heads x 32768 keys, 224 rows 307 / 274; 16 of 2 heads x 20000, 160 rows 57 / 46
+// (the same cut of the keys on both sides); with that sweep's cut of the keys, 32 of 8 heads x 8192, 256 rows 215 / 178; 8 of 4 heads x
+// 4097, 192 rows 30 / 25; one layer of 4 heads x 32768, 224 rows, both sweeps 30.6 / 30.2. Normalisers kept in registers were tried and
+// spill; a tile's loads one at a time between the units cost more instructions than they hide (320 us for 310 with four in a row).
 // The first sweep done the same way was not better at 128 rows (32 layers of 32768 keys 417 / 419, one layer of 8192 9.6 / 10.1),
 // and its sums come out in another order.
 #pragma once
