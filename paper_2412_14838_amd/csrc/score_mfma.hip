@@ -11,7 +11,7 @@
 //                 small kernel of its own when a call covers several layers;
 //   emit kernel:  S_tile = Q . K_tile^T (rows as M, keys as N: a lane holds ONE key and 16 rows, so the sum over
 //                 the rows is an in-lane reduction), p = exp2(S * c - lse2[row]), window/group sum, max-pool,
-//                 write. Here for 65 to 128 rows in short chunks; score_waves.h has the one for all else.
+//                 write. Here for more than 64 rows in short chunks; score_waves.h has the one for all else, and the rule.
 // Both use v_mfma_f32_32x32x16_bf16 with the whole Q block of the wavefront resident in registers and K tiles
 // staged through LDS (coalesced 16-byte global loads, padded rows, 16-byte LDS reads in MFMA operand layout).
 // The MFMAs of one tile are issued in the same step as the exponentials of the tile before it (two accumulator
@@ -59,6 +59,7 @@ template <> struct PieceVec<8> { typedef uint32_t type __attribute__((ext_vector
 
 template <int RS, int KS>
 struct QStage {
+  static constexpr bool kEmitViaLds = KS >= 4;                    // else every wavefront loads its own fragments (first layer of a launch)
   static constexpr int kRows = RS * 64;
   static constexpr int kPieces = kRows * 16 / (RS * KS * 64);     // 16 / KS
   static constexpr int kBytes = kRows * kLdsRow;
@@ -131,6 +132,22 @@ __device__ inline void read_q_frags(const char* __restrict__ qbuf, int rs, bf16x
     const char* row = qbuf + (rs * 64 + t * 32 + (lane & 31)) * kLdsRow + (lane >> 5) * 16;
 #pragma unroll
     for (int j = 0; j < 8; ++j) qf[t][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + j * 32));
+  }
+}
+
+// The same fragments straight from global memory, every wavefront for itself: used by the emit kernel where only
+// two wavefronts share a row slab (KS = 2), for which the detour through LDS measured slower there.
+__device__ inline void load_q_frags(const uint16_t* __restrict__ q_head, int rs, int rows, bf16x8 (&qf)[2][8]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int r = rs * 64 + t * 32 + (lane & 31), src_row = r < rows ? r : rows - 1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (r < tiled_rows(rows)) v = *reinterpret_cast<const uint4*>(q_head + (int64_t)src_row * 128 + j * 16 + (lane >> 5) * 8);
+      qf[t][j] = __builtin_bit_cast(bf16x8, v);
+    }
   }
 }
 
@@ -743,7 +760,9 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   const char* k_ptr;
   {
     const typename PieceVec<TL::kPieces>::type reg0 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 0) * TL::kKeys, len - 1);
-    const typename PieceVec<QS::kPieces>::type q0 = load_q_pieces<RS, KS, true>(src.q[first_layer] + q_off, p.rows);
+    typename PieceVec<QS::kPieces>::type q0;
+    if (QS::kEmitViaLds) q0 = load_q_pieces<RS, KS, true>(src.q[first_layer] + q_off, p.rows);
+    else load_q_frags(src.q[first_layer] + q_off, rs, p.rows, qf);
     const typename PieceVec<TL::kPieces>::type reg1 = load_tile<RS, KS>(src.k[first_layer] + k_off, stride_b, emit_tile(n_iter, 1) * TL::kKeys, len - 1);
     int l2, t2;
     stream_tile(first_layer, 2, n_steps, n_layers, l2, t2);
@@ -751,7 +770,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
     k_layer = l2;
     k_ptr = src.k[l2] + k_off;
     store_tile<RS, KS>(tiles, reg0);
-    store_q_pieces<RS, KS>(qbuf, q0);
+    if (QS::kEmitViaLds) store_q_pieces<RS, KS>(qbuf, q0);
     store_tile<RS, KS>(tiles + TL::kTileBytes, reg1);
   }
   // ---- lse2[row] of the first layer
@@ -768,7 +787,7 @@ __global__ __launch_bounds__(RS * KS * 64) void score_emit_mfma(Params p, int ch
   }
   floatx16 acc[2], nxt[2];
   lds_barrier();                                             // lse2 is complete, the first tile and Q are in place
-  read_q_frags(qbuf, rs, qf);
+  if (QS::kEmitViaLds) read_q_frags(qbuf, rs, qf);
   mfma_tile<false>(tiles + lane_tile, qf, acc);
   lds_barrier();                                             // buffer 0 is rewritten by the first step
 
@@ -977,18 +996,20 @@ bool score_mfma_supported(const Params& p, int dtype, int64_t k_stride_token) {
 // Measured: 1.3 us per 128-key step of a full device, of the sweeps with shared tiles (as the first one is for any number of rows).
 constexpr double kFixedUs = 6.0, kUsPerKey = 0.0102;
 
-// The longest chunk whose column sums fit the LDS of the kernel that writes the scores.
+// The longest chunk whose column sums fit the LDS of score_emit_mfma, and of the kernel that writes the scores: score_emit_waves always
+// has the LDS for kMaxChunk, and only up to 128 rows the other one may have to take what the first sweep's cut is.
+template <int RS, int KS>
+static int longest_shared_chunk() {
+  using TL = Tile<RS, KS>;
+  const long long lds_fixed = 2LL * TL::kTileBytes + QStage<RS, KS>::kBytes;
+  int max_chunk = (int)((kLdsBudget - lds_fixed) / (emit_slabs<RS>() * (long long)sizeof(float))) - kMaxHalo - 2 * TL::kKeys;
+  max_chunk = max_chunk / TL::kKeys * TL::kKeys;
+  return max_chunk < kMaxChunk ? max_chunk : kMaxChunk;
+}
 template <int RS, int KS>
 static int longest_chunk() {
-  using TL = Tile<RS, KS>;
-  int max_chunk = kMaxChunk;                                 // which score_emit_waves always has the LDS for
-  if constexpr (RS == 2) {
-    const long long lds_fixed = 2LL * TL::kTileBytes + QStage<RS, KS>::kBytes;
-    max_chunk = (int)((kLdsBudget - lds_fixed) / (emit_slabs<RS>() * (long long)sizeof(float))) - kMaxHalo - 2 * TL::kKeys;
-    max_chunk = max_chunk / TL::kKeys * TL::kKeys;
-    if (max_chunk > kMaxChunk) max_chunk = kMaxChunk;
-  }
-  return max_chunk;
+  if constexpr (RS == 2) return longest_shared_chunk<RS, KS>();
+  return kMaxChunk;
 }
 
 // Workgroups of a head's chunks: exact for one sequence, an upper bound over several. (Workgroups that find no chunk cost more than
@@ -1111,6 +1132,14 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     emit_threads = wv_threads(NRT);
     lds_emit = wv_lds_emit<NRT>(emit_chunk);
   };
+  auto shared_tiles = [&](auto kernel) {
+    if constexpr (RS > 1) {
+      emit_kernel = kernel;
+      emit_threads = TL::kThreads;
+      lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(emit_chunk) * sizeof(float) +
+                 (size_t)QStage<RS, KS>::kBytes;             // the Q staging area serves the next layer in every variant
+    }
+  };
   static std::atomic<uint64_t> given{0};
   const void* stats_kernel = reinterpret_cast<const void*>(&score_stats_mfma<RS, KS, LAYERS>);
   hipError_t e;
@@ -1121,18 +1150,19 @@ static hipError_t launch_mfma_t(const Params& p, int phases, int n_layers, const
     waves(std::integral_constant<int, 4>{});
     e = allow_lds(given, {{stats_kernel, (int)lds_stats}, {reinterpret_cast<const void*>(emit_kernel), kLdsBudget},
                           {reinterpret_cast<const void*>(&score_emit_mfma<RS, KS, LAYERS>), kLdsBudget}});
-    if (emit_chunk < kWvMinChunk) {
-      emit_kernel = &score_emit_mfma<RS, KS, LAYERS>;
-      emit_threads = TL::kThreads;
-      lds_emit = 2 * TL::kTileBytes + (size_t)emit_slabs<RS>() * emit_part_stride<RS, KS>(emit_chunk) * sizeof(float) +
-                 (size_t)QStage<RS, KS>::kBytes;             // the Q staging area serves the next layer in every variant
-    }
+    if (emit_chunk < kWvMinChunk) shared_tiles(&score_emit_mfma<RS, KS, LAYERS>);
   } else {
     if (p.rows <= 160) waves(std::integral_constant<int, 5>{});
     else if (p.rows <= 192) waves(std::integral_constant<int, 6>{});
     else if (p.rows <= 224) waves(std::integral_constant<int, 7>{});
     else waves(std::integral_constant<int, 8>{});
+    if constexpr (LAYERS > 1) {
+      const int longest = p.max_seq_len - p.w;
+      if (wide_by_shared_tiles(p.rows, longest < emit_chunk ? longest : emit_chunk, emit_each) && emit_chunk <= longest_shared_chunk<RS, KS>())
+        shared_tiles(&score_emit_mfma<RS, KS, LAYERS>);
+    }
     e = allow_lds(given, {{stats_kernel, (int)lds_stats},
+                          {reinterpret_cast<const void*>(&score_emit_mfma<RS, KS, DKV_MAX_SELECT_LAYERS>), kLdsBudget},   // (never for one layer)
                           {reinterpret_cast<const void*>(&score_emit_waves<5, LAYERS>), kLdsBudget},
                           {reinterpret_cast<const void*>(&score_emit_waves<6, LAYERS>), kLdsBudget},
                           {reinterpret_cast<const void*>(&score_emit_waves<7, LAYERS>), kLdsBudget},

@@ -36,3 +36,23 @@ def test_long_chunks(Hq, Hkv, w, seqlens, L):
     k_tm = layers[1][1].transpose(0, 1).contiguous()                     # token-major
     one.score(0, layers[1][0], k_tm, stride_token=cfg.Hkv * 128, stride_head=128)
     assert torch.equal(one.scores[0].view(torch.int32), many.scores[1].view(torch.int32))
+
+
+# Batches of short sequences, several layers to a workgroup: query heads, KV heads, window, lengths, layers
+BY_SHARED_TILES = [(16, 2, 32, (187,) * 100, 16), (14, 2, 32, (133, 40, 170, 33) * 20, 16), (12, 2, 32, (180, 161, 190) * 22, 16),
+                   (64, 8, 32, (180,) * 16, 16), (16, 2, 32, (500, 1200, 333, 1, 900) * 7, 7), (28, 4, 32, (500,) * 50, 4)]
+BY_WAVES = [(16, 2, 32, (130,) * 100, 8), (14, 2, 32, (500,) * 64, 16), (12, 2, 32, (90,) * 64, 16), (10, 2, 32, (130, 77) * 32, 16)]
+
+
+@pytest.mark.parametrize("Hq,Hkv,w,seqlens,L", BY_SHARED_TILES + BY_WAVES)
+@pytest.mark.parametrize("P", [1, 7, 63])
+def test_batches_of_several_layers(Hq, Hkv, w, seqlens, L, P):
+    """Whichever kernel takes them: the bits of the layers one by one, and as exact."""
+    cfg = _cfg(Hq, Hkv, w, seqlens, L=L, P=P)
+    one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
+    layers = _inputs(cfg)
+    for l, (q, k) in enumerate(layers):
+        one.score(l, q, k)
+    many.score_layers(0, [x[0] for x in layers], [x[1] for x in layers])
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+    _check(cfg, many.scores[L - 1], *layers[L - 1])

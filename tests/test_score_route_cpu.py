@@ -1,0 +1,40 @@
+"""The kernel and the cut that the host picks for a scoring call (bf16, head size 128), 256 compute units."""
+import random
+import shutil
+
+import pytest
+
+from score_route import sweeps
+from test_gpu_score_wide import BY_SHARED_TILES, BY_WAVES
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def _call(Hq, Hkv, w, seqlens, L, given=0):
+    return L, Hq, Hkv, w, list(seqlens), given
+
+
+def test_second_sweep_of_more_than_128_rows(tmp_path):
+    """Several layers to a workgroup and a short chunk: the kernel of shared tiles where its finer steps are worth more. One layer: never."""
+    calls = [_call(*s, given=g) for s in BY_SHARED_TILES + BY_WAVES for g in (0, 1)] + [_call(*s[:4], 1) for s in BY_SHARED_TILES]
+    found = [x["emit"] for x in sweeps(tmp_path, calls)]
+    n = 2 * len(BY_SHARED_TILES)
+    assert {(x["kernel"], *x["template"]) for x in found[:n]} == {("score_emit_mfma", 4, 2, 32)}
+    for (L, Hq, Hkv, w, _, _), x in zip(calls[n:], found[n:]):
+        assert (x["kernel"], x["template"]) == ("score_emit_waves", [-(-Hq // Hkv * w // 32), 1 if L == 1 else 32])
+
+
+def test_every_call_fits_and_covers_its_layers(tmp_path):
+    rng = random.Random(5)
+    calls = []
+    for _ in range(400):
+        G, Hkv, n = rng.randint(1, 8), rng.choice([1, 2, 4, 8]), rng.choice([1, 1, 1, 2, 8, 40, 300])
+        calls.append(_call(G * Hkv, Hkv, 32, [rng.randint(1, int(10 ** rng.uniform(1.6, 5.3 if n == 1 else 4))) for _ in range(n)], rng.randint(1, 32),
+                           rng.randint(0, 1)))
+    for (L, Hq, Hkv, w, seqlens, _), x in zip(calls, sweeps(tmp_path, calls)):
+        for s in x.values():
+            shares, each, T = s["grid"][2], abs(s["layers_each"]), sum(seqlens)
+            assert s["lds"] <= 152 * 1024 and 256 <= s["chunk"] <= 4096 and s["layers"] == L
+            assert shares * each <= 32 or s["layers_each"] < 0 or s["kernel"] == "score_stats_mfma"
+            assert (shares - 1) * each < L <= shares * each                              # no share is empty, none is missing
+            assert s["grid"][:2] == [-(-T // s["chunk"]) if len(seqlens) == 1 else T // s["chunk"] + len(seqlens), Hkv]
