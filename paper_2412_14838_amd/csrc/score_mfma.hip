@@ -594,11 +594,13 @@ __device__ inline void merge_chunks(const float2* __restrict__ psrc, int n_full,
   mstage[mgrp * kRows + mrow] = make_float2(M, Lsum);
 }
 
-// merge_chunks<4, 2> by 256 threads: both groups of a row by one thread, side by side, the same bits.
+// merge_chunks<4, 2> by 256 threads: both groups of a row by one thread, side by side, the same bits. As many loads in flight as there:
+// one layer of one head and 256 rows, 131072 keys (512 chunks), both sweeps, us: 38.4 (43.4 with half as many; 512 threads 38.5), 46129 keys
+// 27.0 (30.1; 27.3), 5000 keys 19.1 (19.2; 21.7). Twice as many: 36.0, 27.4, 20.9.
 __device__ inline void merge_chunks_both(const float2* __restrict__ psrc, int n_full, uint32_t chunk_step, float2* __restrict__ mstage) {
   const uint32_t t0 = threadIdx.x;
   float M[2] = {-INFINITY, -INFINITY}, Lsum[2] = {0.0f, 0.0f};
-#pragma unroll 4
+#pragma unroll 8
   for (int cc = 0; cc + 1 < n_full; cc += 2, psrc += 2 * chunk_step) {
     merge_pair(M[0], Lsum[0], psrc[t0]);
     merge_pair(M[1], Lsum[1], psrc[t0 + chunk_step]);

@@ -56,3 +56,17 @@ def test_batches_of_several_layers(Hq, Hkv, w, seqlens, L, P):
     many.score_layers(0, [x[0] for x in layers], [x[1] for x in layers])
     assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
     _check(cfg, many.scores[L - 1], *layers[L - 1])
+
+
+@pytest.mark.parametrize("Hq,w", [(5, 32), (6, 32), (7, 31), (8, 32)])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 15, 16, 17, 31, 32, 33, 181])
+def test_merges_of_chunks(Hq, w, chunks):
+    """One head's chunks of 256 keys: merged by 256 threads in a call of one layer, by 512 in one of several."""
+    cfg = _cfg(Hq, 1, w, (256 * chunks - 100,), L=2)
+    one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
+    layers = _inputs(cfg)
+    for l, (q, k) in enumerate(layers):
+        one.score(l, q, k)
+    many.score_layers(0, [x[0] for x in layers], [x[1] for x in layers])
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+    _check(cfg, one.scores[0], *layers[0])

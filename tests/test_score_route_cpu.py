@@ -38,3 +38,9 @@ def test_every_call_fits_and_covers_its_layers(tmp_path):
             assert shares * each <= 32 or s["layers_each"] < 0 or s["kernel"] == "score_stats_mfma"
             assert (shares - 1) * each < L <= shares * each                              # no share is empty, none is missing
             assert s["grid"][:2] == [-(-T // s["chunk"]) if len(seqlens) == 1 else T // s["chunk"] + len(seqlens), Hkv]
+
+
+def test_chunks_of_one_head(tmp_path):
+    """What test_merges_of_chunks goes by."""
+    calls = [_call(Hq, 1, w, (256 * n - 100,), 1) for Hq, w in ((5, 32), (7, 31)) for n in (1, 33, 181)]
+    assert {x["stats"]["chunk"] for x in sweeps(tmp_path, calls)} == {256}
