@@ -47,7 +47,7 @@
 // 4 heads, 8 layers 69 / 80; 224 rows, 64 of 133, 2 heads, 16 layers 87 / 103, 100 of 500, 8 layers 131 / 144; 192 rows, 64 of 180, 16 layers
 // 85 / 95. The other way: 256 rows, 100 of 130, 8 layers 52 / 49; 224 rows, 64 of 500, 16 layers 179 / 170, 64 of 1400 415 / 374; 192 rows,
 // 64 of 90, 16 layers 86 / 69, 64 of 500 173 / 153; 160 rows, 24 of 130, 4 heads, 8 layers 53 / 43. Of 412 shapes of 129 to 256 rows, most of
-// them batches, the rule's choice is the slower one by 0.16 % on average and 6 % at most; this kernel everywhere by 1.8 and 29, the other one
+// them batches, the rule's choice is the slower one by 0.17 % on average and 6 % at most; this kernel everywhere by 1.8 and 29, the other one
 // by 7.2 and 35. A call of one layer always comes here: 64 prompts of 300 keys, 2 heads of 160 to 256 rows 11.3 to 12.8 / 8.6 to 10.7.
 // The first sweep done the same way was not better at 128 rows (32 layers of 32768 keys 417 / 419, one layer of 8192 9.6 / 10.1),
 // and its sums come out in another order.
@@ -63,7 +63,7 @@ constexpr int wv_ring(int nrt) { return nrt > 4 ? 4 : 3; }         // half tiles
 constexpr int wv_ring_bytes(int nrt) { return wv_waves(nrt) * wv_ring(nrt) * kWvHalfBytes; }
 // Microseconds of a layer in a chunk: its end, and a step of score_emit_mfma (64 keys, at least three of them) or a round of this kernel (128
 // keys); fitted to those shapes. kWvStartUs: what a workgroup of this kernel has ahead at the start.
-constexpr double kStEndUs = 1.5, kStStepUs = 1.08, kWvStartUs = 1.3;
+constexpr double kStEndUs = 1.5, kStStepUs = 1.08, kWvStartUs = 1.0;
 constexpr double kWvEndUs[4] = {2.25, 1.9, 2.1, 2.4}, kWvRoundUs[4] = {1.45, 1.75, 2.0, 2.1};     // 129 to 160 rows, to 192, 224, 256
 // More than 128 rows: true where score_emit_mfma is the faster one for workgroups of layers_each layers and at most `keys` keys.
 static bool wide_by_shared_tiles(int rows, int keys, int layers_each) {
