@@ -1,5 +1,6 @@
 """Scores of 129 to 256 rows per KV head: every number of row tiles, partly filled ones, ends of tiles, chunks and rounds of wavefronts,
-wavefronts without keys, layers that follow each other in one call, batches. Against float64, with the bound of test_gpu_score_waves."""
+wavefronts without keys, layers that follow each other in one workgroup, batches, very long chunks. Against float64, with the bound of
+test_gpu_score_waves; test_score_route_cpu.py has the kernels and cuts."""
 import pytest
 import torch
 
@@ -70,3 +71,40 @@ def test_merges_of_chunks(Hq, w, chunks):
     many.score_layers(0, [x[0] for x in layers], [x[1] for x in layers])
     assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
     _check(cfg, one.scores[0], *layers[0])
+
+
+# Three layers and more to a workgroup, the last chunk of `last` keys: 1, 2 or 3 of its 4 wavefronts have any. In the first sweep's cut (5
+# layers in two shares, 3 in one) and in one of its own (11 in four). Rows: whole row tiles and partly filled ones.
+LAYERS_IN_A_SHARE = [(t * Hkv, Hkv, w, w + S + last, L) for t in (5, 6, 7, 8) for w, last in ((32, 1), (31, 33), (32, 96))
+                     for Hkv, L, S in (((4, 3, 79360) if t == 8 else (8, 5, 2560)), (4, 11, 23040))]
+
+
+@pytest.mark.parametrize("Hq,Hkv,w,S,L", LAYERS_IN_A_SHARE)
+def test_layers_after_each_other(Hq, Hkv, w, S, L):
+    cfg = _cfg(Hq, Hkv, w, (S,), L=L)
+    one, many = Compressor(cfg, keep_cache=False), Compressor(cfg, keep_cache=False)
+    layers = _inputs(cfg)
+    lses = []
+    for l, (q, k) in enumerate(layers):
+        one.score(l, q, k)
+        lses.append(torch.empty((1, Hq, w), device="cuda"))
+        one.row_lse(lses[l])
+    qs, ks = [x[0] for x in layers], [x[1] for x in layers]
+    many.score_layers(0, qs, ks)
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+    for l in (0, 1, L - 1):
+        _check(cfg, many.scores[l], *layers[l])
+    many.score_layers_from_lse(0, qs, ks, lses)
+    for l in range(L):
+        one.score_from_lse(l, *layers[l], lses[l])
+    assert torch.equal(one.scores.view(torch.int32), many.scores.view(torch.int32))
+
+
+@pytest.mark.parametrize("Hq", [40, 64])
+def test_first_sweep_of_very_long_chunks(Hq):
+    """3136 keys: more than score_emit_mfma would have the LDS for."""
+    cfg = _cfg(Hq, 8, 32, (100001,))
+    comp = Compressor(cfg, keep_cache=False)
+    q, k = _inputs(cfg)[0]
+    comp.score(0, q, k)
+    _check(cfg, comp.scores[0], q, k)

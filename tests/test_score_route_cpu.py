@@ -5,7 +5,8 @@ import shutil
 import pytest
 
 from score_route import sweeps
-from test_gpu_score_wide import BY_SHARED_TILES, BY_WAVES
+from test_gpu_emit_cut import UNEVEN
+from test_gpu_score_wide import BY_SHARED_TILES, BY_WAVES, LAYERS_IN_A_SHARE
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 
@@ -44,3 +45,29 @@ def test_chunks_of_one_head(tmp_path):
     """What test_merges_of_chunks goes by."""
     calls = [_call(Hq, 1, w, (256 * n - 100,), 1) for Hq, w in ((5, 32), (7, 31)) for n in (1, 33, 181)]
     assert {x["stats"]["chunk"] for x in sweeps(tmp_path, calls)} == {256}
+
+
+def test_cuts_of_several_layers_to_a_share(tmp_path):
+    """What test_layers_together_give_the_bits_of_each_alone goes by: the second sweep's own cut, shares of several layers, not all as many."""
+    calls = [(*s[:4], list(s[4]), 0) for s in UNEVEN] + [(*s[:4], list(s[4]), 1) for s in UNEVEN if s[1] // s[2] > 2]
+    for (L, *_), x in zip(calls, sweeps(tmp_path, calls)):
+        x = x["emit"]
+        assert x["kernel"] == "score_emit_waves" and x["layers_each"] > 1 and L % x["grid"][2] != 0
+
+
+def test_layers_in_a_share_and_wavefronts_without_keys(tmp_path):
+    """What test_layers_after_each_other goes by."""
+    calls = [_call(Hq, Hkv, w, [S], L) for Hq, Hkv, w, S, L in LAYERS_IN_A_SHARE]
+    cuts = set()
+    for (L, Hq, Hkv, w, (S,), _), x in zip(calls, sweeps(tmp_path, calls)):
+        x, tiles = x["emit"], -(-Hq // Hkv * w // 32)
+        assert x["kernel"] == "score_emit_waves" and x["template"] == [tiles, 32] and abs(x["layers_each"]) >= 3
+        last = (S - w) % x["chunk"]
+        assert 1 <= last <= 96
+        cuts.add((tiles, x["layers_each"] > 0, -(-last // 32)))
+    assert cuts == {(t, own, n) for t in (5, 6, 7, 8) for own in (False, True) for n in (1, 2, 3)}
+
+
+def test_first_sweep_of_very_long_chunks(tmp_path):
+    calls = [_call(Hq, 8, 32, [100001], 1) for Hq in (40, 64)]
+    assert [x[k]["chunk"] for x in sweeps(tmp_path, calls) for k in ("stats", "emit")] == [3136] * 4
