@@ -86,9 +86,6 @@ __host__ __device__ constexpr int wv_sums_bytes(int chunk) {          // column 
 template <int NRT> constexpr size_t wv_lds_emit(int chunk) {
   return wv_ring_bytes(NRT) + wv_rows(NRT) * 256 + 2 * wv_lse_rows(NRT) * sizeof(float) + wv_sums_bytes(chunk);
 }
-template <int NRT> constexpr size_t wv_lds_stats() {
-  return wv_ring_bytes(NRT) + wv_rows(NRT) * 256 + 2 * wv_waves(NRT) * wv_rows(NRT) * sizeof(float2);
-}
 
 // f(0), f(1) .. f(N - 1) with the index as a constant.
 template <typename F, int... I>
@@ -140,9 +137,9 @@ __device__ inline void wait_newer(int n) {
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The keys of one wavefront as a stream of half tiles: of the tiles wave, wave + WAVES, ... of the chunk, first to last (FORWARD) or
-// last to first, layer after layer. issue() asks for the next half, take() brings the oldest one into the operand registers.
-template <int WAVES, int RING, bool FORWARD>
+// The keys of one wavefront as a stream of half tiles: of the tiles wave, wave + WAVES, ... of the chunk, last to first, layer after
+// layer. issue() asks for the next half, take() brings the oldest one into the operand registers.
+template <int WAVES, int RING>
 struct WaveKeys {
   char* lds;                        // of the workgroup
   uint32_t ring;                    // this wavefront's part of it
@@ -185,7 +182,7 @@ struct WaveKeys {
   // The piece that lands in place lane % 8 of row 8 i + lane / 8.
   static __device__ uint32_t piece_off(int lane, int i) { return (uint32_t)((lane & 7) ^ ((lane >> 4) + 4 * (i & 1))) * 16u; }
   __device__ int first_key(int t) const {            // of the wavefront's t-th tile, relative to the chunk
-    return ((FORWARD ? t : my_tiles - 1 - t) * WAVES + wave) * 32;
+    return ((my_tiles - 1 - t) * WAVES + wave) * 32;
   }
   // The first halves: as many as the ring holds.
   __device__ void fill() {
@@ -215,13 +212,8 @@ struct WaveKeys {
     ++issued;
     issue_slot = issue_slot == (RING - 1) * kWvHalfBytes ? 0 : issue_slot + kWvHalfBytes;
     if (H == 1) {
-      if (FORWARD) {
-        row0 += 32 * WAVES;
-        k_ptr += (uint64_t)(32u * WAVES * stride_b);
-      } else {
-        row0 -= 32 * WAVES;
-        k_ptr -= (uint64_t)(32u * WAVES * stride_b);
-      }
+      row0 -= 32 * WAVES;
+      k_ptr -= (uint64_t)(32u * WAVES * stride_b);
       if (__builtin_expect(--tiles_left == 0, 0)) {      // the wavefront's last tile of a layer
         tiles_left = my_tiles;
         ++layer;
@@ -273,7 +265,7 @@ __device__ inline void take_turns(int mine) {
 }
 
 // The Q block of a (sequence, head): kRows rows of 256 bytes in LDS, the wavefronts fetch equal shares of them (rows past p.rows
-// repeat the last one: their statistics are never used, and their normalisers are +inf).
+// repeat the last one: their normalisers are +inf).
 template <int NRT>
 __device__ inline void load_q_block(char* qbuf, const char* q_head, int rows, int wave) {
   constexpr int kLoads = NRT * 8 / wv_waves(NRT);
@@ -358,7 +350,7 @@ __global__ __launch_bounds__(wv_threads(NRT)) void score_emit_waves(Params p, in
   const float* __restrict__ lse_seq = lse_rows + ((int64_t)seq * p.Hkv + head) * p.rows_pad;     // (multi-layer launches)
 
   // Tiles from the last to the first: what the statistics kernel, first to last, left in the caches
-  WaveKeys<wv_waves(NRT), wv_ring(NRT), false> keys;
+  WaveKeys<wv_waves(NRT), wv_ring(NRT)> keys;
   keys.start(smem, src, ((int64_t)begin + kbeg) * stride_token_b + (int64_t)head * stride_head_b, (uint32_t)stride_token_b, len,
              first_layer, n_layers);
   load_q_block<NRT>(qbuf, reinterpret_cast<const char*>(src.q[first_layer]) + q_off, p.rows, keys.wave);
