@@ -20,8 +20,12 @@ BINDING = os.path.join(HERE, "_binding.so")
 # packed fp32 VALU forms are switched off for all device code
 HIPCC_FLAGS = ["-O3", "-fno-honor-nans", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
                "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
-# kernels of more than 256 registers: results of matrix instructions in vector registers, where the exponentials read them
-# (by default they would go to accumulation registers and be copied from there, 16 instructions a unit of 8 products)
+# An option of the compiler's code generator: results of matrix instructions in vector registers, where the exponentials read them. Without it
+# a kernel of more than 256 registers has them in accumulation registers and copies them from there (16 instructions a unit of 8 products).
+# For speed only. The kernels that it changes, us without / with it: the second sweep of 129 to 256 rows (28 layers of 4 heads x 32768 keys,
+# 160, 192, 224, 256 rows 245 / 230, 275 / 260, 303 / 286, 342 / 310) and the first sweep of up to 64 rows (both sweeps: one layer of 8 heads,
+# 2048 keys 12.0 / 11.6, 16384 keys 15.6 / 14.7, 64 prompts of 300 keys 30.4 / 28.8, 8 layers of 16 prompts of 1000 144 / 136; 32 layers
+# of 32768 707 to 720 / 710 to 713, the same).
 SOURCE_FLAGS = {"score_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
