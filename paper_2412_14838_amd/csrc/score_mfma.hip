@@ -1056,13 +1056,18 @@ static int pick_shares(int groups, int n_layers, int chunk, int cus) {
 }
 
 // The second sweep of a call over several layers may cut the keys anew: its sums do not depend on where. A longer chunk in more shares of
-// the layers is as much work for a workgroup in fewer layers, each of which has its end (layer_us: barriers, pooling, the next layer's Q;
-// 4 to 5 K of the 21 K cycles that a layer of 1024 keys and 128 rows takes). Against that stands what a workgroup finds in its XCD's L2
-// of what the first sweep's workgroup in its place read last, kFoundUs, or all of the keys where they fit the L2s (8 x 4 MB).
+// the layers is as much work for a workgroup in fewer layers, each of which has its end (layer_us: barriers, pooling, the next layer's Q).
+// Against that stands what a workgroup finds in its XCD's L2 of what the first sweep's workgroup in its place read last, kFoundUs, or all
+// of the keys where they fit the L2s (8 x 4 MB).
 // Both sweeps / the second one alone, us, the first sweep's cut / the new one, one sequence: 8 heads of 128 rows, 32 layers of 32768 keys
-// 844 / 830, 426 / 407, 16 of 8192 126 / 114, 72 / 56, 8 of 6000 75 / 66, 41 / 29; 224 rows, 4 heads, 28 of 32768 627 / 603, 329 / 307, 4 of
-// 12000 63 / 56, 36 / 28; 160 rows, 2 heads, 16 of 20000 155 / 130, 83 / 58; 64 rows, 2 heads, 32 of 9000 96 / 85, 52 / 37. Not taken: 8 heads
-// of 128 rows, 4 of 12000 50 / 53, 32 / 30; 2 of 5000 29.1 / 30.0; 64 rows, 4 of 16384 53 / 58, 32 / 33, 32 of 32768 715 / 719; 16 rows, 4 of 30000 84 / 92, 47 / 52.
+// 852 / 842 (a whole pass does not show it), 430 / 408, 16 of 8192 130 / 116, 72 / 56, 8 of 6000 74 / 65, 40 / 29; 224 rows, 4 heads, 28 of
+// 32768 608 / 586, 312 / 282, 4 of 12000 63 / 54, 35 / 26; 160 rows, 2 heads, 16 of 20000 144 / 118, 72 / 46; 256 rows, 8 heads, 32 of 8192 407 /
+// 378, 218 / 179; 64 rows, 2 heads, 32 of 9000 80 / 75, 41 / 34. Not taken with both sweeps: 8 heads of 128 rows, 4 of 12000 50 / 52; 16 rows,
+// 4 of 30000 84 / 92; up to 64 rows where the chunk is longer than 256 keys not at all, 4 of 16384 53 / 58, 32 / 33, 32 of 32768 715 / 719.
+// The constants are fitted, not measured one by one: kUsPerKey is the first sweep's, whatever the rows, the kernel that the new chunk
+// leads to (kWvMinChunk, wide_by_shared_tiles) is left out because it follows from the cut, and layer_us is what balances that. Of 110
+// (129 to 256 rows), 90 (65 to 128) and 90 (up to 64) shapes of one sequence both sweeps take 0.5, 1.3 and 1.4 % more than with the best
+// of five values from 0.4 to 3.0 for each shape, and 5.6, 7.0 and 3.1 % more in the first sweep's cut. (3.0 for all rows: 0.5, 0.3 and 0.3.)
 // A batch keeps the first sweep's cut, fitted to its lengths: eight prompts of 4000 to 15000, 32 layers, whole pass 2625, 2678 anew.
 constexpr int64_t kL2Bytes = 32 << 20;
 constexpr double kFoundUs = 8.0;
