@@ -25,8 +25,11 @@
 //   21.6 / 17.7, 128 rows 23.0 / 19.2; 8192 keys, 64 rows 3.74 / 3.20
 //   one layer, 8 heads: 64 rows, 2048 keys 8.7 / 7.3, 16384 11.0 / 8.1, 65536 27.0 / 22.5; 128 rows, 32768 keys 18.6 / 15.9
 // At 65 to 128 rows a wavefront's tile takes four units, and what a layer costs beside them shows when there are few tiles: where the
-// host's chunk is shorter than kWvMinChunk keys score_emit_mfma stays (16 layers in one call, 8 heads of 128 rows, 8192 keys, both sweeps
-// per layer: 8.35 there, 8.96 here; one layer 18.4 and 17.8). A batch's chunk may be cut to half of the host's on the device
+// chunk is shorter than kWvMinChunk keys score_emit_mfma stays (second sweep with the normalisers handed over, there / here: 8 layers of 64
+// prompts of 300 keys, 8 heads of 128 rows 106 / 109, 96 rows 98 / 103; 4 layers of 90 to 3000 keys, 4 heads of 96 rows 17.7 / 18.4; 8 layers of 16
+// prompts of 1000 keys 85 / 85). The rule does not ask for the number of layers: one layer of one sequence has no next one and would be the
+// faster one here (both sweeps, 8 heads of 128 rows, 1000 keys 13.6 / 13.1, 8192 keys 15.3 / 14.7, 64 prompts of 300 keys 38.7 / 38.8).
+// A batch's chunk may be cut to half of the host's on the device
 // (fitted_chunk): this kernel is the faster one there all the same, before / after, 8 heads: 96 rows, 32 prompts of 30 K keys together,
 // 640 of 1024 keys, one layer 32.6 / 31.8, four in one call 77.2 / 71.4; 128 rows, 16 prompts of 16 K, 768 of 1024, 15.6 / 14.2 and
 // 39.4 / 34.5; 16 prompts of 45 K, 896 of 1024, 35.2 / 33.4 and 101 / 92. Up to 64 rows it is taken always, also at one tile to a
